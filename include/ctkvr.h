@@ -257,7 +257,7 @@ int ctkvr_profile_collect(ctkvr_index *idx, float *ms_host, int32_t capacity_ste
  *   CTKVR_FUSED_THREADS      = 256|1024  block size of the single-launch step
  *   CTKVR_BUILD_CANDIDATES   = 0|1 see ctkvr_index_build_route
  *   CTKVR_BUILD_CANDIDATES_REDO    (set: the candidate route also hands every chunk back; tests)
- *   CTKVR_BUILD_SCRATCH_CACHE = 0|1 see ctkvr_release_scratch (read at every build) */
+ *   CTKVR_BUILD_SCRATCH_CACHE = 0|1 see ctkvr_release_scratch (read whenever a block is given back) */
 
 /* ---- how the matrix-core list build chose a unit's top-rho (Algorithm 1 line 4) ---------- */
 /* CTKVR_BUILD_MFMA ranks either all s keys of a (KV head, centroid) unit (their 4-byte ranking keys
@@ -273,13 +273,13 @@ int ctkvr_profile_collect(ctkvr_index *idx, float *ms_host, int32_t capacity_ste
  * CTKVR_BUILD_CANDIDATES = 0 | 1, read at build time, forces the choice where the geometry allows it. */
 int ctkvr_index_build_route(const ctkvr_index *idx, int32_t *by_candidates_host, int32_t *chunks_redone_host);
 
-/* ---- scratch kept between index builds (Algorithm 1 runs once per prompt) ----------------- */
-/* The candidate route of CTKVR_BUILD_MFMA keeps its device scratch (about 1.1 GB for a 128K context,
- * 32/8 heads, C = rho = 2048; never more than 2 GiB -- a build that needs more, or that finds the
- * scratch in use by a build on another host thread, allocates and frees its own) in one allocation per
- * device until this call, so that the next build neither allocates nor frees (0.75 ms of an 8 ms build).
- * Frees the current device's scratch; an error if a build is using it.  The environment variable
- * CTKVR_BUILD_SCRATCH_CACHE = 0, read at build time, switches the keeping off. */
+/* ---- device memory kept between indexes (Algorithm 1 runs once per prompt) ---------------- */
+/* An index and the scratch of its build are one device allocation each.  Blocks that are no longer in use (the
+ * scratch when a build returns, an index's memory when it is freed) are kept, at most 2 GiB per device, the oldest
+ * given up first, and serve later builds and loads of about the same size, from any host thread and stream; they
+ * are freed when an allocation of the library runs out of memory and by this call, which frees the current device's
+ * idle blocks; an error if a build is using scratch on that device.  The environment variable
+ * CTKVR_BUILD_SCRATCH_CACHE = 0, read when a block is given back, switches the keeping off. */
 int ctkvr_release_scratch(void);
 
 /* ---- how a decode step is launched ----------------------------------------- */

@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <map>
 #include <mutex>
 #include <new>
 #include <string>
@@ -77,68 +78,130 @@ int static_scratch(unsigned char **out)
     return CTKVR_OK;
 }
 
-// Scratch of the matrix-core list build's candidate route, kept between builds (an index is built per prompt, and
-// freeing a gigabyte costs 0.6 ms of an 8 ms build): one allocation per device, grown when a build needs more, at most
-// kBuildCacheMax bytes; a build that finds it taken (another host thread is building) or needs more than that allocates
-// its own.  ctkvr_release_scratch() frees it; CTKVR_BUILD_SCRATCH_CACHE=0 switches the cache off.
-constexpr size_t kBuildCacheMax = (size_t)2 << 30;
-struct BuildCache {
-    void *base = nullptr;
-    size_t bytes = 0;
-    bool busy = false;
+// Device memory kept between indexes.  An index and the scratch of its build are one allocation each; an index is built
+// per prompt and freed per request, and hipMalloc / hipFree of what a 32K prompt takes cost 2 ms in the best case and 70 ms
+// where the driver has to map and unmap 2 GB every time (7.6 to 76 ms a build, of which the kernels are 5.9).  Blocks that
+// nothing uses any more are kept per device, at most kPoolMax bytes of them (the oldest go first), and handed out again to
+// a request of at least half their size.  ctkvr_release_scratch() frees them; CTKVR_BUILD_SCRATCH_CACHE=0 switches the
+// keeping off.  A block enters the pool only after the work that used it has ended (a build synchronises its stream, an
+// index its device), so it is idle whichever stream or host thread takes it next.
+constexpr size_t kPoolMax = (size_t)2 << 30;
+struct PoolBlock {
+    void *base;
+    size_t bytes;
 };
-std::mutex g_build_mu;
-BuildCache g_build_cache[kMaxDevices];
+std::mutex g_pool_mu;
+std::vector<PoolBlock> g_pool[kMaxDevices];   // oldest first
+int g_pool_builds[kMaxDevices] = {};          // builds that are using scratch right now
 
-// *cached tells build_scratch_put what to do with the pointer afterwards
-int build_scratch_get(size_t bytes, void **out, bool *cached)
+bool pool_on()
 {
-    *out = nullptr;
-    *cached = false;
-    int dev = -1;
-    HIP_TRY(hipGetDevice(&dev));
     const char *env = getenv("CTKVR_BUILD_SCRATCH_CACHE");
-    const bool use = dev >= 0 && dev < kMaxDevices && bytes <= kBuildCacheMax && !(env && atoi(env) == 0);
-    if (use) {
-        std::lock_guard<std::mutex> lock(g_build_mu);
-        BuildCache &c = g_build_cache[dev];
-        if (!c.busy) {
-            if (c.bytes < bytes) {   // (no build is using it: every build ends with a synchronisation of its stream)
-                if (c.base) (void)hipFree(c.base);
-                c.base = nullptr;
-                c.bytes = 0;
-                hipError_t e = hipMalloc(&c.base, bytes);
-                if (e != hipSuccess) {
-                    c.base = nullptr;
-                    return fail(e == hipErrorOutOfMemory ? CTKVR_ENOMEM : CTKVR_EHIP, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
-                }
-                c.bytes = bytes;
-            }
-            c.busy = true;
-            *out = c.base;
-            *cached = true;
+    return !(env && atoi(env) == 0);
+}
+
+// frees the current device's idle blocks (the caller holds g_pool_mu)
+void pool_drop(int dev)
+{
+    for (PoolBlock &b : g_pool[dev]) (void)hipFree(b.base);
+    g_pool[dev].clear();
+}
+
+// a block of at least `bytes` on the current device `dev`; out->bytes is its real size
+int pool_get(int dev, size_t bytes, PoolBlock *out)
+{
+    const size_t grain = bytes < ((size_t)4 << 20) ? (size_t)64 << 10 : (size_t)2 << 20;
+    bytes = (std::max<size_t>(bytes, 1) + grain - 1) / grain * grain;
+    *out = PoolBlock{nullptr, 0};
+    const bool pooled = dev >= 0 && dev < kMaxDevices;
+    std::unique_lock<std::mutex> lock(g_pool_mu, std::defer_lock);
+    if (pooled) {
+        lock.lock();
+        std::vector<PoolBlock> &v = g_pool[dev];
+        size_t best = v.size();
+        for (size_t i = 0; i < v.size(); ++i)
+            if (v[i].bytes >= bytes && v[i].bytes / 2 <= bytes && (best == v.size() || v[i].bytes < v[best].bytes)) best = i;
+        if (best < v.size()) {
+            *out = v[best];
+            v.erase(v.begin() + best);
             return CTKVR_OK;
         }
     }
-    hipError_t e = hipMalloc(out, bytes ? bytes : 16);
+    hipError_t e = hipMalloc(&out->base, bytes);
+    if (e == hipErrorOutOfMemory && pooled && !g_pool[dev].empty()) {
+        (void)hipGetLastError();
+        pool_drop(dev);
+        e = hipMalloc(&out->base, bytes);
+    }
     if (e != hipSuccess) {
-        *out = nullptr;
+        out->base = nullptr;
         return fail(e == hipErrorOutOfMemory ? CTKVR_ENOMEM : CTKVR_EHIP, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
     }
+    out->bytes = bytes;
     return CTKVR_OK;
 }
 
-void build_scratch_put(void *ptr, bool cached)
+// gives a block of device `dev` back; nothing on that device uses it any more
+void pool_put(int dev, PoolBlock b)
 {
-    if (!ptr) return;
-    if (!cached) {
-        (void)hipFree(ptr);
+    if (!b.base) return;
+    if (dev < 0 || dev >= kMaxDevices || b.bytes > kPoolMax || !pool_on()) {
+        (void)hipFree(b.base);
         return;
     }
-    std::lock_guard<std::mutex> lock(g_build_mu);
-    for (BuildCache &c : g_build_cache)
-        if (c.base == ptr) c.busy = false;
+    std::lock_guard<std::mutex> lock(g_pool_mu);
+    std::vector<PoolBlock> &v = g_pool[dev];
+    v.push_back(b);
+    size_t held = 0;
+    for (PoolBlock &x : v) held += x.bytes;
+    while (held > kPoolMax) {
+        held -= v.front().bytes;
+        (void)hipFree(v.front().base);
+        v.erase(v.begin());
+    }
 }
+
+// Scratch of one build, given back at the end of the scope (the stream has been synchronised by then).
+struct BuildScratch {
+    int dev = -1;
+    PoolBlock b{nullptr, 0};
+    ~BuildScratch() { put(); }
+    int get(int device, size_t bytes)
+    {
+        put();
+        int rc = pool_get(device, bytes, &b);
+        if (rc != CTKVR_OK) return rc;
+        dev = device;
+        if (dev >= 0 && dev < kMaxDevices) {
+            std::lock_guard<std::mutex> lock(g_pool_mu);
+            g_pool_builds[dev]++;
+        }
+        return CTKVR_OK;
+    }
+    void put()
+    {
+        if (!b.base) return;
+        pool_put(dev, b);
+        if (dev >= 0 && dev < kMaxDevices) {
+            std::lock_guard<std::mutex> lock(g_pool_mu);
+            g_pool_builds[dev]--;
+        }
+        b = PoolBlock{nullptr, 0};
+    }
+    unsigned char *base() const { return (unsigned char *)b.base; }
+};
+
+// Lays arrays out one after the other, each 256-byte aligned; with base == nullptr only the size is computed.
+struct Carver {
+    unsigned char *base;
+    size_t off = 0;
+    void align_to(size_t a) { off = (off + a - 1) / a * a; }
+    template <typename P> void take(P **ptr, size_t bytes)
+    {
+        if (base) *ptr = reinterpret_cast<P *>(base + off);
+        off += (std::max<size_t>(bytes, 16) + 255) & ~(size_t)255;
+    }
+};
 }  // namespace
 
 // Buffers of one decode step for every (sequence, KV head) unit: everything ctkvr_decode_step
@@ -168,13 +231,15 @@ struct ctkvr_index {
     int G = 0, c_max = 0, s_max = 0, l_stride = 0, page_shift = 0, units = 0;
     float scale = 0.f;
     std::vector<int32_t> ctx_lens, n_cent;
-    std::vector<void *> allocs;
+    int dev = 0;
+    PoolBlock mem{nullptr, 0};   // everything the index holds on the device
     size_t device_bytes = 0;
     // index proper
     void *centroids = nullptr;
     float *inv_norm_c = nullptr;
     int32_t *lists = nullptr;
     int32_t *d_ctx_lens = nullptr, *d_n_cent = nullptr;
+    int32_t *d_first = nullptr;   // build: [batch] first row of each sequence in q_prefill
     StepWs ws;   // decode workspace
     // dynamic centroid update
     uint32_t *d_dcu_count = nullptr;   // [2]: updates so far (device side, so that captured graphs replay correctly), blocks of the running update that are done
@@ -209,25 +274,19 @@ struct ctkvr_index {
     std::vector<hipEvent_t> events;
     int prof_max = 0, prof_step = 0;
 
-    template <typename P> int alloc(P **ptr, size_t bytes)
-    {
-        void *v = nullptr;
-        hipError_t e = hipMalloc(&v, bytes ? bytes : 16);
-        if (e != hipSuccess)
-            return fail(e == hipErrorOutOfMemory ? CTKVR_ENOMEM : CTKVR_EHIP, "hipMalloc(%zu): %s", bytes,
-                        hipGetErrorString(e));
-        allocs.push_back(v);
-        device_bytes += bytes;
-        *ptr = (P *)v;
-        return CTKVR_OK;
-    }
     ~ctkvr_index()
     {
-        for (void *v : allocs) (void)hipFree(v);
+        // the memory may be handed to another index at once: nothing on its device uses it any more after this
+        int cur = -1;
+        (void)hipGetDevice(&cur);
+        if (cur != dev) (void)hipSetDevice(dev);
+        (void)hipDeviceSynchronize();
+        pool_put(dev, mem);
         for (hipEvent_t e : events) (void)hipEventDestroy(e);
         for (hipEvent_t e : ev_join) (void)hipEventDestroy(e);
         if (ev_fork) (void)hipEventDestroy(ev_fork);
         for (hipStream_t st : side) (void)hipStreamDestroy(st);
+        if (cur != dev && cur >= 0) (void)hipSetDevice(cur);
     }
     // event slot `stage` (0 = before the first kernel) of the step being recorded
     void mark(int stage, hipStream_t st)
@@ -284,12 +343,8 @@ int check_params(const ctkvr_params *p, const int32_t *ctx_lens)
 // with base == nullptr only the size is computed.  The geometry is the index's.
 size_t carve_step_ws(StepWs &w, unsigned char *base, const ctkvr_index *ix)
 {
-    size_t off = 0;
-    auto take = [&](auto **ptr, size_t bytes) {
-        using P = std::remove_reference_t<decltype(**ptr)>;
-        if (base) *ptr = reinterpret_cast<P *>(base + off);
-        off += (std::max<size_t>(bytes, 16) + 255) & ~(size_t)255;
-    };
+    Carver cv{base};
+    auto take = [&](auto **ptr, size_t bytes) { cv.take(ptr, bytes); };
     const ctkvr_params &p = ix->p;
     const size_t U = ix->units, L = ix->l_stride, G = ix->G;
     const size_t bpu = std::max(1, ix->fused_bpu);
@@ -327,14 +382,84 @@ size_t carve_step_ws(StepWs &w, unsigned char *base, const ctkvr_index *ix)
         take(&w.slot_sure, U * bpu * (size_t)p.top_k * 4);
         take(&w.slot_bkt, U * bpu * (size_t)kFusedListCap * 16);
     }
-    return off;
+    return cv.off;
 }
 
-// allocate everything an index holds; fills the host-side geometry
-int create_index(const ctkvr_params *p, const int32_t *ctx_lens, ctkvr_index **out)
+// the single-launch kernel of this geometry, with its shared memory
+int allow_fused(const ctkvr_index *ix)
+{
+    hipError_t e = fused_set_smem(ix->p.dtype == CTKVR_BF16, ix->G, ix->fused_nt, ix->fused_smem);
+    return e == hipSuccess ? CTKVR_OK : fail(CTKVR_EHIP, "single-launch step: %s", hipGetErrorString(e));
+}
+
+// Raises a kernel's limit of dynamic shared memory to at least `bytes` on device `dev`; the runtime is asked only when
+// that is more than before.
+int want_lds(int dev, const void *fn, size_t bytes)
+{
+    static std::mutex mu;
+    static std::map<std::pair<int, const void *>, size_t> limit;
+    std::lock_guard<std::mutex> lock(mu);
+    size_t &now = limit[{dev, fn}];
+    if (bytes <= now) return CTKVR_OK;
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e != hipSuccess) return fail(CTKVR_EHIP, "index set-up: %s", hipGetErrorString(e));
+    now = bytes;
+    return CTKVR_OK;
+}
+
+template <typename T, int G> int want_decode_lds(const ctkvr_index *ix)
+{
+    const int dev = ix->dev;
+    if (ix->c_max <= 512)
+        TRY(want_lds(dev, (const void *)recall_gather_kernel<2>, ix->recall_lds));
+    else if (ix->c_max <= 2048)
+        TRY(want_lds(dev, (const void *)recall_gather_kernel<8>, ix->recall_lds));
+    else
+        TRY(want_lds(dev, (const void *)recall_gather_kernel<32>, ix->recall_lds));
+    TRY(want_lds(dev, (const void *)rerank_select_kernel<G>, std::max(ix->select_lds, ix->build_select_lds)));
+    const bool s8 = ix->attn_slices == 8;
+    if (ix->fused_lds) {
+        const void *fn = s8 ? (const void *)select_attn_kernel<T, G, 8> : (const void *)select_attn_kernel<T, G, 4>;
+        TRY(want_lds(dev, fn, ix->fused_lds));
+    }
+    return want_lds(dev, s8 ? (const void *)sparse_attn_kernel<T, G, 8> : (const void *)sparse_attn_kernel<T, G, 4>, ix->attn_lds);
+}
+
+int want_index_lds(const ctkvr_index *ix)
+{
+    const bool bf = ix->p.dtype == CTKVR_BF16;
+    switch (ix->G) {
+        case 1: return bf ? want_decode_lds<bf16_t, 1>(ix) : want_decode_lds<float, 1>(ix);
+        case 2: return bf ? want_decode_lds<bf16_t, 2>(ix) : want_decode_lds<float, 2>(ix);
+        case 4: return bf ? want_decode_lds<bf16_t, 4>(ix) : want_decode_lds<float, 4>(ix);
+        default: return bf ? want_decode_lds<bf16_t, 8>(ix) : want_decode_lds<float, 8>(ix);
+    }
+}
+
+// n host integers to device memory through kernel arguments: no staging copy, no synchronisation
+int upload_ints(int32_t *dst, const int32_t *src, int n, hipStream_t st)
+{
+    for (int at = 0; at < n; at += IntPack::kMax) {
+        IntPack pack;
+        const int m = std::min(n - at, (int)IntPack::kMax);
+        memcpy(pack.v, src + at, (size_t)m * 4);
+        put_ints_kernel<<<1, 256, 0, st>>>(dst + at, m, pack);
+    }
+    HIP_TRY(hipGetLastError());
+    return CTKVR_OK;
+}
+
+// Lays out and takes everything an index holds; fills the host-side geometry.  What a step expects to find zero is
+// cleared on `st`; so are the tables if a later step of the build leaves rows of them unwritten (clear_tables: sequences
+// with fewer than c_max centroids).
+int create_index(const ctkvr_params *p, const int32_t *ctx_lens, bool clear_tables, hipStream_t st, ctkvr_index **out)
 {
     ctkvr_index *ix = new (std::nothrow) ctkvr_index();
     if (!ix) return fail(CTKVR_ENOMEM, "host allocation failed");
+    if (hipGetDevice(&ix->dev) != hipSuccess) {
+        delete ix;
+        return fail(CTKVR_EHIP, "no current device");
+    }
     ix->p = *p;
     const int B = p->batch, h = p->n_q_heads, g = p->n_kv_heads;
     ix->G = h / g;
@@ -353,23 +478,9 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, ctkvr_index **o
     }
     const size_t es = elem_size(p->dtype);
     const size_t U = ix->units;
-    int rc = CTKVR_OK;
-    auto A = [&](auto **ptr, size_t bytes) {
-        if (rc == CTKVR_OK) rc = ix->alloc(ptr, bytes);
-    };
-    A(&ix->centroids, (size_t)B * h * ix->c_max * 128 * es);
-    A(&ix->inv_norm_c, (size_t)B * h * ix->c_max * 4);
-    A(&ix->lists, U * ix->c_max * p->list_len * 4);
-    A(&ix->d_ctx_lens, (size_t)B * 4);
-    A(&ix->d_n_cent, (size_t)B * 4);
-    A(&ix->d_dcu_count, 8);
-    A(&ix->d_err, 4);
-    A(&ix->d_prof, 64 * 8);
     {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
-            ix->num_cu = cus;
+        int cus = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ix->dev) == hipSuccess && cus > 0) ix->num_cu = cus;
     }
     ix->bitmap_words = (ix->s_max + 31) / 32;
     // The single-launch step needs all its blocks resident at once (one 1024-thread block per CU) and
@@ -408,19 +519,36 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, ctkvr_index **o
         if (!strcmp(e, "staged")) ix->decode_path = CTKVR_PATH_STAGED;
         else if (!strcmp(e, "fused") && ix->fused_bpu) ix->decode_path = CTKVR_PATH_FUSED;
     }
-    if (p->list_len != p->top_k) {
-        A(&ix->dsel, U * (size_t)p->list_len * 4);
-        A(&ix->dnsel, U * 4);
-    }
-    {
-        unsigned char *wsmem = nullptr;
-        A(&wsmem, carve_step_ws(ix->ws, nullptr, ix));
-        if (rc == CTKVR_OK) carve_step_ws(ix->ws, wsmem, ix);
-    }
+    // one allocation for all of it
+    auto lay_out = [&](unsigned char *base) {
+        // (the tables and the workspace on boundaries of 2 MB each, as an allocation of their own would be)
+        Carver cv{base};
+        cv.take(&ix->centroids, (size_t)B * h * ix->c_max * 128 * es);
+        cv.align_to((size_t)2 << 20);
+        cv.take(&ix->inv_norm_c, (size_t)B * h * ix->c_max * 4);
+        cv.align_to((size_t)2 << 20);
+        cv.take(&ix->lists, U * ix->c_max * p->list_len * 4);
+        cv.take(&ix->d_ctx_lens, (size_t)B * 4);
+        cv.take(&ix->d_n_cent, (size_t)B * 4);
+        cv.take(&ix->d_first, (size_t)B * 4);
+        cv.take(&ix->d_dcu_count, 8);
+        cv.take(&ix->d_err, 4);
+        cv.take(&ix->d_prof, 64 * 8);
+        if (p->list_len != p->top_k) {
+            cv.take(&ix->dsel, U * (size_t)p->list_len * 4);
+            cv.take(&ix->dnsel, U * 4);
+        }
+        cv.align_to((size_t)2 << 20);
+        cv.off += carve_step_ws(ix->ws, base ? base + cv.off : nullptr, ix);
+        return cv.off;
+    };
+    ix->device_bytes = lay_out(nullptr);
+    int rc = pool_get(ix->dev, ix->device_bytes, &ix->mem);
     if (rc != CTKVR_OK) {
         delete ix;
         return rc;
     }
+    lay_out((unsigned char *)ix->mem.base);
     // shared-memory plan
     ix->bitmap_words = (ix->s_max + 31) / 32;
     ix->recall_lds = ((size_t)kSelLds + p->n_probe + ix->bitmap_words) * 4;
@@ -435,12 +563,6 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, ctkvr_index **o
     if ((sel_fixed + ix->build_bits + 1) * 4 > 150 * 1024) ix->build_bits = 0;
     ix->build_select_lds = (sel_fixed + ix->build_bits + 1) * 4;
     ix->attn_lds = (size_t)p->top_k * ix->G * 4;
-    {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
-            ix->num_cu = cus;
-    }
     // The selection runs as one 1024-thread block per (sequence, KV head) and is latency-critical:
     // while there are no more such blocks than CUs, ask for over half a CU's shared memory so that
     // two never share a CU.  The recall is spread over recall_split blocks per unit.
@@ -456,76 +578,43 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, ctkvr_index **o
         delete ix;
         return fail(CTKVR_EUNSUPPORTED, "context, top_k or n_probe too large for the shared-memory plan");
     }
+    rc = want_index_lds(ix);
     hipError_t e = hipSuccess;
-    auto want = [&](const void *fn, size_t bytes) {
-        if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    };
-    want((const void *)recall_gather_kernel<2>, ix->recall_lds);
-    want((const void *)recall_gather_kernel<8>, ix->recall_lds);
-    want((const void *)recall_gather_kernel<32>, ix->recall_lds);
-    const size_t sel_b = std::max(ix->select_lds, ix->build_select_lds);
-    want((const void *)rerank_select_kernel<1>, sel_b);
-    want((const void *)rerank_select_kernel<2>, sel_b);
-    want((const void *)rerank_select_kernel<4>, sel_b);
-    want((const void *)rerank_select_kernel<8>, sel_b);
-    if (ix->fused_lds) {
-        if (p->dtype == CTKVR_BF16) {
-            want((const void *)select_attn_kernel<bf16_t, 1, 4>, ix->fused_lds);
-            want((const void *)select_attn_kernel<bf16_t, 1, 8>, ix->fused_lds);
-            want((const void *)select_attn_kernel<bf16_t, 2, 4>, ix->fused_lds);
-            want((const void *)select_attn_kernel<bf16_t, 2, 8>, ix->fused_lds);
-            want((const void *)select_attn_kernel<bf16_t, 4, 4>, ix->fused_lds);
-            want((const void *)select_attn_kernel<bf16_t, 4, 8>, ix->fused_lds);
-            want((const void *)select_attn_kernel<bf16_t, 8, 4>, ix->fused_lds);
-            want((const void *)select_attn_kernel<bf16_t, 8, 8>, ix->fused_lds);
-        } else {
-            want((const void *)select_attn_kernel<float, 1, 4>, ix->fused_lds);
-            want((const void *)select_attn_kernel<float, 1, 8>, ix->fused_lds);
-            want((const void *)select_attn_kernel<float, 2, 4>, ix->fused_lds);
-            want((const void *)select_attn_kernel<float, 2, 8>, ix->fused_lds);
-            want((const void *)select_attn_kernel<float, 4, 4>, ix->fused_lds);
-            want((const void *)select_attn_kernel<float, 4, 8>, ix->fused_lds);
-            want((const void *)select_attn_kernel<float, 8, 4>, ix->fused_lds);
-            want((const void *)select_attn_kernel<float, 8, 8>, ix->fused_lds);
-        }
+    if (rc == CTKVR_OK && ix->fused_bpu && ix->decode_path == CTKVR_PATH_FUSED) rc = allow_fused(ix);
+    if (rc == CTKVR_OK) {
+        ZeroRanges z{};
+        auto zero = [&](void *ptr, size_t words) {
+            z.p[z.n] = (uint32_t *)ptr;
+            z.words[z.n++] = words;
+        };
+        zero(ix->ws.ghist, U * (size_t)kBuckets);
+        zero(ix->d_dcu_count, 2);
+        zero(ix->d_err, 1);
+        zero(ix->d_prof, 64 * 2);
+        zero(ix->ws.bar, U * (size_t)kFusedBarriers);
+        zero(ix->ws.gbits, U * (size_t)ix->bitmap_words);
+        zero(ix->ws.srow, U * (size_t)p->top_k);   // always valid rows (see sparse_attn_kernel)
+        size_t most = 0;
+        for (int i = 0; i < z.n; ++i) most = std::max(most, z.words[i]);
+        zero_ranges_kernel<<<dim3((unsigned)std::min<size_t>(256, (most + 1023) / 1024), z.n), 256, 0, st>>>(z);
+        e = hipGetLastError();
     }
-    if (ix->fused_bpu && e == hipSuccess) e = fused_set_smem(p->dtype == CTKVR_BF16, ix->G, ix->fused_nt, ix->fused_smem);
-    if (p->dtype == CTKVR_BF16) {
-        want((const void *)sparse_attn_kernel<bf16_t, 1, 4>, ix->attn_lds);
-        want((const void *)sparse_attn_kernel<bf16_t, 1, 8>, ix->attn_lds);
-        want((const void *)sparse_attn_kernel<bf16_t, 2, 4>, ix->attn_lds);
-        want((const void *)sparse_attn_kernel<bf16_t, 2, 8>, ix->attn_lds);
-        want((const void *)sparse_attn_kernel<bf16_t, 4, 4>, ix->attn_lds);
-        want((const void *)sparse_attn_kernel<bf16_t, 4, 8>, ix->attn_lds);
-        want((const void *)sparse_attn_kernel<bf16_t, 8, 4>, ix->attn_lds);
-        want((const void *)sparse_attn_kernel<bf16_t, 8, 8>, ix->attn_lds);
-    } else {
-        want((const void *)sparse_attn_kernel<float, 1, 4>, ix->attn_lds);
-        want((const void *)sparse_attn_kernel<float, 1, 8>, ix->attn_lds);
-        want((const void *)sparse_attn_kernel<float, 2, 4>, ix->attn_lds);
-        want((const void *)sparse_attn_kernel<float, 2, 8>, ix->attn_lds);
-        want((const void *)sparse_attn_kernel<float, 4, 4>, ix->attn_lds);
-        want((const void *)sparse_attn_kernel<float, 4, 8>, ix->attn_lds);
-        want((const void *)sparse_attn_kernel<float, 8, 4>, ix->attn_lds);
-        want((const void *)sparse_attn_kernel<float, 8, 8>, ix->attn_lds);
+    if (rc == CTKVR_OK && e == hipSuccess) rc = upload_ints(ix->d_ctx_lens, ix->ctx_lens.data(), B, st);
+    if (rc == CTKVR_OK && e == hipSuccess) rc = upload_ints(ix->d_n_cent, ix->n_cent.data(), B, st);
+    if (rc == CTKVR_OK && e == hipSuccess && clear_tables && *std::min_element(ix->n_cent.begin(), ix->n_cent.end()) < ix->c_max) {
+        ZeroRanges z{};
+        z.n = 2;
+        z.p[0] = (uint32_t *)ix->lists;
+        z.words[0] = U * ix->c_max * p->list_len;
+        z.p[1] = (uint32_t *)ix->centroids;
+        z.words[1] = (size_t)B * h * ix->c_max * 128 * es / 4;
+        zero_ranges_kernel<<<dim3(1024, 2), 256, 0, st>>>(z);
+        e = hipGetLastError();
     }
-    {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
-            ix->num_cu = cus;
+    if (rc != CTKVR_OK) {
+        delete ix;
+        return rc;
     }
-    if (e == hipSuccess) e = hipMemset(ix->ws.ghist, 0, U * (size_t)kBuckets * 4);
-    if (e == hipSuccess) e = hipMemset(ix->d_dcu_count, 0, 8);
-    if (e == hipSuccess) e = hipMemset(ix->d_err, 0, 4);
-    if (e == hipSuccess) e = hipMemset(ix->d_prof, 0, 64 * 8);
-    if (e == hipSuccess) e = hipMemset(ix->ws.bar, 0, U * (size_t)kFusedBarriers * 4);
-    if (e == hipSuccess) e = hipMemset(ix->ws.gbits, 0, U * (size_t)ix->bitmap_words * 4);
-    if (e == hipSuccess) e = hipMemset(ix->ws.srow, 0, U * p->top_k * 4);   // always valid rows (see sparse_attn_kernel)
-    if (e == hipSuccess) e = hipMemcpy(ix->d_ctx_lens, ix->ctx_lens.data(), (size_t)B * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(ix->d_n_cent, ix->n_cent.data(), (size_t)B * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(ix->lists, 0, U * ix->c_max * p->list_len * 4);
-    if (e == hipSuccess) e = hipMemset(ix->centroids, 0, (size_t)B * h * ix->c_max * 128 * es);
     if (e == hipSuccess && ix->n_groups > 1) {
         e = hipEventCreateWithFlags(&ix->ev_fork, hipEventDisableTiming);
         for (int i = 1; i < ix->n_groups && e == hipSuccess; ++i) {
@@ -575,7 +664,7 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
     const bool mfma = ix->p.build_algo == CTKVR_BUILD_MFMA;
     const int total_units = ix->units * ix->c_max;
     const size_t per_unit = (size_t)ix->s_max * G * 4;
-    int chunk = (int)std::min<size_t>(total_units, std::max<size_t>(1, ((size_t)2 << 30) / per_unit));
+    int chunk = (int)std::min<size_t>(total_units, std::max<size_t>(1, ((size_t)512 << 20) / per_unit));
     chunk = std::min(chunk, 16384);
     if (mfma) {   // whole (sequence, KV head) groups per chunk; no scores are stored, only 4-byte keys
         int nbk = (int)std::max<size_t>(1, ((size_t)8 << 30) / ((size_t)ix->s_max * 4 * ix->c_max));
@@ -608,44 +697,35 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
     const bool redo_always = by_cand && getenv("CTKVR_BUILD_CANDIDATES_REDO") != nullptr;   // tests: take the redo path
     uint32_t *ksamp = nullptr, *tau = nullptr, *cursor = nullptr, *d_fail = nullptr;
     uint2 *cand = nullptr;
-    hipError_t e1 = hipSuccess, e2 = hipSuccess, e3 = hipSuccess, e4 = hipSuccess, e5 = hipSuccess;
-    auto alloc_full = [&]() {   // the buffers of the route that keeps every key
-        if (!kbuf) e3 = hipMalloc((void **)&kbuf, (size_t)chunk * ix->s_max * 4);
-        if (!ghist) e4 = hipMalloc((void **)&ghist, (size_t)chunk * kBuckets * 4);
-        return e3 == hipSuccess && e4 == hipSuccess;
+    // one block for what every chunk needs; the redo of the candidate route takes a second one when it comes to that
+    BuildScratch scratch_mem, redo_mem;
+    auto lay_out_full = [&](unsigned char *base) {   // the buffers of the route that keeps every key
+        Carver cv{base};
+        cv.take(&kbuf, (size_t)chunk * ix->s_max * 4);
+        cv.take(&ghist, (size_t)chunk * kBuckets * 4);
+        return cv.off;
     };
-    void *block = nullptr;   // candidates route: all of its buffers in one allocation, kept between builds
-    bool block_cached = false;
-    int rc = CTKVR_OK;
-    if (by_cand) {
-        // a segment per block of the statistics split: room for twice an even share, at least 256 entries
-        const size_t sizes[8] = {(size_t)chunk * G * 4, (size_t)chunk * G * 8, (size_t)chunk * G * kMaxSplits * sizeof(float2),
-                                 (size_t)chunk * sample_stride * 4, (size_t)chunk * 4, (size_t)chunk * kMaxSplits * 4, 4,
-                                 (size_t)chunk * 2 * std::max(cand_cap, 128 * kMaxSplits) * sizeof(uint2)};
-        size_t off[9] = {0};
-        for (int i = 0; i < 8; ++i) off[i + 1] = off[i] + ((sizes[i] + 255) & ~(size_t)255);
-        rc = build_scratch_get(off[8], &block, &block_cached);
-        if (rc == CTKVR_OK) {
-            unsigned char *base = (unsigned char *)block;
-            m_key = (uint32_t *)(base + off[0]);
-            S = (unsigned long long *)(base + off[1]);
-            part = (float2 *)(base + off[2]);
-            ksamp = (uint32_t *)(base + off[3]);
-            tau = (uint32_t *)(base + off[4]);
-            cursor = (uint32_t *)(base + off[5]);
-            d_fail = (uint32_t *)(base + off[6]);
-            cand = (uint2 *)(base + off[7]);
-            e5 = hipFuncSetAttribute((const void *)cand_select_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)cand_lds);
+    auto lay_out = [&](unsigned char *base) {
+        Carver cv{base};
+        cv.take(&m_key, (size_t)chunk * G * 4);
+        cv.take(&S, (size_t)chunk * G * 8);
+        if (mfma) cv.take(&part, (size_t)chunk * G * kMaxSplits * sizeof(float2));
+        if (by_cand) {
+            // a segment per block of the statistics split: room for twice an even share, at least 256 entries
+            cv.take(&ksamp, (size_t)chunk * sample_stride * 4);
+            cv.take(&tau, (size_t)chunk * 4);
+            cv.take(&cursor, (size_t)chunk * kMaxSplits * 4);
+            cv.take(&d_fail, 4);
+            cv.take(&cand, (size_t)chunk * 2 * std::max(cand_cap, 128 * kMaxSplits) * sizeof(uint2));
+        } else {
+            if (!mfma) cv.take(&z, (size_t)chunk * per_unit);
+            cv.off += lay_out_full(base ? base + cv.off : nullptr);
         }
-    } else {
-        if (!mfma) e5 = hipMalloc((void **)&z, (size_t)chunk * per_unit);
-        e1 = hipMalloc((void **)&m_key, (size_t)chunk * G * 4);
-        e2 = hipMalloc((void **)&S, (size_t)chunk * G * 8);
-        if (mfma && e5 == hipSuccess) e5 = hipMalloc((void **)&part, (size_t)chunk * G * kMaxSplits * sizeof(float2));
-        alloc_full();
-    }
-    if (rc == CTKVR_OK && (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess || e4 != hipSuccess || e5 != hipSuccess))
-        rc = fail(CTKVR_ENOMEM, "build scratch allocation failed");
+        return cv.off;
+    };
+    int rc = scratch_mem.get(ix->dev, lay_out(nullptr));
+    if (rc == CTKVR_OK) lay_out(scratch_mem.base());
+    if (rc == CTKVR_OK && by_cand) rc = want_lds(ix->dev, (const void *)cand_select_kernel, cand_lds);
     for (int u0 = 0; rc == CTKVR_OK && u0 < total_units; u0 += chunk) {
         const int nu = std::min(chunk, total_units - u0);
         Units u = decode_units(ix);
@@ -738,9 +818,10 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
                     redo = failed != 0 || redo_always;
                     if (redo) {
                         ix->build_redone++;
-                        if (!alloc_full()) {
-                            rc = fail(CTKVR_ENOMEM, "build scratch allocation failed");
-                            break;
+                        if (!kbuf) {
+                            rc = redo_mem.get(ix->dev, lay_out_full(nullptr));
+                            if (rc != CTKVR_OK) break;
+                            lay_out_full(redo_mem.base());
                         }
                         fill_u32_kernel<<<dim3((unsigned)(((size_t)nu * kBuckets + 255) / 256)), 256, 0, st>>>(ghist, 0u, (size_t)nu * kBuckets);
                     }
@@ -805,16 +886,6 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
     }
     hipError_t es = hipStreamSynchronize(st);
     if (rc == CTKVR_OK && es != hipSuccess) rc = fail(CTKVR_EHIP, "build: %s", hipGetErrorString(es));
-    if (by_cand) {
-        build_scratch_put(block, block_cached);
-    } else {
-        (void)hipFree(z);
-        (void)hipFree(m_key);
-        (void)hipFree(S);
-        (void)hipFree(part);
-    }
-    (void)hipFree(kbuf);
-    (void)hipFree(ghist);
     return rc;
 }
 
@@ -1248,9 +1319,7 @@ template <int G> int run_kmeans_g(ctkvr_index *ix, KmeansArgs ka, hipStream_t st
 {
     const int U = ix->units;
     const size_t hn_lds = (size_t)((ix->c_max + 127) & ~127) * 4;
-    hipError_t e = hipFuncSetAttribute((const void *)kmeans_assign_kernel<G>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)hn_lds);
-    if (e != hipSuccess) return fail(CTKVR_EHIP, "k-means set-up: %s", hipGetErrorString(e));
+    TRY(want_lds(ix->dev, (const void *)kmeans_assign_kernel<G>, hn_lds));
     kmeans_init_kernel<<<dim3(ix->c_max, ix->p.n_q_heads, ix->p.batch), 128, 0, st>>>(ka, G);
     for (int it = 0; it < ix->p.kmeans_iters; ++it) {
         kmeans_halfnorm_kernel<G><<<dim3((ix->c_max + 15) / 16, U), 256, 0, st>>>(ka);
@@ -1277,22 +1346,21 @@ int run_kmeans(ctkvr_index *ix, const bf16_t *q_prefill, const int32_t *d_first,
     ka.q = q_prefill;
     ka.centroids = (bf16_t *)ix->centroids;
     ka.init_pos = init_pos;
-    void *bufs[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-    const size_t sz[6] = {U * ix->c_max * 4, U * ix->s_max * 4, U * ix->c_max * 4,
-                          U * ix->c_max * 4, U * ix->c_max * 4, U * ix->s_max * 4};
-    int rc = CTKVR_OK;
-    for (int i = 0; i < 6 && rc == CTKVR_OK; ++i) {
-        hipError_t e = hipMalloc(&bufs[i], sz[i]);
-        if (e == hipSuccess && i == 2) e = hipMemsetAsync(bufs[i], 0, sz[i], st);
-        if (e != hipSuccess) rc = fail(CTKVR_ENOMEM, "k-means scratch: %s", hipGetErrorString(e));
-    }
+    BuildScratch scratch_mem;
+    auto lay_out = [&](unsigned char *base) {
+        Carver cv{base};
+        cv.take(&ka.half_norm, U * ix->c_max * 4);
+        cv.take(&ka.assign, U * ix->s_max * 4);
+        cv.take(&ka.counts, U * ix->c_max * 4);
+        cv.take(&ka.start, U * ix->c_max * 4);
+        cv.take(&ka.cursor, U * ix->c_max * 4);
+        cv.take(&ka.order, U * ix->s_max * 4);
+        return cv.off;
+    };
+    int rc = scratch_mem.get(ix->dev, lay_out(nullptr));
     if (rc == CTKVR_OK) {
-        ka.half_norm = (float *)bufs[0];
-        ka.assign = (int32_t *)bufs[1];
-        ka.counts = (uint32_t *)bufs[2];
-        ka.start = (uint32_t *)bufs[3];
-        ka.cursor = (uint32_t *)bufs[4];
-        ka.order = (int32_t *)bufs[5];
+        lay_out(scratch_mem.base());
+        fill_u32_kernel<<<dim3((unsigned)((U * ix->c_max + 255) / 256)), 256, 0, st>>>(ka.counts, 0u, U * ix->c_max);
         switch (ix->G) {
             case 1: rc = run_kmeans_g<1>(ix, ka, st); break;
             case 2: rc = run_kmeans_g<2>(ix, ka, st); break;
@@ -1302,8 +1370,6 @@ int run_kmeans(ctkvr_index *ix, const bf16_t *q_prefill, const int32_t *d_first,
     }
     hipError_t es = hipStreamSynchronize(st);
     if (rc == CTKVR_OK && es != hipSuccess) rc = fail(CTKVR_EHIP, "k-means: %s", hipGetErrorString(es));
-    for (void *b : bufs)
-        if (b) (void)hipFree(b);
     return rc;
 }
 
@@ -1446,13 +1512,10 @@ int ctkvr_build_index(const ctkvr_params *p, const void *q_prefill, const int32_
         first_row[b] = kmeans ? cu_seqlens[b] : cu_seqlens[b] + rows - C;
     }
     ctkvr_index *ix = nullptr;
-    TRY(create_index(p, ctx_lens, &ix));
     hipStream_t st = (hipStream_t)hip_stream;
-    int rc = CTKVR_OK;
-    int32_t *d_first = nullptr;
-    hipError_t e = hipMalloc((void **)&d_first, (size_t)p->batch * 4);
-    if (e == hipSuccess) e = hipMemcpy(d_first, first_row.data(), (size_t)p->batch * 4, hipMemcpyHostToDevice);
-    if (e != hipSuccess) rc = fail(CTKVR_EHIP, "build set-up: %s", hipGetErrorString(e));
+    TRY(create_index(p, ctx_lens, true, st, &ix));
+    int rc = upload_ints(ix->d_first, first_row.data(), p->batch, st);
+    const int32_t *d_first = ix->d_first;
     if (rc == CTKVR_OK) {
         dim3 grid(ix->c_max, p->n_q_heads, p->batch);
         if (kmeans) {
@@ -1472,10 +1535,9 @@ int ctkvr_build_index(const ctkvr_params *p, const void *q_prefill, const int32_
         }
     }
     if (rc == CTKVR_OK) {
-        e = hipStreamSynchronize(st);
+        hipError_t e = hipStreamSynchronize(st);
         if (e != hipSuccess) rc = fail(CTKVR_EHIP, "build: %s", hipGetErrorString(e));
     }
-    if (d_first) (void)hipFree(d_first);
     if (rc != CTKVR_OK) {
         delete ix;
         return rc;
@@ -1492,7 +1554,8 @@ int ctkvr_index_load(const ctkvr_params *p, const int32_t *ctx_lens, const void 
     TRY(check_params(p, ctx_lens));
     if (!centroids || !lists) return fail(CTKVR_EINVAL, "a required pointer is NULL");
     ctkvr_index *ix = nullptr;
-    TRY(create_index(p, ctx_lens, &ix));
+    hipStream_t st = (hipStream_t)hip_stream;
+    TRY(create_index(p, ctx_lens, false, st, &ix));
     // every id a decode step may touch must be a valid key id of its sequence
     const int g = p->n_kv_heads;
     for (int b = 0; b < p->batch; ++b)
@@ -1505,7 +1568,6 @@ int ctkvr_index_load(const ctkvr_params *p, const int32_t *ctx_lens, const void 
                         return fail(CTKVR_EINVAL, "list (%d,%d,%d)[%d] = %d is not a key id of the sequence", b, kv, j, r, l[r]);
                     }
             }
-    hipStream_t st = (hipStream_t)hip_stream;
     const size_t es = elem_size(p->dtype);
     hipError_t e = hipMemcpy(ix->centroids, centroids, (size_t)p->batch * p->n_q_heads * ix->c_max * 128 * es,
                              hipMemcpyHostToDevice);
@@ -1592,9 +1654,7 @@ int ctkvr_centroid_update(ctkvr_index *idx, const void *q, void *hip_stream)
 
 void ctkvr_free(ctkvr_index *idx)
 {
-    if (!idx) return;
-    (void)hipDeviceSynchronize();
-    delete idx;
+    delete idx;   // synchronises the index's device
 }
 
 int ctkvr_profile_enable(ctkvr_index *idx, int32_t max_steps)
@@ -1636,6 +1696,7 @@ int ctkvr_index_set_decode_path(ctkvr_index *idx, int32_t path)
     if (path == CTKVR_PATH_FUSED && !idx->fused_bpu)
         return fail(CTKVR_EUNSUPPORTED, "the single-launch step does not fit this geometry (%d units on %d CUs, or its shared memory)",
                     idx->units, idx->num_cu);
+    if (path == CTKVR_PATH_FUSED) TRY(allow_fused(idx));
     idx->decode_path = path;
     return CTKVR_OK;
 }
@@ -1645,12 +1706,9 @@ int ctkvr_release_scratch(void)
     int dev = -1;
     HIP_TRY(hipGetDevice(&dev));
     if (dev < 0 || dev >= kMaxDevices) return CTKVR_OK;
-    std::lock_guard<std::mutex> lock(g_build_mu);
-    BuildCache &c = g_build_cache[dev];
-    if (c.busy) return fail(CTKVR_EINVAL, "an index build is using the scratch");
-    if (c.base) HIP_TRY(hipFree(c.base));
-    c.base = nullptr;
-    c.bytes = 0;
+    std::lock_guard<std::mutex> lock(g_pool_mu);
+    if (g_pool_builds[dev]) return fail(CTKVR_EINVAL, "an index build is using the scratch");
+    pool_drop(dev);
     return CTKVR_OK;
 }
 

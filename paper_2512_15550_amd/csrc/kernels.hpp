@@ -75,6 +75,32 @@ __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, size_t n)
     if (i < n) p[i] = v;
 }
 
+// ranges of words cleared by one launch: grid (any, ranges)
+struct ZeroRanges {
+    static constexpr int kMax = 8;
+    uint32_t *p[kMax];
+    size_t words[kMax];
+    int n;
+};
+__global__ void zero_ranges_kernel(ZeroRanges z)
+{
+    uint32_t *p = z.p[blockIdx.y];
+    const size_t n = z.words[blockIdx.y], step = (size_t)gridDim.x * blockDim.x, n4 = n / 4;
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;   // every range starts on a 256-byte boundary
+    for (size_t i = i0; i < n4; i += step) reinterpret_cast<uint4 *>(p)[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (size_t i = 4 * n4 + i0; i < n; i += step) p[i] = 0u;
+}
+
+// integers that travel as a kernel argument
+struct IntPack {
+    static constexpr int kMax = 512;
+    int32_t v[kMax];
+};
+__global__ void put_ints_kernel(int32_t *dst, int n, IntPack pack)
+{
+    for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = pack.v[i];
+}
+
 // three ranges cleared by one launch: grid ceil((n0 + n1 + n2) / blockDim.x)
 __global__ void zero3_u32_kernel(uint32_t *p0, size_t n0, uint32_t *p1, size_t n1, uint32_t *p2, size_t n2)
 {
