@@ -216,36 +216,53 @@ __device__ __forceinline__ float ordered_value(uint32_t k)
 // ---- wave / block helpers -------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
+// Inclusive scans with DPP shifts and row broadcasts: six dependent vector instructions, where six ds_bpermute round trips
+// took 0.3 us (a block scan 1.0 us; 0.4 us in this form).  CTRLs: row_shr 1, 2, 4, 8 = 0x111, 0x112, 0x114, 0x118 (inside
+// a row of 16 lanes), row_bcast 15 and 31 = 0x142, 0x143 (a row's last lane to the next row; lane 31 to rows 2 and 3).
+template <int CTRL, int ROWS> __device__ __forceinline__ uint32_t dpp_add_u(uint32_t v)
+{
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ uint32_t row_incl_scan(uint32_t v)   // over each row of 16 lanes
+{
+    v = dpp_add_u<0x111, 0xF>(v);
+    v = dpp_add_u<0x112, 0xF>(v);
+    v = dpp_add_u<0x114, 0xF>(v);
+    return dpp_add_u<0x118, 0xF>(v);
+}
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
 {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        uint32_t t = __shfl_up(v, o);
-        if (lane_id() >= o) v += t;
-    }
-    return v;
+    v = row_incl_scan(v);
+    v = dpp_add_u<0x142, 0xA>(v);
+    return dpp_add_u<0x143, 0xC>(v);
+}
+
+// Sum over the wave, valid in lane 63 only.
+__device__ __forceinline__ uint32_t wave_sum_last(uint32_t v)
+{
+    v = dpp_add_u<0x111, 0xF>(v);
+    v = dpp_add_u<0x112, 0xF>(v);
+    v = dpp_add_u<0x114, 0xF>(v);
+    v = dpp_add_u<0x118, 0xF>(v);
+    v = dpp_add_u<0x142, 0xA>(v);
+    return dpp_add_u<0x143, 0xC>(v);
 }
 
 // Exclusive scan of one value per thread over the block; *total gets the sum.
-// s_tmp: at least NT/64 + 1 words.  Contains __syncthreads().
+// s_tmp: at least NT/64 words.  Starts with a barrier (s_tmp may just have been read) and has one more inside; every wave
+// adds up the waves before it by itself.
 template <int NT> __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *s_tmp, uint32_t *total)
 {
     constexpr int NW = NT / 64;
-    uint32_t inc = wave_incl_scan(v);
-    int w = threadIdx.x >> 6;
+    static_assert(NW <= 16, "the waves' totals are scanned in one row of 16 lanes");
+    const uint32_t inc = wave_incl_scan(v);
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), ln = lane_id();
     __syncthreads();
-    if (lane_id() == 63) s_tmp[w] = inc;
+    if (ln == 63) s_tmp[w] = inc;
     __syncthreads();
-    if (w == 0) {
-        uint32_t t = (lane_id() < NW) ? s_tmp[lane_id()] : 0u;
-        uint32_t ti = wave_incl_scan(t);
-        if (lane_id() < NW) s_tmp[lane_id()] = ti - t;
-        if (lane_id() == NW - 1) s_tmp[NW] = ti;
-    }
-    __syncthreads();
-    uint32_t r = s_tmp[w] + inc - v;
-    *total = s_tmp[NW];
-    return r;
+    const uint32_t t = s_tmp[ln & (NW - 1)], ti = row_incl_scan((ln & 15) < NW ? t : 0u);
+    *total = (uint32_t)__builtin_amdgcn_readlane((int)ti, NW - 1);
+    return (uint32_t)__builtin_amdgcn_readlane((int)(ti - t), w) + inc - v;
 }
 
 // Two exclusive scans at once (same barriers as one).  s_tmp: 2 * (NT / 64 + 1) words.
@@ -254,24 +271,18 @@ __device__ __forceinline__ void block_excl_scan2(uint32_t va, uint32_t vb, uint3
 {
     constexpr int NW = NT / 64;
     const uint32_t ia = wave_incl_scan(va), ib = wave_incl_scan(vb);
-    const int w = threadIdx.x >> 6;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), ln = lane_id();
     __syncthreads();
-    if (lane_id() == 63) {
+    if (ln == 63) {
         s_tmp[w] = ia;
         s_tmp[NW + 1 + w] = ib;
     }
     __syncthreads();
-    if (w == 0) {
-        const uint32_t ta = (lane_id() < NW) ? s_tmp[lane_id()] : 0u, tb = (lane_id() < NW) ? s_tmp[NW + 1 + lane_id()] : 0u;
-        const uint32_t sa = wave_incl_scan(ta), sb = wave_incl_scan(tb);
-        if (lane_id() < NW) {
-            s_tmp[lane_id()] = sa - ta;
-            s_tmp[NW + 1 + lane_id()] = sb - tb;
-        }
-    }
-    __syncthreads();
-    ra = s_tmp[w] + ia - va;
-    rb = s_tmp[NW + 1 + w] + ib - vb;
+    const uint32_t ta = s_tmp[ln & (NW - 1)], tb = s_tmp[NW + 1 + (ln & (NW - 1))];
+    const bool in = (ln & 15) < NW;
+    const uint32_t sa = row_incl_scan(in ? ta : 0u) - ta, sb = row_incl_scan(in ? tb : 0u) - tb;
+    ra = (uint32_t)__builtin_amdgcn_readlane((int)sa, w) + ia - va;
+    rb = (uint32_t)__builtin_amdgcn_readlane((int)sb, w) + ib - vb;
 }
 
 // ---- block-wide top-k selection ---------------------------------------------------
