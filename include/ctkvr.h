@@ -228,8 +228,8 @@ int ctkvr_index_last_candidates(const ctkvr_index *idx, int32_t *dst_host);
  * gather into a bitmap, 2 bitmap expansion into the recalled id list fused with key scoring,
  * 3 softmax denominators, 4 ranking keys + their histogram, 5 chip-wide pass over the
  * ranking keys (bitmap + deciding bucket's list), 6 rerank select, 7 sparse attention.  For
- * small batches 6 and 7 are one launch, timed as stage 7 (stage 6 then reads as the cost of
- * an event pair).  While timing is enabled a ninth, empty kernel follows (stage 8): its
+ * small batches 3 to 7 are one launch, for medium ones 6 and 7, timed as stage 7 (the others then read as
+ * the cost of an event pair).  While timing is enabled a ninth, empty kernel follows (stage 8): its
  * figure is what a pair of events costs around a kernel that does nothing. */
 #define CTKVR_N_STAGES 9
 /* After this call every decode step on `idx` records a HIP event before its first
@@ -254,6 +254,10 @@ int ctkvr_profile_collect(ctkvr_index *idx, float *ms_host, int32_t capacity_ste
  *                                  (default: by rank for small batches)
  *   CTKVR_KEYCLASS           = 0|1 ranking-key histogram and classification as two launches / one
  *                                  (default: one for small batches)
+ *   CTKVR_TAIL               = 0|1 what follows the scoring as separate launches / as one (default: one for small batches,
+ *                                  unless CTKVR_KEYCLASS is set)
+ *   CTKVR_TAIL_SPINS         = n   how often a block of that launch looks for its siblings' sums before it takes all of them
+ *                                  itself (0..256, default 256)
  *   CTKVR_FUSED_THREADS      = 256|1024  block size of the single-launch step
  *   CTKVR_BUILD_CANDIDATES   = 0|1 see ctkvr_index_build_route
  *   CTKVR_BUILD_CANDIDATES_REDO    (set: the candidate route also hands every chunk back; tests)

@@ -213,7 +213,7 @@ struct StepWs {
     uint32_t *crow = nullptr, *srow = nullptr, *kbuf = nullptr, *gbits = nullptr, *ghist = nullptr;
     uint32_t *gbm = nullptr, *gcur = nullptr, *ginfo = nullptr;   // classify_kernel's outputs
     uint2 *glist = nullptr;
-    unsigned long long *S = nullptr;
+    unsigned long long *S = nullptr, *xs = nullptr;   // xs: tail_kernel's exchange slots
     float *z = nullptr, *zsel = nullptr;
     float *win = nullptr;   // window_attn_kernel's partial results
     uint32_t *m_key = nullptr;
@@ -247,6 +247,9 @@ struct ctkvr_index {
     bool have_step = false;
     size_t recall_lds = 0, select_lds = 0, attn_lds = 0, build_select_lds = 0;
     size_t fused_lds = 0;   // non-zero: selection and attention run as one launch (select_attn_kernel)
+    size_t tail_lds = 0;    // non-zero: everything after the scoring can run as one launch (tail_kernel)
+    int tail_spins = kTailSpins;
+    int tail = -1;          // ... : -1 chosen per batch, 0 never, 1 whenever possible
     int keyclass = -1;      // key histogram + classification as one launch: -1 chosen per batch, 0 never, 1 always
     int attn_slices = 4;    // blocks per unit of the attention (head-dimension slices): 8 while each has a CU of its own
     int build_redone = 0;   // chunks of the matrix-core list build that the candidate route had to hand back
@@ -367,6 +370,7 @@ size_t carve_step_ws(StepWs &w, unsigned char *base, const ctkvr_index *ix)
     take(&w.win, U * (size_t)kWinSplit * G * (2 + 128) * 4);
     take(&w.srow, U * p.top_k * 4);
     take(&w.S, U * G * 8);
+    take(&w.xs, U * G * 8 * 8);
     take(&w.sel, U * p.top_k * 4);
     take(&w.zsel, U * p.top_k * G * 4);
     take(&w.nsel, U * 4);
@@ -421,6 +425,10 @@ template <typename T, int G> int want_decode_lds(const ctkvr_index *ix)
     if (ix->fused_lds) {
         const void *fn = s8 ? (const void *)select_attn_kernel<T, G, 8> : (const void *)select_attn_kernel<T, G, 4>;
         TRY(want_lds(dev, fn, ix->fused_lds));
+    }
+    if (ix->tail_lds) {
+        const void *fn = s8 ? (const void *)tail_kernel<T, G, 8> : (const void *)tail_kernel<T, G, 4>;
+        TRY(want_lds(dev, fn, ix->tail_lds));
     }
     return want_lds(dev, s8 ? (const void *)sparse_attn_kernel<T, G, 8> : (const void *)sparse_attn_kernel<T, G, 4>, ix->attn_lds);
 }
@@ -513,6 +521,8 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, bool clear_tabl
         if (const char *e = getenv("CTKVR_XCD_UNITS")) ix->xcd_units = atoi(e) != 0;
         if (const char *e = getenv("CTKVR_SCORE_BY_RANK")) ix->score_by_rank = atoi(e) != 0;
         if (const char *e = getenv("CTKVR_KEYCLASS")) ix->keyclass = atoi(e) != 0;
+        if (const char *e = getenv("CTKVR_TAIL")) ix->tail = atoi(e) != 0;
+        if (const char *e = getenv("CTKVR_TAIL_SPINS")) ix->tail_spins = std::max(0, std::min((int)kTailSpins, atoi(e)));
         ix->n_groups = ng;
     }
     if (const char *e = getenv("CTKVR_DECODE_PATH")) {
@@ -573,6 +583,8 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, bool clear_tabl
         const size_t fw = ((size_t)kSelLds + 2 * kListCap + ix->sel_bits + p->top_k + (size_t)p->top_k * ix->G) * 4;
         ix->attn_slices = 8 * (int)U <= ix->num_cu ? 8 : 4;
         if (4 * (int)U <= ix->num_cu && fw <= 150 * 1024) ix->fused_lds = fw;
+        const size_t tw = tail_smem_words(ix->sel_bits, p->top_k, ix->G) * 4;
+        if (4 * (int)U <= ix->num_cu && ix->sel_bits && tw <= 136 * 1024) ix->tail_lds = tw;
     }
     if (ix->recall_lds > 150 * 1024 || ix->select_lds > 150 * 1024 || ix->attn_lds > 128 * 1024) {
         delete ix;
@@ -944,6 +956,7 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         w.win += (size_t)u0 * kWinSplit * Gs * (2 + 128);
         w.srow += (size_t)u0 * p.top_k;
         w.S += u0 * Gs;
+        w.xs += u0 * Gs * ix->attn_slices;
         w.sel += (size_t)u0 * p.top_k;
         w.zsel += (size_t)u0 * p.top_k * Gs;
         w.nsel += u0;
@@ -1059,6 +1072,13 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     ca.h = p.n_q_heads;
     ca.c_max = ix->c_max;
     ca.by_xcd = by_xcd_all;
+    // Everything after the scoring as one launch (tail_kernel): for small batches, whose step is a chain of latencies
+    // (every block of a unit then walks all of the unit's recalled keys, work that is repeated 4 or 8 times), unless one
+    // of the forms it replaces is asked for.
+    const bool tail = ix->tail_lds && ix->keyclass < 0 &&
+                      (ix->tail < 0 ? (long long)ix->l_stride * U <= 2048ll * ix->num_cu : ix->tail != 0);
+    ca.xs = w.xs;
+    ca.n_xs = tail ? ix->attn_slices * G : 0;
     if (whole) ix->mark(0, st);
     centroid_cos_kernel<T, G><<<dim3((ix->c_max + 15) / 16, U), 256, 0, st>>>(ca);
     if (whole) ix->mark(1, st);
@@ -1103,7 +1123,7 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     sa.out_ncand = out_ncand;
     sa.z = w.z;
     sa.m_key = w.m_key;
-    sa.ghist = w.ghist;
+    sa.ghist = tail ? nullptr : w.ghist;
     sa.scale = ix->scale;
     sa.by_xcd = by_xcd_all;
     {
@@ -1134,6 +1154,60 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         if (!launched) recall_score_kernel<T, G, false><<<dim3(nbx, U), 256, 0, st>>>(sa);
     }
     if (whole) ix->mark(3, st);
+
+    AttnArgs aa{};
+    aa.v_pages = v_pages;
+    aa.g = p.n_kv_heads;
+    aa.h = p.n_q_heads;
+    aa.top_k = p.top_k;
+    aa.srow = w.srow;
+    aa.nsel = w.nsel;
+    aa.zsel = w.zsel;
+    aa.out = out;
+    aa.out_lse = out_lse;
+    aa.win = window ? w.win : nullptr;
+    aa.m_key = w.m_key;
+    auto finish = [&]() -> int {
+        if (whole) ix->mark(8, st);
+        if (whole && ix->prof_step < ix->prof_max) {   // a null kernel between two events: what the bracketing itself costs
+            fill_u32_kernel<<<dim3(1), 64, 0, st>>>((uint32_t *)w.nsel, 0u, 0);
+            ix->mark(9, st);
+            ix->prof_step++;
+        }
+        HIP_TRY(hipGetLastError());
+        ix->have_step = &w_all == &ix->ws;   // the update reads the index's own workspace
+        return CTKVR_OK;
+    };
+    if (tail) {
+        TailArgs ta{};
+        ta.ctx_lens = d_ctx_lens;
+        ta.ncand = w.ncand;
+        ta.cand = w.cand;
+        ta.crow = w.crow;
+        ta.l_stride = ix->l_stride;
+        ta.top_k = p.top_k;
+        ta.bits_words = ix->sel_bits;
+        ta.z = w.z;
+        ta.m_key = w.m_key;
+        ta.xs = w.xs;
+        ta.spins = ix->tail_spins;
+        ta.gbits = w.gbits;
+        ta.bitmap_words = ix->bitmap_words;
+        // the update ranks once more, with another budget, from the ranking keys
+        ta.kbuf = p.list_len != p.top_k && &w_all == &ix->ws ? w.kbuf : nullptr;
+        ta.sel = w.sel;
+        ta.nsel = w.nsel;
+        ta.out_sel = out_sel;
+        ta.at = aa;
+        if (whole)
+            for (int k = 4; k <= 7; ++k) ix->mark(k, st);   // stages of this launch: an event pair's cost each
+        if (ix->attn_slices == 8)
+            tail_kernel<T, G, 8><<<dim3(8 * U), kTailThreads, ix->tail_lds, st>>>(ta);
+        else
+            tail_kernel<T, G, 4><<<dim3(4 * U), kTailThreads, ix->tail_lds, st>>>(ta);
+        if (&w_all == &ix->ws) ix->last_step_fused = true;   // no 2048-bucket histogram is left for a second ranking
+        return finish();
+    }
 
     DenomArgs da{};
     da.u = u;
@@ -1234,18 +1308,6 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     se.zsel = w.zsel;
     se.nsel = w.nsel;
     se.out_sel = out_sel;
-    AttnArgs aa{};
-    aa.v_pages = v_pages;
-    aa.g = p.n_kv_heads;
-    aa.h = p.n_q_heads;
-    aa.top_k = p.top_k;
-    aa.srow = w.srow;
-    aa.nsel = w.nsel;
-    aa.zsel = w.zsel;
-    aa.out = out;
-    aa.out_lse = out_lse;
-    aa.win = window ? w.win : nullptr;
-    aa.m_key = w.m_key;
     if (ix->fused_lds) {
         if (whole) ix->mark(7, st);   // no separate selection launch: its stage reads as the cost of an event pair
         if (ix->attn_slices == 8)
@@ -1260,15 +1322,7 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         else
             sparse_attn_kernel<T, G, 4><<<dim3(4 * U), 1024, ix->attn_lds, st>>>(aa);
     }
-    if (whole) ix->mark(8, st);
-    if (whole && ix->prof_step < ix->prof_max) {   // a null kernel between two events: what the bracketing itself costs
-        fill_u32_kernel<<<dim3(1), 64, 0, st>>>((uint32_t *)w.nsel, 0u, 0);
-        if (whole) ix->mark(9, st);
-    }
-    if (whole && ix->prof_step < ix->prof_max) ix->prof_step++;
-    HIP_TRY(hipGetLastError());
-    ix->have_step = &w_all == &ix->ws;   // the update reads the index's own workspace
-    return CTKVR_OK;
+    return finish();
 }
 
 // One step for the whole batch: a single group on the caller's stream, or (several sequences, no per-kernel

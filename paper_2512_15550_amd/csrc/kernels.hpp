@@ -152,6 +152,8 @@ struct CosArgs {
     float *cos;               // [batch*g][c_max]
     uint32_t *m_key;          // [batch*g][G]  cleared here
     unsigned long long *S;    // [batch*g][G]  cleared here
+    unsigned long long *xs;   // [batch*g][n_xs] the tail kernel's exchange slots, cleared here (n_xs <= 64; 0: none)
+    int n_xs;
     int g, h, c_max;
     int by_xcd;               // blocks -> (unit, block of the unit) by unit_block_of
 };
@@ -167,6 +169,7 @@ template <typename T, int G> __global__ __launch_bounds__(256) void centroid_cos
         a.m_key[ul * G + tid] = 0u;
         a.S[ul * G + tid] = 0ull;
     }
+    if (bx == 0 && tid < a.n_xs) a.xs[ul * a.n_xs + tid] = 0ull;
     CTKVR_STAMP(0);
     const int tile0 = bx * 16;
     if (tile0 >= C) return;
@@ -604,7 +607,7 @@ struct RecallScoreArgs {
     int32_t *out_ncand;       // optional copy for the caller
     float *z;                 // [units][l_stride][G]
     uint32_t *m_key;          // [units][G] ordered-key running max (atomicMax)
-    uint32_t *ghist;          // [units][kBuckets] key histogram, cleared here for keyhist
+    uint32_t *ghist;          // optional: [units][kBuckets] key histogram, cleared here for keyhist
     float scale;
     int stream_k;             // the keys of all sequences exceed what the memory-side cache holds: load them non-temporal
     int by_rank;              // how the bitmap is split over a unit's blocks
@@ -634,7 +637,8 @@ template <typename T, int G, bool WIN> __global__ __launch_bounds__(256) void re
     CTKVR_STAMP_BLK(6);
     const int s_len = a.ctx_lens[b];
     const int W = (s_len + 31) >> 5;
-    for (int w = bx * 256 + tid; w < kBuckets; w += (uint32_t)a.nbx * 256) a.ghist[(size_t)ul * kBuckets + w] = 0u;
+    if (a.ghist)
+        for (int w = bx * 256 + tid; w < kBuckets; w += (uint32_t)a.nbx * 256) a.ghist[(size_t)ul * kBuckets + w] = 0u;
     const uint32_t *gb = a.gbits + (size_t)ul * a.bitmap_words;
     if (tid < G) s_max[tid] = 0u;
     uint32_t r0, r1;   // the block's ranks
@@ -2100,12 +2104,13 @@ template <int SL> __device__ __forceinline__ void attn_block_of(int &ul, int &sl
     }
 }
 
-// The attention of one (unit, slice).  row_of(t) = physical row of the t-th selected key (valid for
+// The attention of one (unit, slice), NT threads.  row_of(t) = physical row of the t-th selected key (valid for
 // every t < top_k), z_of(t, zv) = its G logits, nsel_of() = how many keys were selected; nsel_of is
-// asked only after the first value rows have been requested.  s_p: top_k*G floats of shared memory.
-template <typename T, int G, int SL, typename RowFn, typename ZFn, typename NFn>
+// asked only after the first value rows have been requested.  s_p: top_k*G floats of shared memory (z_of may read from it).
+template <typename T, int G, int SL, int NU, int NT, typename RowFn, typename ZFn, typename NFn>
 __device__ __forceinline__ void attend_unit(const AttnArgs &a, int ul, int slice, float *s_p, RowFn row_of, ZFn z_of, NFn nsel_of)
 {
+    constexpr int NW = NT / 64;
     constexpr int kSliceDims = kD / SL;            // head dimensions per block
     constexpr int kSliceLanes = kSliceDims / 8;    // lanes that share a value row (8 dimensions each)
     constexpr int kSliceRows = 64 / kSliceLanes;   // rows per wave and pass
@@ -2113,9 +2118,10 @@ __device__ __forceinline__ void attend_unit(const AttnArgs &a, int ul, int slice
     // A wave's 64 lanes are kSliceLanes parts of kSliceRows rows: lane l works on row (l mod kSliceRows) of the
     // pass and on the 8 values (l / kSliceRows) of the slice.  Every 16-lane row of a wave thus belongs to one part and
     // is one producer of partial sums; kProd of them per part in the block.
-    constexpr int PASS = 16 * kSliceRows, NU = 4, kProd = kSliceRows;   // rows per pass of the block, passes in flight
+    constexpr int PASS = NW * kSliceRows, kProd = NW * kSliceRows / 16;   // rows per pass of the block; NU passes in flight
     __shared__ float s_red[kProd][G];
-    __shared__ float s_m[G], s_l[G];
+    __shared__ float s_m[G];
+    __shared__ uint32_t s_big[NW];
     __shared__ float s_o[kProd][G][kSliceDims];
     const int b = ul / a.g, kv = ul - b * a.g;
     const int tid = threadIdx.x, wv = tid >> 6, ln = tid & 63;
@@ -2161,6 +2167,7 @@ __device__ __forceinline__ void attend_unit(const AttnArgs &a, int ul, int slice
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[hh][e] = 0.0f;
     }
+    if (tid < G) s_m[tid] = ordered_value(a.m_key[ul * G + tid]);
     for (int r0 = 0; r0 < nsel; r0 += NU * PASS) {
         if (r0 > 0) {
 #pragma unroll
@@ -2180,7 +2187,7 @@ __device__ __forceinline__ void attend_unit(const AttnArgs &a, int ul, int slice
 #pragma unroll
                 for (int hh = 0; hh < G; ++hh) {
                     const float pw = __expf(zq[u][hh] - mref[hh]);
-                    lsum[hh] += quad == 0 ? pw : 0.0f;
+                    lsum[hh] += pw;
 #pragma unroll
                     for (int e = 0; e < 8; ++e) acc[hh][e] = __fmaf_rn(pw, vx[e], acc[hh][e]);
                 }
@@ -2188,35 +2195,44 @@ __device__ __forceinline__ void attend_unit(const AttnArgs &a, int ul, int slice
         }
     }
     CTKVR_STAMP(48);
+    // sums over the lanes of each 16-lane row (a DPP butterfly), one barrier for denominators and outputs together
+    auto hand_over = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int hh = 0; hh < G; ++hh) {
-        const float v = group16_sum(lsum[hh]);   // the lanes of the other parts hold zeros
-        if ((ln & 15) == 0 && quad == 0) s_red[prod][hh] = v;
+        for (int hh = 0; hh < G; ++hh)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[hh][e] = group16_sum(acc[hh][e]);
+#pragma unroll
+        for (int hh = 0; hh < G; ++hh) lsum[hh] = group16_sum(lsum[hh]);
+        if ((ln & 15) == 0) {
+#pragma unroll
+            for (int hh = 0; hh < G; ++hh)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s_o[prod][hh][quad * 8 + e] = acc[hh][e];
+            if (quad == 0) {
+#pragma unroll
+                for (int hh = 0; hh < G; ++hh) s_red[prod][hh] = lsum[hh];
+            }
+        }
+    };
+    {
+        uint32_t big = 0;   // heads of which this wave has seen a weight that is not vanishing
+#pragma unroll
+        for (int hh = 0; hh < G; ++hh) big |= (uint32_t)(__ballot(lsum[hh] >= 1e-30f) != 0ull) << hh;
+        if (ln == 0) s_big[wv] = big;
     }
-    __syncthreads();
-    if (tid < G) {
-        float v = 0.0f;
-#pragma unroll
-        for (int w = 0; w < kProd; ++w) v += s_red[w][tid];
-        s_l[tid] = v;
-        s_m[tid] = mref[0];
-#pragma unroll
-        for (int c = 1; c < G; ++c)
-            if (tid == c) s_m[tid] = mref[c];
-    }
+    hand_over();
     __syncthreads();
     CTKVR_STAMP(45);
-    bool underflow = false;   // a head whose selected logits all lie far below its maximum: the same for every thread
+    uint32_t big = 0;
 #pragma unroll
-    for (int hh = 0; hh < G; ++hh) underflow |= !(s_l[hh] >= 1e-30f);
-    if (underflow) {
+    for (int w = 0; w < NW; ++w) big |= s_big[w];
+    if (big != (1u << G) - 1u) {   // uniform: a head whose selected logits all lie far below its maximum
         // two passes instead: the selected keys' own maxima first, then weights relative to them
         __syncthreads();
-        // softmax statistics over the selected keys, per head
         float mx[G];
 #pragma unroll
         for (int hh = 0; hh < G; ++hh) mx[hh] = -__builtin_huge_valf();
-        for (int t = tid; t < nsel; t += 1024) {
+        for (int t = tid; t < nsel; t += NT) {
             float zv[G];
             z_of(t, zv);
 #pragma unroll
@@ -2225,7 +2241,6 @@ __device__ __forceinline__ void attend_unit(const AttnArgs &a, int ul, int slice
                 mx[hh] = fmaxf(mx[hh], zv[hh]);
             }
         }
-        CTKVR_STAMP(48);
 #pragma unroll
         for (int hh = 0; hh < G; ++hh) {
             float v = mx[hh];
@@ -2234,93 +2249,59 @@ __device__ __forceinline__ void attend_unit(const AttnArgs &a, int ul, int slice
             if (ln == 0) s_red[wv][hh] = v;
         }
         __syncthreads();
-        CTKVR_STAMP(49);
         if (tid < G) {
             float v = s_red[0][tid];
 #pragma unroll
-            for (int w = 1; w < 16; ++w) v = fmaxf(v, s_red[w][tid]);
+            for (int w = 1; w < NW; ++w) v = fmaxf(v, s_red[w][tid]);
             s_m[tid] = v;
         }
         __syncthreads();
-        float sm[G];
 #pragma unroll
         for (int hh = 0; hh < G; ++hh) {
             mx[hh] = s_m[hh];
-            sm[hh] = 0.0f;
-        }
-        for (int t = tid; t < nsel; t += 1024) {
-#pragma unroll
-            for (int hh = 0; hh < G; ++hh) {
-                float p = __expf(s_p[t * G + hh] - mx[hh]);
-                s_p[t * G + hh] = p;
-                sm[hh] += p;
-            }
-        }
-        CTKVR_STAMP(50);
-#pragma unroll
-        for (int hh = 0; hh < G; ++hh) {
-            float v = sm[hh];
-#pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-            if (ln == 0) s_red[wv][hh] = v;
-        }
-        __syncthreads();
-        if (tid < G) {
-            float v = 0.0f;
-#pragma unroll
-            for (int w = 0; w < 16; ++w) v += s_red[w][tid];
-            s_l[tid] = v;
-        }
-        __syncthreads();
-        CTKVR_STAMP(45);
-        // weighted sum of the value rows
-#pragma unroll
-        for (int hh = 0; hh < G; ++hh)
+            lsum[hh] = 0.0f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[hh][e] = 0.0f;
+        }
+        // weighted sum of the value rows
         for (int r0 = 0; r0 < nsel; r0 += NU * PASS) {
-            {
 #pragma unroll
-                for (int u = 0; u < NU; ++u) vrow[u] = row_of(min(r0 + u * PASS + rin, a.top_k - 1));
+            for (int u = 0; u < NU; ++u) vrow[u] = row_of(min(r0 + u * PASS + rin, a.top_k - 1));
 #pragma unroll
-                for (int u = 0; u < NU; ++u) cv[u] = load_chunk(V + (size_t)vrow[u] * kD, 0);
-            }
+            for (int u = 0; u < NU; ++u) cv[u] = load_chunk(V + (size_t)vrow[u] * kD, 0);
 #pragma unroll
             for (int u = 0; u < NU; ++u) {
                 int t = r0 + u * PASS + rin;
                 if (t < nsel) {
-                    float vx[8];
+                    float vx[8], zv[G];
                     unpack(cv[u], vx);
-                    float pv[G];
-                    load_z<G>(s_p, t, pv);
+                    load_z<G>(s_p, t, zv);
 #pragma unroll
-                    for (int hh = 0; hh < G; ++hh)
+                    for (int hh = 0; hh < G; ++hh) {
+                        const float pw = __expf(zv[hh] - mx[hh]);
+                        lsum[hh] += pw;
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) acc[hh][e] = __fmaf_rn(pv[hh], vx[e], acc[hh][e]);
+                        for (int e = 0; e < 8; ++e) acc[hh][e] = __fmaf_rn(pw, vx[e], acc[hh][e]);
+                    }
                 }
             }
         }
+        __syncthreads();
+        hand_over();
+        __syncthreads();
     }
-    // sum inside each 16-lane row (a DPP butterfly), then over the part's kProd rows of the block in order
-#pragma unroll
-    for (int hh = 0; hh < G; ++hh)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[hh][e] = group16_sum(acc[hh][e]);
-    if ((ln & 15) == 0) {
-#pragma unroll
-        for (int hh = 0; hh < G; ++hh)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) s_o[prod][hh][quad * 8 + e] = acc[hh][e];
-    }
-    __syncthreads();
     CTKVR_STAMP(46);
+    // then over the part's kProd rows of the block, in order
     if (tid < G * kSliceDims) {
         int hh = tid / kSliceDims, e = tid % kSliceDims;
-        float v = 0.0f;
+        float v = 0.0f, l = 0.0f;
 #pragma unroll
-        for (int w = 0; w < kProd; ++w) v += s_o[w][hh][e];
+        for (int w = 0; w < kProd; ++w) {
+            v += s_o[w][hh][e];
+            l += s_red[w][hh];
+        }
         float lse;
-        const float o = merge_window<G>(a.win, ul, hh, slice * kSliceDims + e, v, s_m[hh], s_l[hh], lse);
+        const float o = merge_window<G>(a.win, ul, hh, slice * kSliceDims + e, v, s_m[hh], l, lse);
         a.out[((size_t)b * a.h + kv * G + hh) * kD + slice * kSliceDims + e] = o;
         if (slice == 0 && e == 0 && a.out_lse) a.out_lse[(size_t)b * a.h + kv * G + hh] = lse;
     }
@@ -2335,7 +2316,7 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(1024) void spa
     attn_block_of<SL>(ul, slice);
     const uint32_t *rb = a.srow + (size_t)ul * a.top_k;
     const float *zb = a.zsel + (size_t)ul * a.top_k * G;
-    attend_unit<T, G, SL>(a, ul, slice, s_p, [&](int t) { return rb[t]; }, [&](int t, float(&zv)[G]) { load_z<G>(zb, t, zv); },
+    attend_unit<T, G, SL, (G == 8 ? 2 : 4), 1024>(a, ul, slice, s_p, [&](int t) { return rb[t]; }, [&](int t, float(&zv)[G]) { load_z<G>(zb, t, zv); },
                       [&]() { return a.nsel[ul]; });
 }
 
@@ -2375,12 +2356,434 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(1024) void sel
     // positions beyond n repeat the last pick; when nothing was recalled every position reads slot 0 of
     // the row table and then names row 0 of the pool (selects, not a branch: the four row numbers of a
     // pass are then requested together)
-    attend_unit<T, G, SL>(a, ul, slice, s_p,
+    attend_unit<T, G, SL, (G == 8 ? 2 : 4), 1024>(a, ul, slice, s_p,
                       [&](int t) {
                           const uint32_t r = rb[n > 0 ? s_idx[min(t, n - 1)] : 0];
                           return n > 0 ? r : 0u;
                       },
                       [&](int t, float(&zv)[G]) { load_z<G>(zb, n > 0 ? s_idx[min(t, n - 1)] : 0, zv); }, [&]() { return n; });
+}
+
+// ------------------------------------------------------------------------------
+// Algorithm 2 lines 5b-9 in ONE launch, for small batches: denominators, ranking, selection and attention.  Three
+// launches (denom, keyclass, select_attn) spent 24 us on it at 32K tokens / 8 KV heads, of which about 9 are the gaps, ramps
+// and drains of the launches and most of the rest round trips of intermediate results through memory.  SL blocks per unit,
+// each of 512 threads and with a CU of its own (every instruction that all waves of a block execute costs it issue slots: eight
+// waves, not sixteen); block x of a unit
+//   1. sums the denominators of its share of the unit's recalled keys (every SL-th group of 64) and leaves them in its
+//      exchange slots: one 64-bit word per head, the sum and a valid bit in one atomic store, so that no fence is needed;
+//      the first wave then reads the slots of all SL blocks until they are valid -- the only thing that crosses blocks,
+//      about 0.7 us against 3 us for a launch.  The wait is bounded (kTailSpins reads): a block that gives up takes the sums of
+//      ALL keys itself, the same integers, so that no result and no progress depends on the other blocks being resident;
+//   2. forms the ranking keys of ALL the unit's recalled keys (their scores and rows were requested before the exchange; up to
+//      16 per thread stay in registers), their histogram, the deciding bucket, the bitmap of the picks and their positions,
+//      all in shared memory -- the same work in every block instead of a hand-over;
+//   3. attends over the picks, for its 128 / SL head dimensions.
+// grid SL*batch*g; dynamic shared memory: tail_smem_words.  Same integers as the separate kernels.
+// ------------------------------------------------------------------------------
+constexpr int kTailSpins = 256;    // reads of the slots before a block gives up (each about 0.5 us)
+constexpr int kTailKeys = 8192;    // recalled keys whose scores, rows and ranking keys a block keeps in registers
+constexpr int kTailThreads = 512;
+
+struct TailArgs {
+    const int32_t *ctx_lens, *ncand, *cand;
+    const uint32_t *crow;
+    int l_stride, top_k, bits_words;
+    const float *z;
+    const uint32_t *m_key;
+    unsigned long long *xs;     // [units][SL][G], zero on entry
+    int spins;                  // reads of the slots before a block gives up (kTailSpins)
+    uint32_t *gbits;            // the recall bitmap, cleared here for the next step
+    int bitmap_words;
+    uint32_t *kbuf;             // optional: [units][l_stride] the ranking keys (for the dynamic centroid update)
+    int32_t *sel, *nsel, *out_sel;
+    AttnArgs at;
+};
+
+__host__ __device__ __forceinline__ size_t tail_smem_words(int bits_words, int top_k, int G)
+{
+    return (size_t)kSelLds + 2 * kListCap + bits_words + 2 * (size_t)((top_k + 3) & ~3) + (size_t)top_k * G;
+}
+
+template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) void tail_kernel(TailArgs a)
+{
+    extern __shared__ __align__(16) uint32_t smem[];
+    constexpr int NT = kTailThreads, NW = NT / 64, KPT = kTailKeys / NT;
+    static_assert(kTailKeys / 64 == 128, "the picks' positions: two groups of 64 ids per lane");
+    __shared__ unsigned long long s_acc[NW][G];
+    __shared__ float s_ls[G];
+    __shared__ uint32_t s_res[4];      // deciding bucket, keys wanted from it, its population, list cursor
+    __shared__ uint32_t s_ok;
+    const int kpad = (a.top_k + 3) & ~3;
+    uint32_t *s_hist = smem;                               // kSelLds
+    uint32_t *s_list = smem + kSelLds;                     // 2 * kListCap
+    uint32_t *s_bits = s_list + 2 * kListCap;              // bits_words: two bitmaps over the recalled ids
+    uint2 *s_pick = (uint2 *)(s_bits + a.bits_words);      // top_k: (position among the recalled keys, row) of the picks, ascending
+    float *s_p = (float *)(s_pick + kpad);                 // top_k * G: their scores
+    int ul, slice;
+    attn_block_of<SL>(ul, slice);
+    const int tid = threadIdx.x, ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const float *zb = a.z + (size_t)ul * a.l_stride * G;
+    const uint32_t *rb = a.crow + (size_t)ul * a.l_stride;
+    CTKVR_STAMP(60);
+    // requested at once, before L is known (slots beyond L hold stale values that are never used)
+    constexpr int PRE = 2;                        // rounds of this block's share of the denominators
+    const int i0 = (wv * SL + slice) * 64 + ln;   // the share: every SL-th group of 64
+    float zo[PRE][G], zr[KPT][G];
+#pragma unroll
+    for (int q = 0; q < PRE; ++q) load_z<G>(zb, min(i0 + q * SL * NT, a.l_stride - 1), zo[q]);
+    const int L = a.ncand[ul];
+    float m[G];
+#pragma unroll
+    for (int hh = 0; hh < G; ++hh) m[hh] = ordered_value(a.m_key[ul * G + hh]);
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) load_z<G>(zb, min(q * NT + tid, a.l_stride - 1), zr[q]);
+    uint32_t rr[KPT];
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) rr[q] = rb[min(q * NT + tid, a.l_stride - 1)];
+    for (int w = tid; w < kBuckets / 4; w += NT) reinterpret_cast<uint4 *>(s_hist)[w] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid == 0) s_res[3] = 0u;
+    {
+        const int W = (a.ctx_lens[ul / a.at.g] + 31) >> 5;
+        for (int w = slice * NT + tid; w < W; w += SL * NT) a.gbits[(size_t)ul * a.bitmap_words + w] = 0u;
+    }
+    CTKVR_STAMP(61);
+    // --- denominators ---------------------------------------------------------------------------------
+    // sums of the terms i = first, first + step, ... (the first PRE of them in zv) as one 64-bit word per wave and head
+    auto sum_terms = [&](const int first, const int step, float(&zv)[PRE][G]) __attribute__((always_inline)) {
+        uint32_t shi[G], slo[G];
+#pragma unroll
+        for (int hh = 0; hh < G; ++hh) shi[hh] = slo[hh] = 0u;
+        auto add = [&](const bool ok, const float(&x)[G]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int hh = 0; hh < G; ++hh) {
+                uint32_t hi, lo;
+                exp_fixed40_parts(x[hh] - m[hh], hi, lo);
+                lo = slo[hh] + (ok ? lo : 0u);             // < 2^25
+                shi[hh] += (ok ? hi : 0u) + (lo >> 24);
+                slo[hh] = lo & 0xffffffu;
+            }
+        };
+#pragma unroll
+        for (int q = 0; q < PRE; ++q)
+            if (first - ln + q * step < L) add(first + q * step < L, zv[q]);   // wave-uniform
+        for (int i = first + PRE * step; i - ln < L; i += step) {
+            load_z<G>(zb, min(i, L - 1), zv[0]);
+            add(i < L, zv[0]);
+        }
+        // hi <= 2^16 per term; at most 2^9 terms per lane where the block takes its share only (contexts up to 2^20), so that
+        // a wave's sum fits 32 bits; the sum of all terms by one block is put together from halves
+#pragma unroll
+        for (int hh = 0; hh < G; ++hh) {
+            const uint32_t l = wave_sum_last(slo[hh]);
+            if (step == NT) {
+                const uint32_t h0 = wave_sum_last(shi[hh] & 0xffffu), h1 = wave_sum_last(shi[hh] >> 16);
+                if (ln == 63) s_acc[wv][hh] = ((unsigned long long)h1 << 40) + ((unsigned long long)h0 << 24) + l;
+            } else {
+                const uint32_t h = wave_sum_last(shi[hh]);
+                if (ln == 63) s_acc[wv][hh] = ((unsigned long long)h << 24) + l;
+            }
+        }
+    };
+    sum_terms(i0, SL * NT, zo);
+    CTKVR_STAMP(62);
+    __syncthreads();
+    if (wv == 0) {
+        constexpr unsigned long long kValid = 1ull << 63;   // a sum is below 2^20 * 2^40
+        unsigned long long *xs = a.xs + (size_t)ul * SL * G;
+        if (ln < G) {
+            unsigned long long v = 0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) v += s_acc[w][ln];
+            __hip_atomic_store(&xs[slice * G + ln], v | kValid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        unsigned long long v = kValid;
+        bool all = false;
+        for (int it = 0; it < a.spins && !all; ++it) {
+            if (ln < SL * G) v = __hip_atomic_load(&xs[ln], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            all = __all((v & kValid) != 0ull);
+        }
+        CTKVR_STAMP(63);
+        v &= ~kValid;
+#pragma unroll
+        for (int o = G; o < SL * G; o <<= 1) v += __shfl_xor(v, o);
+        if (ln < G) s_ls[ln] = (float)log_fixed40(v);
+        if (ln == 0) s_ok = all ? 1u : 0u;
+    }
+    __syncthreads();
+    CTKVR_STAMP(64);
+    if (!s_ok) {   // (uniform) a sibling is late: all terms here
+        float zv[PRE][G];
+#pragma unroll
+        for (int q = 0; q < PRE; ++q) load_z<G>(zb, min(q * NT + tid, a.l_stride - 1), zv[q]);
+        sum_terms(tid, NT, zv);
+        __syncthreads();
+        if (tid < G) {
+            unsigned long long v = 0;
+            for (int w = 0; w < NW; ++w) v += s_acc[w][tid];
+            s_ls[tid] = (float)log_fixed40(v);
+        }
+        __syncthreads();
+    }
+    float ls[G];
+#pragma unroll
+    for (int hh = 0; hh < G; ++hh) ls[hh] = s_ls[hh];
+    // --- ranking keys, histogram, deciding bucket -----------------------------------------------------------
+    auto key_of = [&](const float(&zv)[G]) __attribute__((always_inline)) {
+        float best = (zv[0] - m[0]) - ls[0];
+#pragma unroll
+        for (int hh = 1; hh < G; ++hh) best = fmaxf(best, (zv[hh] - m[hh]) - ls[hh]);
+        return fmaxf(best, -3.0e38f);   // (above the -inf of the slots beyond L)
+    };
+    // key_bucket(ordered_key(x)), from the key as a float
+    auto bucket_of = [&](float x) __attribute__((always_inline)) {
+        return (uint32_t)__builtin_amdgcn_fmed3f(x * -32.0f, 0.0f, (float)(kBuckets - 1));
+    };
+    float kreg[KPT];
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+        kreg[q] = key_of(zr[q]);
+        if (q * NT + tid >= L) kreg[q] = -__builtin_huge_valf();
+    }
+    // f(group of 64 ids, key) for the groups of this wave beyond the first kTailKeys ids, whose keys are formed again
+    auto for_far = [&](auto f) __attribute__((always_inline)) {
+        for (int gq = KPT * NW + wv; gq * 64 < L; gq += NW) {
+            float zv[G];
+            load_z<G>(zb, min(gq * 64 + ln, L - 1), zv);
+            const float kk = key_of(zv);
+            f(gq, gq * 64 + ln < L ? kk : -__builtin_huge_valf());
+        }
+    };
+    CTKVR_STAMP(65);
+    if (a.kbuf) {
+        uint32_t *kb = a.kbuf + (size_t)ul * a.l_stride;
+        auto put = [&](int gq, float kk) __attribute__((always_inline)) {
+            if (gq % SL == slice && gq * 64 + ln < L) kb[gq * 64 + ln] = ordered_key(kk);
+        };
+#pragma unroll
+        for (int q = 0; q < KPT; ++q) put(q * NW + wv, kreg[q]);
+        for_far(put);
+    }
+    CTKVR_STAMP(66);
+    const bool near = L <= kTailKeys;   // uniform
+    int n = L;
+    if (a.top_k >= L) {   // every recalled key is kept
+        for (int i = tid; i < L; i += NT) {
+            float zv[G];
+            load_z<G>(zb, i, zv);
+            s_pick[i] = make_uint2((uint32_t)i, rb[i]);
+            store_z<G>(s_p, i, zv);
+        }
+        __syncthreads();
+    } else {
+        n = a.top_k;
+        // the last bucket (everything below the histogram's range, often most keys) is not counted: L minus the others
+        const float floor_k = -(float)(kBuckets - 1) / 32.0f;
+        // (no branch: lanes that do not count add to a word of their own)
+        auto count = [&](int, float kk) __attribute__((always_inline)) {
+            uint32_t *bin = &s_hist[bucket_of(kk)];
+            bin = kk > floor_k ? bin : s_list + tid;
+            atomicAdd(bin, 1u);
+        };
+#pragma unroll
+        for (int q = 0; q < KPT; ++q) {
+            if (q % 4 == 0 && (q * NW + wv) * 64 >= L) break;
+            count(q, kreg[q]);
+        }
+        for_far(count);
+        __syncthreads();
+        CTKVR_STAMP(67);
+        uint32_t *s_scan = s_hist + 2048 + 4;
+        {
+            constexpr int BPT = kBuckets / NT;   // buckets per thread, in descending key order
+            static_assert(BPT == 4, "one 16-byte read");
+            const uint4 c4 = reinterpret_cast<const uint4 *>(s_hist)[tid];
+            const uint32_t c[4] = {c4.x, c4.y, c4.z, c4.w};
+            uint32_t tot;
+            uint32_t before = block_excl_scan<NT>((c[0] + c[1]) + (c[2] + c[3]), s_scan, &tot);
+            const uint32_t want = (uint32_t)a.top_k;
+            if (want > tot) {   // (uniform) the last bucket decides
+                if (tid == 0) {
+                    s_res[0] = (uint32_t)(kBuckets - 1);
+                    s_res[1] = want - tot;
+                    s_res[2] = (uint32_t)L - tot;
+                }
+            } else
+#pragma unroll
+            for (int q = 0; q < BPT; ++q) {
+                if (before < want && want <= before + c[q]) {
+                    s_res[0] = (uint32_t)(BPT * tid + q);
+                    s_res[1] = want - before;
+                    s_res[2] = c[q];
+                }
+                before += c[q];
+            }
+        }
+        __syncthreads();
+        CTKVR_STAMP(68);
+        const uint32_t bkt = s_res[0], rem = s_res[1], nb = s_res[2];
+        // the deciding bucket as an interval of keys: x > hi is above it, lo < x <= hi in it (exact: x * 32 is)
+        const float hi_k = bkt == 0u ? __builtin_huge_valf() : -(float)bkt / 32.0f;
+        const float lo_k = bkt == (uint32_t)(kBuckets - 1) ? -__builtin_huge_valf() : -(float)(bkt + 1u) / 32.0f;
+        auto emit = [&](int pos, int i) __attribute__((always_inline)) { s_pick[pos].x = (uint32_t)i; };
+        bool placed = false;   // rows and scores are with the positions already
+        if (nb <= (uint32_t)kListCap) {
+            const int nw32 = 2 * ((L + 63) >> 6);
+            uint32_t *s_gt = s_bits, *s_eq = s_bits + nw32;
+            uint2 *l_ent = reinterpret_cast<uint2 *>(s_list);
+            const bool few = nb <= (uint32_t)NT / 2;   // ranked by all-pairs comparison: ids decide between equal keys
+            uint32_t *s_rank = s_hist;     // (everyone has read the histogram)
+            if (tid < NT / 2) s_rank[tid] = 0u;
+            auto list = [&](uint64_t listed, uint32_t at, float kk, int i) __attribute__((always_inline)) {
+                const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(listed >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)listed, at));
+                if (__builtin_amdgcn_inverse_ballot_w64(listed)) l_ent[pos] = make_uint2(ordered_key(kk), (uint32_t)i);
+            };
+            // the wave's verdicts first, then one cursor bump for all its entries of the deciding bucket
+            uint64_t in[KPT];
+            uint64_t mine_gt = 0;   // lane q: the verdicts of group q
+            uint32_t n_in = 0;
+#pragma unroll
+            for (int q = 0; q < KPT; ++q) {
+                const uint64_t above = __ballot(kreg[q] > hi_k);
+                in[q] = __ballot(kreg[q] > lo_k) & ~above;
+                n_in += (uint32_t)__popcll(in[q]);
+                mine_gt = ln == q ? above : mine_gt;
+            }
+            if (ln < KPT && (ln * NW + wv) * 64 < L)
+                *reinterpret_cast<uint2 *>(s_gt + 2 * (ln * NW + wv)) = make_uint2((uint32_t)mine_gt, (uint32_t)(mine_gt >> 32));
+            if (n_in) {
+                uint32_t at0 = 0;
+                if (ln == 0) at0 = atomicAdd(&s_res[3], n_in);
+                at0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)at0);
+#pragma unroll
+                for (int q = 0; q < KPT; ++q)
+                    if (in[q]) {
+                        list(in[q], at0, kreg[q], (q * NW + wv) * 64 + ln);
+                        at0 += (uint32_t)__popcll(in[q]);
+                    }
+            }
+            for_far([&](int gq, float kk) __attribute__((always_inline)) {
+                const uint64_t above = __ballot(kk > hi_k);
+                const uint64_t listed = __ballot(kk > lo_k) & ~above;
+                if (ln == 0) *reinterpret_cast<uint2 *>(s_gt + 2 * gq) = make_uint2((uint32_t)above, (uint32_t)(above >> 32));
+                if (listed) {
+                    uint32_t at1 = 0;
+                    if (ln == 0) at1 = atomicAdd(&s_res[3], (uint32_t)__popcll(listed));
+                    list(listed, (uint32_t)__builtin_amdgcn_readfirstlane((int)at1), kk, gq * 64 + ln);
+                }
+            });
+            if (!few)
+                for (int w = tid; w < nw32; w += NT) s_eq[w] = 0u;
+            __syncthreads();
+            CTKVR_STAMP(69);
+            if (few) {
+                uint32_t cap = 64;
+                while (cap < nb) cap <<= 1;
+                const uint32_t parts = (uint32_t)NT / cap, e = (uint32_t)tid & (cap - 1u), part = (uint32_t)tid / cap;
+                if (e < nb) {
+                    const uint2 me = l_ent[e];
+                    uint32_t rank = 0;
+                    for (uint32_t f = part; f < nb; f += parts) {
+                        const uint2 o = l_ent[f];
+                        rank += (o.x > me.x) || (o.x == me.x && o.y < me.y);
+                    }
+                    atomicAdd(&s_rank[e], rank);
+                }
+                __syncthreads();
+                CTKVR_STAMP(70);
+                if ((uint32_t)tid < nb && s_rank[tid] < rem) {
+                    const uint32_t id = l_ent[tid].y;
+                    atomicOr(&s_gt[id >> 5], 1u << (id & 31u));
+                }
+                __syncthreads();
+                CTKVR_STAMP(71);
+                if (near) {
+                    // every wave counts the whole bitmap (two groups of 64 ids per lane), scans it by itself, and places its
+                    // own groups' picks with their rows and scores, all of which it holds in registers
+                    uint4 w4 = make_uint4(0u, 0u, 0u, 0u);
+                    if (4 * ln < nw32) w4 = *reinterpret_cast<const uint4 *>(s_gt + 4 * ln);
+                    if (4 * ln + 2 >= nw32) w4.z = w4.w = 0u;
+                    const uint32_t c0 = (uint32_t)(__popc(w4.x) + __popc(w4.y)), c1 = (uint32_t)(__popc(w4.z) + __popc(w4.w));
+                    const uint32_t ex = wave_incl_scan(c0 + c1) - c0 - c1;
+                    const uint32_t first = (wv & 1) ? ex + c0 : ex;
+                    const uint32_t mlo = (wv & 1) ? w4.z : w4.x, mhi = (wv & 1) ? w4.w : w4.y;
+                    static_assert(NW % 2 == 0, "a wave's groups are all even or all odd");
+#pragma unroll
+                    for (int q = 0; q < KPT; ++q) {
+                        const int gq = q * NW + wv, src = gq >> 1;
+                        if (q % 4 == 0 && gq * 64 >= L) break;
+                        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)mlo, src);
+                        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)mhi, src);
+                        const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)first, src);
+                        const uint32_t pos = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, base));
+                        if (__builtin_amdgcn_inverse_ballot_w64(((uint64_t)hi << 32) | lo)) {
+                            s_pick[pos] = make_uint2((uint32_t)(gq * 64 + ln), rr[q]);
+                            store_z<G>(s_p, (int)pos, zr[q]);
+                        }
+                    }
+                    placed = true;
+                } else {
+                    // thread t owns the bytes [t bpt, (t + 1) bpt) of the bitmap: count, scan, emit in ascending order
+                    const unsigned char *bytes = reinterpret_cast<const unsigned char *>(s_gt);
+                    const int nbyte = nw32 * 4, bpt = (nbyte + NT - 1) / NT;
+                    const int b0 = min(nbyte, tid * bpt), b1 = min(nbyte, b0 + bpt);
+                    uint32_t cnt = 0;
+                    for (int w = b0; w < b1; ++w) cnt += (uint32_t)__popc((uint32_t)bytes[w]);
+                    uint32_t tot;
+                    uint32_t pos = block_excl_scan<NT>(cnt, s_scan, &tot);
+                    for (int w = b0; w < b1; ++w) {
+                        uint32_t mm = bytes[w];
+                        while (mm) {
+                            const int bit = __ffs((int)mm) - 1;
+                            mm &= mm - 1u;
+                            emit((int)pos++, w * 8 + bit);
+                        }
+                    }
+                }
+            } else {
+                block_resolve_emit<NT>(nb, rem, L, s_hist, s_gt, s_eq, l_ent, emit);
+            }
+        } else {   // a crowded deciding bucket (equal keys, or keys below the histogram's range)
+            block_select_topk<NT, 0>(
+                [&](int i) {
+                    float zv[G];
+                    load_z<G>(zb, i, zv);
+                    return ordered_key(key_of(zv));
+                },
+                L, a.top_k, emit, s_hist);
+        }
+        __syncthreads();
+        if (!placed) {   // uniform
+            for (int pos = tid; pos < n; pos += NT) {
+                const int i = (int)s_pick[pos].x;
+                float zv[G];
+                load_z<G>(zb, i, zv);
+                s_pick[pos].y = rb[i];
+                store_z<G>(s_p, pos, zv);
+            }
+            __syncthreads();
+        }
+    }
+    // --- the picks: their ids (a share per block), then the attention over them --------------------------------
+    const int per = (a.top_k + SL - 1) / SL, p0 = slice * per, p1 = min(a.top_k, p0 + per);
+    const int32_t *cb = a.cand + (size_t)ul * a.l_stride;
+    auto put_ids = [&](int pos, int t) __attribute__((always_inline)) {
+        a.sel[(size_t)ul * a.top_k + pos] = t;
+        if (a.out_sel) a.out_sel[(size_t)ul * a.top_k + pos] = t;
+    };
+    int my_id = -1;   // requested ahead of the value rows, stored after them
+    if (p0 + tid < p1 && p0 + tid < n) my_id = cb[s_pick[p0 + tid].x];
+    CTKVR_STAMP(72);
+    // positions beyond n repeat the last pick; when nothing was recalled they name row 0 of the pool
+    attend_unit<T, G, SL, 4, NT>(a.at, ul, slice, s_p,
+                          [&](int t) {
+                              const uint32_t r = s_pick[max(min(t, n - 1), 0)].y;
+                              return n > 0 ? r : 0u;
+                          },
+                          [&](int t, float(&zv)[G]) { load_z<G>(s_p, max(min(t, n - 1), 0), zv); }, [&]() { return n; });
+    if (p0 + tid < p1) put_ids(p0 + tid, my_id);
+    for (int pos = p0 + NT + tid; pos < p1; pos += NT) put_ids(pos, pos < n ? cb[s_pick[pos].x] : -1);
+    if (slice == 0 && tid == 0) a.nsel[ul] = n;
 }
 
 // ------------------------------------------------------------------------------
