@@ -247,6 +247,7 @@ struct ctkvr_index {
     bool have_step = false;
     size_t recall_lds = 0, select_lds = 0, attn_lds = 0, build_select_lds = 0;
     size_t fused_lds = 0;   // non-zero: selection and attention run as one launch (select_attn_kernel)
+    size_t dcu_lds = 0;     // non-zero: the update's ranking with a budget of its own runs as one launch (dcu_select_kernel)
     size_t tail_lds = 0;    // non-zero: everything after the scoring can run as one launch (tail_kernel)
     int tail_spins = kTailSpins;
     int tail = -1;          // ... : -1 chosen per batch, 0 never, 1 whenever possible
@@ -262,7 +263,6 @@ struct ctkvr_index {
     // single-launch step (decode_fused_kernel): blocks per unit (0: the geometry does not allow it), its shared memory,
     // the path in use (CTKVR_PATH_*), the sticky error word and the phase stamps
     int fused_bpu = 0, fused_nt = 1024, fused_stage = 0, decode_path = CTKVR_PATH_AUTO;
-    bool last_step_fused = false;   // the last step on the index's own workspace left no 2048-bucket key histogram
     size_t fused_smem = 0;
     uint32_t *d_err = nullptr;
     long long *d_prof = nullptr;
@@ -426,6 +426,7 @@ template <typename T, int G> int want_decode_lds(const ctkvr_index *ix)
         const void *fn = s8 ? (const void *)select_attn_kernel<T, G, 8> : (const void *)select_attn_kernel<T, G, 4>;
         TRY(want_lds(dev, fn, ix->fused_lds));
     }
+    if (ix->dcu_lds) TRY(want_lds(dev, (const void *)dcu_select_kernel<T>, ix->dcu_lds));
     if (ix->tail_lds) {
         const void *fn = s8 ? (const void *)tail_kernel<T, G, 8> : (const void *)tail_kernel<T, G, 4>;
         TRY(want_lds(dev, fn, ix->tail_lds));
@@ -584,6 +585,8 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, bool clear_tabl
         ix->attn_slices = 8 * (int)U <= ix->num_cu ? 8 : 4;
         if (4 * (int)U <= ix->num_cu && fw <= 150 * 1024) ix->fused_lds = fw;
         const size_t tw = tail_smem_words(ix->sel_bits, p->top_k, ix->G) * 4;
+        const size_t dw = ((size_t)kSelLds + 2 * kListCap + ix->sel_bits) * 4;
+        if (ix->sel_bits && p->list_len != p->top_k) ix->dcu_lds = dw;
         if (4 * (int)U <= ix->num_cu && ix->sel_bits && tw <= 136 * 1024) ix->tail_lds = tw;
     }
     if (ix->recall_lds > 150 * 1024 || ix->select_lds > 150 * 1024 || ix->attn_lds > 128 * 1024) {
@@ -1056,10 +1059,8 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         }
         HIP_TRY(hipGetLastError());
         ix->have_step = &w_all == &ix->ws;
-        ix->last_step_fused = true;
         return CTKVR_OK;
     }
-    ix->last_step_fused = false;
     CosArgs ca{};
     ca.q = q;
     ca.centroids = cen;
@@ -1205,7 +1206,6 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
             tail_kernel<T, G, 8><<<dim3(8 * U), kTailThreads, ix->tail_lds, st>>>(ta);
         else
             tail_kernel<T, G, 4><<<dim3(4 * U), kTailThreads, ix->tail_lds, st>>>(ta);
-        if (&w_all == &ix->ws) ix->last_step_fused = true;   // no 2048-bucket histogram is left for a second ranking
         return finish();
     }
 
@@ -1247,7 +1247,6 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         kc.by_xcd = by_xcd;
         keyclass_kernel<G><<<dim3(std::max(1, std::min((ix->l_stride + 4095) / 4096, (2 * ix->num_cu + U - 1) / U)), U), 1024, 0, st>>>(kc);
         if (whole) ix->mark(5, st);
-        if (&w_all == &ix->ws) ix->last_step_fused = true;   // no 2048-bucket histogram is left for a second ranking
     } else {
     KeyArgs ka{};
     ka.u = u;
@@ -1449,9 +1448,19 @@ template <typename T, int G> int update_launch(ctkvr_index *ix, const void *q, h
         da.src = ix->ws.sel;
         da.nsrc = ix->ws.nsel;
         da.src_stride = p.top_k;
-    } else {                       // the same ranking once more, with budget rho
+    } else if (ix->dcu_lds) {      // the same ranking once more, with budget rho
+        DcuSelectArgs ds{};
+        ds.d = da;
+        ds.ncand = ix->ws.ncand;
+        ds.cand = ix->ws.cand;
+        ds.kbuf = ix->ws.kbuf;
+        ds.l_stride = ix->l_stride;
+        dcu_select_kernel<T><<<dim3(U), kTailThreads, ix->dcu_lds, st>>>(ds);
+        HIP_TRY(hipGetLastError());
+        ix->have_step = false;
+        return CTKVR_OK;
+    } else {                       // ... by a block that keeps no bitmap of the recalled keys (they do not fit)
         Units u = decode_units(ix);
-        const int chunks = (ix->l_stride + 1023) / 1024;
         SelectArgs se{};
         se.u = u;
         se.ctx_lens = ix->d_ctx_lens;
@@ -1467,43 +1476,6 @@ template <typename T, int G> int update_launch(ctkvr_index *ix, const void *q, h
         se.sel = ix->dsel;
         se.nsel = ix->dnsel;
         se.ids_only = 1;
-        if (ix->sel_bits && ix->last_step_fused) {
-            // the single launch leaves the ranking keys but not their 2048-bucket histogram: taken here
-            fill_u32_kernel<<<dim3((unsigned)(((size_t)U * kBuckets + 255) / 256)), 256, 0, st>>>(ix->ws.ghist, 0u, (size_t)U * kBuckets);
-            KeyArgs ka{};
-            ka.u = u;
-            ka.ctx_lens = ix->d_ctx_lens;
-            ka.ncand = ix->ws.ncand;
-            ka.l_stride = ix->l_stride;
-            ka.z = nullptr;
-            ka.m_key = ix->ws.m_key;
-            ka.S = ix->ws.S;
-            ka.kbuf = ix->ws.kbuf;
-            ka.ghist = ix->ws.ghist;
-            ka.gcur = ix->ws.gcur;
-            keyhist_kernel<G><<<dim3(std::max(1, std::min((ix->l_stride + 4095) / 4096, (2 * ix->num_cu + U - 1) / U)), U), 1024, 0, st>>>(ka);
-        }
-        if (ix->sel_bits) {
-            fill_u32_kernel<<<dim3((U + 255) / 256), 256, 0, st>>>(ix->ws.gcur, 0u, (size_t)U);
-            ClassifyArgs ca{};
-            ca.u = u;
-            ca.ctx_lens = ix->d_ctx_lens;
-            ca.ncand = ix->ws.ncand;
-            ca.l_stride = ix->l_stride;
-            ca.top_k = p.list_len;
-            ca.kbuf = ix->ws.kbuf;
-            ca.ghist = ix->ws.ghist;
-            ca.bits_stride = 2 * ((ix->l_stride + 63) / 64);
-            ca.gbm = ix->ws.gbm;
-            ca.glist = ix->ws.glist;
-            ca.gcur = ix->ws.gcur;
-            ca.ginfo = ix->ws.ginfo;
-            classify_kernel<<<dim3(std::max(1, std::min(chunks, (4 * ix->num_cu + U - 1) / U)), U), 256, 0, st>>>(ca);
-            se.gbm = ix->ws.gbm;
-            se.glist = ix->ws.glist;
-            se.ginfo = ix->ws.ginfo;
-            se.bits_stride = ca.bits_stride;
-        }
         rerank_select_kernel<G><<<dim3(U), 1024, ix->select_lds, st>>>(se);
         da.src = ix->dsel;
         da.nsrc = ix->dnsel;

@@ -2365,6 +2365,189 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(1024) void sel
 }
 
 // ------------------------------------------------------------------------------
+// The top_k largest of L > top_k ranking keys (ties: lowest positions), by one block of NT threads: the keys of positions
+// (q NT/64 + wave) 64 + lane sit in kreg[q] of their thread (-inf beyond L), those beyond KPT NT come from for_far (f(group of
+// 64 positions, key) for the groups of the calling wave).  Histogram over key buckets in shared memory, the deciding
+// bucket, a bitmap of the positions above it, that bucket's own keys ranked against each other, and the picks in
+// ascending order: either place(q, group, rank) for the lane's own key in kreg[q], and the function returns true, or
+// emit(rank, position) by any thread, and it returns false.  s_hist: kSelLds words whose first kBuckets are zero; s_list: 2 kListCap;
+// s_bits: 4 ceil(L / 64); s_res: 4, s_res[3] zero.  The caller places a barrier before and after.
+// key(position) = the key's ordered image, for a crowded deciding bucket (all keys are then walked again).
+// ------------------------------------------------------------------------------
+template <int NT, int KPT, typename FarFn, typename PlaceFn, typename EmitFn, typename KeyFn>
+__device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int L, const int top_k, FarFn for_far, PlaceFn place,
+                                            EmitFn emit, KeyFn key, uint32_t *s_hist, uint32_t *s_list, uint32_t *s_bits, uint32_t *s_res)
+{
+    constexpr int NW = NT / 64;
+    static_assert(KPT * NW <= 128, "the picks' ranks: two groups of 64 positions per lane");
+    const int tid = threadIdx.x, ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // key_bucket(ordered_key(x)), from the key as a float
+    auto bucket_of = [&](float x) __attribute__((always_inline)) {
+        return (uint32_t)__builtin_amdgcn_fmed3f(x * -32.0f, 0.0f, (float)(kBuckets - 1));
+    };
+    // the last bucket (everything below the histogram's range, often most keys) is not counted: L minus the others
+    const float floor_k = -(float)(kBuckets - 1) / 32.0f;
+    // (no branch: lanes that do not count add to a word of their own)
+    auto count = [&](int, float kk) __attribute__((always_inline)) {
+        uint32_t *bin = &s_hist[bucket_of(kk)];
+        bin = kk > floor_k ? bin : s_list + tid;
+        atomicAdd(bin, 1u);
+    };
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+        if (q % 4 == 0 && (q * NW + wv) * 64 >= L) break;
+        count(q, kreg[q]);
+    }
+    for_far(count);
+    __syncthreads();
+    uint32_t *s_scan = s_hist + 2048 + 4;
+    {
+        constexpr int BPT = kBuckets / NT;   // buckets per thread, in descending key order
+        static_assert(BPT == 4, "one 16-byte read");
+        const uint4 c4 = reinterpret_cast<const uint4 *>(s_hist)[tid];
+        const uint32_t c[4] = {c4.x, c4.y, c4.z, c4.w};
+        uint32_t tot;
+        uint32_t before = block_excl_scan<NT>((c[0] + c[1]) + (c[2] + c[3]), s_scan, &tot);
+        const uint32_t want = (uint32_t)top_k;
+        if (want > tot) {   // (uniform) the last bucket decides
+            if (tid == 0) {
+                s_res[0] = (uint32_t)(kBuckets - 1);
+                s_res[1] = want - tot;
+                s_res[2] = (uint32_t)L - tot;
+            }
+        } else
+#pragma unroll
+        for (int q = 0; q < BPT; ++q) {
+            if (before < want && want <= before + c[q]) {
+                s_res[0] = (uint32_t)(BPT * tid + q);
+                s_res[1] = want - before;
+                s_res[2] = c[q];
+            }
+            before += c[q];
+        }
+    }
+    __syncthreads();
+    const uint32_t bkt = s_res[0], rem = s_res[1], nb = s_res[2];
+    // the deciding bucket as an interval of keys: x > hi is above it, lo < x <= hi in it (exact: x * 32 is)
+    const float hi_k = bkt == 0u ? __builtin_huge_valf() : -(float)bkt / 32.0f;
+    const float lo_k = bkt == (uint32_t)(kBuckets - 1) ? -__builtin_huge_valf() : -(float)(bkt + 1u) / 32.0f;
+    if (nb <= (uint32_t)kListCap) {
+        const int nw32 = 2 * ((L + 63) >> 6);
+        uint32_t *s_gt = s_bits, *s_eq = s_bits + nw32;
+        uint2 *l_ent = reinterpret_cast<uint2 *>(s_list);
+        const bool few = nb <= (uint32_t)NT / 2;   // ranked by all-pairs comparison: ids decide between equal keys
+        uint32_t *s_rank = s_hist;     // (everyone has read the histogram)
+        if (tid < NT / 2) s_rank[tid] = 0u;
+        auto list = [&](uint64_t listed, uint32_t at, float kk, int i) __attribute__((always_inline)) {
+            const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(listed >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)listed, at));
+            if (__builtin_amdgcn_inverse_ballot_w64(listed)) l_ent[pos] = make_uint2(ordered_key(kk), (uint32_t)i);
+        };
+        // the wave's verdicts first, then one cursor bump for all its entries of the deciding bucket
+        uint64_t in[KPT];
+        uint64_t mine_gt = 0;   // lane q: the verdicts of group q
+        uint32_t n_in = 0;
+#pragma unroll
+        for (int q = 0; q < KPT; ++q) {
+            const uint64_t above = __ballot(kreg[q] > hi_k);
+            in[q] = __ballot(kreg[q] > lo_k) & ~above;
+            n_in += (uint32_t)__popcll(in[q]);
+            mine_gt = ln == q ? above : mine_gt;
+        }
+        if (ln < KPT && (ln * NW + wv) * 64 < L)
+            *reinterpret_cast<uint2 *>(s_gt + 2 * (ln * NW + wv)) = make_uint2((uint32_t)mine_gt, (uint32_t)(mine_gt >> 32));
+        if (n_in) {
+            uint32_t at0 = 0;
+            if (ln == 0) at0 = atomicAdd(&s_res[3], n_in);
+            at0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)at0);
+#pragma unroll
+            for (int q = 0; q < KPT; ++q)
+                if (in[q]) {
+                    list(in[q], at0, kreg[q], (q * NW + wv) * 64 + ln);
+                    at0 += (uint32_t)__popcll(in[q]);
+                }
+        }
+        for_far([&](int gq, float kk) __attribute__((always_inline)) {
+            const uint64_t above = __ballot(kk > hi_k);
+            const uint64_t listed = __ballot(kk > lo_k) & ~above;
+            if (ln == 0) *reinterpret_cast<uint2 *>(s_gt + 2 * gq) = make_uint2((uint32_t)above, (uint32_t)(above >> 32));
+            if (listed) {
+                uint32_t at1 = 0;
+                if (ln == 0) at1 = atomicAdd(&s_res[3], (uint32_t)__popcll(listed));
+                list(listed, (uint32_t)__builtin_amdgcn_readfirstlane((int)at1), kk, gq * 64 + ln);
+            }
+        });
+        if (!few)
+            for (int w = tid; w < nw32; w += NT) s_eq[w] = 0u;
+        __syncthreads();
+        if (few) {
+            uint32_t cap = 64;
+            while (cap < nb) cap <<= 1;
+            const uint32_t parts = (uint32_t)NT / cap, e = (uint32_t)tid & (cap - 1u), part = (uint32_t)tid / cap;
+            if (e < nb) {
+                const uint2 me = l_ent[e];
+                uint32_t rank = 0;
+                for (uint32_t f = part; f < nb; f += parts) {
+                    const uint2 o = l_ent[f];
+                    rank += (o.x > me.x) || (o.x == me.x && o.y < me.y);
+                }
+                atomicAdd(&s_rank[e], rank);
+            }
+            __syncthreads();
+            if ((uint32_t)tid < nb && s_rank[tid] < rem) {
+                const uint32_t id = l_ent[tid].y;
+                atomicOr(&s_gt[id >> 5], 1u << (id & 31u));
+            }
+            __syncthreads();
+            if (L <= KPT * NT) {   // uniform
+                // every wave counts the whole bitmap (two groups of 64 ids per lane), scans it by itself, and places its
+                // own groups' picks with their rows and scores, all of which it holds in registers
+                uint4 w4 = make_uint4(0u, 0u, 0u, 0u);
+                if (4 * ln < nw32) w4 = *reinterpret_cast<const uint4 *>(s_gt + 4 * ln);
+                if (4 * ln + 2 >= nw32) w4.z = w4.w = 0u;
+                const uint32_t c0 = (uint32_t)(__popc(w4.x) + __popc(w4.y)), c1 = (uint32_t)(__popc(w4.z) + __popc(w4.w));
+                const uint32_t ex = wave_incl_scan(c0 + c1) - c0 - c1;
+                const uint32_t first = (wv & 1) ? ex + c0 : ex;
+                const uint32_t mlo = (wv & 1) ? w4.z : w4.x, mhi = (wv & 1) ? w4.w : w4.y;
+                static_assert(NW % 2 == 0, "a wave's groups are all even or all odd");
+#pragma unroll
+                for (int q = 0; q < KPT; ++q) {
+                    const int gq = q * NW + wv, src = gq >> 1;
+                    if (q % 4 == 0 && gq * 64 >= L) break;
+                    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)mlo, src);
+                    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)mhi, src);
+                    const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)first, src);
+                    const uint32_t pos = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, base));
+                    if (__builtin_amdgcn_inverse_ballot_w64(((uint64_t)hi << 32) | lo)) place(q, gq, pos);
+                }
+                return true;
+            } else {
+                // thread t owns the bytes [t bpt, (t + 1) bpt) of the bitmap: count, scan, emit in ascending order
+                const unsigned char *bytes = reinterpret_cast<const unsigned char *>(s_gt);
+                const int nbyte = nw32 * 4, bpt = (nbyte + NT - 1) / NT;
+                const int b0 = min(nbyte, tid * bpt), b1 = min(nbyte, b0 + bpt);
+                uint32_t cnt = 0;
+                for (int w = b0; w < b1; ++w) cnt += (uint32_t)__popc((uint32_t)bytes[w]);
+                uint32_t tot;
+                uint32_t pos = block_excl_scan<NT>(cnt, s_scan, &tot);
+                for (int w = b0; w < b1; ++w) {
+                    uint32_t mm = bytes[w];
+                    while (mm) {
+                        const int bit = __ffs((int)mm) - 1;
+                        mm &= mm - 1u;
+                        emit((int)pos++, w * 8 + bit);
+                    }
+                }
+            }
+        } else {
+            block_resolve_emit<NT>(nb, rem, L, s_hist, s_gt, s_eq, l_ent, emit);
+        }
+    } else {   // a crowded deciding bucket (equal keys, or keys below the histogram's range)
+        block_select_topk<NT, 0>(key, L, top_k, emit, s_hist);
+    }
+    return false;
+}
+
+// ------------------------------------------------------------------------------
 // Algorithm 2 lines 5b-9 in ONE launch, for small batches: denominators, ranking, selection and attention.  Three
 // launches (denom, keyclass, select_attn) spent 24 us on it at 32K tokens / 8 KV heads, of which about 9 are the gaps, ramps
 // and drains of the launches and most of the rest round trips of intermediate results through memory.  SL blocks per unit,
@@ -2409,7 +2592,6 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
 {
     extern __shared__ __align__(16) uint32_t smem[];
     constexpr int NT = kTailThreads, NW = NT / 64, KPT = kTailKeys / NT;
-    static_assert(kTailKeys / 64 == 128, "the picks' positions: two groups of 64 ids per lane");
     __shared__ unsigned long long s_acc[NW][G];
     __shared__ float s_ls[G];
     __shared__ uint32_t s_res[4];      // deciding bucket, keys wanted from it, its population, list cursor
@@ -2535,10 +2717,6 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
         for (int hh = 1; hh < G; ++hh) best = fmaxf(best, (zv[hh] - m[hh]) - ls[hh]);
         return fmaxf(best, -3.0e38f);   // (above the -inf of the slots beyond L)
     };
-    // key_bucket(ordered_key(x)), from the key as a float
-    auto bucket_of = [&](float x) __attribute__((always_inline)) {
-        return (uint32_t)__builtin_amdgcn_fmed3f(x * -32.0f, 0.0f, (float)(kBuckets - 1));
-    };
     float kreg[KPT];
 #pragma unroll
     for (int q = 0; q < KPT; ++q) {
@@ -2565,7 +2743,6 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
         for_far(put);
     }
     CTKVR_STAMP(66);
-    const bool near = L <= kTailKeys;   // uniform
     int n = L;
     if (a.top_k >= L) {   // every recalled key is kept
         for (int i = tid; i < L; i += NT) {
@@ -2577,181 +2754,19 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
         __syncthreads();
     } else {
         n = a.top_k;
-        // the last bucket (everything below the histogram's range, often most keys) is not counted: L minus the others
-        const float floor_k = -(float)(kBuckets - 1) / 32.0f;
-        // (no branch: lanes that do not count add to a word of their own)
-        auto count = [&](int, float kk) __attribute__((always_inline)) {
-            uint32_t *bin = &s_hist[bucket_of(kk)];
-            bin = kk > floor_k ? bin : s_list + tid;
-            atomicAdd(bin, 1u);
-        };
-#pragma unroll
-        for (int q = 0; q < KPT; ++q) {
-            if (q % 4 == 0 && (q * NW + wv) * 64 >= L) break;
-            count(q, kreg[q]);
-        }
-        for_far(count);
-        __syncthreads();
-        CTKVR_STAMP(67);
-        uint32_t *s_scan = s_hist + 2048 + 4;
-        {
-            constexpr int BPT = kBuckets / NT;   // buckets per thread, in descending key order
-            static_assert(BPT == 4, "one 16-byte read");
-            const uint4 c4 = reinterpret_cast<const uint4 *>(s_hist)[tid];
-            const uint32_t c[4] = {c4.x, c4.y, c4.z, c4.w};
-            uint32_t tot;
-            uint32_t before = block_excl_scan<NT>((c[0] + c[1]) + (c[2] + c[3]), s_scan, &tot);
-            const uint32_t want = (uint32_t)a.top_k;
-            if (want > tot) {   // (uniform) the last bucket decides
-                if (tid == 0) {
-                    s_res[0] = (uint32_t)(kBuckets - 1);
-                    s_res[1] = want - tot;
-                    s_res[2] = (uint32_t)L - tot;
-                }
-            } else
-#pragma unroll
-            for (int q = 0; q < BPT; ++q) {
-                if (before < want && want <= before + c[q]) {
-                    s_res[0] = (uint32_t)(BPT * tid + q);
-                    s_res[1] = want - before;
-                    s_res[2] = c[q];
-                }
-                before += c[q];
-            }
-        }
-        __syncthreads();
-        CTKVR_STAMP(68);
-        const uint32_t bkt = s_res[0], rem = s_res[1], nb = s_res[2];
-        // the deciding bucket as an interval of keys: x > hi is above it, lo < x <= hi in it (exact: x * 32 is)
-        const float hi_k = bkt == 0u ? __builtin_huge_valf() : -(float)bkt / 32.0f;
-        const float lo_k = bkt == (uint32_t)(kBuckets - 1) ? -__builtin_huge_valf() : -(float)(bkt + 1u) / 32.0f;
-        auto emit = [&](int pos, int i) __attribute__((always_inline)) { s_pick[pos].x = (uint32_t)i; };
-        bool placed = false;   // rows and scores are with the positions already
-        if (nb <= (uint32_t)kListCap) {
-            const int nw32 = 2 * ((L + 63) >> 6);
-            uint32_t *s_gt = s_bits, *s_eq = s_bits + nw32;
-            uint2 *l_ent = reinterpret_cast<uint2 *>(s_list);
-            const bool few = nb <= (uint32_t)NT / 2;   // ranked by all-pairs comparison: ids decide between equal keys
-            uint32_t *s_rank = s_hist;     // (everyone has read the histogram)
-            if (tid < NT / 2) s_rank[tid] = 0u;
-            auto list = [&](uint64_t listed, uint32_t at, float kk, int i) __attribute__((always_inline)) {
-                const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(listed >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)listed, at));
-                if (__builtin_amdgcn_inverse_ballot_w64(listed)) l_ent[pos] = make_uint2(ordered_key(kk), (uint32_t)i);
-            };
-            // the wave's verdicts first, then one cursor bump for all its entries of the deciding bucket
-            uint64_t in[KPT];
-            uint64_t mine_gt = 0;   // lane q: the verdicts of group q
-            uint32_t n_in = 0;
-#pragma unroll
-            for (int q = 0; q < KPT; ++q) {
-                const uint64_t above = __ballot(kreg[q] > hi_k);
-                in[q] = __ballot(kreg[q] > lo_k) & ~above;
-                n_in += (uint32_t)__popcll(in[q]);
-                mine_gt = ln == q ? above : mine_gt;
-            }
-            if (ln < KPT && (ln * NW + wv) * 64 < L)
-                *reinterpret_cast<uint2 *>(s_gt + 2 * (ln * NW + wv)) = make_uint2((uint32_t)mine_gt, (uint32_t)(mine_gt >> 32));
-            if (n_in) {
-                uint32_t at0 = 0;
-                if (ln == 0) at0 = atomicAdd(&s_res[3], n_in);
-                at0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)at0);
-#pragma unroll
-                for (int q = 0; q < KPT; ++q)
-                    if (in[q]) {
-                        list(in[q], at0, kreg[q], (q * NW + wv) * 64 + ln);
-                        at0 += (uint32_t)__popcll(in[q]);
-                    }
-            }
-            for_far([&](int gq, float kk) __attribute__((always_inline)) {
-                const uint64_t above = __ballot(kk > hi_k);
-                const uint64_t listed = __ballot(kk > lo_k) & ~above;
-                if (ln == 0) *reinterpret_cast<uint2 *>(s_gt + 2 * gq) = make_uint2((uint32_t)above, (uint32_t)(above >> 32));
-                if (listed) {
-                    uint32_t at1 = 0;
-                    if (ln == 0) at1 = atomicAdd(&s_res[3], (uint32_t)__popcll(listed));
-                    list(listed, (uint32_t)__builtin_amdgcn_readfirstlane((int)at1), kk, gq * 64 + ln);
-                }
-            });
-            if (!few)
-                for (int w = tid; w < nw32; w += NT) s_eq[w] = 0u;
-            __syncthreads();
-            CTKVR_STAMP(69);
-            if (few) {
-                uint32_t cap = 64;
-                while (cap < nb) cap <<= 1;
-                const uint32_t parts = (uint32_t)NT / cap, e = (uint32_t)tid & (cap - 1u), part = (uint32_t)tid / cap;
-                if (e < nb) {
-                    const uint2 me = l_ent[e];
-                    uint32_t rank = 0;
-                    for (uint32_t f = part; f < nb; f += parts) {
-                        const uint2 o = l_ent[f];
-                        rank += (o.x > me.x) || (o.x == me.x && o.y < me.y);
-                    }
-                    atomicAdd(&s_rank[e], rank);
-                }
-                __syncthreads();
-                CTKVR_STAMP(70);
-                if ((uint32_t)tid < nb && s_rank[tid] < rem) {
-                    const uint32_t id = l_ent[tid].y;
-                    atomicOr(&s_gt[id >> 5], 1u << (id & 31u));
-                }
-                __syncthreads();
-                CTKVR_STAMP(71);
-                if (near) {
-                    // every wave counts the whole bitmap (two groups of 64 ids per lane), scans it by itself, and places its
-                    // own groups' picks with their rows and scores, all of which it holds in registers
-                    uint4 w4 = make_uint4(0u, 0u, 0u, 0u);
-                    if (4 * ln < nw32) w4 = *reinterpret_cast<const uint4 *>(s_gt + 4 * ln);
-                    if (4 * ln + 2 >= nw32) w4.z = w4.w = 0u;
-                    const uint32_t c0 = (uint32_t)(__popc(w4.x) + __popc(w4.y)), c1 = (uint32_t)(__popc(w4.z) + __popc(w4.w));
-                    const uint32_t ex = wave_incl_scan(c0 + c1) - c0 - c1;
-                    const uint32_t first = (wv & 1) ? ex + c0 : ex;
-                    const uint32_t mlo = (wv & 1) ? w4.z : w4.x, mhi = (wv & 1) ? w4.w : w4.y;
-                    static_assert(NW % 2 == 0, "a wave's groups are all even or all odd");
-#pragma unroll
-                    for (int q = 0; q < KPT; ++q) {
-                        const int gq = q * NW + wv, src = gq >> 1;
-                        if (q % 4 == 0 && gq * 64 >= L) break;
-                        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)mlo, src);
-                        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)mhi, src);
-                        const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)first, src);
-                        const uint32_t pos = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, base));
-                        if (__builtin_amdgcn_inverse_ballot_w64(((uint64_t)hi << 32) | lo)) {
-                            s_pick[pos] = make_uint2((uint32_t)(gq * 64 + ln), rr[q]);
-                            store_z<G>(s_p, (int)pos, zr[q]);
-                        }
-                    }
-                    placed = true;
-                } else {
-                    // thread t owns the bytes [t bpt, (t + 1) bpt) of the bitmap: count, scan, emit in ascending order
-                    const unsigned char *bytes = reinterpret_cast<const unsigned char *>(s_gt);
-                    const int nbyte = nw32 * 4, bpt = (nbyte + NT - 1) / NT;
-                    const int b0 = min(nbyte, tid * bpt), b1 = min(nbyte, b0 + bpt);
-                    uint32_t cnt = 0;
-                    for (int w = b0; w < b1; ++w) cnt += (uint32_t)__popc((uint32_t)bytes[w]);
-                    uint32_t tot;
-                    uint32_t pos = block_excl_scan<NT>(cnt, s_scan, &tot);
-                    for (int w = b0; w < b1; ++w) {
-                        uint32_t mm = bytes[w];
-                        while (mm) {
-                            const int bit = __ffs((int)mm) - 1;
-                            mm &= mm - 1u;
-                            emit((int)pos++, w * 8 + bit);
-                        }
-                    }
-                }
-            } else {
-                block_resolve_emit<NT>(nb, rem, L, s_hist, s_gt, s_eq, l_ent, emit);
-            }
-        } else {   // a crowded deciding bucket (equal keys, or keys below the histogram's range)
-            block_select_topk<NT, 0>(
-                [&](int i) {
-                    float zv[G];
-                    load_z<G>(zb, i, zv);
-                    return ordered_key(key_of(zv));
-                },
-                L, a.top_k, emit, s_hist);
-        }
+        const bool placed = select_keys<NT, KPT>(
+            kreg, L, a.top_k, for_far,
+            [&](int q, int gq, uint32_t pos) __attribute__((always_inline)) {
+                s_pick[pos] = make_uint2((uint32_t)(gq * 64 + ln), rr[q]);
+                store_z<G>(s_p, (int)pos, zr[q]);
+            },
+            [&](int pos, int i) __attribute__((always_inline)) { s_pick[pos].x = (uint32_t)i; },
+            [&](int i) {
+                float zv[G];
+                load_z<G>(zb, i, zv);
+                return ordered_key(key_of(zv));
+            },
+            s_hist, s_list, s_bits, s_res);
         __syncthreads();
         if (!placed) {   // uniform
             for (int pos = tid; pos < n; pos += NT) {
@@ -2816,15 +2831,15 @@ __device__ __forceinline__ void store_chunk(bf16_t *row, int lane16, const Chunk
     *reinterpret_cast<uint4 *>(row + 8 * lane16) = c.w;
 }
 
-template <typename T> __global__ __launch_bounds__(256) void dcu_write_kernel(DcuArgs a)
+// The slot's list from the step's ranking keys and the slot's centroids, one unit per block (NT threads): emit_list(dst) writes
+// the list; the rest as described above.
+template <typename T, int NT, typename ListFn>
+__device__ __forceinline__ void dcu_write_unit(const DcuArgs &a, const int n, ListFn emit_list)
 {
     const int ul = blockIdx.x, b = ul / a.g, kv = ul - b * a.g, tid = threadIdx.x;
     const int slot = (int)(a.count[0] % (uint32_t)a.n_cent[b]);
-    const int n = min(a.nsrc[ul], a.rho);
     if (n > 0) {
-        const int32_t *src = a.src + (size_t)ul * a.src_stride;
-        int32_t *dst = a.lists + ((size_t)ul * a.c_max + slot) * a.rho;
-        for (int r = tid; r < a.rho; r += 256) dst[r] = src[min(r, n - 1)];
+        emit_list(a.lists + ((size_t)ul * a.c_max + slot) * a.rho);
         if (tid < 16 * a.G) {
             const int hh = tid >> 4, lane16 = tid & 15;
             const size_t head = (size_t)b * a.h + kv * a.G + hh;
@@ -2842,6 +2857,72 @@ template <typename T> __global__ __launch_bounds__(256) void dcu_write_kernel(Dc
         atomicExch(&a.count[1], 0u);
         atomicAdd(&a.count[0], 1u);
     }
+}
+
+// rho = rho': the list is the step's selection.  grid batch*g, 256 threads
+template <typename T> __global__ __launch_bounds__(256) void dcu_write_kernel(DcuArgs a)
+{
+    const int ul = blockIdx.x, tid = threadIdx.x;
+    const int n = min(a.nsrc[ul], a.rho);
+    dcu_write_unit<T, 256>(a, n, [&](int32_t *dst) {
+        const int32_t *src = a.src + (size_t)ul * a.src_stride;
+        for (int r = tid; r < a.rho; r += 256) dst[r] = src[min(r, n - 1)];
+    });
+}
+
+// Another budget: the step's ranking keys selected once more and written in the same launch (six launches -- histogram,
+// classification, selection and the fills they need -- took 21 us of a 65 us step with update; this takes 7).  One
+// block per unit.  grid batch*g, kTailThreads; dynamic shared memory: kSelLds + 2 kListCap + bits_words words
+struct DcuSelectArgs {
+    DcuArgs d;
+    const int32_t *ncand, *cand;   // [units], [units][l_stride]
+    const uint32_t *kbuf;          // [units][l_stride] ordered images of the ranking keys
+    int l_stride;
+};
+
+template <typename T> __global__ __launch_bounds__(kTailThreads) void dcu_select_kernel(DcuSelectArgs a)
+{
+    extern __shared__ __align__(16) uint32_t smem[];
+    constexpr int NT = kTailThreads, NW = NT / 64, KPT = kTailKeys / NT;
+    __shared__ uint32_t s_res[4];
+    uint32_t *s_hist = smem, *s_list = smem + kSelLds, *s_bits = s_list + 2 * kListCap;
+    const int ul = blockIdx.x, tid = threadIdx.x, ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t *kb = a.kbuf + (size_t)ul * a.l_stride;
+    const int32_t *cb = a.cand + (size_t)ul * a.l_stride;
+    uint32_t kk[KPT];
+    int32_t id[KPT];
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) kk[q] = kb[min(q * NT + tid, a.l_stride - 1)];   // before L is known; stale beyond it
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) id[q] = cb[min(q * NT + tid, a.l_stride - 1)];
+    const int L = a.ncand[ul];
+    for (int w = tid; w < kBuckets / 4; w += NT) reinterpret_cast<uint4 *>(s_hist)[w] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid == 0) s_res[3] = 0u;
+    float kreg[KPT];
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+        const float x = fmaxf(ordered_value(kk[q]), -3.0e38f);   // (above the -inf of the slots beyond L)
+        kreg[q] = q * NT + tid < L ? x : -__builtin_huge_valf();
+    }
+    __syncthreads();
+    dcu_write_unit<T, NT>(a.d, L, [&](int32_t *dst) {
+        if (a.d.rho >= L) {   // every recalled key, the last one repeated should there be fewer than rho
+            for (int r = tid; r < a.d.rho; r += NT) dst[r] = cb[min(r, L - 1)];
+            return;
+        }
+        select_keys<NT, KPT>(
+            kreg, L, a.d.rho,
+            [&](auto f) __attribute__((always_inline)) {
+                for (int gq = KPT * NW + wv; gq * 64 < L; gq += NW) {
+                    const int i = gq * 64 + ln;
+                    const float x = fmaxf(ordered_value(kb[min(i, L - 1)]), -3.0e38f);
+                    f(gq, i < L ? x : -__builtin_huge_valf());
+                }
+            },
+            [&](int q, int, uint32_t pos) __attribute__((always_inline)) { dst[pos] = id[q]; },
+            [&](int pos, int i) __attribute__((always_inline)) { dst[pos] = cb[i]; },
+            [&](int i) { return kb[i]; }, s_hist, s_list, s_bits, s_res);
+    });
 }
 
 }  // namespace ctkvr
