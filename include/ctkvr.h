@@ -282,7 +282,8 @@ int ctkvr_index_build_route(const ctkvr_index *idx, int32_t *by_candidates_host,
  * scratch when a build returns, an index's memory when it is freed) are kept, at most 2 GiB per device, the oldest
  * given up first, and serve later builds and loads of about the same size, from any host thread and stream; they
  * are freed when an allocation of the library runs out of memory and by this call, which frees the current device's
- * idle blocks; an error if a build is using scratch on that device.  The environment variable
+ * idle blocks and the 8 MB of pinned host memory that copies of lists and centroids go through; an error if a build
+ * is using scratch on that device.  The environment variable
  * CTKVR_BUILD_SCRATCH_CACHE = 0, read when a block is given back, switches the keeping off. */
 int ctkvr_release_scratch(void);
 

@@ -101,6 +101,18 @@ __global__ void put_ints_kernel(int32_t *dst, int n, IntPack pack)
     for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = pack.v[i];
 }
 
+// The lowest flat index of a list entry that is not a key id of its sequence goes to *bad (~0: none).  grid (c_max, units)
+__global__ void check_lists_kernel(const int32_t *lists, const int32_t *ctx_lens, const int32_t *n_cent, int g, int c_max, int rho,
+                                   unsigned long long *bad)
+{
+    const int j = blockIdx.x, ul = blockIdx.y, b = ul / g;
+    if (j >= n_cent[b]) return;
+    const int s = ctx_lens[b];
+    const size_t row = ((size_t)ul * c_max + j) * rho;
+    for (int r = threadIdx.x; r < rho; r += blockDim.x)
+        if ((uint32_t)lists[row + r] >= (uint32_t)s) atomicMin(bad, (unsigned long long)(row + r));
+}
+
 // three ranges cleared by one launch: grid ceil((n0 + n1 + n2) / blockDim.x)
 __global__ void zero3_u32_kernel(uint32_t *p0, size_t n0, uint32_t *p1, size_t n1, uint32_t *p2, size_t n2)
 {
