@@ -1000,14 +1000,97 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
     return rc;
 }
 
+constexpr size_t kExactChunkBytes = (size_t)512 << 20;
+
+// The same lists with the scores on the fp32 matrix cores (exact_score_kernel) and one block per list behind them
+// (exact_list_kernel); needs shared memory for a bitmap of the context (to about 2^18 tokens).
+size_t exact_list_lds(const ctkvr_index *ix) { return ((size_t)kSelLds + 2 * kListCap + 4 * ((ix->s_max + 63) / 64)) * 4; }
+
+template <typename T, int G> int build_lists_exact_mfma(ctkvr_index *ix, const void *k_pages, const int32_t *block_table, int max_pages, hipStream_t st)
+{
+    constexpr int CT = 32 * (8 / G);
+    const int tiles_per_bk = (ix->c_max + CT - 1) / CT, tiles = ix->units * tiles_per_bk;
+    const int z_stride = (ix->s_max + 3) & ~3;
+    // Chunks of at most 512 MB of scores (they are read back twice, so short-lived chunks help the memory-side cache, but a
+    // chunk should hold several hundred lists: one block each)
+    const size_t per_tile = (size_t)CT * G * z_stride * 4;
+    const int chunk = (int)std::min<size_t>(tiles, std::max<size_t>(1, kExactChunkBytes / per_tile));
+    float *z = nullptr;
+    uint32_t *m_key = nullptr;
+    BuildScratch scratch_mem;
+    auto lay_out = [&](unsigned char *base) {
+        Carver cv{base};
+        cv.take(&z, (size_t)chunk * per_tile);
+        cv.take(&m_key, (size_t)tiles * CT * G * 4);
+        return cv.off;
+    };
+    TRY(scratch_mem.get(ix->dev, lay_out(nullptr)));
+    lay_out(scratch_mem.base());
+    const size_t lds = exact_list_lds(ix);
+    const bool small = ix->s_max <= 8 * 512;
+    const void *fn = small ? (const void *)exact_list_kernel<G, 8> : (const void *)exact_list_kernel<G, 64>;
+    TRY(want_lds(ix->dev, fn, lds));
+    const size_t n_m = (size_t)tiles * CT * G;
+    fill_u32_kernel<<<dim3((unsigned)((n_m + 255) / 256)), 256, 0, st>>>(m_key, 0u, n_m);
+    for (int t0 = 0; t0 < tiles; t0 += chunk) {
+        const int nt = std::min(chunk, tiles - t0);
+        ExactScoreArgs sa{};
+        sa.g = ix->p.n_kv_heads;
+        sa.h = ix->p.n_q_heads;
+        sa.c_max = ix->c_max;
+        sa.tile0 = t0;
+        sa.tiles_per_bk = tiles_per_bk;
+        // one block per CU and round (eight waves of 64-register fragments); at least two steps of 32 keys each
+        const int rounds = std::max(1, (nt * ((ix->s_max + 1023) / 1024) + ix->num_cu / 2) / ix->num_cu);
+        sa.t_splits = std::max(1, std::min((ix->s_max + 63) / 64, (rounds * ix->num_cu + nt - 1) / nt));
+        sa.n_cent = ix->d_n_cent;
+        sa.ctx_lens = ix->d_ctx_lens;
+        sa.centroids = ix->centroids;
+        sa.k = Paged{k_pages, block_table, max_pages, ix->page_shift};
+        sa.z_stride = z_stride;
+        sa.z = z;
+        sa.m_key = m_key + (size_t)t0 * CT * G;
+        sa.scale = ix->scale;
+        exact_score_kernel<T, G><<<dim3(sa.t_splits, nt), 512, 0, st>>>(sa);
+        ExactListArgs la{};
+        la.g = sa.g;
+        la.c_max = ix->c_max;
+        la.tile0 = t0;
+        la.tiles_per_bk = tiles_per_bk;
+        la.ct = CT;
+        la.n_cent = ix->d_n_cent;
+        la.ctx_lens = ix->d_ctx_lens;
+        la.z_stride = z_stride;
+        la.rho = ix->p.list_len;
+        la.n_init = ix->p.n_init;
+        la.n_local = ix->p.n_local;
+        la.z = z;
+        la.m_key = sa.m_key;
+        la.lists = ix->lists;
+        if (small)
+            exact_list_kernel<G, 8><<<dim3(nt * CT), 512, lds, st>>>(la);
+        else
+            exact_list_kernel<G, 64><<<dim3(nt * CT), 512, lds, st>>>(la);
+    }
+    hipError_t e = hipGetLastError();
+    hipError_t es = hipStreamSynchronize(st);   // the scratch is given back
+    if (e == hipSuccess) e = es;
+    return e == hipSuccess ? CTKVR_OK : fail(CTKVR_EHIP, "build: %s", hipGetErrorString(e));
+}
+
 template <typename T>
 int build_lists_dispatch(ctkvr_index *ix, const void *k_pages, const int32_t *bt, int max_pages, hipStream_t st)
 {
+    const bool fixed = ix->p.build_algo == CTKVR_BUILD_EXACT && exact_list_lds(ix) <= 150 * 1024;
+    auto go = [&](auto g) {
+        constexpr int G = decltype(g)::value;
+        return fixed ? build_lists_exact_mfma<T, G>(ix, k_pages, bt, max_pages, st) : build_lists_exact<T, G>(ix, k_pages, bt, max_pages, st);
+    };
     switch (ix->G) {
-        case 1: return build_lists_exact<T, 1>(ix, k_pages, bt, max_pages, st);
-        case 2: return build_lists_exact<T, 2>(ix, k_pages, bt, max_pages, st);
-        case 4: return build_lists_exact<T, 4>(ix, k_pages, bt, max_pages, st);
-        default: return build_lists_exact<T, 8>(ix, k_pages, bt, max_pages, st);
+        case 1: return go(std::integral_constant<int, 1>{});
+        case 2: return go(std::integral_constant<int, 2>{});
+        case 4: return go(std::integral_constant<int, 4>{});
+        default: return go(std::integral_constant<int, 8>{});
     }
 }
 

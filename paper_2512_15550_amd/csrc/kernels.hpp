@@ -2377,8 +2377,8 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(1024) void sel
 }
 
 // ------------------------------------------------------------------------------
-// The top_k largest of L > top_k ranking keys (ties: lowest positions), by one block of NT threads: the keys of positions
-// (q NT/64 + wave) 64 + lane sit in kreg[q] of their thread (-inf beyond L), those beyond KPT NT come from for_far (f(group of
+// The top_k largest of L ranking keys, n_real > top_k of them above -inf (ties: lowest positions), by one block of NT threads: the keys of positions
+// (q NT/64 + wave) 64 + lane sit in kreg[q] of their thread (-inf beyond L and where a key is out of the running), those beyond KPT NT come from for_far (f(group of
 // 64 positions, key) for the groups of the calling wave).  Histogram over key buckets in shared memory, the deciding
 // bucket, a bitmap of the positions above it, that bucket's own keys ranked against each other, and the picks in
 // ascending order: either place(q, group, rank) for the lane's own key in kreg[q], and the function returns true, or
@@ -2387,11 +2387,11 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(1024) void sel
 // key(position) = the key's ordered image, for a crowded deciding bucket (all keys are then walked again).
 // ------------------------------------------------------------------------------
 template <int NT, int KPT, typename FarFn, typename PlaceFn, typename EmitFn, typename KeyFn>
-__device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int L, const int top_k, FarFn for_far, PlaceFn place,
-                                            EmitFn emit, KeyFn key, uint32_t *s_hist, uint32_t *s_list, uint32_t *s_bits, uint32_t *s_res)
+__device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int L, const int n_real, const int top_k, FarFn for_far,
+                                            PlaceFn place, EmitFn emit, KeyFn key, uint32_t *s_hist, uint32_t *s_list, uint32_t *s_bits, uint32_t *s_res)
 {
     constexpr int NW = NT / 64;
-    static_assert(KPT * NW <= 128, "the picks' ranks: two groups of 64 positions per lane");
+    static_assert(KPT <= 64, "the picks' ranks: a round of groups per lane");
     const int tid = threadIdx.x, ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     // key_bucket(ordered_key(x)), from the key as a float
     auto bucket_of = [&](float x) __attribute__((always_inline)) {
@@ -2425,7 +2425,7 @@ __device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int 
             if (tid == 0) {
                 s_res[0] = (uint32_t)(kBuckets - 1);
                 s_res[1] = want - tot;
-                s_res[2] = (uint32_t)L - tot;
+                s_res[2] = (uint32_t)n_real - tot;
             }
         } else
 #pragma unroll
@@ -2455,14 +2455,13 @@ __device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int 
             if (__builtin_amdgcn_inverse_ballot_w64(listed)) l_ent[pos] = make_uint2(ordered_key(kk), (uint32_t)i);
         };
         // the wave's verdicts first, then one cursor bump for all its entries of the deciding bucket
-        uint64_t in[KPT];
         uint64_t mine_gt = 0;   // lane q: the verdicts of group q
         uint32_t n_in = 0;
 #pragma unroll
         for (int q = 0; q < KPT; ++q) {
+            if (q % 4 == 0 && (q * NW + wv) * 64 >= L) break;
             const uint64_t above = __ballot(kreg[q] > hi_k);
-            in[q] = __ballot(kreg[q] > lo_k) & ~above;
-            n_in += (uint32_t)__popcll(in[q]);
+            n_in += (uint32_t)__popcll(__ballot(kreg[q] > lo_k) & ~above);
             mine_gt = ln == q ? above : mine_gt;
         }
         if (ln < KPT && (ln * NW + wv) * 64 < L)
@@ -2472,11 +2471,14 @@ __device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int 
             if (ln == 0) at0 = atomicAdd(&s_res[3], n_in);
             at0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)at0);
 #pragma unroll
-            for (int q = 0; q < KPT; ++q)
-                if (in[q]) {
-                    list(in[q], at0, kreg[q], (q * NW + wv) * 64 + ln);
-                    at0 += (uint32_t)__popcll(in[q]);
+            for (int q = 0; q < KPT; ++q) {
+                if (q % 4 == 0 && (q * NW + wv) * 64 >= L) break;
+                const uint64_t in = __ballot(kreg[q] > lo_k) & ~__ballot(kreg[q] > hi_k);
+                if (in) {
+                    list(in, at0, kreg[q], (q * NW + wv) * 64 + ln);
+                    at0 += (uint32_t)__popcll(in);
                 }
+            }
         }
         for_far([&](int gq, float kk) __attribute__((always_inline)) {
             const uint64_t above = __ballot(kk > hi_k);
@@ -2511,23 +2513,29 @@ __device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int 
             }
             __syncthreads();
             if (L <= KPT * NT) {   // uniform
-                // every wave counts the whole bitmap (two groups of 64 ids per lane), scans it by itself, and places its
-                // own groups' picks with their rows and scores, all of which it holds in registers
-                uint4 w4 = make_uint4(0u, 0u, 0u, 0u);
-                if (4 * ln < nw32) w4 = *reinterpret_cast<const uint4 *>(s_gt + 4 * ln);
-                if (4 * ln + 2 >= nw32) w4.z = w4.w = 0u;
-                const uint32_t c0 = (uint32_t)(__popc(w4.x) + __popc(w4.y)), c1 = (uint32_t)(__popc(w4.z) + __popc(w4.w));
-                const uint32_t ex = wave_incl_scan(c0 + c1) - c0 - c1;
-                const uint32_t first = (wv & 1) ? ex + c0 : ex;
-                const uint32_t mlo = (wv & 1) ? w4.z : w4.x, mhi = (wv & 1) ? w4.w : w4.y;
-                static_assert(NW % 2 == 0, "a wave's groups are all even or all odd");
+                // every wave counts the whole bitmap (lane q: the NW groups of round q), scans it by itself, and places its
+                // own groups' picks
+                uint32_t all = 0, before = 0;
+#pragma unroll
+                for (int j = 0; j < NW; j += 2) {
+                    const int gq = ln * NW + j;
+                    uint4 w4 = make_uint4(0u, 0u, 0u, 0u);
+                    if (ln < KPT && 2 * gq < nw32) w4 = *reinterpret_cast<const uint4 *>(s_gt + 2 * gq);
+                    const uint32_t c0 = (uint32_t)(__popc(w4.x) + __popc(w4.y));
+                    const uint32_t c1 = 2 * gq + 2 < nw32 ? (uint32_t)(__popc(w4.z) + __popc(w4.w)) : 0u;
+                    all += c0 + c1;
+                    before += (j < wv ? c0 : 0u) + (j + 1 < wv ? c1 : 0u);
+                }
+                const uint32_t first = wave_incl_scan(all) - all + before;
+                uint2 mine = make_uint2(0u, 0u);
+                if (ln < KPT && 2 * (ln * NW + wv) < nw32) mine = *reinterpret_cast<const uint2 *>(s_gt + 2 * (ln * NW + wv));
 #pragma unroll
                 for (int q = 0; q < KPT; ++q) {
-                    const int gq = q * NW + wv, src = gq >> 1;
+                    const int gq = q * NW + wv;
                     if (q % 4 == 0 && gq * 64 >= L) break;
-                    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)mlo, src);
-                    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)mhi, src);
-                    const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)first, src);
+                    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)mine.x, q);
+                    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)mine.y, q);
+                    const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)first, q);
                     const uint32_t pos = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, base));
                     if (__builtin_amdgcn_inverse_ballot_w64(((uint64_t)hi << 32) | lo)) place(q, gq, pos);
                 }
@@ -2557,6 +2565,259 @@ __device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int 
         block_select_topk<NT, 0>(key, L, top_k, emit, s_hist);
     }
     return false;
+}
+
+// ------------------------------------------------------------------------------
+// Exact list build (Algorithm 1 lines 2-4 in the fixed arithmetic of the decode path) on the fp32 matrix cores.  A
+// v_mfma_f32_32x32x2f32 adds its two products to the accumulator one after the other, each as a fused multiply-add with
+// one rounding (compared with fmaf chains on 2 M results of random, bf16-valued, wide-range and subnormal inputs: no bit
+// differs), so the fixed dot product -- sixteen chains of eight fused multiply-adds, combined as a balanced tree -- is
+// sixteen groups of four such instructions, each group from zero, and fifteen vector adds.
+// exact_score_kernel: z[unit][head][key] = (c . k) scale for a chunk of tiles of CT = 32 (8 / G) centroids of one
+// (sequence, KV head), all its G heads and all s keys, and each unit's and head's maximum.  Eight waves, each with one item of 32
+// centroids of one head, whose fragments stay in 64 registers (a lane needs every other element: the instruction's two
+// k's sit in the two halves of a wave); the keys go by 32 at a time through shared memory as fp32, even and odd elements of
+// each group of eight apart so that a fragment is one 16-byte read.  Bound by the matrix pipe (64 instructions of 64 clocks
+// per 32 x 32 scores against about 1.2 k clocks of vector work; fp32 peak 157 TFLOP/s): at 32K tokens, C = 512,
+// 32/8 heads 1.1 ms where the scalar form (score_kernel) took 4.7.
+// grid (t_splits, tiles of the chunk), 512 threads
+// ------------------------------------------------------------------------------
+struct ExactScoreArgs {
+    int g, h, c_max;
+    int tile0, tiles_per_bk;   // first tile of the chunk; tiles per (sequence, KV head)
+    int t_splits;
+    const int32_t *n_cent, *ctx_lens;
+    const void *centroids;     // [batch][h][c_max][128]
+    Paged k;
+    int z_stride;              // floats per (unit, head) row: a multiple of 4, >= s_max
+    float *z;                  // [chunk units = tiles * CT][G][z_stride]
+    uint32_t *m_key;           // [chunk units][G] ordered-key maxima, zero on entry
+    float scale;
+};
+
+template <typename T, int G> __global__ __launch_bounds__(512) void exact_score_kernel(ExactScoreArgs a)
+{
+    constexpr int CT = 32 * (8 / G), ROWW = 132;   // floats per staged key row (128 + 4: rows spread over the banks)
+    __shared__ __align__(16) float s_k[2][32 * ROWW];
+    const int tid = threadIdx.x, ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = ln & 31, half = ln >> 5;
+    const int tile = a.tile0 + (int)blockIdx.y, bk = tile / a.tiles_per_bk, jt = tile - bk * a.tiles_per_bk;
+    const int b = bk / a.g, kv = bk - b * a.g;
+    const int C = a.n_cent[b], s = a.ctx_lens[b];
+    const int j0 = jt * CT;
+    if (j0 >= C) return;
+    const int tper = (((s + a.t_splits - 1) / a.t_splits) + 31) & ~31;
+    const int tbeg = (int)blockIdx.x * tper, tend = min(s, tbeg + tper);
+    if (tbeg >= tend) return;
+    const int mt = wv / G, hh = wv - mt * G;   // this wave's item
+    float cf[64];                              // elements 8 l + 2 i + half of centroid j0 + 32 mt + col at [4 l + i]
+    {
+        const int j = min(j0 + mt * 32 + col, C - 1);   // rows beyond C repeat centroid C-1; nothing reads their units
+        const T *row = (const T *)a.centroids + (((size_t)b * a.h + kv * G + hh) * a.c_max + j) * kD;
+#pragma unroll
+        for (int l = 0; l < 16; ++l) {
+            float x[8];
+            unpack(load_chunk(row, l), x);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                asm volatile("" : "+v"(x[2 * i]), "+v"(x[2 * i + 1]));   // (a select of two registers, not an indexed load)
+                cf[4 * l + i] = half ? x[2 * i + 1] : x[2 * i];
+            }
+        }
+    }
+    const T *K = (const T *)a.k.pages;
+    const int srow = tid >> 4, lane16 = tid & 15;
+    const int32_t *bt_row = a.k.block_table + (size_t)b * a.k.max_pages;
+    auto page_at = [&](int t0) { return bt_row[min(t0 + srow, s - 1) >> a.k.page_shift]; };
+    auto fetch = [&](int page, int t0) {
+        const uint32_t row = (uint32_t)((page * a.g + kv) << a.k.page_shift) + (uint32_t)(min(t0 + srow, s - 1) & ((1 << a.k.page_shift) - 1));
+        return load_chunk(K + (size_t)row * kD, lane16);
+    };
+    auto put = [&](const Chunk<T> &c, int buf) {
+        float x[8];
+        unpack(c, x);
+        float4 *dst = reinterpret_cast<float4 *>(&s_k[buf][srow * ROWW + lane16 * 8]);
+        dst[0] = make_float4(x[0], x[2], x[4], x[6]);
+        dst[1] = make_float4(x[1], x[3], x[5], x[7]);
+    };
+    float mx[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mx[r] = -__builtin_huge_valf();
+    // result register r holds centroid row 8 (r / 4) + 4 half + r % 4 of the item against key `col` of the step
+    const size_t unit0 = (size_t)blockIdx.y * CT + mt * 32;
+    const size_t rstep = (size_t)G * a.z_stride;
+    float *zb = a.z + (unit0 * G + hh) * a.z_stride;   // wave-uniform
+    const uint32_t lane_off = (uint32_t)(4 * half * rstep) + col;
+    int pg = page_at(tbeg + 32);
+    Chunk<T> st = fetch(page_at(tbeg), tbeg);
+    put(st, 0);
+    st = fetch(pg, tbeg + 32);
+    pg = page_at(tbeg + 64);
+    __syncthreads();
+    int buf = 0;
+    for (int t0 = tbeg; t0 < tend; t0 += 32, buf ^= 1) {
+        const float *kr = &s_k[buf][col * ROWW + half * 4];
+        auto chain = [&](int l, const float4 &kx) __attribute__((always_inline)) {
+            f32x16_t p = {};
+            p = __builtin_amdgcn_mfma_f32_32x32x2f32(cf[4 * l + 0], kx.x, p, 0, 0, 0);
+            p = __builtin_amdgcn_mfma_f32_32x32x2f32(cf[4 * l + 1], kx.y, p, 0, 0, 0);
+            p = __builtin_amdgcn_mfma_f32_32x32x2f32(cf[4 * l + 2], kx.z, p, 0, 0, 0);
+            return __builtin_amdgcn_mfma_f32_32x32x2f32(cf[4 * l + 3], kx.w, p, 0, 0, 0);
+        };
+        // the tree over the sixteen partials (the wave that shares the SIMD fills the matrix pipe during the adds)
+        f32x16_t lv[4], p;
+        float4 kn = *reinterpret_cast<const float4 *>(kr);
+#pragma unroll
+        for (int l = 0; l < 16; ++l) {
+            const float4 kx = kn;
+            if (l < 15) kn = *reinterpret_cast<const float4 *>(kr + (l + 1) * 8);
+            p = chain(l, kx);
+            if (l & 1) p = lv[0] + p;
+            if ((l & 3) == 3) p = lv[1] + p;
+            if ((l & 7) == 7) p = lv[2] + p;
+            if (l == 15) p = lv[3] + p;
+            // (left to itself the compiler starts all the chains before the first add, and spills: the sum is pinned here)
+            asm volatile("" : "+v"(p));
+            __builtin_amdgcn_sched_barrier(0);
+            if (!(l & 1)) lv[0] = p;
+            else if ((l & 3) == 1) lv[1] = p;
+            else if ((l & 7) == 3) lv[2] = p;
+            else if (l == 7) lv[3] = p;
+        }
+        if (t0 + 32 < tend) {   // the next step's keys to the other buffer, the one after that requested
+            put(st, buf ^ 1);
+            st = fetch(pg, t0 + 64);
+            pg = page_at(t0 + 96);
+        }
+        const bool in = t0 + col < tend;   // (a tail's repeated keys are real ones: harmless for a maximum)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float z = p[r] * a.scale;
+            mx[r] = fmaxf(mx[r], z);
+            if (in) (zb + (8 * (r >> 2) + (r & 3)) * rstep)[lane_off + (uint32_t)t0] = z;
+        }
+        __syncthreads();
+    }
+    // the maxima over the wave's 32 keys of a row: DPP inside rows of 16 lanes, then the two rows of a half
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        float v = mx[r];
+        v = fmaxf(v, dpp_f<0xB1>(v));
+        v = fmaxf(v, dpp_f<0x4E>(v));
+        v = fmaxf(v, dpp_f<0x141>(v));
+        v = fmaxf(v, dpp_f<0x140>(v));
+        v = fmaxf(v, __shfl_xor(v, 16));
+        if (col == r) atomicMax(&a.m_key[(unit0 + 4 * half + 8 * (r >> 2) + (r & 3)) * G + hh], ordered_key(v));
+    }
+}
+
+// exact_list_kernel: the list of one unit of the chunk per block: denominators of its G heads over all s scores, ranking
+// keys max_h ((z - m_h) - log S_h), the rho largest (select_keys; keys of up to KPT 512 positions in registers, the
+// scores of positions beyond that are read again).  The scores are read twice, the second time mostly from the memory-side
+// cache; nothing is written but the list.  grid (chunk units), 512 threads; dynamic shared memory: kSelLds + 2 kListCap +
+// 4 ceil(s_max / 64) words
+struct ExactListArgs {
+    int g, c_max, tile0, tiles_per_bk, ct;   // ct: centroids per tile
+    const int32_t *n_cent, *ctx_lens;
+    int z_stride, rho, n_init, n_local;
+    const float *z;
+    const uint32_t *m_key;
+    int32_t *lists;                          // [all units][c_max][rho]
+};
+
+template <int G, int KPT> __global__ __launch_bounds__(512) void exact_list_kernel(ExactListArgs a)
+{
+    extern __shared__ __align__(16) uint32_t smem[];
+    constexpr int NT = 512, NW = NT / 64;
+    __shared__ unsigned long long s_acc[NW][G];
+    __shared__ float s_ls[G];
+    __shared__ uint32_t s_res[4];
+    uint32_t *s_hist = smem, *s_list = smem + kSelLds, *s_bits = s_list + 2 * kListCap;
+    const int ul = blockIdx.x, tid = threadIdx.x, ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tile = a.tile0 + ul / a.ct, bk = tile / a.tiles_per_bk, j = (tile - bk * a.tiles_per_bk) * a.ct + ul % a.ct;
+    const int b = bk / a.g;
+    if (j >= a.n_cent[b]) return;
+    const int s = a.ctx_lens[b];
+    const float *zb = a.z + (size_t)ul * G * a.z_stride;
+    float m[G];
+#pragma unroll
+    for (int hh = 0; hh < G; ++hh) m[hh] = ordered_value(a.m_key[(size_t)ul * G + hh]);
+    for (int w = tid; w < kBuckets / 4; w += NT) reinterpret_cast<uint4 *>(s_hist)[w] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid == 0) s_res[3] = 0u;
+    // denominators: four keys per load, two loads in flight per head (terms beyond s count as none)
+#pragma unroll
+    for (int hh = 0; hh < G; ++hh) {
+        const float4 *row = reinterpret_cast<const float4 *>(zb + (size_t)hh * a.z_stride);
+        const int n4 = (s + 3) >> 2;
+        unsigned long long acc = 0;
+        constexpr int UN = 4;
+        for (int i0 = tid; i0 - ln < n4; i0 += UN * NT) {
+            float4 v[UN];
+#pragma unroll
+            for (int u = 0; u < UN; ++u) v[u] = row[min(i0 + u * NT, n4 - 1)];
+            uint32_t shi = 0, slo = 0;   // 16 terms: hi <= 2^16 and lo < 2^24 each
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const int i = 4 * (i0 + u * NT);
+                const float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    uint32_t hi, lo;
+                    exp_fixed40_parts(i + e < s ? x[e] - m[hh] : -40.0f, hi, lo);
+                    shi += hi;
+                    slo += lo;
+                }
+            }
+            acc += ((unsigned long long)shi << 24) + slo;
+        }
+        // a wave's sum in three 24-bit pieces: 64 lanes of each fit 32 bits
+        const uint32_t p0 = wave_sum_last((uint32_t)acc & 0xffffffu), p1 = wave_sum_last((uint32_t)(acc >> 24) & 0xffffffu),
+                       p2 = wave_sum_last((uint32_t)(acc >> 48));
+        if (ln == 63) s_acc[wv][hh] = (unsigned long long)p0 + ((unsigned long long)p1 << 24) + ((unsigned long long)p2 << 48);
+    }
+    __syncthreads();
+    if (tid < G) {
+        unsigned long long v = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v += s_acc[w][tid];
+        s_ls[tid] = (float)log_fixed40(v);
+    }
+    __syncthreads();
+    float ls[G];
+#pragma unroll
+    for (int hh = 0; hh < G; ++hh) ls[hh] = s_ls[hh];
+    auto key_at = [&](int i) __attribute__((always_inline)) {   // i < s_max
+        float best = (zb[i] - m[0]) - ls[0];
+#pragma unroll
+        for (int hh = 1; hh < G; ++hh) best = fmaxf(best, (zb[(size_t)hh * a.z_stride + i] - m[hh]) - ls[hh]);
+        return fmaxf(best, -3.0e38f);
+    };
+    auto listed = [&](int i) { return i < s - a.n_local && i >= a.n_init; };   // keys of the resident window enter no list
+    float kreg[KPT];
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+        const int i = q * NT + tid;
+        const float x = key_at(min(i, s - 1));
+        kreg[q] = listed(i) ? x : -__builtin_huge_valf();
+    }
+    int32_t *dst = a.lists + ((size_t)bk * a.c_max + j) * a.rho;
+    const int n_real = s - a.n_local - a.n_init;
+    if (a.rho >= n_real) {   // every key outside the window
+        for (int i = tid; i < a.rho; i += NT) dst[i] = a.n_init + i;
+        return;
+    }
+    select_keys<NT, KPT>(
+        kreg, s, n_real, a.rho,
+        [&](auto f) __attribute__((always_inline)) {
+            for (int gq = KPT * NW + wv; gq * 64 < s; gq += NW) {
+                const int i = gq * 64 + ln;
+                const float x = key_at(min(i, s - 1));
+                f(gq, listed(i) ? x : -__builtin_huge_valf());
+            }
+        },
+        [&](int, int gq, uint32_t pos) __attribute__((always_inline)) { dst[pos] = gq * 64 + ln; },
+        [&](int pos, int i) __attribute__((always_inline)) { dst[pos] = i; },
+        [&](int i) { return listed(i) ? ordered_key(key_at(i)) : 0x007fffffu; }, s_hist, s_list, s_bits, s_res);
 }
 
 // ------------------------------------------------------------------------------
@@ -2767,7 +3028,7 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
     } else {
         n = a.top_k;
         const bool placed = select_keys<NT, KPT>(
-            kreg, L, a.top_k, for_far,
+            kreg, L, L, a.top_k, for_far,
             [&](int q, int gq, uint32_t pos) __attribute__((always_inline)) {
                 s_pick[pos] = make_uint2((uint32_t)(gq * 64 + ln), rr[q]);
                 store_z<G>(s_p, (int)pos, zr[q]);
@@ -2923,7 +3184,7 @@ template <typename T> __global__ __launch_bounds__(kTailThreads) void dcu_select
             return;
         }
         select_keys<NT, KPT>(
-            kreg, L, a.d.rho,
+            kreg, L, L, a.d.rho,
             [&](auto f) __attribute__((always_inline)) {
                 for (int gq = KPT * NW + wv; gq * 64 < L; gq += NW) {
                     const int i = gq * 64 + ln;
