@@ -1028,7 +1028,7 @@ template <typename T, int G> int build_lists_exact_mfma(ctkvr_index *ix, const v
     lay_out(scratch_mem.base());
     const size_t lds = exact_list_lds(ix);
     const bool small = ix->s_max <= 8 * 512;
-    const void *fn = small ? (const void *)exact_list_kernel<G, 8> : (const void *)exact_list_kernel<G, 64>;
+    const void *fn = small ? (const void *)exact_list_kernel<G, 512, 8> : (const void *)exact_list_kernel<G, 1024, 32>;
     TRY(want_lds(ix->dev, fn, lds));
     const size_t n_m = (size_t)tiles * CT * G;
     fill_u32_kernel<<<dim3((unsigned)((n_m + 255) / 256)), 256, 0, st>>>(m_key, 0u, n_m);
@@ -1040,9 +1040,9 @@ template <typename T, int G> int build_lists_exact_mfma(ctkvr_index *ix, const v
         sa.c_max = ix->c_max;
         sa.tile0 = t0;
         sa.tiles_per_bk = tiles_per_bk;
-        // one block per CU and round (eight waves of 64-register fragments); at least two steps of 32 keys each
-        const int rounds = std::max(1, (nt * ((ix->s_max + 1023) / 1024) + ix->num_cu / 2) / ix->num_cu);
-        sa.t_splits = std::max(1, std::min((ix->s_max + 63) / 64, (rounds * ix->num_cu + nt - 1) / nt));
+        // one round of blocks, one per CU (eight waves of 64-register fragments; a block's prologue costs as much as four of
+        // its steps), of at least two steps of 32 keys each
+        sa.t_splits = std::max(1, std::min((ix->s_max + 63) / 64, ix->num_cu / nt));
         sa.n_cent = ix->d_n_cent;
         sa.ctx_lens = ix->d_ctx_lens;
         sa.centroids = ix->centroids;
@@ -1068,9 +1068,9 @@ template <typename T, int G> int build_lists_exact_mfma(ctkvr_index *ix, const v
         la.m_key = sa.m_key;
         la.lists = ix->lists;
         if (small)
-            exact_list_kernel<G, 8><<<dim3(nt * CT), 512, lds, st>>>(la);
+            exact_list_kernel<G, 512, 8><<<dim3(nt * CT), 512, lds, st>>>(la);
         else
-            exact_list_kernel<G, 64><<<dim3(nt * CT), 512, lds, st>>>(la);
+            exact_list_kernel<G, 1024, 32><<<dim3(nt * CT), 1024, lds, st>>>(la);
     }
     hipError_t e = hipGetLastError();
     hipError_t es = hipStreamSynchronize(st);   // the scratch is given back

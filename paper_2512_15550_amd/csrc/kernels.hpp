@@ -2415,11 +2415,14 @@ __device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int 
     uint32_t *s_scan = s_hist + 2048 + 4;
     {
         constexpr int BPT = kBuckets / NT;   // buckets per thread, in descending key order
-        static_assert(BPT == 4, "one 16-byte read");
-        const uint4 c4 = reinterpret_cast<const uint4 *>(s_hist)[tid];
-        const uint32_t c[4] = {c4.x, c4.y, c4.z, c4.w};
+        uint32_t c[BPT], mine = 0;
+#pragma unroll
+        for (int q = 0; q < BPT; ++q) {
+            c[q] = s_hist[BPT * tid + q];
+            mine += c[q];
+        }
         uint32_t tot;
-        uint32_t before = block_excl_scan<NT>((c[0] + c[1]) + (c[2] + c[3]), s_scan, &tot);
+        uint32_t before = block_excl_scan<NT>(mine, s_scan, &tot);
         const uint32_t want = (uint32_t)top_k;
         if (want > tot) {   // (uniform) the last bucket decides
             if (tid == 0) {
@@ -2598,7 +2601,7 @@ struct ExactScoreArgs {
 template <typename T, int G> __global__ __launch_bounds__(512) void exact_score_kernel(ExactScoreArgs a)
 {
     constexpr int CT = 32 * (8 / G), ROWW = 132;   // floats per staged key row (128 + 4: rows spread over the banks)
-    __shared__ __align__(16) float s_k[2][32 * ROWW];
+    __shared__ __align__(16) float s_k[2][64 * ROWW];   // two steps of 32 keys per buffer and barrier
     const int tid = threadIdx.x, ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = ln & 31, half = ln >> 5;
     const int tile = a.tile0 + (int)blockIdx.y, bk = tile / a.tiles_per_bk, jt = tile - bk * a.tiles_per_bk;
@@ -2633,45 +2636,50 @@ template <typename T, int G> __global__ __launch_bounds__(512) void exact_score_
         const uint32_t row = (uint32_t)((page * a.g + kv) << a.k.page_shift) + (uint32_t)(min(t0 + srow, s - 1) & ((1 << a.k.page_shift) - 1));
         return load_chunk(K + (size_t)row * kD, lane16);
     };
-    auto put = [&](const Chunk<T> &c, int buf) {
+    auto put = [&](const Chunk<T> &c, int buf, int sub) __attribute__((always_inline)) {
         float x[8];
         unpack(c, x);
-        float4 *dst = reinterpret_cast<float4 *>(&s_k[buf][srow * ROWW + lane16 * 8]);
+        float4 *dst = reinterpret_cast<float4 *>(&s_k[buf][(sub * 32 + srow) * ROWW + lane16 * 8]);
         dst[0] = make_float4(x[0], x[2], x[4], x[6]);
         dst[1] = make_float4(x[1], x[3], x[5], x[7]);
     };
     float mx[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) mx[r] = -__builtin_huge_valf();
-    // result register r holds centroid row 8 (r / 4) + 4 half + r % 4 of the item against key `col` of the step
+    // The centroids are the rows of the instruction and the keys its columns: result register r holds centroid row
+    // 8 (r / 4) + 4 half + r % 4 of the item against key `col` of the step, and a store writes two whole 128-byte lines (with
+    // the roles exchanged a lane stores 16 bytes, but 32 to a line, and the stores took longer than the matrix work).
     const size_t unit0 = (size_t)blockIdx.y * CT + mt * 32;
     const size_t rstep = (size_t)G * a.z_stride;
-    float *zb = a.z + (unit0 * G + hh) * a.z_stride;   // wave-uniform
-    const uint32_t lane_off = (uint32_t)(4 * half * rstep) + col;
-    int pg = page_at(tbeg + 32);
-    Chunk<T> st = fetch(page_at(tbeg), tbeg);
-    put(st, 0);
-    st = fetch(pg, tbeg + 32);
-    pg = page_at(tbeg + 64);
-    __syncthreads();
-    int buf = 0;
-    for (int t0 = tbeg; t0 < tend; t0 += 32, buf ^= 1) {
-        const float *kr = &s_k[buf][col * ROWW + half * 4];
-        auto chain = [&](int l, const float4 &kx) __attribute__((always_inline)) {
-            f32x16_t p = {};
-            p = __builtin_amdgcn_mfma_f32_32x32x2f32(cf[4 * l + 0], kx.x, p, 0, 0, 0);
-            p = __builtin_amdgcn_mfma_f32_32x32x2f32(cf[4 * l + 1], kx.y, p, 0, 0, 0);
-            p = __builtin_amdgcn_mfma_f32_32x32x2f32(cf[4 * l + 2], kx.z, p, 0, 0, 0);
-            return __builtin_amdgcn_mfma_f32_32x32x2f32(cf[4 * l + 3], kx.w, p, 0, 0, 0);
-        };
-        // the tree over the sixteen partials (the wave that shares the SIMD fills the matrix pipe during the adds)
+    char *zb = reinterpret_cast<char *>(a.z + (unit0 * G + hh) * a.z_stride);   // wave-uniform
+    const uint32_t lane_off = ((uint32_t)(4 * half * rstep) + col) * 4u;
+    // A step's results leave the registers during the next step, a row per chain (all of them at the end of a step, before a
+    // barrier, left the matrix pipe half idle).
+    f32x16_t pz;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) pz[r] = -__builtin_huge_valf();
+    int pt = tend;   // the step they belong to (none yet)
+    auto row_out = [&](int r, bool whole, uint32_t off) __attribute__((always_inline)) {
+        const float z = pz[r] * a.scale;
+        mx[r] = fmaxf(mx[r], z);   // (a tail's repeated keys are real ones: harmless for a maximum)
+        float *dst = reinterpret_cast<float *>(zb + (8 * (r >> 2) + (r & 3)) * rstep * 4 + off);
+        if (whole || pt + col < tend) *dst = z;
+    };
+    auto step = [&](const float *kr, int t0, bool have_prev) __attribute__((always_inline)) {   // have_prev: and it is a whole step
+        const uint32_t off = lane_off + (uint32_t)pt * 4u;
+        // the tree over the sixteen partials
         f32x16_t lv[4], p;
         float4 kn = *reinterpret_cast<const float4 *>(kr);
 #pragma unroll
         for (int l = 0; l < 16; ++l) {
             const float4 kx = kn;
             if (l < 15) kn = *reinterpret_cast<const float4 *>(kr + (l + 1) * 8);
-            p = chain(l, kx);
+            p = f32x16_t{};
+            p = __builtin_amdgcn_mfma_f32_32x32x2f32(cf[4 * l + 0], kx.x, p, 0, 0, 0);
+            p = __builtin_amdgcn_mfma_f32_32x32x2f32(cf[4 * l + 1], kx.y, p, 0, 0, 0);
+            p = __builtin_amdgcn_mfma_f32_32x32x2f32(cf[4 * l + 2], kx.z, p, 0, 0, 0);
+            p = __builtin_amdgcn_mfma_f32_32x32x2f32(cf[4 * l + 3], kx.w, p, 0, 0, 0);
+            if (have_prev) row_out(l, true, off);
             if (l & 1) p = lv[0] + p;
             if ((l & 3) == 3) p = lv[1] + p;
             if ((l & 7) == 7) p = lv[2] + p;
@@ -2684,20 +2692,32 @@ template <typename T, int G> __global__ __launch_bounds__(512) void exact_score_
             else if ((l & 7) == 3) lv[2] = p;
             else if (l == 7) lv[3] = p;
         }
-        if (t0 + 32 < tend) {   // the next step's keys to the other buffer, the one after that requested
-            put(st, buf ^ 1);
-            st = fetch(pg, t0 + 64);
-            pg = page_at(t0 + 96);
-        }
-        const bool in = t0 + col < tend;   // (a tail's repeated keys are real ones: harmless for a maximum)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const float z = p[r] * a.scale;
-            mx[r] = fmaxf(mx[r], z);
-            if (in) (zb + (8 * (r >> 2) + (r & 3)) * rstep)[lane_off + (uint32_t)t0] = z;
-        }
+        pz = p;
+        pt = t0;
+    };
+    int pg0 = page_at(tbeg + 64), pg1 = page_at(tbeg + 96);
+    Chunk<T> st0 = fetch(page_at(tbeg), tbeg), st1 = fetch(page_at(tbeg + 32), tbeg + 32);
+    put(st0, 0, 0);
+    put(st1, 0, 1);
+    __syncthreads();
+    int buf = 0;
+    auto pair = [&](int t0, bool have_prev) __attribute__((always_inline)) {
+        const float *kr = &s_k[buf][col * ROWW + half * 4];
+        st0 = fetch(pg0, t0 + 64);   // the next pair of steps (clamped rows beyond the sequence)
+        st1 = fetch(pg1, t0 + 96);
+        pg0 = page_at(t0 + 128);
+        pg1 = page_at(t0 + 160);
+        step(kr, t0, have_prev);
+        put(st0, buf ^ 1, 0);
+        put(st1, buf ^ 1, 1);
+        if (t0 + 32 < tend) step(kr + 32 * ROWW, t0 + 32, true);   // uniform
         __syncthreads();
-    }
+        buf ^= 1;
+    };
+    pair(tbeg, false);
+    for (int t0 = tbeg + 64; t0 < tend; t0 += 64) pair(t0, true);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) row_out(r, false, lane_off + (uint32_t)pt * 4u);
     // the maxima over the wave's 32 keys of a row: DPP inside rows of 16 lanes, then the two rows of a half
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -2725,10 +2745,10 @@ struct ExactListArgs {
     int32_t *lists;                          // [all units][c_max][rho]
 };
 
-template <int G, int KPT> __global__ __launch_bounds__(512) void exact_list_kernel(ExactListArgs a)
+template <int G, int NT, int KPT> __global__ __launch_bounds__(NT) void exact_list_kernel(ExactListArgs a)
 {
     extern __shared__ __align__(16) uint32_t smem[];
-    constexpr int NT = 512, NW = NT / 64;
+    constexpr int NW = NT / 64;
     __shared__ unsigned long long s_acc[NW][G];
     __shared__ float s_ls[G];
     __shared__ uint32_t s_res[4];
