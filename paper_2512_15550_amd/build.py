@@ -15,6 +15,9 @@ HIPCC_FLAGS = [
     "-ffp-contract=off",
     # no packed-fp32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # matrix results in ordinary vector registers: a kernel of 512 registers a wave otherwise gets them in the accumulation
+    # half, and every vector instruction on a result first copies it
+    "-mllvm", "-amdgpu-mfma-vgpr-form=1",
 ]
 
 

@@ -882,7 +882,7 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
                 ma.scale = ix->scale;
                 ma.step_stride = 1;
                 // passes over the same tiles: softmax statistics first
-                mfma_score_kernel<G, MFMA_STAT><<<dim3(ma.t_splits, tiles), 256, 0, st>>>(ma);
+                mfma_score_kernel<G, MFMA_STAT><<<dim3(ma.t_splits, tiles), (MfmaShape<G, MFMA_STAT>::NT), 0, st>>>(ma);
                 bool redo = !by_cand;
                 if (by_cand) {
                     // keys of a sample of the positions -> a threshold per unit -> all keys again, those at or above
@@ -890,7 +890,7 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
                     ma.kbuf = ksamp;
                     ma.step_stride = step_stride;
                     ma.sample_stride = sample_stride;
-                    mfma_score_kernel<G, MFMA_SAMPLE><<<dim3(ma.t_splits, tiles), 256, 0, st>>>(ma);
+                    mfma_score_kernel<G, MFMA_SAMPLE><<<dim3(ma.t_splits, tiles), (MfmaShape<G, MFMA_SAMPLE>::NT), 0, st>>>(ma);
                     CandArgs ca{};
                     ca.u = u;
                     ca.ctx_lens = ix->d_ctx_lens;
@@ -917,7 +917,7 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
                     ma.cand = cand;
                     ma.seg_cnt = cursor;
                     ma.seg_cap = seg_cap;
-                    mfma_score_kernel<G, MFMA_PICK><<<dim3(ma.t_splits, tiles), 256, 0, st>>>(ma);
+                    mfma_score_kernel<G, MFMA_PICK><<<dim3(ma.t_splits, tiles), (MfmaShape<G, MFMA_PICK>::NT), 0, st>>>(ma);
                     cand_select_kernel<<<dim3(nu), 1024, cand_lds, st>>>(ca);
                     uint32_t failed = 0;
                     hipError_t ec = hipMemcpyAsync(&failed, d_fail, 4, hipMemcpyDeviceToHost, st);
@@ -939,7 +939,7 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
                 }
                 if (redo) {   // every key stored, then histogram and selection over all of them
                     ma.kbuf = kbuf;
-                    mfma_score_kernel<G, MFMA_KEY><<<dim3(ma.t_splits, tiles), 256, 0, st>>>(ma);
+                    mfma_score_kernel<G, MFMA_KEY><<<dim3(ma.t_splits, tiles), (MfmaShape<G, MFMA_KEY>::NT), 0, st>>>(ma);
                     keys_written = true;
                 }
             } else {

@@ -877,11 +877,14 @@ template <typename T, int G, bool WIN> __global__ __launch_bounds__(256) void re
 // Algorithm 1 line 2 on the matrix cores (bf16 only): the same z = (c_{h,j} . k_t) *
 // scale as score_kernel in build mode, but the 128-term dot is a chain of eight
 // v_mfma_f32_32x32x16_bf16.  A block owns 8/G sub-tiles of 32 centroids of one
-// (sequence, KV head) for all G heads (8 wave work items, two per wave -- two heads of the
-// same sub-tile when G >= 2 -- their A fragments resident in registers) and walks a range of
-// keys 32 at a time: B fragments are 16-byte pieces of the paged key rows; in the passes that
-// form ranking keys the 32x32 results of a head pair are reduced in registers and go through
-// shared memory, where the maximum over the pairs is taken.  grid (t_splits, tiles), 256 threads.
+// (sequence, KV head) for all G heads: eight (head, sub-tile) items, their A fragments resident in
+// registers, four to a wave, and walks a range of keys 64 at a time, one wave of each item on either
+// half (B fragments are 16-byte pieces of the paged key rows, staged through shared memory).
+// A wave has all heads of its centroids, so a ranking key is finished in its registers and the block meets only for
+// the key rows; one fragment read feeds four matrix instructions.  (Two items per wave and the head pairs
+// meeting in shared memory, 128K x 8 KV heads x 2048 centroids, half of the heads per launch: candidate pass 1.69 ms,
+// 0.65 PFLOP/s, now 1.11 ms, 0.99 PFLOP/s; statistics 1.16 -> 1.11 ms, bound by the exponentials.)
+// grid (t_splits, tiles), MfmaShape::NT threads.
 // The scores differ from the fixed arithmetic in the accumulation order inside the MFMA and
 // the softmax denominators in how they are summed; on inputs whose dot products are exact in
 // fp32 only the latter is left.
@@ -926,26 +929,38 @@ struct MfmaScoreArgs {
 // chunk is redone by the KEY route: the result never depends on the sample.
 enum { MFMA_STAT = 0, MFMA_KEY = 2, MFMA_SAMPLE = 3, MFMA_PICK = 4 };
 
-template <int G, int MODE> __global__ __launch_bounds__(256, 2) void mfma_score_kernel(MfmaScoreArgs a)
+// A wave's share of a block: ITEMS (head, 32-centroid sub-tile) pairs with their fragments resident, against one of
+// the two 32-key halves of a step.  The key passes give a wave all heads of its sub-tiles, so a ranking key is
+// complete in the wave's own registers; with eight heads that is 256 registers of fragments, one wave per SIMD.
+template <int G, int MODE> struct MfmaShape {
+    static constexpr int CT = 32 * (8 / G);                            // centroids of a block
+    static constexpr int ITEMS = MODE != MFMA_STAT && G == 8 ? 8 : 4;
+    static constexpr int WC = 8 / ITEMS;                               // waves side by side over the items
+    static constexpr int NT = 2 * WC * 64;
+    static constexpr int kWaves = ITEMS == 8 ? 1 : 2;                  // per SIMD
+};
+
+template <int G, int MODE>
+__global__ __launch_bounds__((MfmaShape<G, MODE>::NT), (MfmaShape<G, MODE>::kWaves)) void mfma_score_kernel(MfmaScoreArgs a)
 {
-    constexpr int MT = 8 / G;        // 32-centroid sub-tiles per block
-    constexpr int CT = 32 * MT;      // centroids per block
-    // The key passes: the result tiles, [head pair][centroid][key] -- a wave's two work items are two heads of
-    // the same 32 centroids (G >= 2), so the maximum over that pair is taken in registers and one plane per
-    // pair goes through shared memory; a lane's four consecutive keys are one 16-byte write, a reader's four
-    // keys one 16-byte read; 36-word rows spread both over the banks
-    constexpr int ZS = 36;
-    constexpr int NPL = G >= 2 ? G / 2 : 1;    // planes
-    constexpr bool KEYS = MODE != MFMA_STAT;   // the passes that form ranking keys
-    __shared__ __align__(16) float s_z[KEYS ? 2 * NPL * CT * ZS : 4];   // two buffers: see keys_out
+    using S = MfmaShape<G, MODE>;
+    constexpr int CT = S::CT, ITEMS = S::ITEMS, NT = S::NT;
+    constexpr bool KEYS = MODE != MFMA_STAT;       // the passes that form ranking keys
+    constexpr int SUB = ITEMS >= G ? ITEMS / G : 1;   // sub-tiles of a wave (key passes: each with all G heads)
     // PICK: the tile's thresholds and how many candidates this block has found for each of its centroids.  A block
     // owns a segment of every unit's candidate list, so positions are handed out by shared-memory counters: no
     // atomic on device memory (on this part those are served beyond the XCD's cache, a round trip each).
-    __shared__ float s_tauf[MODE == MFMA_PICK ? CT : 1];
     __shared__ uint32_t s_cnt[MODE == MFMA_PICK ? CT : 1];
-    __shared__ __align__(16) unsigned char s_k[2][32 * 272];
+    // key passes: 32 x 32 ranking keys of a wave on their way out, [centroid][key]; a wave's own, so no barrier.  A
+    // lane's four consecutive keys are one 16-byte access, 36-word rows spread them over the banks.
+    constexpr int ZS = 36;
+    __shared__ __align__(16) float s_z[KEYS ? (NT / 64) * 32 * ZS : 4];
+    __shared__ float2 s_stat[KEYS ? 1 : S::WC * ITEMS * 32];
+    constexpr int ROWB = 272;   // bytes per staged key row (256 + padding: fragment reads spread over the banks)
+    __shared__ __align__(16) unsigned char s_k[2][64 * ROWB];
     const int tid = threadIdx.x, wv = tid >> 6, ln = tid & 63;
     const int col = ln & 31, half = ln >> 5;
+    const int wc = wv >> 1, sub = wv & 1;          // the wave's items, its half of a step's keys
     const int bkl = blockIdx.y / a.tiles_per_bk, jt = blockIdx.y - bkl * a.tiles_per_bk;
     const int bk = a.bk0 + bkl;
     const int b = bk / a.g, kv = bk - b * a.g;
@@ -953,175 +968,129 @@ template <int G, int MODE> __global__ __launch_bounds__(256, 2) void mfma_score_
     const int j0 = jt * CT;
     if (j0 >= C) return;
     const int tper = (((s + a.t_splits - 1) / a.t_splits) + 31) & ~31;
-    const int ST = MODE == MFMA_SAMPLE ? 32 * a.step_stride : 32;   // keys from one step to the next
-    // SAMPLE: the steps taken are those that start at a multiple of ST; a block starts at the first one in its range
+    // a step is two groups of 32 keys, ST apart.  SAMPLE: the groups taken are those that start at a multiple of ST; a
+    // block starts at the first one in its range
+    const int ST = MODE == MFMA_SAMPLE ? 32 * a.step_stride : 32;
     const int tbeg = MODE == MFMA_SAMPLE ? ((int)(blockIdx.x * tper) + ST - 1) / ST * ST : (int)(blockIdx.x * tper);
     const int tend = min(s, (int)(blockIdx.x * tper) + tper);
     if (tbeg >= tend) return;
     if constexpr (MODE == MFMA_PICK) {
-        if (tid < CT) {
-            const uint32_t tk = a.tau[(size_t)bkl * a.c_max + min(j0 + tid, C - 1)];
-            s_tauf[tid] = tk ? ordered_value(tk) : -__builtin_huge_valf();   // 0: no threshold, every key is a candidate
-            s_cnt[tid] = 0u;
-        }
+        for (int c = tid; c < CT; c += NT) s_cnt[c] = 0u;
     }
     // The matrix instruction is issued with the keys as its row operand and the centroids as its
     // column operand: a lane then holds ONE centroid (column `col` of its sub-tile) against 16
     // keys (rows 8 (r / 4) + 4 half + r % 4), and that centroid's statistics are single registers.
-    int hh[2], mt[2];
-    bf16x8_t cfrag[2][8];                  // the centroid fragments, resident
-    float mx[2];                           // STAT: running maximum; KEY: the final maximum m
-    float lsv[2];                          // STAT: running sum of exp(z - mx); KEY: log S
-    size_t stat[2];
+    // Item q of the wave: head q % G of sub-tile wc * SUB + q / G (G = 8 with four items: head 4 wc + q of the one).
+    auto head_of = [&](int q) { return ITEMS >= G ? q % G : wc * ITEMS + q; };
+    auto tile_of = [&](int q) { return ITEMS >= G ? wc * SUB + q / G : 0; };
+    bf16x8_t cfrag[ITEMS][8];              // the centroid fragments, resident
+    float mx[ITEMS];                       // STAT: running maximum (base two)
+    float lsv[ITEMS];                      // STAT: running sum of 2^(z log2(e) - mx)
+    float off[ITEMS];                      // key passes: -(m + log S), so that a key is one fused multiply-add per score
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        int it = wv * 2 + q;
-        mt[q] = it / G;   // G >= 2: both items of a wave are heads of one sub-tile; G = 1: two sub-tiles
-        hh[q] = it - mt[q] * G;
-        const int j = min(j0 + mt[q] * 32 + col, C - 1);   // columns beyond C repeat centroid C-1 and are dropped at the end
-        const bf16_t *row = a.centroids + (((size_t)b * a.h + kv * G + hh[q]) * a.c_max + j) * kD;
+    for (int q = 0; q < ITEMS; ++q) {
+        const int j = min(j0 + tile_of(q) * 32 + col, C - 1);   // columns beyond C repeat centroid C-1 and are dropped at the end
+        const bf16_t *row = a.centroids + (((size_t)b * a.h + kv * G + head_of(q)) * a.c_max + j) * kD;
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) cfrag[q][ks] = *reinterpret_cast<const bf16x8_t *>(row + ks * 16 + 8 * half);
-        stat[q] = ((size_t)bkl * a.c_max + j) * G + hh[q];
         mx[q] = -__builtin_huge_valf();
-        lsv[q] = 0.0f;
+        lsv[q] = off[q] = 0.0f;
         if constexpr (KEYS) {
             // the blocks' pairs in block order: the same value in every block that reads them
-            const float2 *pp = a.part + stat[q] * a.t_splits;
+            const float2 *pp = a.part + (((size_t)bkl * a.c_max + j) * G + head_of(q)) * a.t_splits;
             float m = -__builtin_huge_valf();
             for (int x = 0; x < a.t_splits && x * tper < s; ++x) m = fmaxf(m, pp[x].x);
-            float S = 0.0f;
-            for (int x = 0; x < a.t_splits && x * tper < s; ++x) S += pp[x].y * __builtin_amdgcn_exp2f(pp[x].x - m);
-            mx[q] = m * 0.693147180559945309f;   // the pairs hold base-two maxima
-            lsv[q] = logf(S);
+            float sum = 0.0f;
+            for (int x = 0; x < a.t_splits && x * tper < s; ++x) sum += pp[x].y * __builtin_amdgcn_exp2f(pp[x].x - m);
+            off[q] = -(m * 0.693147180559945309f + logf(sum));   // the pairs hold base-two maxima
+        }
+    }
+    float tau[SUB];
+    uint2 *seg[SUB];   // PICK: the block's segment of the lane's centroid
+    if constexpr (MODE == MFMA_PICK) {
+#pragma unroll
+        for (int m = 0; m < SUB; ++m) {
+            const size_t unit = (size_t)bkl * a.c_max + min(j0 + tile_of(m * G) * 32 + col, C - 1);
+            const uint32_t tk = a.tau[unit];
+            // 0: no threshold, every key is a candidate.  A column beyond C keeps nothing
+            tau[m] = tk ? ordered_value(tk) : -__builtin_huge_valf();
+            seg[m] = a.cand + (unit * a.t_splits + blockIdx.x) * a.seg_cap;
         }
     }
     const float sc2 = a.scale * 1.44269504088896341f;   // scores in base two (statistics pass)
-    // key passes: the score's offset -(m + log S), so that a key is one fused multiply-add per score
-    const float off[2] = {-(mx[0] + lsv[0]), -(mx[1] + lsv[1])};
-    // The 32 key rows of a step (8 KB) go through shared memory once for the four waves, in two
-    // buffers; a step's rows are requested two steps ahead and their block-table entries four
-    // steps ahead, so that neither latency is waited for.  Rows beyond the sequence are clamped
-    // to its last key.
+    // The 64 key rows of a step (16 KB) go through shared memory once for all waves, in two
+    // buffers; a step's rows are requested one step ahead (a step is 2048 cycles of matrix work per SIMD with two
+    // waves on it) and their block-table entries two.  Rows beyond the sequence are clamped to its last key.
     const bf16_t *K = (const bf16_t *)a.k.pages;
-    constexpr int ROWB = 272;   // bytes per staged key row (256 + padding: fragment reads spread over the banks)
-    const int srow = tid >> 3, spart = tid & 7;
-    // A row's block-table entry is requested four steps ahead and turned into the row only when
-    // the row itself is requested: computing it at once would wait for the entry, and with it for
-    // every key request still in flight.
+    constexpr int TPR = NT / 64, NU = 16 / TPR;   // threads per row, 16-byte pieces per thread
+    const int srow = tid / TPR, spart = tid % TPR;
+    const int skey = (srow >> 5) * ST + (srow & 31);
     const int32_t *bt_row = a.k.block_table + (size_t)b * a.k.max_pages;
-    auto page_at = [&](int t0) { return bt_row[min(t0 + srow, s - 1) >> a.k.page_shift]; };
+    auto page_at = [&](int t0) { return bt_row[min(t0 + skey, s - 1) >> a.k.page_shift]; };
     auto row_from = [&](int page, int t0) {
-        return (uint32_t)((page * a.g + kv) << a.k.page_shift) + (uint32_t)(min(t0 + srow, s - 1) & ((1 << a.k.page_shift) - 1));
+        return (uint32_t)((page * a.g + kv) << a.k.page_shift) + (uint32_t)(min(t0 + skey, s - 1) & ((1 << a.k.page_shift) - 1));
     };
-    // staging registers as named variables: an array indexed through the helpers would be kept in
-    // private memory, and every request would then be waited for at once to be stored there
-    uint4 st0a, st0b, st1a, st1b;
-    auto fetch = [&](uint4 &x, uint4 &y, uint32_t row) {
-        const uint4 *src = reinterpret_cast<const uint4 *>(K + (size_t)row * kD + spart * 16);
-        x = src[0];
-        y = src[1];
+    auto piece_of = [&](uint32_t row, int u) { return (reinterpret_cast<const uint4 *>(K + (size_t)row * kD) + spart)[u * TPR]; };
+    auto put = [&](const uint4 &x, int u, int buf) {
+        *reinterpret_cast<uint4 *>(&s_k[buf][srow * ROWB + (u * TPR + spart) * 16]) = x;
     };
-    auto put = [&](const uint4 &x, const uint4 &y, int buf) {
-        uint4 *dst = reinterpret_cast<uint4 *>(&s_k[buf][srow * ROWB + spart * 32]);
-        dst[0] = x;
-        dst[1] = y;
-    };
-    bool have_prev = false, prev_tail = false;
-    int prev_t0 = 0, zb = 0;
-    // Second half of a key pass's step: the tile's keys leave shared memory (zsrc: the buffer the step's results
-    // were written to).  It runs one step late, after the NEXT step's matrix work, so that one barrier per step serves
-    // both the key rows' hand-over and this one (the result tiles are double-buffered).
-    auto keys_out = [&](const bool tail, int t0, const float *zsrc) __attribute__((always_inline)) {
-        // four consecutive keys of one centroid per thread: maximum over the heads, one 16-byte
-        // store where the key rows allow it (whole step in range, row length a multiple of four)
-        const bool wide = !tail && ((MODE == MFMA_SAMPLE ? a.sample_stride : a.l_stride) & 3) == 0;
+    // the wave's 32 ranking keys of a sub-tile's 32 centroids, keys tb .. tb + 31
+    float *const zw = &s_z[KEYS ? wv * (32 * ZS) : 0];
+    auto keys_out = [&](const bool tail, int tb, int m, const float (&best)[16]) __attribute__((always_inline)) {
+        const int jt0 = j0 + tile_of(m * G) * 32;
         if constexpr (MODE == MFMA_PICK) {
-            // Few keys pass (a few per cent): the verdicts of all of a thread's keys first, then one
-            // shared-memory counter bump per (thread, centroid) for the whole group of four, then the stores.
-            constexpr int NP = CT * 8 / 256;
-            float bv[NP][4];
-            uint32_t msk[NP], at[NP];
-            const bool inner = !tail && t0 >= a.n_init && t0 + 32 <= s - a.n_local && j0 + CT <= C;
-            if (t0 < tend) {
+            // Few keys pass (a few per cent): a lane's verdicts as a mask, one counter bump for all of them, then as
+            // many rounds as the fullest lane has candidates (about three); the keys are picked out of shared memory
+            // because registers have no run-time index.  Compared as floats: the same verdict as on the ordered images
+            // except that -0 passes a threshold of +0, i.e. at most a candidate too many.
+            uint32_t msk = 0;
+            const bool inner = !tail && tb >= a.n_init && tb + 32 <= s - a.n_local && jt0 + 32 <= C;
+            if (inner) {   // the whole group lies inside the block's range and outside the window, every centroid is real
 #pragma unroll
-                for (int it = 0; it < NP; ++it) {
-                    const int p = tid + 256 * it, n4 = (p & 7) * 4, jl = p >> 3;
-                    float4 best = *reinterpret_cast<const float4 *>(&zsrc[jl * ZS + n4]);
+                for (int r = 0; r < 16; ++r) msk |= (uint32_t)(best[r] >= tau[m]) << r;
+            } else {
 #pragma unroll
-                    for (int c = 1; c < NPL; ++c) {
-                        const float4 o = *reinterpret_cast<const float4 *>(&zsrc[(c * CT + jl) * ZS + n4]);
-                        best.x = fmaxf(best.x, o.x);
-                        best.y = fmaxf(best.y, o.y);
-                        best.z = fmaxf(best.z, o.z);
-                        best.w = fmaxf(best.w, o.w);
-                    }
-                    const int t = t0 + n4;
-                    bv[it][0] = best.x;
-                    bv[it][1] = best.y;
-                    bv[it][2] = best.z;
-                    bv[it][3] = best.w;
-                    // compared as floats: the same verdict as on the ordered images except that -0 passes a
-                    // threshold of +0, i.e. at most a candidate too many
-                    const float tau = s_tauf[jl];
-                    uint32_t m = 0;
-                    if (inner) {   // the whole step lies inside the block's range and outside the window, every centroid is real
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) m |= (uint32_t)(bv[it][e] >= tau) << e;
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const bool in = (t + e) < tend && (t + e) >= a.n_init && (t + e) < s - a.n_local && (j0 + jl) < C;
-                            m |= (uint32_t)(in && bv[it][e] >= tau) << e;
-                        }
-                    }
-                    msk[it] = m;
-                }
-#pragma unroll
-                for (int it = 0; it < NP; ++it) {
-                    at[it] = 0u;
-                    if (msk[it]) at[it] = atomicAdd(&s_cnt[(tid + 256 * it) >> 3], (uint32_t)__popc(msk[it]));
-                }
-#pragma unroll
-                for (int it = 0; it < NP; ++it) {
-                    if (msk[it]) {
-                        const int p = tid + 256 * it, n4 = (p & 7) * 4, jl = p >> 3;
-                        uint2 *seg = a.cand + (((size_t)bkl * a.c_max + j0 + jl) * a.t_splits + blockIdx.x) * a.seg_cap;
-                        uint32_t w = at[it];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            if ((msk[it] >> e) & 1u) {
-                                if (w < (uint32_t)a.seg_cap) seg[w] = make_uint2(ordered_key(bv[it][e]), (uint32_t)(t0 + n4 + e));
-                                ++w;
-                            }
-                        }
-                    }
+                for (int r = 0; r < 16; ++r) {
+                    const int t = tb + 8 * (r >> 2) + 4 * half + (r & 3);
+                    const bool in = t < tend && t >= a.n_init && t < s - a.n_local && (jt0 + col) < C;
+                    msk |= (uint32_t)(in && best[r] >= tau[m]) << r;
                 }
             }
-        } else if (t0 < tend) {
-            for (int p = tid; p < CT * 8; p += 256) {
-                const int n4 = (p & 7) * 4, jl = p >> 3;
-                if ((j0 + jl) >= C) continue;
-                float4 best = *reinterpret_cast<const float4 *>(&zsrc[jl * ZS + n4]);
+            float *const mine = zw + col * ZS + 4 * half;
 #pragma unroll
-                for (int c = 1; c < NPL; ++c) {
-                    const float4 o = *reinterpret_cast<const float4 *>(&zsrc[(c * CT + jl) * ZS + n4]);
-                    best.x = fmaxf(best.x, o.x);
-                    best.y = fmaxf(best.y, o.y);
-                    best.z = fmaxf(best.z, o.z);
-                    best.w = fmaxf(best.w, o.w);
-                }
-                const int t = t0 + n4;
-                uint32_t ok[4] = {ordered_key(best.x), ordered_key(best.y), ordered_key(best.z), ordered_key(best.w)};
-                bool win[4];
+            for (int rq = 0; rq < 4; ++rq)
+                *reinterpret_cast<float4 *>(mine + 8 * rq) = make_float4(best[4 * rq], best[4 * rq + 1], best[4 * rq + 2], best[4 * rq + 3]);
+            if (msk) {
+                uint32_t at = atomicAdd(&s_cnt[tile_of(m * G) * 32 + col], (uint32_t)__popc(msk));
+                do {
+                    const int r = __ffs(msk) - 1, k = 2 * (r & 12) + (r & 3);
+                    msk &= msk - 1u;
+                    if (at < (uint32_t)a.seg_cap) seg[m][at] = make_uint2(ordered_key(mine[k]), (uint32_t)(tb + 4 * half + k));
+                    ++at;
+                } while (msk);
+            }
+        } else {
+            // through the wave's shared memory so that eight lanes store 128 contiguous bytes of a unit's keys, 16 each
+            // where the key rows allow it (whole group in range, row length a multiple of four)
+            float *const mine = zw + col * ZS + 4 * half;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    win[e] = (t + e) < a.n_init || (t + e) >= s - a.n_local;
-                    if (win[e]) ok[e] = 0x007fffffu;   // the image of -inf
-                }
-                const size_t unit = (size_t)bkl * a.c_max + j0 + jl;
-                {
-                    uint32_t *dst = MODE == MFMA_SAMPLE ? a.kbuf + unit * a.sample_stride + (t0 / ST) * 32 + n4
+            for (int rq = 0; rq < 4; ++rq)
+                *reinterpret_cast<float4 *>(mine + 8 * rq) = make_float4(best[4 * rq], best[4 * rq + 1], best[4 * rq + 2], best[4 * rq + 3]);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const bool wide = !tail && ((MODE == MFMA_SAMPLE ? a.sample_stride : a.l_stride) & 3) == 0;
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+                const int n4 = (ln & 7) * 4, jl = it * 8 + (ln >> 3);
+                const float4 v = *reinterpret_cast<const float4 *>(&zw[jl * ZS + n4]);
+                const int t = tb + n4;
+                uint32_t ok[4] = {ordered_key(v.x), ordered_key(v.y), ordered_key(v.z), ordered_key(v.w)};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if ((t + e) < a.n_init || (t + e) >= s - a.n_local) ok[e] = 0x007fffffu;   // the image of -inf
+                if (jt0 + jl < C && tb < tend) {
+                    const size_t unit = (size_t)bkl * a.c_max + jt0 + jl;
+                    uint32_t *dst = MODE == MFMA_SAMPLE ? a.kbuf + unit * a.sample_stride + (tb / ST) * 32 + n4
                                                         : a.kbuf + unit * a.l_stride + t;
                     if (wide) {
                         // written once, read much later by other kernels: kept out of the caches that hold the keys
@@ -1134,137 +1103,116 @@ template <int G, int MODE> __global__ __launch_bounds__(256, 2) void mfma_score_
                     }
                 }
             }
+            __builtin_amdgcn_wave_barrier();   // read before the next sub-tile's keys overwrite it (a wave's accesses are served in order)
         }
-        };
+    };
     // tail: a step whose keys may reach beyond the block's range (a literal at every call).  Such
     // keys are real keys of the sequence, repeated: harmless for a maximum, left out of a sum,
     // not written as ranking keys.
-    auto compute = [&](const bool tail, int buf, int t0) __attribute__((always_inline)) {
-        bf16x8_t kfrag[8];
+    auto compute = [&](const bool tail, int buf, int tb) __attribute__((always_inline)) {
+        const unsigned char *kr = &s_k[buf][(sub * 32 + col) * ROWB + half * 16];
+        // four items at a time: independent back-to-back matrix instructions
+        float best[16];
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks)
-            kfrag[ks] = *reinterpret_cast<const bf16x8_t *>(&s_k[buf][col * ROWB + ks * 32 + half * 16]);
-        // the two work items' chains interleaved: independent back-to-back matrix instructions
-        f32x16_t acc0, acc1;
+        for (int q0 = 0; q0 < ITEMS; q0 += 4) {
+            f32x16_t acc[4];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc0[r] = acc1[r] = 0.0f;
+            for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag[ks], cfrag[0][ks], acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag[ks], cfrag[1][ks], acc1, 0, 0, 0);
-        }
+                for (int r = 0; r < 16; ++r) acc[q][r] = 0.0f;
+            bf16x8_t kf[2];
+            kf[0] = *reinterpret_cast<const bf16x8_t *>(kr);
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const f32x16_t &acc = q == 0 ? acc0 : acc1;
+            for (int ks = 0; ks < 8; ++ks) {
+                if (ks < 7) kf[(ks + 1) & 1] = *reinterpret_cast<const bf16x8_t *>(kr + (ks + 1) * 32);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks & 1], cfrag[q0 + q][ks], acc[q], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);   // the next fragment is requested before these products, not behind them
+            }
             if constexpr (MODE == MFMA_STAT) {
-                // the step's maximum first (repeated keys of a tail are real keys: harmless), then its sixteen
-                // terms relative to the new running maximum, summed as a tree, and the old sum rescaled
-                // (in base two: the scores' maximum as fl(max acc * sc2), monotone since sc2 > 0, and each term
-                // 2^(acc * sc2 - m) with one fused multiply-add and the hardware's base-two exponential)
-                float am = acc[0];
 #pragma unroll
-                for (int r = 1; r < 16; r += 2) am = fmaxf(fmaxf(acc[r], r + 1 < 16 ? acc[r + 1] : acc[r]), am);
-                const float m = fmaxf(mx[q], am * sc2);
-                float e[16];
+                for (int q = 0; q < 4; ++q) {
+                    // the step's maximum first (repeated keys of a tail are real keys: harmless), then its sixteen
+                    // terms relative to the new running maximum, summed as a tree, and the old sum rescaled
+                    // (in base two: the scores' maximum as fl(max acc * sc2), monotone since sc2 > 0, and each term
+                    // 2^(acc * sc2 - m) with one fused multiply-add and the hardware's base-two exponential)
+                    float am = acc[q][0];
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    e[r] = __builtin_amdgcn_exp2f(__fmaf_rn(acc[r], sc2, -m));
-                    if (tail) e[r] = (t0 + 8 * (r >> 2) + 4 * half + (r & 3)) < tend ? e[r] : 0.0f;
+                    for (int r = 1; r < 16; r += 2) am = fmaxf(fmaxf(acc[q][r], r + 1 < 16 ? acc[q][r + 1] : acc[q][r]), am);
+                    const float m = fmaxf(mx[q], am * sc2);
+                    float e[16];
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        e[r] = __builtin_amdgcn_exp2f(__fmaf_rn(acc[q][r], sc2, -m));
+                        if (tail) e[r] = (tb + 8 * (r >> 2) + 4 * half + (r & 3)) < tend ? e[r] : 0.0f;
+                    }
+#pragma unroll
+                    for (int w = 8; w >= 1; w >>= 1)
+#pragma unroll
+                        for (int r = 0; r < w; ++r) e[r] += e[r + w];
+                    lsv[q] = __fmaf_rn(lsv[q], __builtin_amdgcn_exp2f(mx[q] - m), e[0]);   // first step: 0 * 2^(-inf) = 0
+                    mx[q] = m;
                 }
+            } else {
 #pragma unroll
-                for (int w = 8; w >= 1; w >>= 1)
+                for (int q = 0; q < 4; ++q) {
 #pragma unroll
-                    for (int r = 0; r < w; ++r) e[r] += e[r + w];
-                lsv[q] = __fmaf_rn(lsv[q], __builtin_amdgcn_exp2f(mx[q] - m), e[0]);   // first step: 0 * 2^(-inf) = 0
-                mx[q] = m;
-            } else if constexpr (G == 1) {   // KEY, SAMPLE, PICK with one head: each item is a sub-tile of its own
-                float *zrow = &s_z[zb * (NPL * CT * ZS) + (mt[q] * 32 + col) * ZS + 4 * half];
-#pragma unroll
-                for (int rq = 0; rq < 4; ++rq) {
-                    float4 v;
-                    v.x = __fmaf_rn(acc[4 * rq + 0], a.scale, off[q]);
-                    v.y = __fmaf_rn(acc[4 * rq + 1], a.scale, off[q]);
-                    v.z = __fmaf_rn(acc[4 * rq + 2], a.scale, off[q]);
-                    v.w = __fmaf_rn(acc[4 * rq + 3], a.scale, off[q]);
-                    *reinterpret_cast<float4 *>(zrow + 8 * rq) = v;
+                    for (int r = 0; r < 16; ++r) {
+                        const float v = __fmaf_rn(acc[q][r], a.scale, off[q0 + q]);
+                        best[r] = (q0 + q) % G == 0 ? v : fmaxf(best[r], v);
+                    }
+                    if ((q0 + q) % G == G - 1) keys_out(tail, tb, (q0 + q) / G, best);
                 }
             }
-        }
-        if constexpr (KEYS && G >= 2) {   // the wave's two heads of the same centroids: their maximum, one plane
-            float *zrow = &s_z[zb * (NPL * CT * ZS) + ((hh[0] >> 1) * CT + mt[0] * 32 + col) * ZS + 4 * half];
-#pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-                float4 v;
-                v.x = fmaxf(__fmaf_rn(acc0[4 * rq + 0], a.scale, off[0]), __fmaf_rn(acc1[4 * rq + 0], a.scale, off[1]));
-                v.y = fmaxf(__fmaf_rn(acc0[4 * rq + 1], a.scale, off[0]), __fmaf_rn(acc1[4 * rq + 1], a.scale, off[1]));
-                v.z = fmaxf(__fmaf_rn(acc0[4 * rq + 2], a.scale, off[0]), __fmaf_rn(acc1[4 * rq + 2], a.scale, off[1]));
-                v.w = fmaxf(__fmaf_rn(acc0[4 * rq + 3], a.scale, off[0]), __fmaf_rn(acc1[4 * rq + 3], a.scale, off[1]));
-                *reinterpret_cast<float4 *>(zrow + 8 * rq) = v;
-            }
-        }
-        if constexpr (KEYS) {
-            if (have_prev) keys_out(prev_tail, prev_t0, s_z + (zb ^ 1) * (NPL * CT * ZS));
-            have_prev = true;
-            prev_tail = tail;
-            prev_t0 = t0;
-            zb ^= 1;
         }
     };
-    // A step's rows are requested four steps ahead (four register sets).
+    int pg = page_at(tbeg + 2 * ST);
     {
-        uint4 st2a, st2b, st3a, st3b;
-        int pg_a = page_at(tbeg + 4 * ST), pg_b = page_at(tbeg + 5 * ST), pg_c = page_at(tbeg + 6 * ST), pg_d = page_at(tbeg + 7 * ST);
-        fetch(st0a, st0b, row_from(page_at(tbeg), tbeg));
-        fetch(st1a, st1b, row_from(page_at(tbeg + ST), tbeg + ST));
-        fetch(st2a, st2b, row_from(page_at(tbeg + 2 * ST), tbeg + 2 * ST));
-        fetch(st3a, st3b, row_from(page_at(tbeg + 3 * ST), tbeg + 3 * ST));
-        put(st0a, st0b, 0);
-        __syncthreads();
-        // four steps per trip.  Step i (set i % 4, buffer i % 2): request step i+4 into the set it
-        // frees and the entry of step i+8, compute, write step i+1 to the other buffer.
-        auto trip = [&](const bool tail, int t0) __attribute__((always_inline)) {
-            fetch(st0a, st0b, row_from(pg_a, t0 + 4 * ST));
-            pg_a = page_at(t0 + 8 * ST);
-            compute(tail, 0, t0);
-            put(st1a, st1b, 1);
-            __syncthreads();
-            fetch(st1a, st1b, row_from(pg_b, t0 + 5 * ST));
-            pg_b = page_at(t0 + 9 * ST);
-            compute(tail, 1, t0 + ST);
-            put(st2a, st2b, 0);
-            __syncthreads();
-            fetch(st2a, st2b, row_from(pg_c, t0 + 6 * ST));
-            pg_c = page_at(t0 + 10 * ST);
-            compute(tail, 0, t0 + 2 * ST);
-            put(st3a, st3b, 1);
-            __syncthreads();
-            fetch(st3a, st3b, row_from(pg_d, t0 + 7 * ST));
-            pg_d = page_at(t0 + 11 * ST);
-            compute(tail, 1, t0 + 3 * ST);
-            put(st0a, st0b, 0);
-            __syncthreads();
-        };
-        int t0 = tbeg;
-        for (; t0 + 3 * ST + 32 <= tend; t0 += 4 * ST) trip(false, t0);
-        if (t0 < tend) trip(true, t0);
+        const uint32_t row = row_from(page_at(tbeg), tbeg);
+#pragma unroll
+        for (int u = 0; u < NU; ++u) put(piece_of(row, u), u, 0);
     }
-    if constexpr (KEYS) {   // the last step's keys (the last trip ended with a barrier)
-        if (have_prev) keys_out(prev_tail, prev_t0, s_z + (zb ^ 1) * (NPL * CT * ZS));
-    }
-    if constexpr (MODE == MFMA_PICK) {
+    __syncthreads();
+    auto step = [&](const bool tail, int buf, int t0) __attribute__((always_inline)) {
+        uint4 st[NU];   // used in this body only: an array that other helpers index would be kept in private memory
+        const uint32_t row = row_from(pg, t0 + 2 * ST);
+#pragma unroll
+        for (int u = 0; u < NU; ++u) st[u] = piece_of(row, u);
+        pg = page_at(t0 + 4 * ST);
+        compute(tail, buf, t0 + sub * ST);
+#pragma unroll
+        for (int u = 0; u < NU; ++u) put(st[u], u, buf ^ 1);
         __syncthreads();
-        if (tid < CT && j0 + tid < C) a.seg_cnt[((size_t)bkl * a.c_max + j0 + tid) * a.t_splits + blockIdx.x] = s_cnt[tid];
+    };
+    int t0 = tbeg, buf = 0;
+    for (; t0 + ST + 32 <= tend; t0 += 2 * ST, buf ^= 1) step(false, buf, t0);
+    if (t0 < tend) step(true, buf, t0);
+    if constexpr (MODE == MFMA_PICK) {   // the last step ended with a barrier
+        for (int c = tid; c < CT; c += NT)
+            if (j0 + c < C) a.seg_cnt[((size_t)bkl * a.c_max + j0 + c) * a.t_splits + blockIdx.x] = s_cnt[c];
     }
     if constexpr (KEYS) return;
-    // the two halves of a wave hold different keys of the same (centroid, head): merged (the same value
-    // on both sides, a sum of two products), then one pair per block
+    // the two halves of a wave, then the two waves of an item, hold different keys of the same (centroid, head):
+    // merged, one pair per block
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const bool mine = half == 0 && (j0 + mt[q] * 32 + col) < C;
+    for (int q = 0; q < ITEMS; ++q) {
         const float m_o = __shfl_xor(mx[q], 32), l_o = __shfl_xor(lsv[q], 32);
         const float m = fmaxf(mx[q], m_o);
-        const float l = lsv[q] * __builtin_amdgcn_exp2f(mx[q] - m) + l_o * __builtin_amdgcn_exp2f(m_o - m);
-        if (mine) a.part[stat[q] * a.t_splits + blockIdx.x] = make_float2(m, l);
+        lsv[q] = lsv[q] * __builtin_amdgcn_exp2f(mx[q] - m) + l_o * __builtin_amdgcn_exp2f(m_o - m);
+        mx[q] = m;
+        if (sub == 1 && half == 0) s_stat[(wc * ITEMS + q) * 32 + col] = make_float2(m, lsv[q]);
+    }
+    __syncthreads();
+    if (sub == 0 && half == 0) {
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q) {
+            const int j = j0 + tile_of(q) * 32 + col;
+            const float2 o = s_stat[(wc * ITEMS + q) * 32 + col];
+            const float m = fmaxf(mx[q], o.x);
+            const float l = lsv[q] * __builtin_amdgcn_exp2f(mx[q] - m) + o.y * __builtin_amdgcn_exp2f(o.x - m);
+            if (j < C) a.part[(((size_t)bkl * a.c_max + j) * G + head_of(q)) * a.t_splits + blockIdx.x] = make_float2(m, l);
+        }
     }
 }
 
