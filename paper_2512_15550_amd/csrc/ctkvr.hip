@@ -1550,12 +1550,12 @@ int decode_dispatch(ctkvr_index *ix, const StepWs &w, const void *q, const void 
 template <int G> int run_kmeans_g(ctkvr_index *ix, KmeansArgs ka, hipStream_t st)
 {
     const int U = ix->units;
-    const size_t hn_lds = (size_t)((ix->c_max + 127) & ~127) * 4;
-    TRY(want_lds(ix->dev, (const void *)kmeans_assign_kernel<G>, hn_lds));
+    using AS = AssignShape<G>;
+    TRY(want_lds(ix->dev, (const void *)kmeans_assign_kernel<G>, AS::kLds));
     kmeans_init_kernel<<<dim3(ix->c_max, ix->p.n_q_heads, ix->p.batch), 128, 0, st>>>(ka, G);
     for (int it = 0; it < ix->p.kmeans_iters; ++it) {
         kmeans_halfnorm_kernel<G><<<dim3((ix->c_max + 15) / 16, U), 256, 0, st>>>(ka);
-        kmeans_assign_kernel<G><<<dim3((ix->s_max + 255) / 256, U), 512, hn_lds, st>>>(ka);
+        kmeans_assign_kernel<G><<<dim3((ix->s_max + AS::kPoints - 1) / AS::kPoints, U), 256, AS::kLds, st>>>(ka);
         kmeans_offsets_kernel<<<dim3(U), 1024, 0, st>>>(ka);
         kmeans_scatter_kernel<<<dim3((ix->s_max + 255) / 256, U), 256, 0, st>>>(ka);
         kmeans_reduce_kernel<G><<<dim3(ix->c_max, U), 512, 0, st>>>(ka);

@@ -58,116 +58,186 @@ template <int G> __global__ __launch_bounds__(256) void kmeans_halfnorm_kernel(K
 }
 
 // assignment: argmax_c (x . mu_c - |mu_c|^2/2), ties to the lowest c.  A = 32 centres x 16 dims,
-// B = 16 dims x 32 points per v_mfma_f32_32x32x16_bf16.  A block owns 256 points, a wave 32 of
-// them with their B fragments resident in registers (G <= 4); the centres are walked 128 at a
-// time, and each 128-centre x 64-dim piece of the centre table goes through shared memory once
-// for the eight waves (double-buffered, requested two pieces ahead; rows padded to 144 bytes so that the 16-byte fragment reads of a
-// wave spread over the banks).  With G = 8 the fragments do not fit the registers and are
-// re-read from memory.  Counts the members of every centre as it goes.
-// grid (ceil(s_max/256), batch*g), 512 threads; dynamic shared memory: c_max rounded up to 128, floats.
-// The accumulators start from -|mu_c|^2/2, so the result tile is the score itself.
-template <int G> __global__ __launch_bounds__(512) void kmeans_assign_kernel(KmeansArgs a)
+// B = 16 dims x 32 points per v_mfma_f32_32x32x16_bf16.  What bounds it is shared memory as much as the
+// matrix pipe: a 16-byte fragment read per lane takes 8 cycles of the CU's LDS, a matrix instruction 32 of one
+// of its four SIMDs, so with one read per instruction both are full at once.  Hence a wave holds the whole
+// points of PT = 2 column tiles in registers (256 of them at G = 4: one wave per SIMD, 512 registers) and every
+// centre fragment read feeds two instructions.  The centres go by in tiles of 32 CTN, whole (all G heads),
+// through two shared-memory buffers in fragment order -- reads and writes are linear, free of bank conflicts --,
+// the next tile requested and written while this one is multiplied, one barrier per tile.  With a
+// single wave per SIMD nothing else hides the vector work, so the accumulators are two sets: the argmax of a
+// row tile runs between the matrix instructions of the next.  128K points x 2048 centres x 8 heads of G = 4: 1.86 ms,
+// 1.18 PFLOP/s (32 points a wave, two waves per SIMD, 1.95 ms).
+// With G = 8 (a point takes 256 registers) a wave has one column tile and the centre tiles are half as high.
+// Counts the members of every centre as it goes.  The accumulators start from -|mu_c|^2/2, so the result tile
+// is the score itself.
+// grid (ceil(s_max / (128 PT)), batch*g), 256 threads, dynamic shared memory AssignShape<G>::kLds.
+template <int G> struct AssignShape {
+    static constexpr int KS = 8 * G;             // k-steps of 16 dims
+    static constexpr int PT = G <= 4 ? 2 : 1;    // column tiles (32 points each) of a wave
+    static constexpr int CTN = G <= 4 ? 2 : 1;   // row tiles (32 centres each) of a step
+    static constexpr int NC = 32 * CTN;
+    static constexpr int kTile = KS * CTN * 1024;   // bytes of a centre tile
+    static constexpr int kLds = 2 * (kTile + NC * 4);
+    static constexpr int kPoints = 4 * PT * 32;     // points of a block
+};
+
+template <int G> __global__ __launch_bounds__(256, G <= 2 ? 2 : 1) void kmeans_assign_kernel(KmeansArgs a)
 {
-    extern __shared__ __align__(16) float s_hn[];   // c_max rounded up to 128 floats
-    constexpr int KS = 8 * G;                 // k-steps of 16 dims
-    constexpr bool REG_B = (G <= 4);
-    constexpr int ROWB = 144;                 // bytes per staged centre row (64 dims + padding)
-    __shared__ __align__(16) unsigned char s_a[2][128 * ROWB];
+    using S = AssignShape<G>;
+    constexpr int KS = S::KS, PT = S::PT, CTN = S::CTN, NC = S::NC;
+    constexpr int AHEAD = 4;   // centre fragments in registers: requested three k-steps before their use
+    extern __shared__ __align__(16) unsigned char s_dyn[];   // two centre tiles, then their half-norms
+    float *const s_hn = reinterpret_cast<float *>(s_dyn + 2 * S::kTile);
     const int ul = blockIdx.y, b = ul / a.g, kv = ul - b * a.g;
     const int C = a.n_cent[b], s = a.ctx_lens[b];
-    if ((int)blockIdx.x * 256 >= s) return;
+    if ((int)blockIdx.x * S::kPoints >= s) return;
     const int tid = threadIdx.x, wv = tid >> 6, ln = tid & 63, col = ln & 31, half = ln >> 5;
-    // -|mu_c|^2 / 2, the value every accumulator starts from; -inf for the padding up to a whole tile
-    for (int c = tid; c < ((C + 127) & ~127); c += 512)
-        s_hn[c] = c < C ? -a.half_norm[(size_t)ul * a.c_max + c] : -__builtin_huge_valf();
-    const int p0 = blockIdx.x * 256 + wv * 32;
-    const int t = min(p0 + col, s - 1);
-    const bf16_t *xrow = a.q + ((size_t)(a.first_row[b] + t) * a.h + kv * G) * kD + 8 * half;
-    bf16x8_t bfrag[REG_B ? KS : 1];
-    if constexpr (REG_B) {
+    const int p0 = blockIdx.x * S::kPoints + wv * (PT * 32);
+    bf16x8_t bfrag[PT][KS];
 #pragma unroll
-        for (int kk = 0; kk < KS; ++kk) bfrag[kk] = *reinterpret_cast<const bf16x8_t *>(xrow + kk * 16);
+    for (int pt = 0; pt < PT; ++pt) {
+        const int t = min(p0 + pt * 32 + col, s - 1);
+        const bf16_t *xrow = a.q + ((size_t)(a.first_row[b] + t) * a.h + kv * G) * kD + 8 * half;
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) bfrag[pt][kk] = *reinterpret_cast<const bf16x8_t *>(xrow + kk * 16);
     }
-    // staging: thread t moves a quarter row (32 bytes) of piece (c0, kc): centre c0 + t/4, head kc/2,
-    // dims 64*(kc%2) + 16*(t%4) ..
-    constexpr int NKC = 2 * G;                // 64-dim pieces per 128-centre tile
-    static_assert(NKC % 2 == 0, "piece parity must carry over from one centre tile to the next");
-    const int srow = tid >> 2, sq = tid & 3;
+    // Staging: a tile is NC rows of 2 KS 16-byte pieces; a wave moves 8 rows x 8 pieces at a time (128 contiguous
+    // bytes of a row each), lane l row l % 8 and piece l / 8 of them.  All of a tile's moves are requested in the
+    // first quarter of a step and written in its last: with one wave per SIMD a request that is not back is waited
+    // for by everything (requested and written by quarters, 4 waits a tile, the launch took 2.4 ms).
+    constexpr int NLD = NC * 2 * KS / 256, STEPS = CTN * KS, QUARTER = STEPS / 4;
     const bf16_t *cbase = a.centroids + ((size_t)b * a.h + kv * G) * a.c_max * kD;
-    // two pieces ahead in registers: piece i+2 is requested while piece i feeds the matrix cores
-    // and piece i+1 waits to be written to the other buffer
-    // (named variables: an array indexed through the helpers would be kept in private memory)
-    uint4 st0a, st0b, st1a, st1b;
-    auto fetch = [&](uint4 &x, uint4 &y, int c0, int kc) {
-        const int c = min(c0 + srow, C - 1);
-        const uint4 *src = reinterpret_cast<const uint4 *>(cbase + ((size_t)(kc >> 1) * a.c_max + c) * kD + (kc & 1) * 64 + sq * 16);
-        x = src[0];
-        y = src[1];
+    const float *hnrow = a.half_norm + (size_t)ul * a.c_max;
+    // move p: rows 32 (p % CTN) .., pieces 8 (p / CTN) .. of every row
+    const int r0 = wv * 8 + (ln & 7);
+    auto fetch = [&](int p, int c0) {   // rows beyond C repeat the last centre; their accumulators start from -inf
+        const int c = min(c0 + (p % CTN) * 32 + r0, C - 1), qb = p / CTN;
+        const char *from = reinterpret_cast<const char *>(cbase + (size_t)(qb >> 1) * a.c_max * kD + (qb & 1) * 64);
+        return *reinterpret_cast<const uint4 *>(from + (uint32_t)(c * (kD * 2) + (ln >> 3) * 16));
     };
-    auto put = [&](const uint4 &x, const uint4 &y, int buf) {
-        uint4 *dst = reinterpret_cast<uint4 *>(&s_a[buf][srow * ROWB + sq * 32]);
-        dst[0] = x;
-        dst[1] = y;
+    unsigned char *const put_at = s_dyn + (ln >> 4) * (CTN * 1024) + ((ln >> 3) & 1) * 512 + r0 * 16;
+    auto put = [&](int p, const uint4 &x, int buf) {
+        *reinterpret_cast<uint4 *>(put_at + buf * S::kTile + ((p / CTN) * 4 * CTN + p % CTN) * 1024) = x;
     };
-    float best = -__builtin_huge_valf();
-    int bi = 0;
-    fetch(st0a, st0b, 0, 0);
-    fetch(st1a, st1b, 0, 1);
-    put(st0a, st0b, 0);
-    __syncthreads();
-    for (int c0 = 0; c0 < C; c0 += 128) {
-        f32x16_t acc[4];
+    auto hn_at = [&](int c0) {
+        const int c = c0 + (tid & (NC - 1));
+        const float v = -hnrow[min(c, C - 1)];
+        return c < C ? v : -__builtin_huge_valf();
+    };
+    float best[PT];
+    int bi[PT];
+    f32x16_t acc_a[PT], acc_b[PT];
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct)
+    for (int pt = 0; pt < PT; ++pt) {
+        best[pt] = -__builtin_huge_valf();
+        bi[pt] = 0;
 #pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-                const float4 v = *reinterpret_cast<const float4 *>(&s_hn[c0 + ct * 32 + 8 * rq + 4 * half]);
-                acc[ct][4 * rq + 0] = v.x;
-                acc[ct][4 * rq + 1] = v.y;
-                acc[ct][4 * rq + 2] = v.z;
-                acc[ct][4 * rq + 3] = v.w;
-            }
+        for (int r = 0; r < 16; ++r) acc_a[pt][r] = acc_b[pt][r] = -__builtin_huge_valf();
+    }
+    // scores of a finished row tile against the best so far; `loc` is the row inside it
+    constexpr int E = PT * 16;
+    float was[PT];
+    int loc[PT];
+    auto argmax_begin = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int kc = 0; kc < NKC; ++kc) {
-            const int buf = kc & 1;
-            {   // piece i + 2
-                const int c2 = kc + 2 < NKC ? c0 : c0 + 128, k2 = kc + 2 < NKC ? kc + 2 : kc + 2 - NKC;
-                if (c2 < C) {
-                    if ((kc & 1) == 0) fetch(st0a, st0b, c2, k2);
-                    else fetch(st1a, st1b, c2, k2);
-                }
-            }
+        for (int pt = 0; pt < PT; ++pt) {
+            was[pt] = best[pt];
+            loc[pt] = 0;
+        }
+    };
+    auto argmax_part = [&](const f32x16_t (&acc)[PT], int e_lo, int e_hi) __attribute__((always_inline)) {
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                bf16x8_t bf;
-                if constexpr (REG_B) bf = bfrag[kc * 4 + ks];
-                else bf = *reinterpret_cast<const bf16x8_t *>(xrow + (kc * 4 + ks) * 16);
+        for (int e = e_lo; e < e_hi; ++e) {
+            const int pt = e % PT, r = e / PT;
+            const float v = acc[pt][r];
+            loc[pt] = v > best[pt] ? 8 * (r >> 2) + (r & 3) : loc[pt];
+            best[pt] = v > best[pt] ? v : best[pt];
+            asm volatile("" : "+v"(loc[pt]));   // or the selects are gathered behind the last product, where nothing hides them
+        }
+    };
+    auto argmax_end = [&](int c) __attribute__((always_inline)) {   // c: first row of the finished tile
 #pragma unroll
-                for (int ct = 0; ct < 4; ++ct) {
-                    bf16x8_t af = *reinterpret_cast<const bf16x8_t *>(&s_a[buf][(ct * 32 + col) * ROWB + ks * 32 + half * 16]);
-                    acc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, bf, acc[ct], 0, 0, 0);
-                }
-            }
-            if (kc + 1 < NKC || c0 + 128 < C) {   // piece i + 1
-                if (((kc + 1) & 1) == 0) put(st0a, st0b, buf ^ 1);
-                else put(st1a, st1b, buf ^ 1);
-            }
-            __syncthreads();
+        for (int pt = 0; pt < PT; ++pt) bi[pt] = best[pt] > was[pt] ? c + loc[pt] + 4 * half : bi[pt];
+    };
+    // one row tile: its products into cur, the scores of the one before (prev) compared on the way
+    auto row_tile = [&](f32x16_t (&cur)[PT], const f32x16_t (&prev)[PT], int ct, int buf, int c0, uint4 (&st)[NLD]) __attribute__((always_inline)) {
+        const unsigned char *tile = s_dyn + buf * S::kTile + ct * 1024 + ln * 16;
+        f32x16_t hn;
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+            const float4 v = *reinterpret_cast<const float4 *>(&s_hn[buf * NC + ct * 32 + 8 * rq + 4 * half]);
+            hn[4 * rq + 0] = v.x;
+            hn[4 * rq + 1] = v.y;
+            hn[4 * rq + 2] = v.z;
+            hn[4 * rq + 3] = v.w;
         }
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct)
+        for (int pt = 0; pt < PT; ++pt) cur[pt] = hn;
+        argmax_begin();
+        bf16x8_t af[AHEAD];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int c = c0 + ct * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                if (acc[ct][r] > best) { best = acc[ct][r]; bi = c; }
+        for (int kk = 0; kk < AHEAD - 1; ++kk) af[kk] = *reinterpret_cast<const bf16x8_t *>(tile + kk * CTN * 1024);
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) {
+            const int at = ct * KS + kk;   // of STEPS
+            if (at < QUARTER) {
+#pragma unroll
+                for (int p = at * NLD / QUARTER; p < (at + 1) * NLD / QUARTER; ++p) st[p] = fetch(p, c0 + NC);
             }
+            if (kk + AHEAD - 1 < KS)
+                af[(kk + AHEAD - 1) % AHEAD] = *reinterpret_cast<const bf16x8_t *>(tile + (kk + AHEAD - 1) * CTN * 1024);
+#pragma unroll
+            for (int pt = 0; pt < PT; ++pt)
+                cur[pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk % AHEAD], bfrag[pt][kk], cur[pt], 0, 0, 0);
+            argmax_part(prev, kk * E / KS, (kk + 1) * E / KS);
+            if (at >= STEPS - QUARTER) {
+                constexpr int F = STEPS - QUARTER;
+#pragma unroll
+                for (int p = (at - F) * NLD / QUARTER; p < (at - F + 1) * NLD / QUARTER; ++p) put(p, st[p], buf ^ 1);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // the order written here is the schedule
+        }
+        argmax_end(c0 + ct * 32 - 32);
+    };
+    // a tile, its row tiles into x and y in turn.  The next tile goes into the other buffer (past
+    // the end: the last centre again, never used).
+    auto step = [&](f32x16_t (&x)[PT], f32x16_t (&y)[PT], int buf, int c0) __attribute__((always_inline)) {
+        uint4 st[NLD];
+        const float hn_next = hn_at(c0 + NC);
+        row_tile(x, y, 0, buf, c0, st);
+        if constexpr (CTN == 2) row_tile(y, x, 1, buf, c0, st);
+        s_hn[(buf ^ 1) * NC + (tid & (NC - 1))] = hn_next;   // the four waves write the same values
+        __syncthreads();
+    };
+#pragma unroll
+    for (int p = 0; p < NLD; ++p) put(p, fetch(p, 0), 0);
+    s_hn[tid & (NC - 1)] = hn_at(0);
+    __syncthreads();
+    int buf = 0, c0 = 0;
+    if constexpr (CTN == 2) {
+        for (; c0 < C; c0 += NC, buf ^= 1) step(acc_a, acc_b, buf, c0);
+        argmax_begin();
+        argmax_part(acc_b, 0, E);
+    } else {
+        for (; c0 < C; c0 += 2 * NC) {   // an odd last tile: the second step of its pair multiplies rows that start from -inf
+            step(acc_a, acc_b, 0, c0);
+            step(acc_b, acc_a, 1, c0 + NC);
+        }
+        argmax_begin();
+        argmax_part(acc_b, 0, E);
     }
-    float ob = __shfl_xor(best, 32);
-    int oi = __shfl_xor(bi, 32);
-    if (ob > best || (ob == best && oi < bi)) bi = oi;
-    if (half == 0 && (p0 + col) < s) {
-        a.assign[(size_t)ul * a.s_max + p0 + col] = bi;
-        atomicAdd(&a.counts[(size_t)ul * a.c_max + bi], 1u);
+    argmax_end(c0 - 32);
+#pragma unroll
+    for (int pt = 0; pt < PT; ++pt) {
+        const float ob = __shfl_xor(best[pt], 32);
+        const int oi = __shfl_xor(bi[pt], 32);
+        if (ob > best[pt] || (ob == best[pt] && oi < bi[pt])) bi[pt] = oi;
+        const int t = p0 + pt * 32 + col;
+        if (half == 0 && t < s) {
+            a.assign[(size_t)ul * a.s_max + t] = bi[pt];
+            atomicAdd(&a.counts[(size_t)ul * a.c_max + bi[pt]], 1u);
+        }
     }
 }
 
