@@ -1558,7 +1558,7 @@ template <int G> int run_kmeans_g(ctkvr_index *ix, KmeansArgs ka, hipStream_t st
         kmeans_assign_kernel<G><<<dim3((ix->s_max + AS::kPoints - 1) / AS::kPoints, U), 256, AS::kLds, st>>>(ka);
         kmeans_offsets_kernel<<<dim3(U), 1024, 0, st>>>(ka);
         kmeans_scatter_kernel<<<dim3((ix->s_max + 255) / 256, U), 256, 0, st>>>(ka);
-        kmeans_reduce_kernel<G><<<dim3(ix->c_max, U), 512, 0, st>>>(ka);
+        kmeans_reduce_kernel<G><<<dim3(ix->c_max + ka.ext_max, U), 512, 0, st>>>(ka);
     }
     HIP_TRY(hipGetLastError());
     return CTKVR_OK;
@@ -1578,6 +1578,8 @@ int run_kmeans(ctkvr_index *ix, const bf16_t *q_prefill, const int32_t *d_first,
     ka.q = q_prefill;
     ka.centroids = (bf16_t *)ix->centroids;
     ka.init_pos = init_pos;
+    ka.ext_max = ix->s_max / (int)kPartRows + 1;
+    const size_t n_sums = U * ka.ext_max * ix->G * kD;
     BuildScratch scratch_mem;
     auto lay_out = [&](unsigned char *base) {
         Carver cv{base};
@@ -1585,14 +1587,21 @@ int run_kmeans(ctkvr_index *ix, const bf16_t *q_prefill, const int32_t *d_first,
         cv.take(&ka.assign, U * ix->s_max * 4);
         cv.take(&ka.counts, U * ix->c_max * 4);
         cv.take(&ka.start, U * ix->c_max * 4);
-        cv.take(&ka.cursor, U * ix->c_max * 4);
+        cv.take(&ka.rank, U * ix->s_max * 4);
         cv.take(&ka.order, U * ix->s_max * 4);
+        cv.take(&ka.part, U * ka.ext_max * sizeof(uint2));
+        cv.take(&ka.n_part, U * 4);
+        cv.take(&ka.slot, U * ix->c_max * 4);
+        cv.take(&ka.sums, n_sums * 8);
+        cv.take(&ka.done, U * ka.ext_max * 4);
         return cv.off;
     };
     int rc = scratch_mem.get(ix->dev, lay_out(nullptr));
     if (rc == CTKVR_OK) {
         lay_out(scratch_mem.base());
         fill_u32_kernel<<<dim3((unsigned)((U * ix->c_max + 255) / 256)), 256, 0, st>>>(ka.counts, 0u, U * ix->c_max);
+        fill_u32_kernel<<<dim3((unsigned)((n_sums * 2 + 255) / 256)), 256, 0, st>>>((uint32_t *)ka.sums, 0u, n_sums * 2);
+        fill_u32_kernel<<<dim3((unsigned)((U * ka.ext_max + 255) / 256)), 256, 0, st>>>(ka.done, 0u, U * ka.ext_max);
         switch (ix->G) {
             case 1: rc = run_kmeans_g<1>(ix, ka, st); break;
             case 2: rc = run_kmeans_g<2>(ix, ka, st); break;

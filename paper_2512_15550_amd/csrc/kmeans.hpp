@@ -22,9 +22,17 @@ struct KmeansArgs {
     int32_t *assign;               // [batch*g][s_max]
     uint32_t *counts;              // [batch*g][c_max] members per centre (zero before the assignment)
     uint32_t *start;               // [batch*g][c_max] first slot of each centre in `order`
-    uint32_t *cursor;              // [batch*g][c_max] next free slot while scattering
+    uint32_t *rank;                // [batch*g][s_max] which member of its centre a position is, in arrival order
     int32_t *order;                // [batch*g][s_max] positions grouped by centre
+    // centres of more than kPartRows members: the blocks that sum their further parts, and where the parts meet
+    uint2 *part;                   // [batch*g][ext_max] (centre, part) of the blocks behind the first c_max
+    uint32_t *n_part;              // [batch*g] how many of them there are
+    uint32_t *slot;                // [batch*g][c_max] first of the centre's entries in `part`; its accumulator
+    unsigned long long *sums;      // [batch*g][ext_max][G*128], all zero between iterations
+    uint32_t *done;                // [batch*g][ext_max] parts of the slot's centre that are in `sums`; zero likewise
+    int ext_max;                   // s_max / kPartRows + 1
 };
+constexpr uint32_t kPartRows = 256;
 
 // centres start as the prompt queries at init_pos; grid (c_max, h, batch), 128 threads
 __global__ void kmeans_init_kernel(KmeansArgs a, int G)
@@ -69,7 +77,8 @@ template <int G> __global__ __launch_bounds__(256) void kmeans_halfnorm_kernel(K
 // row tile runs between the matrix instructions of the next.  128K points x 2048 centres x 8 heads of G = 4: 1.86 ms,
 // 1.18 PFLOP/s (32 points a wave, two waves per SIMD, 1.95 ms).
 // With G = 8 (a point takes 256 registers) a wave has one column tile and the centre tiles are half as high.
-// Counts the members of every centre as it goes.  The accumulators start from -|mu_c|^2/2, so the result tile
+// Counts the members of every centre as it goes and keeps what the count was before each: the position's place among
+// them.  The accumulators start from -|mu_c|^2/2, so the result tile
 // is the score itself.
 // grid (ceil(s_max / (128 PT)), batch*g), 256 threads, dynamic shared memory AssignShape<G>::kLds.
 template <int G> struct AssignShape {
@@ -236,47 +245,54 @@ template <int G> __global__ __launch_bounds__(256, G <= 2 ? 2 : 1) void kmeans_a
         const int t = p0 + pt * 32 + col;
         if (half == 0 && t < s) {
             a.assign[(size_t)ul * a.s_max + t] = bi[pt];
-            atomicAdd(&a.counts[(size_t)ul * a.c_max + bi[pt]], 1u);
+            a.rank[(size_t)ul * a.s_max + t] = atomicAdd(&a.counts[(size_t)ul * a.c_max + bi[pt]], 1u);
         }
     }
 }
 
-// start[c] = number of positions assigned to centres below c; cursor[c] = start[c].
+// start[c] = number of positions assigned to centres below c; the blocks of the update behind the first c_max get
+// the further parts of the large centres.  Clears the counts for the next iteration.
 // grid batch*g, 1024 threads (C <= 8192: eight centres per thread)
 __global__ __launch_bounds__(1024) void kmeans_offsets_kernel(KmeansArgs a)
 {
     __shared__ uint32_t s_tmp[32];
     const int ul = blockIdx.x, b = ul / a.g;
     const int C = a.n_cent[b], tid = threadIdx.x;
-    uint32_t c[8], mine = 0;
+    uint32_t c[8], mine = 0, parts = 0;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         int j = tid * 8 + q;
         c[q] = j < C ? a.counts[(size_t)ul * a.c_max + j] : 0u;
         mine += c[q];
+        parts += c[q] ? (c[q] - 1u) / kPartRows : 0u;
     }
-    uint32_t tot;
+    uint32_t tot, n_ext;
     uint32_t before = block_excl_scan<1024>(mine, s_tmp, &tot);
+    uint32_t at = block_excl_scan<1024>(parts, s_tmp, &n_ext);   // at most s / kPartRows
+    if (tid == 0) a.n_part[ul] = n_ext;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         int j = tid * 8 + q;
         if (j < C) {
             a.start[(size_t)ul * a.c_max + j] = before;
-            a.cursor[(size_t)ul * a.c_max + j] = before;
+            a.slot[(size_t)ul * a.c_max + j] = at;
+            a.counts[(size_t)ul * a.c_max + j] = 0u;
+            for (uint32_t p = 1; (p * kPartRows) < c[q]; ++p) a.part[(size_t)ul * a.ext_max + at++] = make_uint2((uint32_t)j, p);
         }
         before += c[q];
     }
 }
 
-// order[cursor[assign[t]]++] = t.  The order inside a centre's range is whatever the atomics give:
-// the sums taken over it are integer sums.  grid (ceil(s_max/256), batch*g), 256 threads
+// order[start[assign[t]] + rank[t]] = t.  The order inside a centre's range is whatever the counting atomics gave: the
+// sums taken over it are integer sums.  (A second round of atomics for the places took 166 us a launch at 128K x 8
+// heads, served beyond the XCD's cache.)  grid (ceil(s_max/256), batch*g), 256 threads
 __global__ __launch_bounds__(256) void kmeans_scatter_kernel(KmeansArgs a)
 {
     const int ul = blockIdx.y, b = ul / a.g;
     const int t = blockIdx.x * 256 + threadIdx.x;
     if (t >= a.ctx_lens[b]) return;
     const int c = a.assign[(size_t)ul * a.s_max + t];
-    const uint32_t pos = atomicAdd(&a.cursor[(size_t)ul * a.c_max + c], 1u);
+    const uint32_t pos = a.start[(size_t)ul * a.c_max + c] + a.rank[(size_t)ul * a.s_max + t];
     a.order[(size_t)ul * a.s_max + pos] = t;
 }
 
@@ -285,17 +301,29 @@ __global__ __launch_bounds__(256) void kmeans_scatter_kernel(KmeansArgs a)
 // empty centre keeps its place.  Four groups of 128 threads take the members eight at a time in
 // turn (their ids are requested one round ahead of their rows); thread e of a group owns the G
 // consecutive elements e*G .. e*G+G-1 of the G*128-element point, and the groups' integer sums
-// are added through shared memory.  Clears the count for the next iteration.
-// grid (c_max, batch*g), 512 threads
+// are added through shared memory.  A centre of more than kPartRows members is summed by several blocks (the first
+// iterations have centres of many times the average: their one block was most of the launch, 1.3 ms against 0.27):
+// each adds its sums to the centre's 64-bit accumulators, and the last of them takes those and leaves zeros.
+// grid (c_max + ext_max, batch*g), 512 threads
 template <int G> __global__ __launch_bounds__(512) void kmeans_reduce_kernel(KmeansArgs a)
 {
     __shared__ long long s_part[3][128][G];
     const int ul = blockIdx.y, b = ul / a.g, kv = ul - b * a.g;
-    const int c = blockIdx.x;
-    if (c >= a.n_cent[b]) return;
-    const uint32_t n = a.counts[(size_t)ul * a.c_max + c];
+    __shared__ uint32_t s_last;
+    const int C = a.n_cent[b];
+    int c = blockIdx.x;
+    uint32_t p = 0;
+    if (c >= a.c_max) {
+        if ((uint32_t)(c - a.c_max) >= a.n_part[ul]) return;
+        const uint2 cp = a.part[(size_t)ul * a.ext_max + (c - a.c_max)];
+        c = (int)cp.x;
+        p = cp.y;
+    }
+    if (c >= C) return;
     const uint32_t st = a.start[(size_t)ul * a.c_max + c];
-    const int32_t *ord = a.order + (size_t)ul * a.s_max + st;
+    const uint32_t n_all = (c + 1 < C ? a.start[(size_t)ul * a.c_max + c + 1] : (uint32_t)a.ctx_lens[b]) - st;
+    const uint32_t n = min(n_all - p * kPartRows, kPartRows);   // of this part
+    const int32_t *ord = a.order + (size_t)ul * a.s_max + st + p * kPartRows;
     const int e = threadIdx.x & 127, grp = threadIdx.x >> 7;
     const bf16_t *base = a.q + ((size_t)a.first_row[b] * a.h + kv * G) * kD + e * G;
     const size_t rstride = (size_t)a.h * kD;
@@ -348,18 +376,44 @@ template <int G> __global__ __launch_bounds__(512) void kmeans_reduce_kernel(Kme
         for (int r = 0; r < G; ++r) s_part[grp - 1][e][r] = acc[r];
     }
     __syncthreads();
-    if (grp == 0 && n) {
+    const uint32_t n_parts = (n_all + kPartRows - 1) / kPartRows;
+    long long tot[G];
+    if (grp == 0) {
+#pragma unroll
+        for (int r = 0; r < G; ++r) tot[r] = acc[r] + s_part[0][e][r] + s_part[1][e][r] + s_part[2][e][r];
+    }
+    if (n_parts > 1) {
+        const size_t slot = (size_t)ul * a.ext_max + a.slot[(size_t)ul * a.c_max + c];
+        unsigned long long *sums = a.sums + slot * (G * 128) + e;
+        if (grp == 0) {
+#pragma unroll
+            for (int r = 0; r < G; ++r) atomicAdd(&sums[r * 128], (unsigned long long)tot[r]);
+            __threadfence();
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const uint32_t had = atomicAdd(&a.done[slot], 1u);
+            s_last = had == n_parts - 1;
+            if (s_last) a.done[slot] = 0u;
+            __threadfence();
+        }
+        __syncthreads();
+        if (!s_last) return;
+        if (grp == 0) {
+#pragma unroll
+            for (int r = 0; r < G; ++r) tot[r] = (long long)atomicExch(&sums[r * 128], 0ull);
+        }
+    }
+    if (grp == 0 && n_all) {
 #pragma unroll
         for (int r = 0; r < G; ++r) {
-            const long long tot = acc[r] + s_part[0][e][r] + s_part[1][e][r] + s_part[2][e][r];
             const int ee = e * G + r, hh = ee >> 7, dim = ee & 127;
-            float m = (float)((double)tot * (1.0 / 1048576.0) / (double)n);
+            float m = (float)((double)tot[r] * (1.0 / 1048576.0) / (double)n_all);
             uint32_t u = __float_as_uint(m);
             u += 0x7fffu + ((u >> 16) & 1u);
             a.centroids[(((size_t)b * a.h + kv * G + hh) * a.c_max + c) * kD + dim] = (bf16_t)(u >> 16);
         }
     }
-    if (threadIdx.x == 0) a.counts[(size_t)ul * a.c_max + c] = 0u;
 }
 
 }  // namespace ctkvr
