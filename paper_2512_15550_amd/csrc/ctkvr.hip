@@ -766,6 +766,9 @@ template <typename T> int launch_inv_norms(ctkvr_index *ix, hipStream_t st)
     return CTKVR_OK;
 }
 
+// shared memory of exact_list_kernel and key_list_kernel
+size_t exact_list_lds(const ctkvr_index *ix) { return ((size_t)kSelLds + 2 * kListCap + 4 * ((ix->s_max + 63) / 64)) * 4; }
+
 // Algorithm 1 lines 2-4 in the decode path's own arithmetic: for chunks of
 // (sequence, KV head, centroid) units, score all keys, then per unit sum the
 // denominators and select the top-rho.
@@ -790,12 +793,15 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
     constexpr int kMaxSplits = 64;
     // Matrix-core route, candidates only (see mfma_score_kernel): when every sequence is long against rho, so that
     // about 2 rho candidates are a small part of its keys and a 1-in-16 sample of the positions places the threshold
-    // well, and the selection's bitmaps and candidate list fit the shared memory.  CTKVR_BUILD_CANDIDATES=0/1 forces
-    // the choice where the second condition allows it (1 on short sequences mostly ends in the redo below).
+    // well, and the selection's bitmaps and candidate list fit the shared memory.  Every key against candidates, lists of
+    // 1024 keys, C = s / 64, one to eight heads a group: 30K 0.66..0.80 / 0.75..1.13 ms, 40K 1.08..1.35 / 1.04..1.49,
+    // 50K 1.61..2.05 / 1.37..1.81, 90K 4.9..7.3 / 2.8..3.5 ms.  CTKVR_BUILD_CANDIDATES=0/1 forces the choice where the second
+    // condition allows it.
     const int rho = ix->p.list_len;
     const int step_stride = std::max(16, ((ix->s_max + 31) / 32 + 255) / 256);
     const int sample_stride = ((ix->s_max + 32 * step_stride - 1) / (32 * step_stride)) * 32;
-    const int cand_cap = std::min(kCandCap, std::max(3 * rho, 2 * rho + 1024));   // about 2 rho + 256 are expected (+-6 % at rho = 2048)
+    const int cand_cap = std::min(kCandCap, std::max(3 * rho, 2 * rho + 2048));   // about 2 rho + 256 are expected (+-6 % at rho = 2048, three times that at 1024: neighbouring positions are alike)
+    const int cand_room = 2 * std::max(cand_cap, 128 * kMaxSplits);   // entries per unit, over all segments
     const size_t cand_lds = ((size_t)2112 + 2 * (size_t)cand_cap + kCandTies + (size_t)((ix->s_max + 31) / 32)) * 4;
     bool by_cand = false;
     if (mfma && cand_lds <= 150 * 1024 && sample_stride <= kSampleCap && cand_cap >= rho) {
@@ -804,6 +810,8 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
         if (const char *e = getenv("CTKVR_BUILD_CANDIDATES")) by_cand = atoi(e) != 0;
     }
     ix->build_by_cand = by_cand;
+    // one block per list behind the keys, where its bitmap of the context fits the shared memory (to about 2^18 tokens)
+    const bool by_list = mfma && exact_list_lds(ix) <= 150 * 1024;
     if (by_cand) chunk = std::min(chunk, 4 * ix->c_max);   // half the scratch, as fast
     const bool redo_always = by_cand && getenv("CTKVR_BUILD_CANDIDATES_REDO") != nullptr;   // tests: take the redo path
     uint32_t *ksamp = nullptr, *tau = nullptr, *cursor = nullptr, *d_fail = nullptr;
@@ -813,21 +821,23 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
     auto lay_out_full = [&](unsigned char *base) {   // the buffers of the route that keeps every key
         Carver cv{base};
         cv.take(&kbuf, (size_t)chunk * ix->s_max * 4);
-        cv.take(&ghist, (size_t)chunk * kBuckets * 4);
+        if (!by_list) cv.take(&ghist, (size_t)chunk * kBuckets * 4);
         return cv.off;
     };
     auto lay_out = [&](unsigned char *base) {
         Carver cv{base};
-        cv.take(&m_key, (size_t)chunk * G * 4);
-        cv.take(&S, (size_t)chunk * G * 8);
+        if (!mfma) {
+            cv.take(&m_key, (size_t)chunk * G * 4);
+            cv.take(&S, (size_t)chunk * G * 8);
+        }
         if (mfma) cv.take(&part, (size_t)chunk * G * kMaxSplits * sizeof(float2));
         if (by_cand) {
-            // a segment per block of the statistics split: room for twice an even share, at least 256 entries
+            // a segment per block of the statistics split
             cv.take(&ksamp, (size_t)chunk * sample_stride * 4);
             cv.take(&tau, (size_t)chunk * 4);
             cv.take(&cursor, (size_t)chunk * kMaxSplits * 4);
             cv.take(&d_fail, 4);
-            cv.take(&cand, (size_t)chunk * 2 * std::max(cand_cap, 128 * kMaxSplits) * sizeof(uint2));
+            cv.take(&cand, (size_t)chunk * cand_room * sizeof(uint2));
         } else {
             if (!mfma) cv.take(&z, (size_t)chunk * per_unit);
             cv.off += lay_out_full(base ? base + cv.off : nullptr);
@@ -837,13 +847,20 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
     int rc = scratch_mem.get(ix->dev, lay_out(nullptr));
     if (rc == CTKVR_OK) lay_out(scratch_mem.base());
     if (rc == CTKVR_OK && by_cand) rc = want_lds(ix->dev, (const void *)cand_select_kernel, cand_lds);
+    if (rc == CTKVR_OK && by_list)
+        rc = want_lds(ix->dev, ix->s_max <= 8 * 512    ? (const void *)key_list_kernel<512, 8>
+                               : ix->s_max <= 32 * 512 ? (const void *)key_list_kernel<512, 32>
+                               : ix->s_max <= 64 * 512 ? (const void *)key_list_kernel<512, 64>
+                                                       : (const void *)key_list_kernel<1024, 32>, exact_list_lds(ix));
     for (int u0 = 0; rc == CTKVR_OK && u0 < total_units; u0 += chunk) {
         const int nu = std::min(chunk, total_units - u0);
         Units u = decode_units(ix);
         u.build = 1;
         u.unit0 = u0;
-        fill_u32_kernel<<<dim3((unsigned)((nu * G + 255) / 256)), 256, 0, st>>>(m_key, 0u, (size_t)nu * G);
-        fill_u32_kernel<<<dim3((unsigned)((nu * G * 2 + 255) / 256)), 256, 0, st>>>((uint32_t *)S, 0u, (size_t)nu * G * 2);
+        if (!mfma) {
+            fill_u32_kernel<<<dim3((unsigned)((nu * G + 255) / 256)), 256, 0, st>>>(m_key, 0u, (size_t)nu * G);
+            fill_u32_kernel<<<dim3((unsigned)((nu * G * 2 + 255) / 256)), 256, 0, st>>>((uint32_t *)S, 0u, (size_t)nu * G * 2);
+        }
         if (ghist) fill_u32_kernel<<<dim3((unsigned)(((size_t)nu * kBuckets + 255) / 256)), 256, 0, st>>>(ghist, 0u, (size_t)nu * kBuckets);
         bool keys_written = false;   // kbuf holds this chunk's ranking keys (matrix-core route)
         ScoreArgs sa{};
@@ -902,7 +919,7 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
                     ca.n_local = ix->p.n_local;
                     ca.ksamp = ksamp;
                     ca.tau = tau;
-                    const int seg_cap = std::min(cand_cap, std::max(256, 2 * cand_cap / ma.t_splits));   // t_splits * seg_cap <= 2 max(cand_cap, 128 t_splits)
+                    const int seg_cap = std::min(cand_cap, cand_room / ma.t_splits);   // candidates cluster: all the room there is
                     ca.cand = cand;
                     ca.seg_cnt = cursor;
                     ca.t_splits = ma.t_splits;
@@ -934,7 +951,7 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
                             if (rc != CTKVR_OK) break;
                             lay_out_full(redo_mem.base());
                         }
-                        fill_u32_kernel<<<dim3((unsigned)(((size_t)nu * kBuckets + 255) / 256)), 256, 0, st>>>(ghist, 0u, (size_t)nu * kBuckets);
+                        if (ghist) fill_u32_kernel<<<dim3((unsigned)(((size_t)nu * kBuckets + 255) / 256)), 256, 0, st>>>(ghist, 0u, (size_t)nu * kBuckets);
                     }
                 }
                 if (redo) {   // every key stored, then histogram and selection over all of them
@@ -960,6 +977,31 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
             denom_kernel<G><<<dim3(std::min((ix->s_max + 1023) / 1024, 64), nu), 256, 0, st>>>(da);
         }
         if (mfma && !keys_written) {   // the candidate route has written this chunk's lists
+            hipError_t e = hipGetLastError();
+            if (e != hipSuccess) rc = fail(CTKVR_EHIP, "build launch: %s", hipGetErrorString(e));
+            continue;
+        }
+        if (by_list) {
+            KeyListArgs la{};
+            la.g = ix->p.n_kv_heads;
+            la.c_max = ix->c_max;
+            la.unit0 = u0;
+            la.n_cent = ix->d_n_cent;
+            la.ctx_lens = ix->d_ctx_lens;
+            la.l_stride = ix->s_max;
+            la.rho = rho;
+            la.n_init = ix->p.n_init;
+            la.n_local = ix->p.n_local;
+            la.kbuf = kbuf;
+            la.lists = ix->lists;
+            if (ix->s_max <= 8 * 512)
+                key_list_kernel<512, 8><<<dim3(nu), 512, exact_list_lds(ix), st>>>(la);
+            else if (ix->s_max <= 32 * 512)
+                key_list_kernel<512, 32><<<dim3(nu), 512, exact_list_lds(ix), st>>>(la);
+            else if (ix->s_max <= 64 * 512)
+                key_list_kernel<512, 64><<<dim3(nu), 512, exact_list_lds(ix), st>>>(la);
+            else
+                key_list_kernel<1024, 32><<<dim3(nu), 1024, exact_list_lds(ix), st>>>(la);
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) rc = fail(CTKVR_EHIP, "build launch: %s", hipGetErrorString(e));
             continue;
@@ -1004,8 +1046,6 @@ constexpr size_t kExactChunkBytes = (size_t)512 << 20;
 
 // The same lists with the scores on the fp32 matrix cores (exact_score_kernel) and one block per list behind them
 // (exact_list_kernel); needs shared memory for a bitmap of the context (to about 2^18 tokens).
-size_t exact_list_lds(const ctkvr_index *ix) { return ((size_t)kSelLds + 2 * kListCap + 4 * ((ix->s_max + 63) / 64)) * 4; }
-
 template <typename T, int G> int build_lists_exact_mfma(ctkvr_index *ix, const void *k_pages, const int32_t *block_table, int max_pages, hipStream_t st)
 {
     constexpr int CT = 32 * (8 / G);

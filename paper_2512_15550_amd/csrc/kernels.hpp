@@ -2788,6 +2788,60 @@ template <int G, int NT, int KPT> __global__ __launch_bounds__(NT) void exact_li
         [&](int i) { return listed(i) ? ordered_key(key_at(i)) : 0x007fffffu; }, s_hist, s_list, s_bits, s_res);
 }
 
+// key_list_kernel: the list of one unit of the chunk per block, from its s ranking keys (the matrix-core build's every-key
+// route): the same selection, keys of up to KPT NT positions read once into registers.  A histogram launch and a
+// selection launch, each reading all keys and meeting in memory, took 0.41 + 0.40 ms for the 160 M keys of 9720 lists;
+// this 0.47 ms, bound by the latencies of a list's phases: two blocks of 512 threads per CU hide them better than one of
+// 1024 (0.61 ms).  Beyond 32768 positions, where keys are read again, 1024 threads are 5 % faster.
+// grid (chunk units), NT threads, dynamic shared memory as above.
+struct KeyListArgs {
+    int g, c_max, unit0;
+    const int32_t *n_cent, *ctx_lens;
+    int l_stride, rho, n_init, n_local;
+    const uint32_t *kbuf;                    // [chunk units][l_stride], the window's keys the image of -inf
+    int32_t *lists;                          // [all units][rho]
+};
+
+template <int NT, int KPT> __global__ __launch_bounds__(NT, 4) void key_list_kernel(KeyListArgs a)
+{
+    extern __shared__ __align__(16) uint32_t smem[];
+    constexpr int NW = NT / 64;
+    __shared__ uint32_t s_res[4];
+    uint32_t *s_hist = smem, *s_list = smem + kSelLds, *s_bits = s_list + 2 * kListCap;
+    const int ul = blockIdx.x, tid = threadIdx.x, ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int unit = a.unit0 + ul, bk = unit / a.c_max, b = bk / a.g;
+    if (unit - bk * a.c_max >= a.n_cent[b]) return;
+    const int s = a.ctx_lens[b];
+    const uint32_t *kb = a.kbuf + (size_t)ul * a.l_stride;
+    int32_t *dst = a.lists + (size_t)unit * a.rho;
+    const int n_real = s - a.n_local - a.n_init;
+    if (a.rho >= n_real) {   // every key outside the window
+        for (int i = tid; i < a.rho; i += NT) dst[i] = a.n_init + i;
+        return;
+    }
+    auto key_at = [&](int i) __attribute__((always_inline)) {   // above -inf exactly outside the window
+        const float x = fmaxf(ordered_value(kb[min(i, s - 1)]), -3.0e38f);
+        return i < s - a.n_local && i >= a.n_init ? x : -__builtin_huge_valf();
+    };
+    float kreg[KPT];
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+        if (q % 4 == 0 && (q * NW + wv) * 64 >= s) break;   // rounds that select_keys does not look at either
+        kreg[q] = key_at(q * NT + tid);
+    }
+    for (int w = tid; w < kBuckets / 4; w += NT) reinterpret_cast<uint4 *>(s_hist)[w] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid == 0) s_res[3] = 0u;
+    __syncthreads();
+    select_keys<NT, KPT>(
+        kreg, s, n_real, a.rho,
+        [&](auto f) __attribute__((always_inline)) {
+            for (int gq = KPT * NW + wv; gq * 64 < s; gq += NW) f(gq, key_at(gq * 64 + ln));
+        },
+        [&](int, int gq, uint32_t pos) __attribute__((always_inline)) { dst[pos] = gq * 64 + ln; },
+        [&](int pos, int i) __attribute__((always_inline)) { dst[pos] = i; },
+        [&](int i) { return ordered_key(key_at(i)); }, s_hist, s_list, s_bits, s_res);
+}
+
 // ------------------------------------------------------------------------------
 // Algorithm 2 lines 5b-9 in ONE launch, for small batches: denominators, ranking, selection and attention.  Three
 // launches (denom, keyclass, select_attn) spent 24 us on it at 32K tokens / 8 KV heads, of which about 9 are the gaps, ramps
