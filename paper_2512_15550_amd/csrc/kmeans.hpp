@@ -3,8 +3,8 @@
 // prompt positions are clustered; a point is the concatenation of the G query-head
 // vectors of the group at one position (G*128 numbers, contiguous in q_prefill).
 // Lloyd iteration = half-norms -> assignment on the matrix cores (which also counts the
-// members of every centre) -> counting sort of the positions by centre -> one block per
-// centre sums its members in fixed point and writes the new centre.  The centres live in the index's centroid table
+// members of every centre) -> counting sort of the positions by centre -> blocks per centre, one for
+// every 256 members, sum them in fixed point and the last writes the new centre.  The centres live in the index's centroid table
 // [b][h][c_max][128] all along: head hh of centre c is one 128-element row.
 #pragma once
 #include "kernels.hpp"
