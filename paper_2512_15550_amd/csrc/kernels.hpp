@@ -1093,9 +1093,9 @@ __global__ __launch_bounds__((MfmaShape<G, MODE>::NT), (MfmaShape<G, MODE>::kWav
                     uint32_t *dst = MODE == MFMA_SAMPLE ? a.kbuf + unit * a.sample_stride + (tb / ST) * 32 + n4
                                                         : a.kbuf + unit * a.l_stride + t;
                     if (wide) {
-                        // written once, read much later by other kernels: kept out of the caches that hold the keys
-                        u32x4_t v4 = {ok[0], ok[1], ok[2], ok[3]};
-                        __builtin_nontemporal_store(v4, reinterpret_cast<u32x4_t *>(dst));
+                        // plain stores: the keys of a 20K build (200 MB) then wait for their reader in the memory-side cache (480 ->
+                        // 461 us against non-temporal ones); where they do not fit (0.64 GB) there is no difference
+                        *reinterpret_cast<uint4 *>(dst) = make_uint4(ok[0], ok[1], ok[2], ok[3]);
                     } else {
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
