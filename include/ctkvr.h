@@ -199,7 +199,8 @@ int ctkvr_decode_step_static(ctkvr_index *idx, const void *q, const void *k_page
  */
 int ctkvr_centroid_update(ctkvr_index *idx, const void *q, void *hip_stream);
 
-/* Release an index (NULL is allowed).  Synchronises the device first. */
+/* Release an index (NULL is allowed).  Synchronises the index's device first; where that is refused (a stream of it is being
+ * captured) the index's memory is kept back until a later wait succeeds. */
 void ctkvr_free(ctkvr_index *idx);
 
 /* Thread-local description of the last non-OK return of this library. */
@@ -283,7 +284,9 @@ int ctkvr_index_build_route(const ctkvr_index *idx, int32_t *by_candidates_host,
  * given up first, and serve later builds and loads of about the same size, from any host thread and stream; they
  * are freed when an allocation of the library runs out of memory and by this call, which frees the current device's
  * idle blocks and the 8 MB of pinned host memory that copies of lists and centroids go through; an error if a build
- * is using scratch on that device.  The environment variable
+ * is using scratch on that device.  Memory whose users could not be waited for (ctkvr_free while a stream is being captured)
+ * is kept back and joins the idle blocks at the next build, load or call of this function that can wait for the device.
+ * The environment variable
  * CTKVR_BUILD_SCRATCH_CACHE = 0, read when a block is given back, switches the keeping off. */
 int ctkvr_release_scratch(void);
 

@@ -84,7 +84,9 @@ int static_scratch(unsigned char **out)
 // nothing uses any more are kept per device, at most kPoolMax bytes of them (the oldest go first), and handed out again to
 // a request of at least half their size.  ctkvr_release_scratch() frees them; CTKVR_BUILD_SCRATCH_CACHE=0 switches the
 // keeping off.  A block enters the pool only after the work that used it has ended (a build synchronises its stream, an
-// index its device), so it is idle whichever stream or host thread takes it next.
+// index its device), so it is idle whichever stream or host thread takes it next.  Where that wait fails -- a device cannot
+// be waited for while one of its streams is being captured in global mode -- the block is set aside: nothing has it, and it is not
+// freed, before a later wait for the device has succeeded (pool_settle).
 constexpr size_t kPoolMax = (size_t)2 << 30;
 struct PoolBlock {
     void *base;
@@ -92,6 +94,7 @@ struct PoolBlock {
 };
 std::mutex g_pool_mu;
 std::vector<PoolBlock> g_pool[kMaxDevices];   // oldest first
+std::vector<PoolBlock> g_aside[kMaxDevices];  // blocks that work may still be using
 int g_pool_builds[kMaxDevices] = {};          // builds that are using scratch right now
 
 bool pool_on()
@@ -107,6 +110,40 @@ void pool_drop(int dev)
     g_pool[dev].clear();
 }
 
+// the work on the current device has ended
+bool device_idle()
+{
+    if (hipDeviceSynchronize() == hipSuccess) return true;
+    (void)hipGetLastError();   // (a launch's own check would report it)
+    return false;
+}
+
+// an idle block into the pool, or to the runtime where it is not kept (the caller holds g_pool_mu)
+void pool_keep(int dev, PoolBlock b)
+{
+    if (b.bytes > kPoolMax || !pool_on()) {
+        (void)hipFree(b.base);
+        return;
+    }
+    std::vector<PoolBlock> &v = g_pool[dev];
+    v.push_back(b);
+    size_t held = 0;
+    for (PoolBlock &x : v) held += x.bytes;
+    while (held > kPoolMax) {
+        held -= v.front().bytes;
+        (void)hipFree(v.front().base);
+        v.erase(v.begin());
+    }
+}
+
+// the blocks set aside on the current device, if it can be waited for now (the caller holds g_pool_mu)
+void pool_settle(int dev)
+{
+    if (g_aside[dev].empty() || !device_idle()) return;
+    for (PoolBlock &b : g_aside[dev]) pool_keep(dev, b);
+    g_aside[dev].clear();
+}
+
 // a block of at least `bytes` on the current device `dev`; out->bytes is its real size
 int pool_get(int dev, size_t bytes, PoolBlock *out)
 {
@@ -117,6 +154,7 @@ int pool_get(int dev, size_t bytes, PoolBlock *out)
     std::unique_lock<std::mutex> lock(g_pool_mu, std::defer_lock);
     if (pooled) {
         lock.lock();
+        pool_settle(dev);
         std::vector<PoolBlock> &v = g_pool[dev];
         size_t best = v.size();
         for (size_t i = 0; i < v.size(); ++i)
@@ -141,29 +179,25 @@ int pool_get(int dev, size_t bytes, PoolBlock *out)
     return CTKVR_OK;
 }
 
-// gives a block of device `dev` back; nothing on that device uses it any more
-void pool_put(int dev, PoolBlock b)
+// gives a block of device `dev` back; idle: its users have been waited for
+void pool_put(int dev, PoolBlock b, bool idle)
 {
     if (!b.base) return;
-    if (dev < 0 || dev >= kMaxDevices || b.bytes > kPoolMax || !pool_on()) {
+    if (dev < 0 || dev >= kMaxDevices) {
         (void)hipFree(b.base);
         return;
     }
     std::lock_guard<std::mutex> lock(g_pool_mu);
-    std::vector<PoolBlock> &v = g_pool[dev];
-    v.push_back(b);
-    size_t held = 0;
-    for (PoolBlock &x : v) held += x.bytes;
-    while (held > kPoolMax) {
-        held -= v.front().bytes;
-        (void)hipFree(v.front().base);
-        v.erase(v.begin());
-    }
+    if (idle)
+        pool_keep(dev, b);
+    else
+        g_aside[dev].push_back(b);
 }
 
-// Scratch of one build, given back at the end of the scope (the stream has been synchronised by then).
+// Scratch of one build, given back at the end of the scope: as idle if waited() has heard of a synchronisation that succeeded.
 struct BuildScratch {
     int dev = -1;
+    bool idle = false;
     PoolBlock b{nullptr, 0};
     ~BuildScratch() { put(); }
     int get(int device, size_t bytes)
@@ -172,6 +206,7 @@ struct BuildScratch {
         int rc = pool_get(device, bytes, &b);
         if (rc != CTKVR_OK) return rc;
         dev = device;
+        idle = false;
         if (dev >= 0 && dev < kMaxDevices) {
             std::lock_guard<std::mutex> lock(g_pool_mu);
             g_pool_builds[dev]++;
@@ -181,26 +216,29 @@ struct BuildScratch {
     void put()
     {
         if (!b.base) return;
-        pool_put(dev, b);
+        pool_put(dev, b, idle);
         if (dev >= 0 && dev < kMaxDevices) {
             std::lock_guard<std::mutex> lock(g_pool_mu);
             g_pool_builds[dev]--;
         }
         b = PoolBlock{nullptr, 0};
     }
+    void waited(hipError_t e) { idle = e == hipSuccess; }
     unsigned char *base() const { return (unsigned char *)b.base; }
 };
 
 // Copies between pageable host memory and the device through pinned memory of the library: while a chunk is on the bus the next
 // one is copied by the CPU.  Moving 16 MB to the device took 0.52 to 0.64 ms as one hipMemcpy and 0.97 ms back, the
 // bus alone 0.30 ms.  One ring of kStageSlots chunks per device (8 MB, made on first use, freed by ctkvr_release_scratch); a
-// caller that finds it in use takes plain copies.
+// caller that finds it in use takes plain copies, and so does one that finds it left by copies that could not be waited for, unless
+// the device can be waited for now.
 constexpr size_t kStageChunk = (size_t)1 << 20;
 constexpr int kStageSlots = 8;
 struct Staging {
     unsigned char *buf = nullptr;
     hipEvent_t ev[kStageSlots] = {};
     bool busy = false;
+    bool unsure = false;   // copies may still be under way
 };
 Staging g_staging[kMaxDevices];   // (g_pool_mu)
 
@@ -229,7 +267,8 @@ hipError_t copy_segments(int dev, const CopySeg *segs, int n, bool to_device, hi
     if (dev >= 0 && dev < kMaxDevices && total >= ((size_t)128 << 10)) {
         std::lock_guard<std::mutex> lock(g_pool_mu);
         Staging &x = g_staging[dev];
-        if (!x.busy) {
+        if (!x.busy && (!x.unsure || device_idle())) {
+            x.unsure = false;
             bool ok = true;
             if (!x.buf) {
                 ok = hipHostMalloc((void **)&x.buf, kStageChunk * kStageSlots, hipHostMallocDefault) == hipSuccess;
@@ -281,8 +320,9 @@ hipError_t copy_segments(int dev, const CopySeg *segs, int n, bool to_device, hi
             used[at] = e == hipSuccess;
         }
     for (int k = 0; k < kStageSlots; ++k) settle((at + k) % kStageSlots);
-    if (e != hipSuccess) (void)hipStreamSynchronize(st);   // nothing may still be using the ring
+    const bool done = e == hipSuccess || hipStreamSynchronize(st) == hipSuccess;   // nothing uses the ring any more
     std::lock_guard<std::mutex> lock(g_pool_mu);
+    sg->unsure = !done;
     sg->busy = false;
     return e;
 }
@@ -375,12 +415,11 @@ struct ctkvr_index {
 
     ~ctkvr_index()
     {
-        // the memory may be handed to another index at once: nothing on its device uses it any more after this
+        // the memory may be handed to another index at once, if nothing on its device uses it any more
         int cur = -1;
         (void)hipGetDevice(&cur);
-        if (cur != dev) (void)hipSetDevice(dev);
-        (void)hipDeviceSynchronize();
-        pool_put(dev, mem);
+        const bool there = cur == dev || hipSetDevice(dev) == hipSuccess;
+        pool_put(dev, mem, there && device_idle());
         for (hipEvent_t e : events) (void)hipEventDestroy(e);
         for (hipEvent_t e : ev_join) (void)hipEventDestroy(e);
         if (ev_fork) (void)hipEventDestroy(ev_fork);
@@ -1038,6 +1077,8 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
         if (e != hipSuccess) rc = fail(CTKVR_EHIP, "build launch: %s", hipGetErrorString(e));
     }
     hipError_t es = hipStreamSynchronize(st);
+    scratch_mem.waited(es);
+    redo_mem.waited(es);
     if (rc == CTKVR_OK && es != hipSuccess) rc = fail(CTKVR_EHIP, "build: %s", hipGetErrorString(es));
     return rc;
 }
@@ -1114,6 +1155,7 @@ template <typename T, int G> int build_lists_exact_mfma(ctkvr_index *ix, const v
     }
     hipError_t e = hipGetLastError();
     hipError_t es = hipStreamSynchronize(st);   // the scratch is given back
+    scratch_mem.waited(es);
     if (e == hipSuccess) e = es;
     return e == hipSuccess ? CTKVR_OK : fail(CTKVR_EHIP, "build: %s", hipGetErrorString(e));
 }
@@ -1650,6 +1692,7 @@ int run_kmeans(ctkvr_index *ix, const bf16_t *q_prefill, const int32_t *d_first,
         }
     }
     hipError_t es = hipStreamSynchronize(st);
+    scratch_mem.waited(es);
     if (rc == CTKVR_OK && es != hipSuccess) rc = fail(CTKVR_EHIP, "k-means: %s", hipGetErrorString(es));
     return rc;
 }
@@ -1964,8 +2007,12 @@ int ctkvr_release_scratch(void)
     if (dev < 0 || dev >= kMaxDevices) return CTKVR_OK;
     std::lock_guard<std::mutex> lock(g_pool_mu);
     if (g_pool_builds[dev]) return fail(CTKVR_EINVAL, "an index build is using the scratch");
+    pool_settle(dev);
     pool_drop(dev);
-    if (!g_staging[dev].busy) staging_drop(g_staging[dev]);
+    if (!g_staging[dev].busy && (!g_staging[dev].unsure || device_idle())) {
+        g_staging[dev].unsure = false;
+        staging_drop(g_staging[dev]);
+    }
     return CTKVR_OK;
 }
 

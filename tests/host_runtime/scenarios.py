@@ -1,0 +1,117 @@
+"""Scenarios of tests/test_host_runtime.py: each runs in a process of its own, as
+``python -m tests.host_runtime.scenarios NAME FAKE_LIBRARY``, with the library's HIP calls going to fake_hip.cpp."""
+import ctypes
+import sys
+
+import numpy as np
+
+import paper_2512_15550_amd as ck
+
+OK, EINVAL, EHIP = 0, -1, -3
+
+
+class Host:
+    def __init__(self, fake_path):
+        self.fake = ctypes.CDLL(fake_path, mode=ctypes.RTLD_GLOBAL)
+        self.fake.fake_live_bytes.restype = ctypes.c_size_t
+        self.lib = ck.load_library()
+
+    def device(self, d):
+        assert self.fake.hipSetDevice(d) == 0
+
+    def current(self):
+        d = ctypes.c_int(-1)
+        self.fake.hipGetDevice(ctypes.byref(d))
+        return d.value
+
+    def load(self, s=4096, C=64, rho=256, h=8, g=2, probe=8, top_k=256, batch=1, expect=OK):
+        p = ck.Params(batch=batch, n_q_heads=h, n_kv_heads=g, dtype=ck.BF16, n_centroids=C, list_len=rho, n_probe=probe, top_k=top_k).c()
+        lens = np.full(batch, s, np.int32)
+        cen = np.random.RandomState(s).randint(0, 1 << 16, (batch, h, C, 128)).astype(np.uint16)
+        lists = np.tile(np.arange(rho, dtype=np.int32), (batch, g, C, 1))
+        out = ctypes.c_void_p()
+        rc = self.lib.ctkvr_index_load(ctypes.byref(p), lens.ctypes.data, cen.ctypes.data, lists.ctypes.data, None, ctypes.byref(out))
+        assert rc == expect, (rc, ck.ctkvr_last_error())
+        return out.value, cen, lists
+
+    def info(self, ix):
+        i = ck.binding._CInfo()
+        assert self.lib.ctkvr_index_info(ix, ctypes.byref(i)) == OK
+        return i
+
+
+def refused_wait(x):
+    """An index freed while the device cannot be waited for (a stream is being captured): its memory goes to no other
+    index, and is not freed, until a later wait has succeeded."""
+    a, _, _ = x.load()
+    n, held = x.fake.fake_mallocs(), x.fake.fake_live_bytes(0)
+    x.fake.fake_refuse_syncs(1, 0)
+    x.lib.ctkvr_free(a)
+    assert x.fake.fake_live_bytes(0) == held
+    assert x.fake.hipGetLastError() == 0, "the refused wait is left for the next check of a launch"
+    b, _, _ = x.load()                       # still refused: memory of its own
+    assert x.fake.fake_mallocs() == n + 1, "memory that may still be in use was handed to another index"
+    assert x.lib.ctkvr_release_scratch() == OK and x.fake.fake_live_bytes(0) == 2 * held
+    x.fake.fake_refuse_syncs(0, 0)
+    s = x.fake.fake_syncs(0)
+    c, _, _ = x.load()                       # waited for now: the first index's memory
+    assert x.fake.fake_syncs(0) > s and x.fake.fake_mallocs() == n + 1
+    x.lib.ctkvr_free(b)
+    x.lib.ctkvr_free(c)
+    assert x.lib.ctkvr_release_scratch() == OK and x.fake.fake_live_bytes(0) == 0
+
+
+def refused_wait_released(x):
+    """... and ctkvr_release_scratch frees it once the wait succeeds."""
+    a, _, _ = x.load()
+    x.fake.fake_refuse_syncs(1, 0)
+    x.lib.ctkvr_free(a)
+    x.fake.fake_refuse_syncs(0, 0)
+    assert x.lib.ctkvr_release_scratch() == OK and x.fake.fake_live_bytes(0) == 0
+
+
+def refused_build(x):
+    """A build whose stream cannot be waited for fails, and its scratch is set aside like the memory of an index."""
+    p = ck.Params(batch=1, n_q_heads=8, n_kv_heads=2, dtype=ck.BF16, n_centroids=64, list_len=256, n_probe=8, top_k=256).c()
+    lens, cu, out = np.array([4096], np.int32), np.array([0, 64], np.int32), ctypes.c_void_p()
+    ptr = ctypes.c_void_p(4096)              # (kernels do nothing here)
+
+    def build():
+        return x.lib.ctkvr_build_index(ctypes.byref(p), ptr, cu.ctypes.data, 1, ptr, ptr, 256, lens.ctypes.data, None, None,
+                                       ctypes.byref(out))
+
+    x.fake.fake_refuse_syncs(1, 1)
+    assert build() == EHIP
+    n, held = x.fake.fake_mallocs(), x.fake.fake_live_bytes(0)
+    assert n == 2 and x.fake.fake_frees() == 0
+    assert build() == EHIP and x.fake.fake_mallocs() == 2 * n, "scratch that may still be in use was handed to another build"
+    x.fake.fake_refuse_syncs(0, 0)
+    assert build() == OK and x.fake.fake_mallocs() == 2 * n
+    x.lib.ctkvr_free(out.value)
+    assert x.lib.ctkvr_release_scratch() == OK and x.fake.fake_live_bytes(0) == 0
+
+
+def refused_copy(x):
+    """A load whose copies cannot be waited for fails, and the pinned memory they go through serves no other copy, and is not
+    freed, until the device has been waited for."""
+    a, cen, _ = x.load(C=512)                # (large enough for the pinned memory)
+    assert x.fake.fake_pinned() == 1 and x.fake.fake_records() > 0
+    x.fake.fake_refuse_syncs(1, 1)
+    x.load(C=512, expect=EHIP)
+    n = x.fake.fake_records()
+    got = np.empty_like(cen)
+    x.fake.fake_refuse_syncs(1, 0)
+    x.load(C=512)
+    assert x.fake.fake_records() == n, "pinned memory that may still be in use took part in another copy"
+    assert x.lib.ctkvr_release_scratch() == OK and x.fake.fake_pinned() == 1
+    x.fake.fake_refuse_syncs(0, 0)
+    assert x.lib.ctkvr_index_centroids(a, got.ctypes.data) == OK and np.array_equal(got, cen)
+    assert x.fake.fake_records() > n
+    assert x.lib.ctkvr_release_scratch() == OK and x.fake.fake_pinned() == 0
+
+
+SCENARIOS = {f.__name__: f for f in (refused_wait, refused_wait_released, refused_build, refused_copy)}
+
+if __name__ == "__main__":
+    SCENARIOS[sys.argv[1]](Host(sys.argv[2]))
+    print("ok")
