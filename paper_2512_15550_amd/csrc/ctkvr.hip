@@ -46,6 +46,23 @@ int fail(int code, const char *fmt, ...)
                         hipGetErrorString(e_));                                                 \
     } while (0)
 
+// Makes a device the calling thread's current one for a scope.  Events, the null stream, function attributes and
+// device-wide waits are those of the current device, which need not be the one an index lives on.
+struct DeviceScope {
+    int before = -1;
+    hipError_t err;
+    explicit DeviceScope(int dev)
+    {
+        err = hipGetDevice(&before);
+        if (err == hipSuccess && before == dev) before = -1;   // nothing to restore
+        else err = hipSetDevice(dev);
+    }
+    ~DeviceScope()
+    {
+        if (before >= 0) (void)hipSetDevice(before);
+    }
+};
+
 size_t elem_size(int dtype) { return dtype == CTKVR_BF16 ? 2 : 4; }
 
 }  // namespace
@@ -416,15 +433,12 @@ struct ctkvr_index {
     ~ctkvr_index()
     {
         // the memory may be handed to another index at once, if nothing on its device uses it any more
-        int cur = -1;
-        (void)hipGetDevice(&cur);
-        const bool there = cur == dev || hipSetDevice(dev) == hipSuccess;
-        pool_put(dev, mem, there && device_idle());
+        DeviceScope on(dev);
+        pool_put(dev, mem, on.err == hipSuccess && device_idle());
         for (hipEvent_t e : events) (void)hipEventDestroy(e);
         for (hipEvent_t e : ev_join) (void)hipEventDestroy(e);
         if (ev_fork) (void)hipEventDestroy(ev_fork);
         for (hipStream_t st : side) (void)hipStreamDestroy(st);
-        if (cur != dev && cur >= 0) (void)hipSetDevice(cur);
     }
     // event slot `stage` (0 = before the first kernel) of the step being recorded
     void mark(int stage, hipStream_t st)
@@ -1959,6 +1973,8 @@ void ctkvr_free(ctkvr_index *idx)
 int ctkvr_profile_enable(ctkvr_index *idx, int32_t max_steps)
 {
     if (!idx || max_steps < 0) return fail(CTKVR_EINVAL, "bad argument");
+    DeviceScope on(idx->dev);
+    HIP_TRY(on.err);
     HIP_TRY(hipDeviceSynchronize());
     for (hipEvent_t e : idx->events) (void)hipEventDestroy(e);
     idx->events.clear();
@@ -1975,6 +1991,8 @@ int ctkvr_profile_enable(ctkvr_index *idx, int32_t max_steps)
 int ctkvr_profile_collect(ctkvr_index *idx, float *ms_host, int32_t capacity_steps, int32_t *n_steps)
 {
     if (!idx || !ms_host || !n_steps) return fail(CTKVR_EINVAL, "NULL argument");
+    DeviceScope on(idx->dev);
+    HIP_TRY(on.err);
     HIP_TRY(hipDeviceSynchronize());
     int n = std::min<int>(idx->prof_step, capacity_steps);
     for (int s = 0; s < n; ++s)
@@ -2033,6 +2051,8 @@ int ctkvr_index_decode_path(const ctkvr_index *idx)
 int ctkvr_index_check(ctkvr_index *idx)
 {
     if (!idx) return fail(CTKVR_EINVAL, "index is NULL");
+    DeviceScope on(idx->dev);
+    HIP_TRY(on.err);
     HIP_TRY(hipDeviceSynchronize());
     uint32_t e = 0;
     HIP_TRY(hipMemcpy(&e, idx->d_err, 4, hipMemcpyDeviceToHost));
@@ -2045,6 +2065,8 @@ int ctkvr_index_check(ctkvr_index *idx)
 int ctkvr_profile_phases(ctkvr_index *idx, int32_t enable, long long *ticks_host)
 {
     if (!idx) return fail(CTKVR_EINVAL, "index is NULL");
+    DeviceScope on(idx->dev);
+    HIP_TRY(on.err);
     HIP_TRY(hipDeviceSynchronize());
     if (ticks_host) HIP_TRY(hipMemcpy(ticks_host, idx->d_prof, 64 * sizeof(long long), hipMemcpyDeviceToHost));
     idx->prof_phases = enable != 0;
@@ -2130,6 +2152,8 @@ int ctkvr_index_info(const ctkvr_index *idx, ctkvr_index_info_t *out)
 int ctkvr_index_lists(const ctkvr_index *idx, int32_t *dst_host)
 {
     if (!idx || !dst_host) return fail(CTKVR_EINVAL, "NULL argument");
+    DeviceScope on(idx->dev);
+    HIP_TRY(on.err);
     HIP_TRY(hipDeviceSynchronize());
     const CopySeg seg{dst_host, idx->lists, (size_t)idx->units * idx->c_max * idx->p.list_len * 4};
     HIP_TRY(copy_segments(idx->dev, &seg, 1, false, nullptr));
@@ -2139,6 +2163,8 @@ int ctkvr_index_lists(const ctkvr_index *idx, int32_t *dst_host)
 int ctkvr_index_centroids(const ctkvr_index *idx, void *dst_host)
 {
     if (!idx || !dst_host) return fail(CTKVR_EINVAL, "NULL argument");
+    DeviceScope on(idx->dev);
+    HIP_TRY(on.err);
     HIP_TRY(hipDeviceSynchronize());
     const CopySeg seg{dst_host, idx->centroids,
                       (size_t)idx->p.batch * idx->p.n_q_heads * idx->c_max * 128 * elem_size(idx->p.dtype)};
@@ -2149,6 +2175,8 @@ int ctkvr_index_centroids(const ctkvr_index *idx, void *dst_host)
 int ctkvr_index_last_candidates(const ctkvr_index *idx, int32_t *dst_host)
 {
     if (!idx || !dst_host) return fail(CTKVR_EINVAL, "NULL argument");
+    DeviceScope on(idx->dev);
+    HIP_TRY(on.err);
     HIP_TRY(hipDeviceSynchronize());
     HIP_TRY(hipMemcpy(dst_host, idx->ws.cand, (size_t)idx->units * idx->l_stride * 4, hipMemcpyDeviceToHost));
     return CTKVR_OK;

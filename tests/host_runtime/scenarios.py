@@ -110,7 +110,33 @@ def refused_copy(x):
     assert x.lib.ctkvr_release_scratch() == OK and x.fake.fake_pinned() == 0
 
 
-SCENARIOS = {f.__name__: f for f in (refused_wait, refused_wait_released, refused_build, refused_copy)}
+def other_device(x):
+    """The inspection calls work on the index's device whichever is current, wait for that one, and leave the current one."""
+    x.device(1)
+    a, cen, lists = x.load(C=512)
+    assert x.lib.ctkvr_release_scratch() == OK      # (the pinned memory is made again, now with device 0 current)
+    x.device(0)
+    got_c, got_l, last = np.empty_like(cen), np.empty_like(lists), np.empty((2, 8 * 256), np.int32)
+    err = ctypes.c_int32(0)
+    for call in (lambda: x.lib.ctkvr_index_centroids(a, got_c.ctypes.data), lambda: x.lib.ctkvr_index_lists(a, got_l.ctypes.data),
+                 lambda: x.lib.ctkvr_index_last_candidates(a, last.ctypes.data), lambda: x.lib.ctkvr_profile_phases(a, 0, None),
+                 lambda: x.lib.ctkvr_profile_enable(a, 2), lambda: x.lib.ctkvr_profile_collect(a, last.ctypes.data, 2, ctypes.byref(err))):
+        n0, n1 = x.fake.fake_syncs(0), x.fake.fake_syncs(1)
+        assert call() == OK, ck.ctkvr_last_error()
+        assert x.current() == 0 and x.fake.fake_syncs(0) == n0 and x.fake.fake_syncs(1) > n1
+    n1 = x.fake.fake_syncs(1)
+    x.lib.ctkvr_index_check(a)                      # (its word reads as an error: no kernel has cleared it)
+    assert x.current() == 0 and x.fake.fake_syncs(1) > n1
+    assert np.array_equal(got_c, cen) and np.array_equal(got_l, lists)
+    x.device(1)
+    b, _, _ = x.load(C=512)                         # the pinned memory as the export left it
+    assert x.lib.ctkvr_index_centroids(b, got_c.ctypes.data) == OK
+    x.device(0)
+    x.lib.ctkvr_free(a)
+    assert x.current() == 0
+
+
+SCENARIOS = {f.__name__: f for f in (refused_wait, refused_wait_released, refused_build, refused_copy, other_device)}
 
 if __name__ == "__main__":
     SCENARIOS[sys.argv[1]](Host(sys.argv[2]))
