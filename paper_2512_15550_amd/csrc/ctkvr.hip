@@ -538,9 +538,11 @@ size_t carve_step_ws(StepWs &w, unsigned char *base, const ctkvr_index *ix)
     return cv.off;
 }
 
-// the single-launch kernel of this geometry, with its shared memory
+// the single-launch kernel of this geometry, with its shared memory (a limit that belongs to a device)
 int allow_fused(const ctkvr_index *ix)
 {
+    DeviceScope on(ix->dev);
+    HIP_TRY(on.err);
     hipError_t e = fused_set_smem(ix->p.dtype == CTKVR_BF16, ix->G, ix->fused_nt, ix->fused_smem);
     return e == hipSuccess ? CTKVR_OK : fail(CTKVR_EHIP, "single-launch step: %s", hipGetErrorString(e));
 }

@@ -136,7 +136,17 @@ def other_device(x):
     assert x.current() == 0
 
 
-SCENARIOS = {f.__name__: f for f in (refused_wait, refused_wait_released, refused_build, refused_copy, other_device)}
+def path_of_other_device(x):
+    """Choosing the single launch raises the kernel's shared-memory limit on the index's device."""
+    x.device(1)
+    a, _, _ = x.load()
+    x.device(0)
+    n = x.fake.fake_attr_calls()
+    assert x.lib.ctkvr_index_set_decode_path(a, ck.PATH_FUSED) == OK
+    assert x.fake.fake_attr_calls() > n and x.fake.fake_attr_device() == 1 and x.current() == 0
+
+
+SCENARIOS = {f.__name__: f for f in (refused_wait, refused_wait_released, refused_build, refused_copy, other_device, path_of_other_device)}
 
 if __name__ == "__main__":
     SCENARIOS[sys.argv[1]](Host(sys.argv[2]))
