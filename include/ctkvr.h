@@ -213,7 +213,7 @@ typedef struct {
     int32_t list_len, n_probe, top_k;
     int32_t l_stride;        /* candidate slots per (sequence, KV head): max_i min(s_i, C' * rho) */
     int64_t index_bytes;     /* bytes of the inverted lists: b * g * C_max * rho * 4 */
-    int64_t device_bytes;    /* everything the index holds on the device */
+    int64_t device_bytes;    /* everything the index holds on the device (kept memory it was given may be a quarter more than it needs) */
 } ctkvr_index_info_t;
 
 int ctkvr_index_info(const ctkvr_index *idx, ctkvr_index_info_t *out);
@@ -281,7 +281,8 @@ int ctkvr_index_build_route(const ctkvr_index *idx, int32_t *by_candidates_host,
 /* ---- device memory kept between indexes (Algorithm 1 runs once per prompt) ---------------- */
 /* An index and the scratch of its build are one device allocation each.  Blocks that are no longer in use (the
  * scratch when a build returns, an index's memory when it is freed) are kept, at most 2 GiB per device, the oldest
- * given up first, and serve later builds and loads of about the same size, from any host thread and stream; they
+ * given up first, and serve later builds and loads of about the same size (a block is at most twice what scratch needs and
+ * five quarters of what an index needs), from any host thread and stream; they
  * are freed when an allocation of the library runs out of memory and by this call, which frees the current device's
  * idle blocks and the 8 MB of pinned host memory that copies of lists and centroids go through; an error if a build
  * is using scratch on that device.  Memory whose users could not be waited for (ctkvr_free while a stream is being captured)

@@ -98,8 +98,9 @@ int static_scratch(unsigned char **out)
 // Device memory kept between indexes.  An index and the scratch of its build are one allocation each; an index is built
 // per prompt and freed per request, and hipMalloc / hipFree of what a 32K prompt takes cost 2 ms in the best case and 70 ms
 // where the driver has to map and unmap 2 GB every time (7.6 to 76 ms a build, of which the kernels are 5.9).  Blocks that
-// nothing uses any more are kept per device, at most kPoolMax bytes of them (the oldest go first), and handed out again to
-// a request of at least half their size.  ctkvr_release_scratch() frees them; CTKVR_BUILD_SCRATCH_CACHE=0 switches the
+// nothing uses any more are kept per device, at most kPoolMax bytes of them (the oldest go first), and handed out again: to a
+// build for its scratch if it needs at least half of one, to an index, which has it as long as it lives, if that needs four fifths.
+// ctkvr_release_scratch() frees them; CTKVR_BUILD_SCRATCH_CACHE=0 switches the
 // keeping off.  A block enters the pool only after the work that used it has ended (a build synchronises its stream, an
 // index its device), so it is idle whichever stream or host thread takes it next.  Where that wait fails -- a device cannot
 // be waited for while one of its streams is being captured in global mode -- the block is set aside: nothing has it, and it is not
@@ -161,8 +162,9 @@ void pool_settle(int dev)
     g_aside[dev].clear();
 }
 
-// a block of at least `bytes` on the current device `dev`; out->bytes is its real size
-int pool_get(int dev, size_t bytes, PoolBlock *out)
+// a block of at least `bytes` on the current device `dev`, and of at most bytes / spare more if it was kept; out->bytes is its
+// real size
+int pool_get(int dev, size_t bytes, size_t spare, PoolBlock *out)
 {
     const size_t grain = bytes < ((size_t)4 << 20) ? (size_t)64 << 10 : (size_t)2 << 20;
     bytes = (std::max<size_t>(bytes, 1) + grain - 1) / grain * grain;
@@ -175,7 +177,7 @@ int pool_get(int dev, size_t bytes, PoolBlock *out)
         std::vector<PoolBlock> &v = g_pool[dev];
         size_t best = v.size();
         for (size_t i = 0; i < v.size(); ++i)
-            if (v[i].bytes >= bytes && v[i].bytes / 2 <= bytes && (best == v.size() || v[i].bytes < v[best].bytes)) best = i;
+            if (v[i].bytes >= bytes && v[i].bytes <= bytes + bytes / spare && (best == v.size() || v[i].bytes < v[best].bytes)) best = i;
         if (best < v.size()) {
             *out = v[best];
             v.erase(v.begin() + best);
@@ -220,7 +222,7 @@ struct BuildScratch {
     int get(int device, size_t bytes)
     {
         put();
-        int rc = pool_get(device, bytes, &b);
+        int rc = pool_get(device, bytes, 1, &b);
         if (rc != CTKVR_OK) return rc;
         dev = device;
         idle = false;
@@ -386,7 +388,6 @@ struct ctkvr_index {
     std::vector<int32_t> ctx_lens, n_cent;
     int dev = 0;
     PoolBlock mem{nullptr, 0};   // everything the index holds on the device
-    size_t device_bytes = 0;
     // index proper
     void *centroids = nullptr;
     float *inv_norm_c = nullptr;
@@ -682,13 +683,15 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, bool clear_tabl
         else if (!strcmp(e, "fused") && ix->fused_bpu) ix->decode_path = CTKVR_PATH_FUSED;
     }
     // one allocation for all of it
+    size_t edge = 256;
     auto lay_out = [&](unsigned char *base) {
-        // (the tables and the workspace on boundaries of 2 MB each, as an allocation of their own would be)
+        // (the tables and the workspace on boundaries of 2 MB, as an allocation of their own would be -- with 1 MB a 32K step took
+        // 38.9 in place of 38.7 us -- or less where the three of them would come to over a fifth of the rest)
         Carver cv{base};
         cv.take(&ix->centroids, (size_t)B * h * ix->c_max * 128 * es);
-        cv.align_to((size_t)2 << 20);
+        cv.align_to(edge);
         cv.take(&ix->inv_norm_c, (size_t)B * h * ix->c_max * 4);
-        cv.align_to((size_t)2 << 20);
+        cv.align_to(edge);
         cv.take(&ix->lists, U * ix->c_max * p->list_len * 4);
         cv.take(&ix->d_ctx_lens, (size_t)B * 4);
         cv.take(&ix->d_n_cent, (size_t)B * 4);
@@ -700,12 +703,13 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, bool clear_tabl
             cv.take(&ix->dsel, U * (size_t)p->list_len * 4);
             cv.take(&ix->dnsel, U * 4);
         }
-        cv.align_to((size_t)2 << 20);
+        cv.align_to(edge);
         cv.off += carve_step_ws(ix->ws, base ? base + cv.off : nullptr, ix);
         return cv.off;
     };
-    ix->device_bytes = lay_out(nullptr);
-    int rc = pool_get(ix->dev, ix->device_bytes, &ix->mem);
+    const size_t content = lay_out(nullptr);
+    while (edge < (size_t)2 << 20 && 3 * 5 * 2 * edge <= content) edge *= 2;
+    int rc = pool_get(ix->dev, lay_out(nullptr), 4, &ix->mem);
     if (rc != CTKVR_OK) {
         delete ix;
         return rc;
@@ -2147,7 +2151,7 @@ int ctkvr_index_info(const ctkvr_index *idx, ctkvr_index_info_t *out)
     out->top_k = idx->p.top_k;
     out->l_stride = idx->l_stride;
     out->index_bytes = (int64_t)idx->units * idx->c_max * idx->p.list_len * 4;
-    out->device_bytes = (int64_t)idx->device_bytes;
+    out->device_bytes = (int64_t)idx->mem.bytes;
     return CTKVR_OK;
 }
 

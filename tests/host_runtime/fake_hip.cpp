@@ -1,5 +1,5 @@
 // A stand-in for the HIP runtime, for tests of the library's host code without a GPU: two devices whose memory is host
-// memory, kernels that do nothing, and calls that fail when a test asks for it or when they mix objects of two devices.  Loaded with
+// memory, kernels that do nothing (but for the one that fills words), and calls that fail when a test asks for it or when they mix objects of two devices.  Loaded with
 // its symbols global before libctkvr.so, whose HIP calls then come here.  Fresh device memory reads as ones in every bit.
 #include <cstddef>
 #include <cstdint>
@@ -34,6 +34,7 @@ thread_local struct {
 int n_malloc = 0, n_free = 0, n_launch = 0, n_record = 0, n_pinned = 0, n_sync[2] = {}, attr_dev = -1, n_attr = 0;
 int refuse_device_sync = 0, refuse_stream_sync = 0;
 std::map<const void *, void *> symbols;
+const void *fill_words = nullptr;
 
 int ret(int e)
 {
@@ -150,9 +151,13 @@ int hipGetSymbolAddress(void **p, const void *sym)
     *p = at;
     return kOk;
 }
-int hipLaunchKernel(const void *, Dim3, Dim3, void **, size_t, void *)
+int hipLaunchKernel(const void *fn, Dim3, Dim3, void **args, size_t, void *)
 {
     n_launch++;
+    if (fn == fill_words) {
+        uint32_t *p = *(uint32_t **)args[0], v = *(uint32_t *)args[1];
+        for (size_t i = 0, n = *(size_t *)args[2]; i < n; ++i) p[i] = v;
+    }
     return kOk;
 }
 int hipStreamBeginCapture(void *, int) { return ret(kBadValue); }
@@ -175,7 +180,10 @@ int __hipPopCallConfiguration(Dim3 *g, Dim3 *b, size_t *lds, void **st)
     return kOk;
 }
 void **__hipRegisterFatBinary(const void *) { return (void **)calloc(1, sizeof(void *)); }
-void __hipRegisterFunction(void **, const void *, char *, const char *, unsigned, void *, void *, Dim3 *, Dim3 *, int *) {}
+void __hipRegisterFunction(void **, const void *fn, char *, const char *name, unsigned, void *, void *, Dim3 *, Dim3 *, int *)
+{
+    if (strstr(name, "fill_u32_kernel")) fill_words = fn;
+}
 void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
 void __hipUnregisterFatBinary(void **) {}
 }

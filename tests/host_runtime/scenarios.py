@@ -146,7 +146,30 @@ def path_of_other_device(x):
     assert x.fake.fake_attr_calls() > n and x.fake.fake_attr_device() == 1 and x.current() == 0
 
 
-SCENARIOS = {f.__name__: f for f in (refused_wait, refused_wait_released, refused_build, refused_copy, other_device, path_of_other_device)}
+def memory_held(x):
+    """ctkvr_index_info names all that an index holds; kept memory makes that at most a quarter more than the index needs, and
+    the boundaries between an index's parts at most a fifth."""
+    big = dict(s=32768, C=512, rho=1024, h=32, g=8, probe=32, top_k=1024)
+    own = {}
+    for name, over in (("big", {}), ("near", dict(C=460)), ("less", dict(C=300)), ("small", dict(s=4096, C=64, rho=256, h=8, g=2, probe=8, top_k=256))):
+        a, _, _ = x.load(**{**big, **over})
+        own[name] = x.info(a).device_bytes
+        assert own[name] == x.fake.fake_live_bytes(0)
+        x.lib.ctkvr_free(a)
+        assert x.lib.ctkvr_release_scratch() == OK
+    a, _, _ = x.load(**big)
+    x.lib.ctkvr_free(a)
+    n = x.fake.fake_mallocs()
+    a, _, _ = x.load(**{**big, **dict(C=460)})
+    assert x.fake.fake_mallocs() == n and x.info(a).device_bytes == own["big"] <= 1.25 * own["near"]
+    x.lib.ctkvr_free(a)
+    a, _, _ = x.load(**{**big, **dict(C=300)})
+    assert x.info(a).device_bytes == own["less"], "an index holds far more than it needs"
+    # the 4K index: centroids, their norms and lists (0.26 MiB), what a step writes (1.7 MiB)
+    assert own["small"] <= 5 << 19
+
+
+SCENARIOS = {f.__name__: f for f in (refused_wait, refused_wait_released, refused_build, refused_copy, other_device, path_of_other_device, memory_held)}
 
 if __name__ == "__main__":
     SCENARIOS[sys.argv[1]](Host(sys.argv[2]))
