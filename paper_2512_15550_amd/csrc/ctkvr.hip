@@ -1354,11 +1354,20 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     ca.h = p.n_q_heads;
     ca.c_max = ix->c_max;
     ca.by_xcd = by_xcd_all;
-    // Everything after the scoring as one launch (tail_kernel): for small batches, whose step is a chain of latencies
-    // (every block of a unit then walks all of the unit's recalled keys, work that is repeated 4 or 8 times), unless one
-    // of the forms it replaces is asked for.
+    // Everything after the scoring as one launch (tail_kernel): for small batches, whose step is a chain of latencies,
+    // and only up to a number of recalled keys: every block of a unit walks all of them, and beyond the 8192 it keeps, reads
+    // them three times (one CU takes about 20 GB/s).  The number of recalled keys L is known on the device only; l_stride bounds
+    // it, and neighbouring lists overlap: L is 0.2 to 0.28 of l_stride on the benchmark inputs.  Step with / without, G = 4, us:
+    //   L           8192        16384       32768        65536
+    //   4 units     40.8/48.6   50.7/50.5   70.5/56.8    110.1/72.1    (loads from other XCDs' caches: unit_block_of)
+    //   8 units     39.0/45.9   46.0/49.5   63.0/59.1    101.3/85.8
+    //   16 units    44.0/51.8   55.3/58.7   84.0/82.0    136.1/114.7
+    //   32 units    53.0/61.1   73.3/77.9   118.1/116.4  196.7/179.4
+    // (G = 1, 2 and 8 cross at the same L.)  The lines are twice the crossings: no loss while at most half the probed entries are
+    // distinct.  Not where one of the forms it replaces is asked for.
+    const int tail_most = by_xcd ? 65536 : 32768;
     const bool tail = ix->tail_lds && ix->keyclass < 0 &&
-                      (ix->tail < 0 ? (long long)ix->l_stride * U <= 2048ll * ix->num_cu : ix->tail != 0);
+                      (ix->tail < 0 ? (long long)ix->l_stride * U <= 2048ll * ix->num_cu && ix->l_stride <= tail_most : ix->tail != 0);
     ca.xs = w.xs;
     ca.n_xs = tail ? ix->attn_slices * G : 0;
     if (whole) ix->mark(0, st);

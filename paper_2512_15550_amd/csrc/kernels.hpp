@@ -2854,8 +2854,9 @@ template <int NT, int KPT> __global__ __launch_bounds__(NT, 4) void key_list_ker
 //      about 0.7 us against 3 us for a launch.  The wait is bounded (kTailSpins reads): a block that gives up takes the sums of
 //      ALL keys itself, the same integers, so that no result and no progress depends on the other blocks being resident;
 //   2. forms the ranking keys of ALL the unit's recalled keys (their scores and rows were requested before the exchange; up to
-//      16 per thread stay in registers), their histogram, the deciding bucket, the bitmap of the picks and their positions,
-//      all in shared memory -- the same work in every block instead of a hand-over;
+//      16 per thread stay in registers, later ones are read again, eight rounds requested together: one after the other a unit's
+//      65536 cost 11 us more), their histogram, the deciding bucket, the bitmap of the picks and their positions, all in shared
+//      memory -- the same work in every block instead of a hand-over;
 //   3. attends over the picks, for its 128 / SL head dimensions.
 // grid SL*batch*g; dynamic shared memory: tail_smem_words.  Same integers as the separate kernels.
 // ------------------------------------------------------------------------------
@@ -2905,6 +2906,7 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
     CTKVR_STAMP(60);
     // requested at once, before L is known (slots beyond L hold stale values that are never used)
     constexpr int PRE = 2;                        // rounds of this block's share of the denominators
+    constexpr int NF = G == 8 ? 4 : 8;            // rounds of later keys, which are not kept, requested together
     const int i0 = (wv * SL + slice) * 64 + ln;   // the share: every SL-th group of 64
     float zo[PRE][G], zr[KPT][G];
 #pragma unroll
@@ -2944,9 +2946,13 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
 #pragma unroll
         for (int q = 0; q < PRE; ++q)
             if (first - ln + q * step < L) add(first + q * step < L, zv[q]);   // wave-uniform
-        for (int i = first + PRE * step; i - ln < L; i += step) {
-            load_z<G>(zb, min(i, L - 1), zv[0]);
-            add(i < L, zv[0]);
+        for (int i = first + PRE * step; i - ln < L; i += NF * step) {
+            float zf[NF][G];
+#pragma unroll
+            for (int u = 0; u < NF; ++u) load_z<G>(zb, min(i + u * step, L - 1), zf[u]);
+#pragma unroll
+            for (int u = 0; u < NF; ++u)
+                if (i - ln + u * step < L) add(i + u * step < L, zf[u]);
         }
         // hi <= 2^16 per term; at most 2^9 terms per lane where the block takes its share only (contexts up to 2^20), so that
         // a wave's sum fits 32 bits; the sum of all terms by one block is put together from halves
@@ -3020,11 +3026,17 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
     }
     // f(group of 64 ids, key) for the groups of this wave beyond the first kTailKeys ids, whose keys are formed again
     auto for_far = [&](auto f) __attribute__((always_inline)) {
-        for (int gq = KPT * NW + wv; gq * 64 < L; gq += NW) {
-            float zv[G];
-            load_z<G>(zb, min(gq * 64 + ln, L - 1), zv);
-            const float kk = key_of(zv);
-            f(gq, gq * 64 + ln < L ? kk : -__builtin_huge_valf());
+        for (int g0 = KPT * NW + wv; g0 * 64 < L; g0 += NF * NW) {
+            float zv[NF][G];
+#pragma unroll
+            for (int u = 0; u < NF; ++u) load_z<G>(zb, min((g0 + u * NW) * 64 + ln, L - 1), zv[u]);
+#pragma unroll
+            for (int u = 0; u < NF; ++u) {
+                const int gq = g0 + u * NW;
+                if (gq * 64 >= L) break;
+                const float kk = key_of(zv[u]);
+                f(gq, gq * 64 + ln < L ? kk : -__builtin_huge_valf());
+            }
         }
     };
     CTKVR_STAMP(65);

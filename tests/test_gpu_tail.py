@@ -16,6 +16,7 @@ CASES = {  # dtype, h, g, ctx_lens, C, n_probe, rho, top_k, lattice
     "ordinary": ("bf16", 8, 2, (3000,), 48, 6, 200, 160, False),
     "one_unit_f32": ("f32", 4, 1, (900,), 24, 4, 64, 48, False),
     "beyond_registers": ("bf16", 8, 2, (20000, 9000), 64, 24, 2400, 1000, False),
+    "rounds_of_later_keys": ("bf16", 8, 2, (12289, 16447), 32, 32, 8000, 900, False),   # whole and broken rounds of eight
     "just_past_registers": ("bf16", 4, 1, (8257,), 32, 32, 6000, 700, False),
     "every_key_kept": ("bf16", 8, 2, (700,), 24, 2, 60, 300, False),
     "equal_keys": ("bf16", 8, 2, (4000,), 32, 8, 600, 500, True),
@@ -56,7 +57,7 @@ def test_one_launch_equals_the_separate_ones(name, monkeypatch):
     else:
         bt = gen_batch(wl)
     ref = _steps(wl, bt, {"CTKVR_TAIL": "0"}, monkeypatch)
-    if name == "beyond_registers":
+    if name in ("beyond_registers", "rounds_of_later_keys"):
         assert ref[0][3].max() > 8192
     for env in ({"CTKVR_TAIL": "1"}, {"CTKVR_TAIL": "1", "CTKVR_TAIL_SPINS": "0"}):
         for st, (a, b) in enumerate(zip(_steps(wl, bt, env, monkeypatch), ref)):
