@@ -399,6 +399,7 @@ struct ctkvr_index {
     uint32_t *d_dcu_count = nullptr;   // [2]: updates so far (device side, so that captured graphs replay correctly), blocks of the running update that are done
     int32_t *dsel = nullptr, *dnsel = nullptr;   // top-rho ids of the second ranking (only when rho != rho')
     bool have_step = false;
+    bool have_hist = false;   // the last step on the index's own workspace left the histogram of its ranking keys
     size_t recall_lds = 0, select_lds = 0, attn_lds = 0, build_select_lds = 0;
     size_t fused_lds = 0;   // non-zero: selection and attention run as one launch (select_attn_kernel)
     size_t dcu_lds = 0;     // non-zero: the update's ranking with a budget of its own runs as one launch (dcu_select_kernel)
@@ -741,7 +742,11 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, bool clear_tabl
         if (4 * (int)U <= ix->num_cu && fw <= 150 * 1024) ix->fused_lds = fw;
         const size_t tw = tail_smem_words(ix->sel_bits, p->top_k, ix->G) * 4;
         const size_t dw = ((size_t)kSelLds + 2 * kListCap + ix->sel_bits) * 4;
-        if (ix->sel_bits && p->list_len != p->top_k) ix->dcu_lds = dw;
+        // One block per unit for the update's second ranking up to a number of recalled keys, of which l_stride is the bound
+        // known here.  Update in one launch / by the chip-wide passes, G = 4, us, at 8, 16, 29 and 53 thousand recalled keys:
+        //   4 units 8.6/20  17.4/22  30/22  54/24;  8 units 8.1/22  13.4/22  23/22  46/24;  64 units 8.6/21  14.5/21  30/22  52/25
+        // They cross at about 24000; the line is twice that, as for tail_kernel.
+        if (ix->sel_bits && p->list_len != p->top_k && ix->l_stride <= kDcuStride) ix->dcu_lds = dw;
         if (4 * (int)U <= ix->num_cu && ix->sel_bits && tw <= 136 * 1024) ix->tail_lds = tw;
     }
     if (ix->recall_lds > 150 * 1024 || ix->select_lds > 150 * 1024 || ix->attn_lds > 128 * 1024) {
@@ -1340,6 +1345,7 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         }
         HIP_TRY(hipGetLastError());
         ix->have_step = &w_all == &ix->ws;
+        ix->have_hist = false;
         return CTKVR_OK;
     }
     CosArgs ca{};
@@ -1458,6 +1464,9 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     aa.out_lse = out_lse;
     aa.win = window ? w.win : nullptr;
     aa.m_key = w.m_key;
+    // Small batches: the key histogram and the classification pass as one launch, every block taking the unit's
+    // whole histogram itself (keyclass_kernel); otherwise two chip-wide launches.
+    const bool keyclass = ix->sel_bits && (ix->keyclass < 0 ? (long long)ix->l_stride * U <= 2048ll * ix->num_cu : ix->keyclass != 0);
     auto finish = [&]() -> int {
         if (whole) ix->mark(8, st);
         if (whole && ix->prof_step < ix->prof_max) {   // a null kernel between two events: what the bracketing itself costs
@@ -1467,6 +1476,7 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         }
         HIP_TRY(hipGetLastError());
         ix->have_step = &w_all == &ix->ws;   // the update reads the index's own workspace
+        ix->have_hist = ix->have_step && !tail && !keyclass;
         return CTKVR_OK;
     };
     if (tail) {
@@ -1515,9 +1525,6 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     denom_kernel<G><<<dim3(std::max(1, std::min(chunks, (4 * ix->num_cu + U - 1) / U)), U), 256, 0, st>>>(da);
     if (whole) ix->mark(4, st);
 
-    // Small batches: the key histogram and the classification pass as one launch, every block taking the unit's
-    // whole histogram itself (keyclass_kernel); otherwise two chip-wide launches.
-    const bool keyclass = ix->sel_bits && (ix->keyclass < 0 ? (long long)ix->l_stride * U <= 2048ll * ix->num_cu : ix->keyclass != 0);
     if (keyclass) {
         KeyClassArgs kc{};
         kc.u = u;
@@ -1759,7 +1766,7 @@ template <typename T, int G> int update_launch(ctkvr_index *ix, const void *q, h
         HIP_TRY(hipGetLastError());
         ix->have_step = false;
         return CTKVR_OK;
-    } else {                       // ... by a block that keeps no bitmap of the recalled keys (they do not fit)
+    } else {                       // ... by chip-wide passes and a selection, as in the step
         Units u = decode_units(ix);
         SelectArgs se{};
         se.u = u;
@@ -1776,6 +1783,41 @@ template <typename T, int G> int update_launch(ctkvr_index *ix, const void *q, h
         se.sel = ix->dsel;
         se.nsel = ix->dnsel;
         se.ids_only = 1;
+        if (ix->sel_bits) {
+            if (!ix->have_hist) {   // taken here; this launch clears the list cursors too
+                fill_u32_kernel<<<dim3((unsigned)(((size_t)U * kBuckets + 255) / 256)), 256, 0, st>>>(ix->ws.ghist, 0u, (size_t)U * kBuckets);
+                KeyArgs ka{};
+                ka.u = u;
+                ka.ctx_lens = ix->d_ctx_lens;
+                ka.ncand = ix->ws.ncand;
+                ka.l_stride = ix->l_stride;
+                ka.z = nullptr;   // the keys are there
+                ka.kbuf = ix->ws.kbuf;
+                ka.ghist = ix->ws.ghist;
+                ka.gcur = ix->ws.gcur;
+                keyhist_kernel<G><<<dim3(std::max(1, std::min((ix->l_stride + 4095) / 4096, (2 * ix->num_cu + U - 1) / U)), U), 1024, 0, st>>>(ka);
+            } else {
+                fill_u32_kernel<<<dim3((U + 255) / 256), 256, 0, st>>>(ix->ws.gcur, 0u, (size_t)U);
+            }
+            ClassifyArgs ca{};
+            ca.u = u;
+            ca.ctx_lens = ix->d_ctx_lens;
+            ca.ncand = ix->ws.ncand;
+            ca.l_stride = ix->l_stride;
+            ca.top_k = p.list_len;
+            ca.kbuf = ix->ws.kbuf;
+            ca.ghist = ix->ws.ghist;
+            ca.bits_stride = 2 * ((ix->l_stride + 63) / 64);
+            ca.gbm = ix->ws.gbm;
+            ca.glist = ix->ws.glist;
+            ca.gcur = ix->ws.gcur;
+            ca.ginfo = ix->ws.ginfo;
+            classify_kernel<<<dim3(std::max(1, std::min((ix->l_stride + 1023) / 1024, (4 * ix->num_cu + U - 1) / U)), U), 256, 0, st>>>(ca);
+            se.gbm = ix->ws.gbm;
+            se.glist = ix->ws.glist;
+            se.ginfo = ix->ws.ginfo;
+            se.bits_stride = ca.bits_stride;
+        }
         rerank_select_kernel<G><<<dim3(U), 1024, ix->select_lds, st>>>(se);
         da.src = ix->dsel;
         da.nsrc = ix->dnsel;

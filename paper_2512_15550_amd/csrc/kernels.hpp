@@ -3177,9 +3177,11 @@ template <typename T> __global__ __launch_bounds__(256) void dcu_write_kernel(Dc
     });
 }
 
-// Another budget: the step's ranking keys selected once more and written in the same launch (six launches -- histogram,
-// classification, selection and the fills they need -- took 21 us of a 65 us step with update; this takes 7).  One
-// block per unit.  grid batch*g, kTailThreads; dynamic shared memory: kSelLds + 2 kListCap + bits_words words
+// Another budget: the step's ranking keys selected once more and written in the same launch (histogram, classification,
+// selection, write and the fills they need took 21 us of a 65 us step with update; this takes 8 up to the 8192 keys it keeps).  One
+// block per unit, which reads later keys again, twice, at the 20 GB/s of its CU: the host takes it up to kDcuStride.  grid batch*g, kTailThreads; dynamic shared memory: kSelLds + 2 kListCap + bits_words words
+constexpr int kDcuStride = 49152;
+
 struct DcuSelectArgs {
     DcuArgs d;
     const int32_t *ncand, *cand;   // [units], [units][l_stride]
@@ -3220,10 +3222,17 @@ template <typename T> __global__ __launch_bounds__(kTailThreads) void dcu_select
         select_keys<NT, KPT>(
             kreg, L, L, a.d.rho,
             [&](auto f) __attribute__((always_inline)) {
-                for (int gq = KPT * NW + wv; gq * 64 < L; gq += NW) {
-                    const int i = gq * 64 + ln;
-                    const float x = fmaxf(ordered_value(kb[min(i, L - 1)]), -3.0e38f);
-                    f(gq, i < L ? x : -__builtin_huge_valf());
+                constexpr int NF = 8;   // rounds requested together
+                for (int g0 = KPT * NW + wv; g0 * 64 < L; g0 += NF * NW) {
+                    uint32_t x[NF];
+#pragma unroll
+                    for (int u = 0; u < NF; ++u) x[u] = kb[min((g0 + u * NW) * 64 + ln, L - 1)];
+#pragma unroll
+                    for (int u = 0; u < NF; ++u) {
+                        const int gq = g0 + u * NW;
+                        if (gq * 64 >= L) break;
+                        f(gq, gq * 64 + ln < L ? fmaxf(ordered_value(x[u]), -3.0e38f) : -__builtin_huge_valf());
+                    }
                 }
             },
             [&](int q, int, uint32_t pos) __attribute__((always_inline)) { dst[pos] = id[q]; },

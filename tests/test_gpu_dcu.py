@@ -92,3 +92,61 @@ def test_update_needs_a_decode_step_first(ck):
         ck.ctkvr_centroid_update(idx, q)     # one update per step
     torch.cuda.synchronize()
     ck.ctkvr_free(idx)
+
+
+# recalled keys (probes x list length, lists that do not overlap), the update's budget being the list length: what one block keeps
+# in registers and beyond, whole and broken rounds of later keys, both sides of the line to the chip-wide passes (l_stride 49152)
+SECOND = [(8, 1024, 500), (3, 2731, 900), (12, 1024, 300), (11, 1119, 300), (13, 1567, 2000), (12, 4096, 800), (12, 4097, 800),
+          (13, 5000, 1000), (31, 1900, 2500)]
+
+
+@pytest.mark.parametrize("step", ["tail", "keyclass", "separate"])   # the last leaves its keys' histogram to the update
+@pytest.mark.parametrize("g,n_probe,rho,top_k,equal", [(2, *c, False) for c in SECOND] + [(8, 12, 1024, 300, False), (8, 13, 4000, 700, False),
+                         (2, 12, 1024, 300, True), (2, 13, 5000, 1000, True)])
+def test_second_ranking_is_the_selection_of_a_step_with_that_budget(ck, g, n_probe, rho, top_k, equal, step, monkeypatch):
+    """The slot's list after an update with rho != rho' is what a step of budget rho selects, id for id."""
+    import torch
+    monkeypatch.setenv("CTKVR_TAIL", "1" if step == "tail" else "0")
+    if step == "separate":
+        monkeypatch.setenv("CTKVR_KEYCLASS", "0")
+    s, h, C = 65537, 2 * g, 40
+    rng = np.random.Generator(np.random.Philox(950 + n_probe + rho))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rho)
+    n_pages = (s + 15) // 16
+
+    def rows(*shape):
+        x = torch.randn(shape, generator=gen, device="cuda")
+        return (x.round() if equal else x).to(torch.bfloat16)
+
+    k, v = rows(n_pages, g, 16, 128), rows(n_pages, g, 16, 128)
+    table = torch.arange(n_pages, dtype=torch.int32, device="cuda").view(1, -1)
+    q = rows(1, h, 128)
+    if equal:
+        q = torch.where(torch.arange(128, device="cuda") < 12, q, torch.zeros_like(q))   # scores on a coarse lattice
+    cen = rows(1, h, C, 128).view(torch.int16).cpu().numpy().view(np.uint16)
+    lists = np.empty((1, g, C, rho), np.int32)
+    for kv in range(g):   # rows of a permutation, so that any n_probe of its s // rho rows are disjoint
+        part = np.sort(rng.permutation(s)[:(s // rho) * rho].reshape(-1, rho), axis=1)
+        lists[0, kv] = part[np.arange(C) % part.shape[0]]
+    got = {}
+    for budget in (top_k, rho):
+        p = ck.Params(batch=1, n_q_heads=h, n_kv_heads=g, n_centroids=C, list_len=rho, n_probe=n_probe, top_k=budget)
+        idx = ck.ctkvr_index_load(p, [s], cen, lists)
+        out = torch.empty((1, h, 128), device="cuda")
+        sel = torch.empty((1, g, budget), dtype=torch.int32, device="cuda")
+        nc = torch.empty((1, g), dtype=torch.int32, device="cuda")
+        ck.ctkvr_decode_step(idx, q, k, v, table, out, out_sel=sel, out_ncand=nc)
+        if budget == top_k:
+            ck.ctkvr_centroid_update(idx, q)
+            got["list"] = ck.ctkvr_index_lists(idx)[0, :, 0]
+            assert np.array_equal(ck.ctkvr_index_lists(idx)[0, :, 1:], lists[0, :, 1:])
+        else:
+            got["sel"] = sel.cpu().numpy()[0]
+        got["L"] = nc.cpu().numpy()[0]
+        ck.ctkvr_free(idx)
+    print(f"[dcu second] L {got['L'].min()}..{got['L'].max()} of {min(s, n_probe * rho)}", flush=True)
+    n = np.minimum(got["L"], rho)
+    for kv in range(g):
+        assert np.array_equal(got["list"][kv, :n[kv]], got["sel"][kv, :n[kv]])
+        assert (got["list"][kv, n[kv]:] == got["list"][kv, n[kv] - 1]).all()
