@@ -46,13 +46,13 @@ def build_library(verbose: bool = False) -> str:
     return LIB
 
 
-PROBES = ["sync_probe", "latency_probe", "gather_probe", "xcd_probe"]
+PROBES = ["sync_probe", "latency_probe", "gather_probe", "xcd_probe", "mfma_chain_probe"]
 PROBE_DIR = os.path.join(HERE, "probes")
 
 
 def build_probes(verbose: bool = False):
-    """The stand-alone measurement programs under csrc/probes (launch floor, in-launch barriers, visibility,
-    latencies): executables in probes/, not used by the library."""
+    """The stand-alone programs under csrc/probes (launch floor, in-launch barriers, visibility,
+    latencies; a check of the fp32 matrix instruction): executables in probes/, not used by the library."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(PROBE_DIR, exist_ok=True)
     out = []

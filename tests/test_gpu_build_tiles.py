@@ -1,11 +1,13 @@
 """The matrix-core build kernels at the edges of their tiles: key steps of 64 that end after 1, 31, 32, 33 or 63 keys,
 centroid tiles of one row more or less than they hold, every group size; in k-means the same for points and centres, and
-centres of more members than one block sums."""
+centres of more members than one block sums; lists of long contexts; and the fp32 matrix instruction itself."""
+import os
+
 import numpy as np
 import pytest
 
 import oracle
-from ctkvr_inputs import Batch, bf16_bits_to_f32, gen_lattice_sequence, paginate, small_workload
+from ctkvr_inputs import Batch, bf16_bits_to_f32, gen_batch, gen_lattice_sequence, paginate, small_workload
 from ctkvr_inputs.kmeans_init import kmeanspp_for_sequence
 from tests import harness as H
 from tests.test_gpu_kmeans import _lattice_batch
@@ -62,3 +64,40 @@ def test_kmeans_first_update_at_tile_edges(h, g, s, C, crowd):
         cen = bf16_bits_to_f32(ck.ctkvr_index_centroids(idx))
         ck.ctkvr_free(idx)
         assert np.array_equal(cen[0], Qc)
+
+
+@pytest.mark.parametrize("s,lattice", [(16385, False), (32768, True), (32769, False), (40001, False), (65600, True)])
+def test_every_key_lists_of_long_contexts(s, lattice, monkeypatch):
+    """One block per list over all its keys, beyond 16384 positions (64 keys a thread in registers) and beyond 32768 (1024
+    threads, later keys read again): the lists of the candidate route, which selects otherwise, and the oracle's within the band;
+    on the lattice many keys are equal."""
+    h, g, C, rho = 8, 2, 33, 700
+    wl = small_workload("long_lists", "bf16", h, g, (s,), (60 + s,), C, 0, 4, rho, 60, 1)
+    if lattice:
+        sq = gen_lattice_sequence(60 + s, s, h, g, 128, C, 1, denom=2, span=1)
+        bt = Batch(wl=wl, seqs=[sq], paged=paginate([sq], wl.page_size, 5))
+    else:
+        bt = gen_batch(wl)
+        sq = bt.seqs[0]
+    db = H.device_batch(bt)
+    got = {}
+    for cand in ("0", "1"):
+        monkeypatch.setenv("CTKVR_BUILD_CANDIDATES", cand)
+        idx = ck.ctkvr_build_index(H.params_of(wl, build_algo=ck.BUILD_MFMA), db.q_prefill, db.cu_seqlens, True, db.k_pages,
+                                   db.block_table, db.ctx_lens)
+        by_cand, redone = ck.ctkvr_index_build_route(idx)
+        assert by_cand == (cand == "1") and (lattice or not redone)
+        got[cand] = ck.ctkvr_index_lists(idx)[0]
+        ck.ctkvr_free(idx)
+    assert np.array_equal(got["0"], got["1"])
+    pairs = np.array([[kv, j] for kv in range(g) for j in (0, 1, 16, 31, 32)], np.int32)
+    _check_lists_within_band(got["0"], sq, oracle.centroids_last_c(sq.q_tail, C), wl, pairs=pairs, exact_dots=lattice)
+
+
+def test_fp32_matrix_instruction_is_a_chain_of_fused_multiply_adds():
+    """What the exact list build's bit-reproducibility rests on (the program compares 2 M results with fmaf)."""
+    import subprocess
+    from paper_2512_15550_amd.build import PROBE_DIR
+    r = subprocess.run([os.path.join(PROBE_DIR, "mfma_chain_probe")], capture_output=True, text=True, timeout=60)
+    print(r.stdout, flush=True)
+    assert r.returncode == 0 and r.stdout.count(": 0 of 524288") == 4, r.stdout + r.stderr
