@@ -255,8 +255,9 @@ int ctkvr_profile_collect(ctkvr_index *idx, float *ms_host, int32_t capacity_ste
  *                                  (default: by rank for small batches)
  *   CTKVR_KEYCLASS           = 0|1 ranking-key histogram and classification as two launches / one
  *                                  (default: one for small batches)
- *   CTKVR_TAIL               = 0|1 what follows the scoring as separate launches / as one (default: one for small batches,
- *                                  unless CTKVR_KEYCLASS is set)
+ *   CTKVR_TAIL               = 0|1 what follows the scoring as separate launches / as one (default: one for small batches
+ *                                  of up to 32768 candidate slots per unit, 65536 where a unit has an XCD of its own, unless
+ *                                  CTKVR_KEYCLASS is set)
  *   CTKVR_TAIL_SPINS         = n   how often a block of that launch looks for its siblings' sums before it takes all of them
  *                                  itself (0..256, default 256)
  *   CTKVR_FUSED_THREADS      = 256|1024  block size of the single-launch step

@@ -342,7 +342,7 @@ def ctkvr_index_build_route(idx: Index):
 
 
 def ctkvr_release_scratch() -> None:
-    """Frees the device scratch the matrix-core list build keeps between builds (current device)."""
+    """Frees the current device's memory kept between indexes and builds, and the pinned memory of list and centroid copies."""
     _check(load_library().ctkvr_release_scratch())
 
 

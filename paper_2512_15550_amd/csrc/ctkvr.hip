@@ -874,7 +874,7 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
         if (const char *e = getenv("CTKVR_BUILD_CANDIDATES")) by_cand = atoi(e) != 0;
     }
     ix->build_by_cand = by_cand;
-    // one block per list behind the keys, where its bitmap of the context fits the shared memory (to about 2^18 tokens)
+    // one block per list behind the keys, where its bitmap of the context fits the shared memory (to 515072 tokens)
     const bool by_list = mfma && exact_list_lds(ix) <= 150 * 1024;
     if (by_cand) chunk = std::min(chunk, 4 * ix->c_max);   // half the scratch, as fast
     const bool redo_always = by_cand && getenv("CTKVR_BUILD_CANDIDATES_REDO") != nullptr;   // tests: take the redo path
@@ -1111,7 +1111,7 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
 constexpr size_t kExactChunkBytes = (size_t)512 << 20;
 
 // The same lists with the scores on the fp32 matrix cores (exact_score_kernel) and one block per list behind them
-// (exact_list_kernel); needs shared memory for a bitmap of the context (to about 2^18 tokens).
+// (exact_list_kernel); needs shared memory for a bitmap of the context (to 515072 tokens).
 template <typename T, int G> int build_lists_exact_mfma(ctkvr_index *ix, const void *k_pages, const int32_t *block_table, int max_pages, hipStream_t st)
 {
     constexpr int CT = 32 * (8 / G);

@@ -2521,8 +2521,8 @@ __device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int 
 // ------------------------------------------------------------------------------
 // Exact list build (Algorithm 1 lines 2-4 in the fixed arithmetic of the decode path) on the fp32 matrix cores.  A
 // v_mfma_f32_32x32x2f32 adds its two products to the accumulator one after the other, each as a fused multiply-add with
-// one rounding (compared with fmaf chains on 2 M results of random, bf16-valued, wide-range and subnormal inputs: no bit
-// differs), so the fixed dot product -- sixteen chains of eight fused multiply-adds, combined as a balanced tree -- is
+// one rounding (probes/mfma_chain_probe.hip compares 2 M results of normal, bf16, wide-range and subnormal values with fmaf: no
+// bit differs), so the fixed dot product -- sixteen chains of eight fused multiply-adds, combined as a balanced tree -- is
 // sixteen groups of four such instructions, each group from zero, and fifteen vector adds.
 // exact_score_kernel: z[unit][head][key] = (c . k) scale for a chunk of tiles of CT = 32 (8 / G) centroids of one
 // (sequence, KV head), all its G heads and all s keys, and each unit's and head's maximum.  Eight waves, each with one item of 32
@@ -2530,7 +2530,8 @@ __device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int 
 // k's sit in the two halves of a wave); the keys go by 32 at a time through shared memory as fp32, even and odd elements of
 // each group of eight apart so that a fragment is one 16-byte read.  Bound by the matrix pipe (64 instructions of 64 clocks
 // per 32 x 32 scores against about 1.2 k clocks of vector work; fp32 peak 157 TFLOP/s): at 32K tokens, C = 512,
-// 32/8 heads 1.1 ms where the scalar form (score_kernel) took 4.7.
+// 32/8 heads 1.45 ms (four chunks of 361 us, 95 TFLOP/s) where the scalar form (score_kernel) took 4.7; at 128K 104 TFLOP/s with the
+// matrix pipe busy for 65 % of the cycles, vector instructions issuing for another 20 %, waves waiting for 24 %.
 // grid (t_splits, tiles of the chunk), 512 threads
 // ------------------------------------------------------------------------------
 struct ExactScoreArgs {
@@ -2680,10 +2681,10 @@ template <typename T, int G> __global__ __launch_bounds__(512) void exact_score_
 }
 
 // exact_list_kernel: the list of one unit of the chunk per block: denominators of its G heads over all s scores, ranking
-// keys max_h ((z - m_h) - log S_h), the rho largest (select_keys; keys of up to KPT 512 positions in registers, the
+// keys max_h ((z - m_h) - log S_h), the rho largest (select_keys; keys of up to KPT NT positions in registers, the
 // scores of positions beyond that are read again).  The scores are read twice, the second time mostly from the memory-side
-// cache; nothing is written but the list.  grid (chunk units), 512 threads; dynamic shared memory: kSelLds + 2 kListCap +
-// 4 ceil(s_max / 64) words
+// cache; nothing is written but the list.  grid (chunk units), NT threads (512 for up to 4096 positions, else 1024); dynamic shared
+// memory: kSelLds + 2 kListCap + 4 ceil(s_max / 64) words
 struct ExactListArgs {
     int g, c_max, tile0, tiles_per_bk, ct;   // ct: centroids per tile
     const int32_t *n_cent, *ctx_lens;
