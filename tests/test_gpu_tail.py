@@ -64,3 +64,37 @@ def test_one_launch_equals_the_separate_ones(name, monkeypatch):
             assert np.array_equal(a[2], b[2]) and np.array_equal(a[3], b[3]), f"{env} step {st}: selection differs"
             assert np.allclose(a[0], b[0], rtol=2e-5, atol=2e-5 * np.abs(b[0]).max()), f"{env} step {st}"
             assert np.allclose(a[1], b[1], rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("g,s,one", [(2, 32768, True), (2, 32769, False), (8, 65536, True), (8, 65537, False)])
+def test_the_choice_on_both_sides_of_its_lines(g, s, one, monkeypatch):
+    """One launch up to l_stride 32768, or 65536 with a multiple of eight units; the same integers either way, and the bits of the
+    attention, which each form sums in its own order, tell which form ran."""
+    h, C, n_probe, rho, top_k = 4 * g, 40, 24, 3000, 700
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(s)
+    n_pages = (s + 15) // 16
+    k = torch.randn((n_pages, g, 16, 128), generator=gen, device="cuda").to(torch.bfloat16)
+    v = torch.randn((n_pages, g, 16, 128), generator=gen, device="cuda").to(torch.bfloat16)
+    q = torch.randn((1, h, 128), generator=gen, device="cuda").to(torch.bfloat16)
+    table = torch.randperm(n_pages, generator=gen, device="cuda").to(torch.int32).view(1, -1)
+    cen = torch.randn((1, h, C, 128), generator=gen, device="cuda").to(torch.bfloat16).view(torch.int16).cpu().numpy().view(np.uint16)
+    rng = np.random.Generator(np.random.Philox(s))
+    lists = np.stack([np.sort(rng.choice(s, rho, replace=False)) for _ in range(g * C)]).astype(np.int32).reshape(1, g, C, rho)
+    p = ck.Params(batch=1, n_q_heads=h, n_kv_heads=g, n_centroids=C, list_len=rho, n_probe=n_probe, top_k=top_k)
+    got = {}
+    for tail in (None, "0", "1"):
+        monkeypatch.delenv("CTKVR_TAIL", raising=False)
+        if tail:
+            monkeypatch.setenv("CTKVR_TAIL", tail)
+        idx = ck.ctkvr_index_load(p, [s], cen, lists)
+        assert ck.ctkvr_index_info(idx)["l_stride"] == s
+        out = torch.full((1, h, 128), float("nan"), device="cuda")
+        sel = torch.full((1, g, top_k), -5, dtype=torch.int32, device="cuda")
+        ck.ctkvr_decode_step(idx, q, k, v, table, out, out_sel=sel)
+        got[tail] = (out.cpu().numpy(), sel.cpu().numpy())
+        ck.ctkvr_free(idx)
+    assert np.array_equal(got["0"][1], got["1"][1]) and np.array_equal(got[None][1], got["1"][1])
+    assert np.allclose(got["0"][0], got["1"][0], rtol=2e-5, atol=2e-5 * np.abs(got["1"][0]).max())
+    assert not np.array_equal(got["0"][0], got["1"][0])
+    assert np.array_equal(got[None][0], got["1" if one else "0"][0])
