@@ -173,15 +173,18 @@ int pool_get(int dev, size_t bytes, size_t spare, PoolBlock *out)
     std::unique_lock<std::mutex> lock(g_pool_mu, std::defer_lock);
     if (pooled) {
         lock.lock();
-        pool_settle(dev);
         std::vector<PoolBlock> &v = g_pool[dev];
-        size_t best = v.size();
-        for (size_t i = 0; i < v.size(); ++i)
-            if (v[i].bytes >= bytes && v[i].bytes <= bytes + bytes / spare && (best == v.size() || v[i].bytes < v[best].bytes)) best = i;
-        if (best < v.size()) {
-            *out = v[best];
-            v.erase(v.begin() + best);
-            return CTKVR_OK;
+        for (int turn = 0; turn < 2; ++turn) {
+            size_t best = v.size();
+            for (size_t i = 0; i < v.size(); ++i)
+                if (v[i].bytes >= bytes && v[i].bytes <= bytes + bytes / spare && (best == v.size() || v[i].bytes < v[best].bytes)) best = i;
+            if (best < v.size()) {
+                *out = v[best];
+                v.erase(v.begin() + best);
+                return CTKVR_OK;
+            }
+            if (turn || g_aside[dev].empty()) break;
+            pool_settle(dev);   // only where nothing idle serves: a wait for the device can disturb a capture under way
         }
     }
     hipError_t e = hipMalloc(&out->base, bytes);
