@@ -402,7 +402,6 @@ struct ctkvr_index {
     uint32_t *d_dcu_count = nullptr;   // [2]: updates so far (device side, so that captured graphs replay correctly), blocks of the running update that are done
     int32_t *dsel = nullptr, *dnsel = nullptr;   // top-rho ids of the second ranking (only when rho != rho')
     bool have_step = false;
-    bool have_hist = false;   // the last step on the index's own workspace left the histogram of its ranking keys
     size_t recall_lds = 0, select_lds = 0, attn_lds = 0, build_select_lds = 0;
     size_t fused_lds = 0;   // non-zero: selection and attention run as one launch (select_attn_kernel)
     size_t dcu_lds = 0;     // non-zero: the update's ranking with a budget of its own runs as one launch (dcu_select_kernel)
@@ -746,9 +745,9 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, bool clear_tabl
         const size_t tw = tail_smem_words(ix->sel_bits, p->top_k, ix->G) * 4;
         const size_t dw = ((size_t)kSelLds + 2 * kListCap + ix->sel_bits) * 4;
         // One block per unit for the update's second ranking up to a number of recalled keys, of which l_stride is the bound
-        // known here.  Update in one launch / by the chip-wide passes, G = 4, us, at 8, 16, 29 and 53 thousand recalled keys:
-        //   4 units 8.6/20  17.4/22  30/22  54/24;  8 units 8.1/22  13.4/22  23/22  46/24;  64 units 8.6/21  14.5/21  30/22  52/25
-        // They cross at about 24000; the line is twice that, as for tail_kernel.
+        // known here.  Update in one launch / by the chip-wide passes, G = 4, us, at 16, 29 and 53 thousand recalled keys:
+        //   4 units 17.4/20.3  30/20.3  54/21.2;   8 units 13.4/18.7  23/19.7  46/21.3;   64 units 14.5/26.1  30/27.8  52/30.1
+        // They cross between 19000 and 29000; the line is twice that, as for tail_kernel.
         if (ix->sel_bits && p->list_len != p->top_k && ix->l_stride <= kDcuStride) ix->dcu_lds = dw;
         if (4 * (int)U <= ix->num_cu && ix->sel_bits && tw <= 136 * 1024) ix->tail_lds = tw;
     }
@@ -1348,7 +1347,6 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         }
         HIP_TRY(hipGetLastError());
         ix->have_step = &w_all == &ix->ws;
-        ix->have_hist = false;
         return CTKVR_OK;
     }
     CosArgs ca{};
@@ -1467,9 +1465,6 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     aa.out_lse = out_lse;
     aa.win = window ? w.win : nullptr;
     aa.m_key = w.m_key;
-    // Small batches: the key histogram and the classification pass as one launch, every block taking the unit's
-    // whole histogram itself (keyclass_kernel); otherwise two chip-wide launches.
-    const bool keyclass = ix->sel_bits && (ix->keyclass < 0 ? (long long)ix->l_stride * U <= 2048ll * ix->num_cu : ix->keyclass != 0);
     auto finish = [&]() -> int {
         if (whole) ix->mark(8, st);
         if (whole && ix->prof_step < ix->prof_max) {   // a null kernel between two events: what the bracketing itself costs
@@ -1479,7 +1474,6 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         }
         HIP_TRY(hipGetLastError());
         ix->have_step = &w_all == &ix->ws;   // the update reads the index's own workspace
-        ix->have_hist = ix->have_step && !tail && !keyclass;
         return CTKVR_OK;
     };
     if (tail) {
@@ -1528,6 +1522,9 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     denom_kernel<G><<<dim3(std::max(1, std::min(chunks, (4 * ix->num_cu + U - 1) / U)), U), 256, 0, st>>>(da);
     if (whole) ix->mark(4, st);
 
+    // Small batches: the key histogram and the classification pass as one launch, every block taking the unit's
+    // whole histogram itself (keyclass_kernel); otherwise two chip-wide launches.
+    const bool keyclass = ix->sel_bits && (ix->keyclass < 0 ? (long long)ix->l_stride * U <= 2048ll * ix->num_cu : ix->keyclass != 0);
     if (keyclass) {
         KeyClassArgs kc{};
         kc.u = u;
@@ -1787,21 +1784,19 @@ template <typename T, int G> int update_launch(ctkvr_index *ix, const void *q, h
         se.nsel = ix->dnsel;
         se.ids_only = 1;
         if (ix->sel_bits) {
-            if (!ix->have_hist) {   // taken here; this launch clears the list cursors too
-                fill_u32_kernel<<<dim3((unsigned)(((size_t)U * kBuckets + 255) / 256)), 256, 0, st>>>(ix->ws.ghist, 0u, (size_t)U * kBuckets);
-                KeyArgs ka{};
-                ka.u = u;
-                ka.ctx_lens = ix->d_ctx_lens;
-                ka.ncand = ix->ws.ncand;
-                ka.l_stride = ix->l_stride;
-                ka.z = nullptr;   // the keys are there
-                ka.kbuf = ix->ws.kbuf;
-                ka.ghist = ix->ws.ghist;
-                ka.gcur = ix->ws.gcur;
-                keyhist_kernel<G><<<dim3(std::max(1, std::min((ix->l_stride + 4095) / 4096, (2 * ix->num_cu + U - 1) / U)), U), 1024, 0, st>>>(ka);
-            } else {
-                fill_u32_kernel<<<dim3((U + 255) / 256), 256, 0, st>>>(ix->ws.gcur, 0u, (size_t)U);
-            }
+            // The keys' histogram is taken here, whatever the step left: most forms of it leave none, groups of one batch may take
+            // different forms, and a replayed step leaves what it was captured with.  This launch clears the list cursors too.
+            fill_u32_kernel<<<dim3((unsigned)(((size_t)U * kBuckets + 255) / 256)), 256, 0, st>>>(ix->ws.ghist, 0u, (size_t)U * kBuckets);
+            KeyArgs ka{};
+            ka.u = u;
+            ka.ctx_lens = ix->d_ctx_lens;
+            ka.ncand = ix->ws.ncand;
+            ka.l_stride = ix->l_stride;
+            ka.z = nullptr;   // the keys are there
+            ka.kbuf = ix->ws.kbuf;
+            ka.ghist = ix->ws.ghist;
+            ka.gcur = ix->ws.gcur;
+            keyhist_kernel<G><<<dim3(std::max(1, std::min((ix->l_stride + 4095) / 4096, (2 * ix->num_cu + U - 1) / U)), U), 1024, 0, st>>>(ka);
             ClassifyArgs ca{};
             ca.u = u;
             ca.ctx_lens = ix->d_ctx_lens;

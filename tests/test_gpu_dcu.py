@@ -100,16 +100,10 @@ SECOND = [(8, 1024, 500), (3, 2731, 900), (12, 1024, 300), (11, 1119, 300), (13,
           (13, 5000, 1000), (31, 1900, 2500)]
 
 
-@pytest.mark.parametrize("step", ["tail", "keyclass", "separate"])   # the last leaves its keys' histogram to the update
-@pytest.mark.parametrize("g,n_probe,rho,top_k,equal", [(2, *c, False) for c in SECOND] + [(8, 12, 1024, 300, False), (8, 13, 4000, 700, False),
-                         (2, 12, 1024, 300, True), (2, 13, 5000, 1000, True)])
-def test_second_ranking_is_the_selection_of_a_step_with_that_budget(ck, g, n_probe, rho, top_k, equal, step, monkeypatch):
-    """The slot's list after an update with rho != rho' is what a step of budget rho selects, id for id."""
+def _second_ranking(ck, batch, s, g, n_probe, rho, top_k, equal):
+    """The slot's lists after an update with budget top_k != rho against what a step of budget rho selects, id for id."""
     import torch
-    monkeypatch.setenv("CTKVR_TAIL", "1" if step == "tail" else "0")
-    if step == "separate":
-        monkeypatch.setenv("CTKVR_KEYCLASS", "0")
-    s, h, C = 65537, 2 * g, 40
+    h, C = 2 * g, 40
     rng = np.random.Generator(np.random.Philox(950 + n_probe + rho))
     gen = torch.Generator(device="cuda")
     gen.manual_seed(rho)
@@ -119,34 +113,53 @@ def test_second_ranking_is_the_selection_of_a_step_with_that_budget(ck, g, n_pro
         x = torch.randn(shape, generator=gen, device="cuda")
         return (x.round() if equal else x).to(torch.bfloat16)
 
-    k, v = rows(n_pages, g, 16, 128), rows(n_pages, g, 16, 128)
-    table = torch.arange(n_pages, dtype=torch.int32, device="cuda").view(1, -1)
-    q = rows(1, h, 128)
+    k, v = rows(batch * n_pages, g, 16, 128), rows(batch * n_pages, g, 16, 128)
+    table = torch.arange(batch * n_pages, dtype=torch.int32, device="cuda").view(batch, n_pages)
+    q = rows(batch, h, 128)
     if equal:
         q = torch.where(torch.arange(128, device="cuda") < 12, q, torch.zeros_like(q))   # scores on a coarse lattice
-    cen = rows(1, h, C, 128).view(torch.int16).cpu().numpy().view(np.uint16)
-    lists = np.empty((1, g, C, rho), np.int32)
-    for kv in range(g):   # rows of a permutation, so that any n_probe of its s // rho rows are disjoint
-        part = np.sort(rng.permutation(s)[:(s // rho) * rho].reshape(-1, rho), axis=1)
-        lists[0, kv] = part[np.arange(C) % part.shape[0]]
+    cen = rows(batch, h, C, 128).view(torch.int16).cpu().numpy().view(np.uint16)
+    lists = np.empty((batch, g, C, rho), np.int32)
+    for b in range(batch):
+        for kv in range(g):   # rows of a permutation, so that any n_probe of its s // rho rows are disjoint
+            part = np.sort(rng.permutation(s)[:(s // rho) * rho].reshape(-1, rho), axis=1)
+            lists[b, kv] = part[np.arange(C) % part.shape[0]]
     got = {}
     for budget in (top_k, rho):
-        p = ck.Params(batch=1, n_q_heads=h, n_kv_heads=g, n_centroids=C, list_len=rho, n_probe=n_probe, top_k=budget)
-        idx = ck.ctkvr_index_load(p, [s], cen, lists)
-        out = torch.empty((1, h, 128), device="cuda")
-        sel = torch.empty((1, g, budget), dtype=torch.int32, device="cuda")
-        nc = torch.empty((1, g), dtype=torch.int32, device="cuda")
+        p = ck.Params(batch=batch, n_q_heads=h, n_kv_heads=g, n_centroids=C, list_len=rho, n_probe=n_probe, top_k=budget)
+        idx = ck.ctkvr_index_load(p, [s] * batch, cen, lists)
+        out = torch.empty((batch, h, 128), device="cuda")
+        sel = torch.empty((batch, g, budget), dtype=torch.int32, device="cuda")
+        nc = torch.empty((batch, g), dtype=torch.int32, device="cuda")
         ck.ctkvr_decode_step(idx, q, k, v, table, out, out_sel=sel, out_ncand=nc)
         if budget == top_k:
             ck.ctkvr_centroid_update(idx, q)
-            got["list"] = ck.ctkvr_index_lists(idx)[0, :, 0]
-            assert np.array_equal(ck.ctkvr_index_lists(idx)[0, :, 1:], lists[0, :, 1:])
+            new = ck.ctkvr_index_lists(idx)
+            assert np.array_equal(new[:, :, 1:], lists[:, :, 1:])
         else:
-            got["sel"] = sel.cpu().numpy()[0]
-        got["L"] = nc.cpu().numpy()[0]
+            want = sel.cpu().numpy()
+        L = nc.cpu().numpy()
         ck.ctkvr_free(idx)
-    print(f"[dcu second] L {got['L'].min()}..{got['L'].max()} of {min(s, n_probe * rho)}", flush=True)
-    n = np.minimum(got["L"], rho)
-    for kv in range(g):
-        assert np.array_equal(got["list"][kv, :n[kv]], got["sel"][kv, :n[kv]])
-        assert (got["list"][kv, n[kv]:] == got["list"][kv, n[kv] - 1]).all()
+    print(f"[dcu second] L {L.min()}..{L.max()} of {min(s, n_probe * rho)}", flush=True)
+    for b in range(batch):
+        for kv in range(g):
+            n = min(L[b, kv], rho)
+            assert np.array_equal(new[b, kv, 0, :n], want[b, kv, :n])
+            assert (new[b, kv, 0, n:] == new[b, kv, 0, n - 1]).all()
+
+
+@pytest.mark.parametrize("step", ["tail", "keyclass", "separate"])
+@pytest.mark.parametrize("g,n_probe,rho,top_k,equal", [(2, *c, False) for c in SECOND] + [(8, 12, 1024, 300, False), (8, 13, 4000, 700, False),
+                         (2, 12, 1024, 300, True), (2, 13, 5000, 1000, True)])
+def test_second_ranking_is_the_selection_of_a_step_with_that_budget(ck, g, n_probe, rho, top_k, equal, step, monkeypatch):
+    monkeypatch.setenv("CTKVR_TAIL", "1" if step == "tail" else "0")
+    if step == "separate":
+        monkeypatch.setenv("CTKVR_KEYCLASS", "0")
+    _second_ranking(ck, 1, 65537, g, n_probe, rho, top_k, equal)
+
+
+@pytest.mark.parametrize("n_probe,rho", [(12, 4096), (15, 4000)])
+def test_second_ranking_where_groups_of_a_batch_step_in_different_forms(ck, n_probe, rho, monkeypatch):
+    """Two sequences of four KV heads in one group (one launch behind the scoring), three in the other (separate launches)."""
+    monkeypatch.setenv("CTKVR_DECODE_GROUPS", "2")
+    _second_ranking(ck, 5, 61000, 4, n_probe, rho, 700, False)
