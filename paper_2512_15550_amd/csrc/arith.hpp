@@ -810,6 +810,130 @@ __device__ __forceinline__ uint32_t wave_sum_uniform(uint32_t v)
            (uint32_t)__builtin_amdgcn_readlane((int)v, 32) + (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
 }
 
+// f over one value per lane of the wave, wave-uniform (f associative, commutative and idempotent)
+template <typename F> __device__ __forceinline__ uint32_t wave_fold_uniform(uint32_t v, F f)
+{
+    v = f(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false));
+    v = f(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false));
+    v = f(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false));
+    v = f(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, false));
+    return f(f((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16)),
+             f((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48)));
+}
+
+// ---- top-k selection for k <= 64 by single waves ------------------------------------------
+// The k largest of a wave's keys (slot it of a lane in kreg[it]; 0: no key; at least k keys; ties: lowest slot, then lowest lane):
+// emit(pos, it) by the lane of each pick, pos its rank in (slot, lane) order.  An interval [lo, up] that holds the k-th
+// largest is halved until a midpoint is reached by exactly k keys (then those are the picks) or one image is left (ties).
+// Bound by the latency of a round's dependent instructions (about 50 ns at one or two keys a lane), so three points a round, or
+// one maximum after another for a handful of picks (0.15 us each), took longer.  Many keys a lane make a round dearer:
+// there a few rounds on the lanes' maxima alone come first, whose k-th largest is reached by at least k keys.
+template <int KPT, typename EmitFn> __device__ __forceinline__ void wave_pick(const uint32_t (&kreg)[KPT], const uint32_t k, EmitFn emit)
+{
+    const int ln = lane_id();
+    uint32_t top = kreg[0];
+#pragma unroll
+    for (int it = 1; it < KPT; ++it) top = max(top, kreg[it]);
+    auto reached = [&](uint32_t t) __attribute__((always_inline)) {   // how many keys are >= t (t >= 1)
+        uint32_t c = 0;
+#pragma unroll
+        for (int it = 0; it < KPT; ++it) c += KPT <= 8 ? (uint32_t)__popcll(__ballot(kreg[it] >= t)) : (kreg[it] >= t ? 1u : 0u);
+        return KPT <= 8 ? c : wave_sum_uniform(c);
+    };
+    uint32_t up = wave_fold_uniform(top, [](uint32_t x, uint32_t y) { return max(x, y); });
+    uint32_t lo = 1u, c = (uint32_t)__popcll(__ballot(top != 0u));
+    if (c >= k) {   // as many lanes with a key: the least of their maxima is reached by k keys
+        lo = wave_fold_uniform(top ? top : 0xffffffffu, [](uint32_t x, uint32_t y) { return min(x, y); });
+        if constexpr (KPT > 2) {
+            uint32_t most = up;
+            for (int r = 0; r < 6 && lo < most; ++r) {
+                const uint32_t mid = lo + ((most - lo + 1u) >> 1);
+                const bool in = (uint32_t)__popcll(__ballot(top >= mid)) >= k;
+                lo = in ? mid : lo;
+                most = in ? most : mid - 1u;
+            }
+        }
+    }
+    if (KPT > 1) c = reached(lo);
+    // (the largest value first: k keys may well share it, where a query's copies are centroids, and halving would go through
+    // every bit to find that out)
+    if (const uint32_t cm = reached(up); cm >= k) {
+        lo = up;
+        c = cm;
+    }
+    while (c != k && lo < up) {   // up is at least the k-th largest, c >= k keys reach lo
+        const uint32_t mid = lo + ((up - lo + 1u) >> 1), cm = reached(mid);
+        const bool in = cm >= k;
+        lo = in ? mid : lo;
+        c = in ? cm : c;
+        up = in ? up : mid - 1u;
+    }
+    const bool ties = c != k;   // uniform: lo is the k-th largest key and not all keys equal to it are wanted
+    const uint32_t need_eq = ties ? k - (lo == 0xffffffffu ? 0u : reached(lo + 1u)) : 0u;
+    uint32_t run = 0, run_eq = 0;   // picks and ties in the slots so far
+#pragma unroll
+    for (int it = 0; it < KPT; ++it) {
+        uint64_t pick = __ballot(kreg[it] >= lo);
+        if (ties) {
+            const uint64_t eq = __ballot(kreg[it] == lo);
+            const uint32_t eq_before = __builtin_amdgcn_mbcnt_hi((uint32_t)(eq >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eq, run_eq));
+            pick = __ballot(kreg[it] > lo || (kreg[it] == lo && eq_before < need_eq));
+            run_eq += (uint32_t)__popcll(eq);
+        }
+        if ((pick >> ln) & 1ull)
+            emit(__builtin_amdgcn_mbcnt_hi((uint32_t)(pick >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)pick, run)), it);
+        run += (uint32_t)__popcll(pick);
+    }
+}
+
+template <int N> struct Slots { static constexpr int n = N; };
+
+// Same contract as block_bisect_topk, for k <= 64 and n <= NT KPT, and key(i) may be asked for every i < n_most, a bound of n
+// that is known earlier.  Wave w finds the k largest of the ids from w 64 KPT on by itself, and after one barrier every wave the
+// k largest among those.  One barrier where a block-wide halving or extraction takes one (and two trips through shared memory) a round:
+// the probes of a step were known 5.2 us into recall_gather at 8 of 64 centroids, 3.1 at 32 of 512, 3.7 at 4 and 6.1 at 64 of
+// 2048; now 1.5, 2.2, 2.9 and 4.5.
+// s_tmp: 2 * 64 * NT / 64 words.
+template <int NT, int KPT, typename KeyFn, typename EmitFn>
+__device__ __forceinline__ void split_topk(KeyFn key, int n_most, int n, int k, EmitFn emit, uint32_t *s_tmp)
+{
+    constexpr int NW = NT / 64;
+    const int tid = threadIdx.x, ln = lane_id(), wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // the wave's keys (loaded at clamped ids and then masked: a load under a per-lane condition would be waited for before
+    // the next one is requested)
+    uint32_t kreg[KPT];
+    const int first = wv * 64 * KPT;
+#pragma unroll
+    for (int it = 0; it < KPT; ++it) kreg[it] = key(min(first + it * 64 + ln, n_most - 1));
+    if (k >= n) {
+        for (int i = tid; i < n; i += NT) emit(i, i);
+        return;
+    }
+#pragma unroll
+    for (int it = 0; it < KPT; ++it) kreg[it] = first + it * 64 + ln < n ? kreg[it] : 0u;
+    uint32_t *s_key = s_tmp, *s_id = s_tmp + 64 * NW;
+    const int kw = min(k, min(n - first, 64 * KPT));   // candidates of this wave; the waves before it have k each
+    if (kw > 0)
+        wave_pick<KPT>(kreg, (uint32_t)kw, [&](uint32_t pos, int it) {
+            s_key[wv * k + pos] = kreg[it];
+            s_id[wv * k + pos] = (uint32_t)(first + it * 64 + ln);
+        });
+    __syncthreads();
+    const int w_last = (n - 1) / (64 * KPT), total = w_last * k + min(k, n - w_last * 64 * KPT);
+    auto final_pick = [&](auto slots) __attribute__((always_inline)) {
+        constexpr int S = decltype(slots)::n;
+        uint32_t cand[S];
+#pragma unroll
+        for (int it = 0; it < S; ++it) cand[it] = it * 64 + ln < total ? s_key[it * 64 + ln] : 0u;
+        wave_pick<S>(cand, (uint32_t)k, [&](uint32_t pos, int it) {
+            if (it % NW == wv) emit((int)pos, (int)s_id[it * 64 + ln]);
+        });
+    };
+    if (total <= 64) final_pick(Slots<1>{});
+    else if (total <= 128) final_pick(Slots<2>{});
+    else final_pick(Slots<NW>{});
+}
+
 // ---- small-n top-k selection by bisection ----------------------------------------------
 // Same contract as block_select_topk for n <= NT*KPT keys held in registers (slot it of
 // thread t is id it*NT + t).  The k-th largest key is found two bits at a time from the top: up to

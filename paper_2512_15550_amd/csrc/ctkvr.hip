@@ -566,15 +566,20 @@ int want_lds(int dev, const void *fn, size_t bytes)
     return CTKVR_OK;
 }
 
+// most centroids of a sequence -> cosines a thread of recall_gather_kernel holds
+void (*gather_kernel_for(int c_max))(GatherArgs)
+{
+    return c_max <= 256    ? recall_gather_kernel<1>
+           : c_max <= 512  ? recall_gather_kernel<2>
+           : c_max <= 1024 ? recall_gather_kernel<4>
+           : c_max <= 2048 ? recall_gather_kernel<8>
+                           : recall_gather_kernel<32>;
+}
+
 template <typename T, int G> int want_decode_lds(const ctkvr_index *ix)
 {
     const int dev = ix->dev;
-    if (ix->c_max <= 512)
-        TRY(want_lds(dev, (const void *)recall_gather_kernel<2>, ix->recall_lds));
-    else if (ix->c_max <= 2048)
-        TRY(want_lds(dev, (const void *)recall_gather_kernel<8>, ix->recall_lds));
-    else
-        TRY(want_lds(dev, (const void *)recall_gather_kernel<32>, ix->recall_lds));
+    TRY(want_lds(dev, (const void *)gather_kernel_for(ix->c_max), ix->recall_lds));
     TRY(want_lds(dev, (const void *)rerank_select_kernel<G>, std::max(ix->select_lds, ix->build_select_lds)));
     const bool s8 = ix->attn_slices == 8;
     if (ix->fused_lds) {
@@ -1396,12 +1401,7 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     ga.bitmap_words = ix->bitmap_words;
     ga.by_xcd = by_xcd;
     const dim3 rgrid(ix->recall_split, U);
-    if (ix->c_max <= 512)
-        recall_gather_kernel<2><<<rgrid, 256, ix->recall_lds, st>>>(ga);
-    else if (ix->c_max <= 2048)
-        recall_gather_kernel<8><<<rgrid, 256, ix->recall_lds, st>>>(ga);
-    else
-        recall_gather_kernel<32><<<rgrid, 256, ix->recall_lds, st>>>(ga);
+    gather_kernel_for(ix->c_max)<<<rgrid, 256, ix->recall_lds, st>>>(ga);
     if (whole) ix->mark(2, st);
 
     // lines 4-5: bitmap -> recalled ids, their rows and their scores in one launch

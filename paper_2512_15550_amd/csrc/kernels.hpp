@@ -219,7 +219,7 @@ template <typename T, int G> __global__ __launch_bounds__(256) void centroid_cos
 // ascending id list in recall_score_kernel).
 //
 // recall_gather: every block of a unit finds the same top-C' centroids (keys in
-// registers, C <= 256*KPT, bisection on the key), takes every gridDim.x-th probed list, ORs its ids into a bitmap in shared memory and then
+// registers, C <= 256*KPT), takes every gridDim.x-th probed list, ORs its ids into a bitmap in shared memory and then
 // ORs the non-empty words into the unit's bitmap in global memory (integer ORs: any
 // order gives the same bitmap).  grid (blocks per unit, batch*g), 256 threads; dynamic shared
 // memory: kSelLds + n_probe + bitmap words.
@@ -259,14 +259,14 @@ template <int KPT> __global__ __launch_bounds__(256) void recall_gather_kernel(G
         }
     };
     // line 3
-    // (a handful of probes, the paper's C' = 4: one block-wide maximum per probe; thousands of
-    // centroids: 11-bit radix rounds instead of sixteen rounds of 3 x KPT ballots)
-    if (a.n_probe <= 8)
-        block_extract_topk<256, KPT>([&](int j) { return ordered_key(cosv[j]); }, C, a.n_probe, keep, s_sel);
+    // (more than 64 probes: bisection by the block, of thousands of centroids 11-bit radix rounds)
+    auto cos_key = [&](int j) { return ordered_key(cosv[j]); };
+    if (a.n_probe <= 64)
+        split_topk<256, KPT>(cos_key, a.c_max, C, a.n_probe, keep, s_sel);   // (every row of a.cos has c_max entries)
     else if constexpr (KPT > 8)
-        block_select_topk<256, KPT>([&](int j) { return ordered_key(cosv[j]); }, C, a.n_probe, keep, s_sel);
+        block_select_topk<256, KPT>(cos_key, C, a.n_probe, keep, s_sel);
     else
-        block_bisect_topk<256, KPT>([&](int j) { return ordered_key(cosv[j]); }, C, a.n_probe, keep, s_sel);
+        block_bisect_topk<256, KPT>(cos_key, C, a.n_probe, keep, s_sel);
     __syncthreads();
     CTKVR_STAMP(9);
     // line 4: this block's share of the probed lists, one list per wave at a time
