@@ -513,7 +513,7 @@ size_t carve_step_ws(StepWs &w, unsigned char *base, const ctkvr_index *ix)
     take(&w.z, U * LS * G * 4);
     take(&w.m_key, U * G * 4);
     take(&w.crow, U * LS * 4);
-    take(&w.gbits, U * (size_t)((ix->s_max + 31) / 32) * 4);
+    take(&w.gbits, U * (size_t)ix->bitmap_words * 4);
     take(&w.kbuf, U * L * 4);
     take(&w.ghist, U * (size_t)kBuckets * 4);
     take(&w.gbm, U * (size_t)(2 * ((L + 63) / 64)) * 4);
@@ -651,7 +651,7 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, bool clear_tabl
         int cus = 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ix->dev) == hipSuccess && cus > 0) ix->num_cu = cus;
     }
-    ix->bitmap_words = (ix->s_max + 31) / 32;
+    ix->bitmap_words = (((ix->s_max + 31) / 32) + 3) & ~3;   // (rows of words on 16-byte boundaries)
     // The single-launch step needs all its blocks resident at once (one 1024-thread block per CU) and
     // its shared-memory plan to fit; up to 32 blocks work on a unit.
     if ((int)U <= ix->num_cu) {
@@ -724,7 +724,6 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, bool clear_tabl
     }
     lay_out((unsigned char *)ix->mem.base);
     // shared-memory plan
-    ix->bitmap_words = (ix->s_max + 31) / 32;
     ix->recall_lds = ((size_t)kSelLds + p->n_probe + ix->bitmap_words) * 4;
     // selection: radix scratch, the deciding bucket's list, two id bitmaps, the picked positions;
     // where the bitmaps would not fit the histogram route is switched off
@@ -1426,14 +1425,15 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     sa.by_xcd = by_xcd_all;
     {
         // Few rows per CU (a small batch): a block's rows are one round trip to memory and the slowest block
-        // is the launch, so the ids are split by rank -- two blocks per CU, at least 32 per unit and 64 ranks
+        // is the launch, so the ids are split by rank -- three blocks per two CUs (steps at two: 32K 36.4 against 36.1 us, with a
+        // resident window, whose blocks come on top, 43.7 against 42.5), at least 32 per unit and 64 ranks
         // per block.  Otherwise by id range: enough blocks to fill the chip a few times over, each owning
         // 8..64 words of the bitmap.
         const bool by_rank = ix->score_by_rank < 0 ? (long long)ix->l_stride * U <= 2048ll * ix->num_cu : ix->score_by_rank != 0;
         sa.by_rank = by_rank;
         int nbx;
         if (by_rank) {
-            nbx = std::min(std::max(32, (2 * ix->num_cu + U - 1) / U), (ix->l_stride + 63) / 64);
+            nbx = std::min(std::max(32, (3 * ix->num_cu / 2 + U - 1) / U), (ix->l_stride + 63) / 64);
             nbx = std::max({1, nbx, (ix->l_stride + kRecallCap - 1) / kRecallCap});
         } else {
             const int target = std::max(32, (8 * ix->num_cu + U - 1) / U);
@@ -1441,15 +1441,28 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
             nbx = (ix->bitmap_words + wpb - 1) / wpb;
         }
         sa.nbx = nbx;
+        if (by_rank) {
+            // the bitmap with the ids before each word, and the block table of a sequence, where they fit 64 KB beside the block's ids
+            const int words = (((ix->bitmap_words + 255) / 256 + 3) & ~3) * 256;
+            sa.lds.words = words <= kRecallWords ? words : 0;
+            const int pages = (std::min(max_pages, ((ix->s_max - 1) >> ix->page_shift) + 1) + 255) & ~255;
+            RecallLds all = sa.lds;
+            all.pages = pages;
+            sa.lds.pages = words && pages <= kRecallWords && all.total() * 4 <= 60 * 1024 ? pages : 0;
+        } else {
+            sa.lds.pages = 256;
+            sa.lds.words = 0;
+        }
+        const size_t slds = (size_t)sa.lds.total() * 4;
         bool launched = false;
         if constexpr (G <= 4) {
             if (window) {
                 sa.win = wa;
-                recall_score_kernel<T, G, true><<<dim3(nbx + kWinSplit, U), 256, 0, st>>>(sa);
+                recall_score_kernel<T, G, true><<<dim3(nbx + kWinSplit, U), 256, slds, st>>>(sa);
                 launched = true;
             }
         }
-        if (!launched) recall_score_kernel<T, G, false><<<dim3(nbx, U), 256, 0, st>>>(sa);
+        if (!launched) recall_score_kernel<T, G, false><<<dim3(nbx, U), 256, slds, st>>>(sa);
     }
     if (whole) ix->mark(3, st);
 

@@ -596,15 +596,26 @@ template <typename T, int G> __global__ __launch_bounds__(256) void window_attn_
 //     so some blocks get several times the rows of others, which does not matter while every CU has
 //     many blocks' worth of rows to stream.
 //   by rank -- block x takes ranks [x q, (x + 1) q), q = ceil(L / blocks): every block counts the whole
-//     bitmap (a contiguous stretch of words per thread, one block scan), which gives L and tells the
-//     two threads whose stretches hold the block's first and last rank to name their words.  One more
-//     round trip to the cache, but every block then has the same number of rows: for small batches,
-//     where a block's rows are one or two round trips to memory and the slowest block is the launch.
+//     bitmap (a contiguous stretch of words per thread, one block scan), which gives L, and the threads
+//     whose stretches hold the block's ranks leave their words with the ids before each in shared memory.  Every block
+//     then has the same number of rows: for small batches, where a block's rows are one or two round trips to memory and the
+//     slowest block is the launch.
+// Either way all that the prologue reads -- words, the block-table entries of the block's pages, the queries -- is
+// requested at once, one round trip before the rows (under load a dependent trip takes 2-4 us); ids and rows are written
+// behind the scoring, off that chain.
 // The block that sees the unit's last word (by id) or block 0 (by rank) also writes L.
-// grid (nbx [+ kWinSplit], units), 256 threads; by id nbx >= W_max / 64, by rank nbx >= l_stride / kRecallCap.
+// grid (nbx [+ kWinSplit], units), 256 threads; by id nbx >= W_max / 64, by rank nbx >= l_stride / kRecallCap.  Dynamic shared
+// memory: RecallLds.
 // ------------------------------------------------------------------------------
 constexpr int kRecallWpb = 64;     // by id range: at most 2048 ids per block
 constexpr int kRecallCap = 2048;   // ids per block at most
+constexpr int kRecallWords = 4096; // by rank: bitmap words (contexts up to 128K) that the prologue takes in one trip
+
+// words of shared memory: ids and rows of the block, block-table entries, by rank the bitmap and the ids before each word
+struct RecallLds {
+    int pages, words;
+    __host__ __device__ int total() const { return 2 * kRecallCap + pages + 2 * words; }
+};
 
 struct RecallScoreArgs {
     Units u;
@@ -624,6 +635,7 @@ struct RecallScoreArgs {
     int stream_k;             // the keys of all sequences exceed what the memory-side cache holds: load them non-temporal
     int by_rank;              // how the bitmap is split over a unit's blocks
     int by_xcd;               // blocks -> (unit, block of the unit) by unit_block_of
+    RecallLds lds;            // by rank: words = 0 where the bitmap is read again instead, pages = 0 where the pages do not fit
     int nbx;                  // blocks per unit that score; with WIN blocks nbx .. nbx + kWinSplit - 1 take the resident window
     WindowArgs win;
 };
@@ -631,8 +643,10 @@ struct RecallScoreArgs {
 template <typename T, int G, bool WIN> __global__ __launch_bounds__(256) void recall_score_kernel(RecallScoreArgs a)
 {
     constexpr int R = 8, TILE = 16 * R;
-    __shared__ uint32_t s_ids[kRecallCap];        // ids of this block's ranks, then their rows
-    __shared__ int32_t s_page[256];               // block-table entries of the pages its ids lie in
+    extern __shared__ __align__(16) uint32_t smem[];
+    uint32_t *s_ids = smem, *s_rows = smem + kRecallCap;     // ids of this block's ranks, their rows
+    int32_t *s_page = (int32_t *)(smem + 2 * kRecallCap);    // block-table entries
+    uint32_t *s_word = smem + 2 * kRecallCap + a.lds.pages, *s_before = s_word + a.lds.words;
     __shared__ uint32_t s_tmp[8];
     __shared__ uint32_t s_edge[3];                // first word, ids before it, last word
     __shared__ uint32_t s_max[G];
@@ -646,43 +660,103 @@ template <typename T, int G, bool WIN> __global__ __launch_bounds__(256) void re
     }
     const int b = ul / a.u.g, kv = ul - b * a.u.g;
     const int tid = threadIdx.x, lane16 = tid & 15, grp = tid >> 4;
+    const int ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     CTKVR_STAMP_BLK(6);
-    const int s_len = a.ctx_lens[b];
-    const int W = (s_len + 31) >> 5;
-    if (a.ghist)
-        for (int w = bx * 256 + tid; w < kBuckets; w += (uint32_t)a.nbx * 256) a.ghist[(size_t)ul * kBuckets + w] = 0u;
     const uint32_t *gb = a.gbits + (size_t)ul * a.bitmap_words;
+    const int32_t *bt_row = a.k.block_table + (size_t)b * a.k.max_pages;
+    const int pmask = (1 << a.k.page_shift) - 1;
     if (tid < G) s_max[tid] = 0u;
+    // The ids of byte `part` of word w, the first of them at rank rk: those of ranks [r0, r1) with their rows into shared
+    // memory.  page_of(p): the block-table entry of page p
+    auto expand = [&](uint32_t word, int w, int part, uint32_t rk, uint32_t r0, uint32_t r1, auto page_of) __attribute__((always_inline)) {
+        uint32_t m = (word >> (part << 3)) & 0xffu;
+        if (!m) return;
+        const int id0 = (w << 5) + (part << 3);
+        int page = a.k.page_shift >= 3 ? page_of(id0 >> a.k.page_shift) : 0;   // one page holds all eight
+        do {
+            const int t = id0 + __ffs((int)m) - 1;
+            m &= m - 1u;
+            if (rk >= r0 && rk < r1) {
+                if (a.k.page_shift < 3) page = page_of(t >> a.k.page_shift);
+                s_ids[rk - r0] = (uint32_t)t;
+                s_rows[rk - r0] = (uint32_t)((page * a.u.g + kv) << a.k.page_shift) + (uint32_t)(t & pmask);
+            }
+            ++rk;
+        } while (m);
+    };
+    auto clear_hist = [&]() {
+        if (a.ghist)
+            for (int w = bx * 256 + tid; w < kBuckets; w += (uint32_t)a.nbx * 256) a.ghist[(size_t)ul * kBuckets + w] = 0u;
+    };
     uint32_t r0, r1;   // the block's ranks
-    if (a.by_rank) {
-        // thread t counts words [t wpt, (t + 1) wpt), wpt a multiple of four: 16-byte loads where the
-        // unit's words start on a 16-byte boundary (words from W up to the row's end are zero)
-        const int wpt = ((((W + 255) >> 8) + 3) >> 2) << 2;
-        const int w0 = tid * wpt;
-        const bool wide = ((reinterpret_cast<uintptr_t>(gb) | ((uintptr_t)a.bitmap_words << 2)) & 15u) == 0;
-        // up to 16 words per thread (contexts up to 128K) stay in registers, so that the two threads that
-        // name the block's edge words below need no further load
-        const bool in_regs = wide && wpt <= 16;
-        uint4 v[4] = {};
+    if (a.by_rank && a.lds.words) {
+        // thread t counts words [t wpt, (t + 1) wpt), wpt a multiple of four, and keeps them (those from the sequence's end up to
+        // the row's are zero)
+        constexpr int NV = kRecallWords / 1024, NP = kRecallWords / 256;
+        const int wpt = a.lds.words >> 8, w0 = tid * wpt;
+        uint4 v[NV];
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+            if (4 * i < wpt) v[i] = *reinterpret_cast<const uint4 *>(gb + min(w0 + 4 * i, a.bitmap_words - 4));   // uniform
+        int32_t pg[NP];
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+            if (i * 256 < a.lds.pages) pg[i] = bt_row[min(i * 256 + tid, a.k.max_pages - 1)];   // uniform
+        clear_hist();
         uint32_t cnt = 0;
-        if (in_regs) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int w = w0 + 4 * i;
-                const uint4 x = *reinterpret_cast<const uint4 *>(gb + min(w, a.bitmap_words - 4));
-                if (i * 4 < wpt && w < a.bitmap_words) v[i] = x;
-            }
+        for (int i = 0; i < NV; ++i) {
+            if (4 * i >= wpt || w0 + 4 * i >= a.bitmap_words) v[i] = make_uint4(0u, 0u, 0u, 0u);
+            cnt += (uint32_t)(__popc(v[i].x) + __popc(v[i].y) + __popc(v[i].z) + __popc(v[i].w));
+        }
+        uint32_t L;
+        const uint32_t pre = block_excl_scan<256>(cnt, s_tmp, &L);   // barriers inside
+        if (bx == 0 && tid == 0) {
+            a.ncand[ul] = (int32_t)L;
+            if (a.out_ncand) a.out_ncand[ul] = (int32_t)L;
+        }
+        const uint32_t qn = (L + (uint32_t)a.nbx - 1) / (uint32_t)a.nbx;
+        r0 = bx * qn;
+        if (r0 >= L) return;
+        r1 = min(L, r0 + qn);
+        // the threads that hold ranks of the block leave their words and the ids before each (also those without ids between two
+        // with some: pre lies strictly between r0 and r1 there)
+        if (pre < r1 && pre + cnt > r0) {
+            uint32_t p = pre;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) cnt += (uint32_t)(__popc(v[i].x) + __popc(v[i].y) + __popc(v[i].z) + __popc(v[i].w));
-        } else if (wide) {
+            for (int i = 0; i < NV; ++i)
+                if (4 * i < wpt) {   // uniform
+                    const uint32_t p1 = p + (uint32_t)__popc(v[i].x), p2 = p1 + (uint32_t)__popc(v[i].y), p3 = p2 + (uint32_t)__popc(v[i].z);
+                    *reinterpret_cast<uint4 *>(s_word + w0 + 4 * i) = v[i];
+                    *reinterpret_cast<uint4 *>(s_before + w0 + 4 * i) = make_uint4(p, p1, p2, p3);
+                    p = p3 + (uint32_t)__popc(v[i].w);
+                }
+            if (pre <= r0) s_edge[0] = (uint32_t)w0;
+            if (pre + cnt >= r1) s_edge[2] = (uint32_t)(w0 + wpt);
+        }
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+            if (i * 256 < a.lds.pages) s_page[i * 256 + tid] = pg[i];
+        __syncthreads();
+        CTKVR_STAMP_BLK(7);
+        const int wb = (int)s_edge[2], part = tid & 3;
+        for (int w = (int)s_edge[0] + (tid >> 2); w < wb; w += 64) {
+            const uint32_t word = s_word[w], rk = s_before[w] + (uint32_t)__popc(word & ((1u << (part << 3)) - 1u));
+            if (a.lds.pages)
+                expand(word, w, part, rk, r0, r1, [&](int p) { return s_page[p]; });
+            else
+                expand(word, w, part, rk, r0, r1, [&](int p) { return bt_row[p]; });
+        }
+    } else if (a.by_rank) {
+        // longer contexts: two passes over the words, the second over those between the block's first and last rank
+        const int wpt = ((((a.bitmap_words + 255) >> 8) + 3) >> 2) << 2;
+        const int w0 = tid * wpt, w1 = min(w0 + wpt, a.bitmap_words);
+        clear_hist();
+        uint32_t cnt = 0;
 #pragma unroll 4
-            for (int w = w0; w < min(w0 + wpt, a.bitmap_words); w += 4) {
-                const uint4 x = *reinterpret_cast<const uint4 *>(gb + w);
-                cnt += (uint32_t)(__popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w));
-            }
-        } else {
-#pragma unroll 4
-            for (int w = w0; w < min(w0 + wpt, W); ++w) cnt += (uint32_t)__popc(gb[w]);
+        for (int w = w0; w < w1; w += 4) {
+            const uint4 x = *reinterpret_cast<const uint4 *>(gb + w);
+            cnt += (uint32_t)(__popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w));
         }
         uint32_t L;
         const uint32_t pre = block_excl_scan<256>(cnt, s_tmp, &L);   // barriers inside
@@ -695,130 +769,88 @@ template <typename T, int G, bool WIN> __global__ __launch_bounds__(256) void re
         if (r0 >= L) return;
         r1 = min(L, r0 + qn);
         // the threads whose stretches hold ranks r0 and r1 - 1 walk their words to the one that holds it
-        const bool own_first = cnt && pre <= r0 && r0 < pre + cnt;
-        const bool own_last = cnt && pre < r1 && r1 <= pre + cnt;
-        if (in_regs) {
-            if (own_first || own_last) {
-                const uint32_t wd[16] = {v[0].x, v[0].y, v[0].z, v[0].w, v[1].x, v[1].y, v[1].z, v[1].w,
-                                         v[2].x, v[2].y, v[2].z, v[2].w, v[3].x, v[3].y, v[3].z, v[3].w};
-                uint32_t p = pre, e0 = 0, e1 = 0, e2 = 0;
-                bool f0 = !own_first, f2 = !own_last;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const uint32_t c = (uint32_t)__popc(wd[i]);
-                    if (!f0 && r0 < p + c) {
-                        e0 = (uint32_t)(w0 + i);
-                        e1 = p;
-                        f0 = true;
-                    }
-                    p += c;
-                    if (!f2 && r1 <= p) {
-                        e2 = (uint32_t)(w0 + i);
-                        f2 = true;
-                    }
+        if (cnt && pre <= r0 && r0 < pre + cnt) {
+            uint32_t p = pre;
+            for (int w = w0; w < w1; ++w) {
+                const uint32_t c = (uint32_t)__popc(gb[w]);
+                if (r0 < p + c) {
+                    s_edge[0] = (uint32_t)w;
+                    s_edge[1] = p;
+                    break;
                 }
-                if (own_first) {
-                    s_edge[0] = e0;
-                    s_edge[1] = e1;
-                }
-                if (own_last) s_edge[2] = e2;
+                p += c;
             }
-        } else {
-            if (own_first) {
-                uint32_t p = pre;
-                for (int w = w0; w < w0 + wpt; ++w) {
-                    const uint32_t c = (uint32_t)__popc(gb[w]);
-                    if (r0 < p + c) {
-                        s_edge[0] = (uint32_t)w;
-                        s_edge[1] = p;
-                        break;
-                    }
-                    p += c;
+        }
+        if (cnt && pre < r1 && r1 <= pre + cnt) {
+            uint32_t p = pre;
+            for (int w = w0; w < w1; ++w) {
+                p += (uint32_t)__popc(gb[w]);
+                if (r1 <= p) {
+                    s_edge[2] = (uint32_t)w;
+                    break;
                 }
             }
-            if (own_last) {
-                uint32_t p = pre;
-                for (int w = w0; w < w0 + wpt; ++w) {
-                    p += (uint32_t)__popc(gb[w]);
-                    if (r1 <= p) {
-                        s_edge[2] = (uint32_t)w;
-                        break;
-                    }
-                }
-            }
+        }
+        __syncthreads();
+        const int wa = (int)s_edge[0], wb = (int)s_edge[2], part = tid & 3;
+        uint32_t rank0 = s_edge[1];   // ids before the pass's first word
+        for (int wp = wa; wp <= wb; wp += 64) {
+            const int w = wp + (tid >> 2);
+            const uint32_t word = w <= wb ? gb[w] : 0u;
+            uint32_t n_pass;
+            const uint32_t rk = rank0 + block_excl_scan<256>((uint32_t)__popc((word >> (part << 3)) & 0xffu), s_tmp, &n_pass);
+            expand(word, w, part, rk, r0, r1, [&](int p) { return bt_row[p]; });
+            rank0 += n_pass;
         }
     } else {
         // the unit's own words split evenly over the blocks of its row (a short sequence of a ragged
         // batch still uses all of them)
+        const int W = (a.ctx_lens[b] + 31) >> 5;
         const int wpb = min(kRecallWpb, (W + a.nbx - 1) / a.nbx);
-        const int w_beg = bx * wpb;
+        const int w_beg = bx * wpb, w_end = min(W, w_beg + wpb);
+        clear_hist();
         if (w_beg >= W) return;
+        const int mine = w_beg + (tid >> 2), part = tid & 3;
+        uint32_t word = gb[min(mine, W - 1)];
+        const int page0 = (w_beg << 5) >> a.k.page_shift;
+        const int npages = min((((w_end << 5) - 1) >> a.k.page_shift) - page0 + 1, a.k.max_pages - page0);
+        const bool lds_pages = npages <= a.lds.pages;
+        int32_t pg = 0;
+        if (lds_pages) pg = bt_row[page0 + min(tid, npages - 1)];
         uint32_t before = 0;
-#pragma unroll 4
-        for (int w = tid; w < w_beg; w += 256) before += (uint32_t)__popc(gb[w]);
+        for (int w8 = 0; w8 < w_beg; w8 += 8 * 256) {   // eight words a thread requested together
+            uint32_t x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = gb[min(w8 + u * 256 + tid, w_beg - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) before += w8 + u * 256 + tid < w_beg ? (uint32_t)__popc(x[u]) : 0u;
+        }
+        if (mine >= w_end) word = 0u;
+        // one barrier for the ids before the block's words and the scan over its own
+        const uint32_t c = (uint32_t)__popc((word >> (part << 3)) & 0xffu), inc = wave_incl_scan(c);
         before = wave_sum_uniform(before);
-        if ((tid & 63) == 0) s_tmp[tid >> 6] = before;
+        if (ln == 63) {
+            s_tmp[wv] = inc;
+            s_tmp[4 + wv] = before;
+        }
+        if (lds_pages && tid < npages) s_page[tid] = pg;
         __syncthreads();
-        if (tid == 0) {
-            s_edge[0] = (uint32_t)w_beg;
-            s_edge[1] = s_tmp[0] + s_tmp[1] + s_tmp[2] + s_tmp[3];
-            s_edge[2] = (uint32_t)(min(W, w_beg + wpb) - 1);
-        }
-        r0 = r1 = 0u;   // known after the (single) pass over the block's words
-    }
-    __syncthreads();
-    const int wa = (int)s_edge[0], wb = (int)s_edge[2];
-    uint32_t rank0 = s_edge[1];   // ids before the pass's first word
-    if (!a.by_rank) {
-        r0 = rank0;
-        r1 = 0xffffffffu;
-    }
-    CTKVR_STAMP_BLK(7);
-    // requested together: the first pass's words and the block-table entries of the pages between the two words
-    uint32_t myword = (wa + (tid >> 2) <= wb) ? gb[wa + (tid >> 2)] : 0u;
-    const int page0 = (wa << 5) >> a.k.page_shift;
-    const int npages = ((min((wb << 5) + 31, s_len - 1)) >> a.k.page_shift) - page0 + 1;
-    const bool lds_pages = npages <= 256;
-    if (lds_pages && tid < npages) s_page[tid] = a.k.block_table[(size_t)b * a.k.max_pages + page0 + tid];
-    for (int wp = wa; wp <= wb; wp += 64) {
-        if (wp != wa) myword = (wp + (tid >> 2) <= wb) ? gb[wp + (tid >> 2)] : 0u;
-        uint32_t m = (myword >> ((tid & 3) << 3)) & 0xffu;
-        uint32_t n_pass;
-        uint32_t rk = rank0 + block_excl_scan<256>((uint32_t)__popc(m), s_tmp, &n_pass);   // barriers inside
-        const uint32_t id0 = ((uint32_t)(wp + (tid >> 2)) << 5) + ((uint32_t)(tid & 3) << 3);
-        while (m) {
-            const int bit = __ffs((int)m) - 1;
-            m &= m - 1u;
-            if (rk >= r0 && rk < r1) s_ids[rk - r0] = id0 + (uint32_t)bit;
-            ++rk;
-        }
-        rank0 += n_pass;
-    }
-    if (!a.by_rank) {   // one pass: the block's ids are all the ids of its words
-        r1 = rank0;
-        if (wb == W - 1 && tid == 0) {
+        r0 = s_tmp[4] + s_tmp[5] + s_tmp[6] + s_tmp[7];
+        const uint32_t t0 = s_tmp[0], t1 = s_tmp[1], t2 = s_tmp[2], t3 = s_tmp[3];
+        r1 = r0 + t0 + t1 + t2 + t3;
+        CTKVR_STAMP_BLK(7);
+        if (w_end == W && tid == 0) {
             a.ncand[ul] = (int32_t)r1;
             if (a.out_ncand) a.out_ncand[ul] = (int32_t)r1;
         }
         if (r1 == r0) return;
-    }
-    const uint32_t n_blk = r1 - r0;
-    __syncthreads();
-    const uint32_t base = r0;
-    int32_t *cd = a.cand + (size_t)ul * a.l_stride + base;
-    uint32_t *rw = a.crow + (size_t)ul * a.l_stride + base;
-    const int pmask = (1 << a.k.page_shift) - 1;
-    for (uint32_t i = tid; i < n_blk; i += 256) {
-        const int t = (int)s_ids[i];
-        uint32_t row;
+        const uint32_t rk = r0 + (wv > 0 ? t0 : 0u) + (wv > 1 ? t1 : 0u) + (wv > 2 ? t2 : 0u) + inc - c;
         if (lds_pages)
-            row = (uint32_t)((s_page[(t >> a.k.page_shift) - page0] * a.u.g + kv) << a.k.page_shift) + (uint32_t)(t & pmask);
+            expand(word, mine, part, rk, r0, r1, [&](int p) { return s_page[p - page0]; });
         else
-            row = row_of(a.k.block_table, a.k.max_pages, a.k.page_shift, a.u.g, b, kv, t);
-        cd[i] = t;
-        rw[i] = row;
-        s_ids[i] = row;   // each slot is read and rewritten by the same thread
+            expand(word, mine, part, rk, r0, r1, [&](int p) { return bt_row[p]; });
     }
+    const uint32_t n_blk = r1 - r0, base = r0;
     __syncthreads();
     CTKVR_STAMP_BLK(2);
     const T *K = (const T *)a.k.pages;
@@ -835,17 +867,22 @@ template <typename T, int G, bool WIN> __global__ __launch_bounds__(256) void re
     for (int t0 = 0; t0 < (int)n_blk; t0 += TILE) {
         Chunk<T> ck[R];
         const T *krow[R];
+        // (rounds of sixteen rows of which the tile has none are left out, uniformly, the first four aside)
+        constexpr int R0 = 4;
 #pragma unroll
-        for (int r = 0; r < R; ++r) krow[r] = K + (size_t)s_ids[min(t0 + r * 16 + grp, last)] * kD;
+        for (int r = 0; r < R; ++r) krow[r] = K + (size_t)s_rows[min(t0 + r * 16 + grp, last)] * kD;
         if (a.stream_k) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) ck[r] = load_chunk_nt(krow[r], lane16);
+            for (int r = 0; r < R; ++r)
+                if (r < R0 || t0 + r * 16 <= last) ck[r] = load_chunk_nt(krow[r], lane16);
         } else {
 #pragma unroll
-            for (int r = 0; r < R; ++r) ck[r] = load_chunk(krow[r], lane16);
+            for (int r = 0; r < R; ++r)
+                if (r < R0 || t0 + r * 16 <= last) ck[r] = load_chunk(krow[r], lane16);
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
+            if (r >= R0 && t0 + r * 16 > last) break;
             float kx[8];
             unpack(ck[r], kx);
             float mine_z = 0.0f;
@@ -867,6 +904,12 @@ template <typename T, int G, bool WIN> __global__ __launch_bounds__(256) void re
         v = __builtin_amdgcn_fmed3f(v, __shfl_xor(v, 16), __builtin_huge_valf());
         v = __builtin_amdgcn_fmed3f(v, __shfl_xor(v, 32), __builtin_huge_valf());
         if (lane_id() < G) atomicMax(&s_max[lane_id()], ordered_key(v));
+    }
+    int32_t *cd = a.cand + (size_t)ul * a.l_stride + base;
+    uint32_t *rw = a.crow + (size_t)ul * a.l_stride + base;
+    for (uint32_t i = tid; i < n_blk; i += 256) {
+        cd[i] = (int32_t)s_ids[i];
+        rw[i] = s_rows[i];
     }
     __syncthreads();
     if (tid < G) atomicMax(&a.m_key[ul * G + tid], s_max[tid]);

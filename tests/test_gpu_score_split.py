@@ -1,0 +1,29 @@
+"""The prologue of the scoring launch (Algorithm 2 line 4: recalled ids and their rows) where it changes form: pages smaller than the
+eight ids of a byte of the bitmap, pages larger than a block's ids, block tables that fit beside the bitmap and not (beyond
+4096 entries), contexts whose bitmap is kept (to 4096 words) and read again (beyond), lengths that end inside a word, few
+recalled ids for many blocks; by id range and by rank."""
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import paper_2512_15550_amd as ck
+from ctkvr_inputs import gen_batch, small_workload
+from tests import harness as H
+
+
+@pytest.mark.parametrize("by_rank", [0, 1])
+@pytest.mark.parametrize("h,g,lens,page,rho,n_probe", [(2, 1, (301,), 1, 40, 3), (4, 2, (1003, 77), 2, 30, 4), (8, 2, (2021,), 4, 200, 6),
+                                                       (8, 2, (2049, 513), 8, 256, 4), (8, 1, (40007,), 256, 900, 5),
+                                                       (2, 2, (70001, 9000), 16, 700, 4), (4, 1, (131072,), 32, 3000, 4),
+                                                       (4, 1, (132001,), 16, 5000, 4), (4, 1, (9001,), 16, 3, 2), (1, 1, (64,), 16, 64, 2)])
+def test_recalled_ids_and_rows_match_the_oracle(h, g, lens, page, rho, n_probe, by_rank, monkeypatch):
+    monkeypatch.setenv("CTKVR_SCORE_BY_RANK", str(by_rank))
+    wl = small_workload("score_split", "bf16", h, g, lens, tuple(800 + i for i in range(len(lens))), 8, 0, n_probe, rho, min(rho, 100), 2, page_size=page)
+    bt = gen_batch(wl)
+    db = H.device_batch(bt)
+    idx = ck.ctkvr_build_index(H.params_of(wl), db.q_prefill, db.cu_seqlens, True, db.k_pages, db.block_table, db.ctx_lens)
+    try:
+        H.run_decode_parity(bt, H.oracle_index(bt), idx, db)
+    finally:
+        ck.ctkvr_free(idx)
