@@ -108,6 +108,14 @@ __device__ __forceinline__ float group16_sum(float v)
     return v;
 }
 
+// Two values summed over the 16-lane rows 2 i and 2 i + 1 of a wave, lane by lane: the even row gets the sum of a, the odd row that of b
+// (one swap and one add for two values).
+__device__ __forceinline__ float row_pair_sum(float a, float b)
+{
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+
 __device__ __forceinline__ float lane_partial(const float (&a)[8], const float (&b)[8])
 {
     float acc = 0.0f;

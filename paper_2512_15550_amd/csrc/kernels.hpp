@@ -2119,9 +2119,11 @@ __device__ __forceinline__ void attend_unit(const AttnArgs &a, int ul, int slice
     constexpr int kSliceRows = 64 / kSliceLanes;   // rows per wave and pass
     static_assert(kSliceRows % 16 == 0, "the sum over a wave's rows starts with a butterfly inside each 16-lane row");
     // A wave's 64 lanes are kSliceLanes parts of kSliceRows rows: lane l works on row (l mod kSliceRows) of the
-    // pass and on the 8 values (l / kSliceRows) of the slice.  Every 16-lane row of a wave thus belongs to one part and
-    // is one producer of partial sums; kProd of them per part in the block.
-    constexpr int PASS = NW * kSliceRows, kProd = NW * kSliceRows / 16;   // rows per pass of the block; NU passes in flight
+    // pass and on the 8 values (l / kSliceRows) of the slice.  Every 16-lane row of a wave thus belongs to one part; the two rows of
+    // a part (eight slices) are summed pairwise, each keeping half of the values.  A wave is one producer of partial sums per part.
+    constexpr int PASS = NW * kSliceRows, kProd = NW;   // rows per pass of the block; NU passes in flight
+    constexpr bool kPairs = kSliceRows == 32;
+    static_assert(kPairs || kSliceRows == 16, "one or two rows of 16 lanes per part");
     __shared__ float s_red[kProd][G];
     __shared__ float s_m[G];
     __shared__ uint32_t s_big[NW];
@@ -2129,7 +2131,6 @@ __device__ __forceinline__ void attend_unit(const AttnArgs &a, int ul, int slice
     const int b = ul / a.g, kv = ul - b * a.g;
     const int tid = threadIdx.x, wv = tid >> 6, ln = tid & 63;
     const int quad = ln / kSliceRows, rin = wv * kSliceRows + (ln % kSliceRows);
-    const int prod = wv * (kSliceRows / 16) + ((ln % kSliceRows) >> 4);   // this lane's 16-lane row among its part's producers
     CTKVR_STAMP(44);
     CTKVR_STAMP_BLK(4);
     const T *V = (const T *)a.v_pages + slice * kSliceDims + quad * 8;
@@ -2198,22 +2199,45 @@ __device__ __forceinline__ void attend_unit(const AttnArgs &a, int ul, int slice
         }
     }
     CTKVR_STAMP(48);
-    // sums over the lanes of each 16-lane row (a DPP butterfly), one barrier for denominators and outputs together
+    // Sums over the lanes of a part: two values at a time across its two 16-lane rows (then the even row has the first
+    // of them and the odd row the second), then inside a row (a DPP butterfly); one barrier for denominators and outputs together.
     auto hand_over = [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int hh = 0; hh < G; ++hh)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc[hh][e] = group16_sum(acc[hh][e]);
-#pragma unroll
-        for (int hh = 0; hh < G; ++hh) lsum[hh] = group16_sum(lsum[hh]);
-        if ((ln & 15) == 0) {
+        if constexpr (kPairs) {
+            const int odd = (ln >> 4) & 1;
+            float o[G][4];
 #pragma unroll
             for (int hh = 0; hh < G; ++hh)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) s_o[prod][hh][quad * 8 + e] = acc[hh][e];
-            if (quad == 0) {
+                for (int e = 0; e < 4; ++e) o[hh][e] = group16_sum(row_pair_sum(acc[hh][e], acc[hh][e + 4]));
+            float l[(G + 1) / 2];
 #pragma unroll
-                for (int hh = 0; hh < G; ++hh) s_red[prod][hh] = lsum[hh];
+            for (int j = 0; j < (G + 1) / 2; ++j) l[j] = group16_sum(row_pair_sum(lsum[2 * j], lsum[G > 1 ? 2 * j + 1 : 0]));
+            if ((ln & 15) == 0) {
+#pragma unroll
+                for (int hh = 0; hh < G; ++hh)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) s_o[wv][hh][quad * 8 + odd * 4 + e] = o[hh][e];
+                if (quad == 0) {
+#pragma unroll
+                    for (int j = 0; j < (G + 1) / 2; ++j) s_red[wv][G > 1 ? 2 * j + odd : 0] = l[j];   // (G = 1: both rows write the sum)
+                }
+            }
+        } else {
+#pragma unroll
+            for (int hh = 0; hh < G; ++hh)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[hh][e] = group16_sum(acc[hh][e]);
+#pragma unroll
+            for (int hh = 0; hh < G; ++hh) lsum[hh] = group16_sum(lsum[hh]);
+            if ((ln & 15) == 0) {
+#pragma unroll
+                for (int hh = 0; hh < G; ++hh)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) s_o[wv][hh][quad * 8 + e] = acc[hh][e];
+                if (quad == 0) {
+#pragma unroll
+                    for (int hh = 0; hh < G; ++hh) s_red[wv][hh] = lsum[hh];
+                }
             }
         }
     };
@@ -2294,7 +2318,7 @@ __device__ __forceinline__ void attend_unit(const AttnArgs &a, int ul, int slice
         __syncthreads();
     }
     CTKVR_STAMP(46);
-    // then over the part's kProd rows of the block, in order
+    // then over the block's waves, in order
     if (tid < G * kSliceDims) {
         int hh = tid / kSliceDims, e = tid % kSliceDims;
         float v = 0.0f, l = 0.0f;
@@ -2941,7 +2965,7 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
     uint32_t *s_list = smem + kSelLds;                     // 2 * kListCap
     uint32_t *s_bits = s_list + 2 * kListCap;              // bits_words: two bitmaps over the recalled ids
     uint2 *s_pick = (uint2 *)(s_bits + a.bits_words);      // top_k: (position among the recalled keys, row) of the picks, ascending
-    float *s_p = (float *)(s_pick + kpad);                 // top_k * G: their scores
+    float *s_p = (float *)(s_pick + kpad);                 // top_k * G: their scores (the two-pass fallback)
     int ul, slice;
     attn_block_of<SL>(ul, slice);
     const int tid = threadIdx.x, ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2959,11 +2983,19 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
     float m[G];
 #pragma unroll
     for (int hh = 0; hh < G; ++hh) m[hh] = ordered_value(a.m_key[ul * G + hh]);
-#pragma unroll
-    for (int q = 0; q < KPT; ++q) load_z<G>(zb, min(q * NT + tid, a.l_stride - 1), zr[q]);
+    // The unit's keys, as far as they are kept, and their rows: requested by the first wave now, by the others once their
+    // denominators are handed over -- a wave's requests are issued in order, 32 of them from eight waves take the CU's one
+    // address path 1.5 us, and the exchange waits for the slowest
     uint32_t rr[KPT];
+    auto request_keys = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < KPT; ++q) rr[q] = rb[min(q * NT + tid, a.l_stride - 1)];
+        for (int q = 0; q < KPT; ++q)
+            if (q * NT + wv * 64 < L) {   // uniform
+                load_z<G>(zb, min(q * NT + tid, a.l_stride - 1), zr[q]);
+                rr[q] = rb[min(q * NT + tid, a.l_stride - 1)];
+            }
+    };
+    if (wv == 0) request_keys();
     for (int w = tid; w < kBuckets / 4; w += NT) reinterpret_cast<uint4 *>(s_hist)[w] = make_uint4(0u, 0u, 0u, 0u);
     if (tid == 0) s_res[3] = 0u;
     {
@@ -3015,6 +3047,7 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
     sum_terms(i0, SL * NT, zo);
     CTKVR_STAMP(62);
     __syncthreads();
+    if (wv) request_keys();
     if (wv == 0) {
         constexpr unsigned long long kValid = 1ull << 63;   // a sum is below 2^20 * 2^40
         unsigned long long *xs = a.xs + (size_t)ul * SL * G;
@@ -3151,6 +3184,7 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
                               const uint32_t r = s_pick[max(min(t, n - 1), 0)].y;
                               return n > 0 ? r : 0u;
                           },
+                          // (the picks' scores travel with their value rows: kept in shared memory, writing them cost 0.7 us)
                           [&](int t, float(&zv)[G]) { load_z<G>(s_p, max(min(t, n - 1), 0), zv); }, [&]() { return n; });
     if (p0 + tid < p1) put_ids(p0 + tid, my_id);
     for (int pos = p0 + NT + tid; pos < p1; pos += NT) put_ids(pos, pos < n ? cb[s_pick[pos].x] : -1);
