@@ -1687,7 +1687,8 @@ template <int G> int run_kmeans_g(ctkvr_index *ix, KmeansArgs ka, hipStream_t st
     for (int it = 0; it < ix->p.kmeans_iters; ++it) {
         kmeans_halfnorm_kernel<G><<<dim3((ix->c_max + 15) / 16, U), 256, 0, st>>>(ka);
         kmeans_assign_kernel<G><<<dim3((ix->s_max + AS::kPoints - 1) / AS::kPoints, U), 256, AS::kLds, st>>>(ka);
-        kmeans_offsets_kernel<<<dim3(U), 1024, 0, st>>>(ka);
+        kmeans_rank_kernel<<<dim3(ka.n_stretch, U), 1024, (size_t)ix->c_max * 4, st>>>(ka);
+        kmeans_offsets_kernel<<<dim3(U), 1024, (size_t)ix->c_max * 4, st>>>(ka);
         kmeans_scatter_kernel<<<dim3((ix->s_max + 255) / 256, U), 256, 0, st>>>(ka);
         kmeans_reduce_kernel<G><<<dim3(ix->c_max + ka.ext_max, U), 512, 0, st>>>(ka);
     }
@@ -1710,13 +1711,15 @@ int run_kmeans(ctkvr_index *ix, const bf16_t *q_prefill, const int32_t *d_first,
     ka.centroids = (bf16_t *)ix->centroids;
     ka.init_pos = init_pos;
     ka.ext_max = ix->s_max / (int)kPartRows + 1;
+    ka.stretch = std::max(1024, (ix->s_max + kStretches - 1) / kStretches);
+    ka.n_stretch = (ix->s_max + ka.stretch - 1) / ka.stretch;
     const size_t n_sums = U * ka.ext_max * ix->G * kD;
     BuildScratch scratch_mem;
     auto lay_out = [&](unsigned char *base) {
         Carver cv{base};
         cv.take(&ka.half_norm, U * ix->c_max * 4);
         cv.take(&ka.assign, U * ix->s_max * 4);
-        cv.take(&ka.counts, U * ix->c_max * 4);
+        cv.take(&ka.counts, U * ka.n_stretch * ix->c_max * 4);
         cv.take(&ka.start, U * ix->c_max * 4);
         cv.take(&ka.rank, U * ix->s_max * 4);
         cv.take(&ka.order, U * ix->s_max * 4);
@@ -1730,7 +1733,6 @@ int run_kmeans(ctkvr_index *ix, const bf16_t *q_prefill, const int32_t *d_first,
     int rc = scratch_mem.get(ix->dev, lay_out(nullptr));
     if (rc == CTKVR_OK) {
         lay_out(scratch_mem.base());
-        fill_u32_kernel<<<dim3((unsigned)((U * ix->c_max + 255) / 256)), 256, 0, st>>>(ka.counts, 0u, U * ix->c_max);
         fill_u32_kernel<<<dim3((unsigned)((n_sums * 2 + 255) / 256)), 256, 0, st>>>((uint32_t *)ka.sums, 0u, n_sums * 2);
         fill_u32_kernel<<<dim3((unsigned)((U * ka.ext_max + 255) / 256)), 256, 0, st>>>(ka.done, 0u, U * ka.ext_max);
         switch (ix->G) {

@@ -2,8 +2,8 @@
 // paper itself takes the last C prompt queries).  Per (sequence, KV head) the s
 // prompt positions are clustered; a point is the concatenation of the G query-head
 // vectors of the group at one position (G*128 numbers, contiguous in q_prefill).
-// Lloyd iteration = half-norms -> assignment on the matrix cores (which also counts the
-// members of every centre) -> counting sort of the positions by centre -> blocks per centre, one for
+// Lloyd iteration = half-norms -> assignment on the matrix cores -> counting sort of the positions by
+// centre (ranks inside stretches of positions, offsets, scatter) -> blocks per centre, one for
 // every 256 members, sum them in fixed point and the last writes the new centre.  The centres live in the index's centroid table
 // [b][h][c_max][128] all along: head hh of centre c is one 128-element row.
 #pragma once
@@ -20,9 +20,10 @@ struct KmeansArgs {
     const int32_t *init_pos;       // [batch][g][c_max]
     float *half_norm;              // [batch*g][c_max]
     int32_t *assign;               // [batch*g][s_max]
-    uint32_t *counts;              // [batch*g][c_max] members per centre (zero before the assignment)
+    uint32_t *counts;              // [batch*g][n_stretch][c_max] members per centre in a stretch; then those in the stretches before it
+    int stretch, n_stretch;        // positions of a stretch, ceil(s_max / stretch)
     uint32_t *start;               // [batch*g][c_max] first slot of each centre in `order`
-    uint32_t *rank;                // [batch*g][s_max] which member of its centre a position is, in arrival order
+    uint32_t *rank;                // [batch*g][s_max] which member of its centre a position is in its stretch, in arrival order
     int32_t *order;                // [batch*g][s_max] positions grouped by centre
     // centres of more than kPartRows members: the blocks that sum their further parts, and where the parts meet
     uint2 *part;                   // [batch*g][ext_max] (centre, part) of the blocks behind the first c_max
@@ -33,6 +34,7 @@ struct KmeansArgs {
     int ext_max;                   // s_max / kPartRows + 1
 };
 constexpr uint32_t kPartRows = 256;
+constexpr int kStretches = 32;   // of a sequence, of at least 1024 positions each
 
 // centres start as the prompt queries at init_pos; grid (c_max, h, batch), 128 threads
 __global__ void kmeans_init_kernel(KmeansArgs a, int G)
@@ -71,14 +73,13 @@ template <int G> __global__ __launch_bounds__(256) void kmeans_halfnorm_kernel(K
 // of its four SIMDs, so with one read per instruction both are full at once.  Hence a wave holds the whole
 // points of PT = 2 column tiles in registers (256 of them at G = 4: one wave per SIMD, 512 registers) and every
 // centre fragment read feeds two instructions.  The centres go by in tiles of 32 CTN, whole (all G heads),
-// through two shared-memory buffers in fragment order -- reads and writes are linear, free of bank conflicts --,
-// the next tile requested and written while this one is multiplied, one barrier per tile.  With a
+// through two shared-memory buffers, the next tile loaded straight into shared memory while this one is multiplied, one barrier
+// per tile.  With a
 // single wave per SIMD nothing else hides the vector work, so the accumulators are two sets: the argmax of a
 // row tile runs between the matrix instructions of the next.  128K points x 2048 centres x 8 heads of G = 4: 1.86 ms,
 // 1.18 PFLOP/s (32 points a wave, two waves per SIMD, 1.95 ms).
 // With G = 8 (a point takes 256 registers) a wave has one column tile and the centre tiles are half as high.
-// Counts the members of every centre as it goes and keeps what the count was before each: the position's place among
-// them.  The accumulators start from -|mu_c|^2/2, so the result tile
+// The accumulators start from -|mu_c|^2/2, so the result tile
 // is the score itself.
 // grid (ceil(s_max / (128 PT)), batch*g), 256 threads, dynamic shared memory AssignShape<G>::kLds.
 template <int G> struct AssignShape {
@@ -86,7 +87,7 @@ template <int G> struct AssignShape {
     static constexpr int PT = G <= 4 ? 2 : 1;    // column tiles (32 points each) of a wave
     static constexpr int CTN = G <= 4 ? 2 : 1;   // row tiles (32 centres each) of a step
     static constexpr int NC = 32 * CTN;
-    static constexpr int kTile = KS * CTN * 1024;   // bytes of a centre tile
+    static constexpr int kTile = NC * G * kD * 2;   // bytes of a centre tile
     static constexpr int kLds = 2 * (kTile + NC * 4);
     static constexpr int kPoints = 4 * PT * 32;     // points of a block
 };
@@ -101,7 +102,7 @@ template <int G> __global__ __launch_bounds__(256, G <= 2 ? 2 : 1) void kmeans_a
     const int ul = blockIdx.y, b = ul / a.g, kv = ul - b * a.g;
     const int C = a.n_cent[b], s = a.ctx_lens[b];
     if ((int)blockIdx.x * S::kPoints >= s) return;
-    const int tid = threadIdx.x, wv = tid >> 6, ln = tid & 63, col = ln & 31, half = ln >> 5;
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), ln = tid & 63, col = ln & 31, half = ln >> 5;
     const int p0 = blockIdx.x * S::kPoints + wv * (PT * 32);
     bf16x8_t bfrag[PT][KS];
 #pragma unroll
@@ -111,23 +112,21 @@ template <int G> __global__ __launch_bounds__(256, G <= 2 ? 2 : 1) void kmeans_a
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) bfrag[pt][kk] = *reinterpret_cast<const bf16x8_t *>(xrow + kk * 16);
     }
-    // Staging: a tile is NC rows of 2 KS 16-byte pieces; a wave moves 8 rows x 8 pieces at a time (128 contiguous
-    // bytes of a row each), lane l row l % 8 and piece l / 8 of them.  All of a tile's moves are requested in the
-    // first quarter of a step and written in its last: with one wave per SIMD a request that is not back is waited
-    // for by everything (requested and written by quarters, 4 waits a tile, the launch took 2.4 ms).
-    constexpr int NLD = NC * 2 * KS / 256, STEPS = CTN * KS, QUARTER = STEPS / 4;
+    // Staging: a tile is 2 G lines of 128 bytes of NC rows, line after line; 16-byte piece p of a line of row r lies at
+    // p ^ swz(r), so that a fragment read (one piece of 32 rows) spreads over the banks.  Loaded straight into shared memory, eight
+    // rows of a line (1 KB, whole lines) an instruction, wave w the row groups w, w + 4, ..; all of a tile's loads are requested in
+    // the first quarter of a step and waited for at its end.  (Through registers -- 16 loads, 16 writes and 64 registers a
+    // thread and tile, in a wave that is alone on its SIMD -- the loop took 100 us per block where the products alone take 77.)
+    constexpr int RG = NC / 32, NLD = RG * 2 * G, STEPS = CTN * KS, QUARTER = STEPS / 4;   // row groups, loads of a wave
     const bf16_t *cbase = a.centroids + ((size_t)b * a.h + kv * G) * a.c_max * kD;
     const float *hnrow = a.half_norm + (size_t)ul * a.c_max;
-    // move p: rows 32 (p % CTN) .., pieces 8 (p / CTN) .. of every row
-    const int r0 = wv * 8 + (ln & 7);
-    auto fetch = [&](int p, int c0) {   // rows beyond C repeat the last centre; their accumulators start from -inf
-        const int c = min(c0 + (p % CTN) * 32 + r0, C - 1), qb = p / CTN;
-        const char *from = reinterpret_cast<const char *>(cbase + (size_t)(qb >> 1) * a.c_max * kD + (qb & 1) * 64);
-        return *reinterpret_cast<const uint4 *>(from + (uint32_t)(c * (kD * 2) + (ln >> 3) * 16));
-    };
-    unsigned char *const put_at = s_dyn + (ln >> 4) * (CTN * 1024) + ((ln >> 3) & 1) * 512 + r0 * 16;
-    auto put = [&](int p, const uint4 &x, int buf) {
-        *reinterpret_cast<uint4 *>(put_at + buf * S::kTile + ((p / CTN) * 4 * CTN + p % CTN) * 1024) = x;
+    const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char *)s_dyn);
+    auto request = [&](int p, int c0, int buf) __attribute__((always_inline)) {   // load p: row group p % RG, line p / RG
+        const int rg = wv + 4 * (p % RG), line = p / RG;
+        const int c = min(c0 + rg * 8 + (ln >> 3), C - 1);   // rows beyond C repeat the last centre; their accumulators start from -inf
+        const uint32_t piece = (uint32_t)((ln & 7) ^ (ln >> 3) ^ (rg & 1));
+        const char *from = reinterpret_cast<const char *>(cbase + (size_t)(line >> 1) * a.c_max * kD) + (line & 1) * 128;
+        load_to_lds(lds0 + buf * S::kTile + line * (NC * 128) + rg * 1024, from, (uint32_t)c * (kD * 2) + piece * 16);
     };
     auto hn_at = [&](int c0) {
         const int c = c0 + (tid & (NC - 1));
@@ -170,8 +169,15 @@ template <int G> __global__ __launch_bounds__(256, G <= 2 ? 2 : 1) void kmeans_a
         for (int pt = 0; pt < PT; ++pt) bi[pt] = best[pt] > was[pt] ? c + loc[pt] + 4 * half : bi[pt];
     };
     // one row tile: its products into cur, the scores of the one before (prev) compared on the way
-    auto row_tile = [&](f32x16_t (&cur)[PT], const f32x16_t (&prev)[PT], int ct, int buf, int c0, uint4 (&st)[NLD]) __attribute__((always_inline)) {
-        const unsigned char *tile = s_dyn + buf * S::kTile + ct * 1024 + ln * 16;
+    auto row_tile = [&](f32x16_t (&cur)[PT], const f32x16_t (&prev)[PT], int ct, int buf, int c0) __attribute__((always_inline)) {
+        // fragment kk: 8 elements of row ct * 32 + col: piece 2 (kk % 4) + half of line kk / 4
+        const uint32_t mine = (uint32_t)(col * 128 + ((half ^ (col & 7) ^ ((col >> 3) & 1)) * 16));
+        uint32_t at4[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) at4[x] = (mine ^ (x * 32)) + buf * S::kTile;
+        auto frag = [&](int kk) __attribute__((always_inline)) {
+            return *reinterpret_cast<const bf16x8_t *>(s_dyn + at4[kk & 3] + (kk >> 2) * (NC * 128) + ct * 4096);
+        };
         f32x16_t hn;
 #pragma unroll
         for (int rq = 0; rq < 4; ++rq) {
@@ -186,25 +192,20 @@ template <int G> __global__ __launch_bounds__(256, G <= 2 ? 2 : 1) void kmeans_a
         argmax_begin();
         bf16x8_t af[AHEAD];
 #pragma unroll
-        for (int kk = 0; kk < AHEAD - 1; ++kk) af[kk] = *reinterpret_cast<const bf16x8_t *>(tile + kk * CTN * 1024);
+        for (int kk = 0; kk < AHEAD - 1; ++kk) af[kk] = frag(kk);
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
             const int at = ct * KS + kk;   // of STEPS
             if (at < QUARTER) {
 #pragma unroll
-                for (int p = at * NLD / QUARTER; p < (at + 1) * NLD / QUARTER; ++p) st[p] = fetch(p, c0 + NC);
+                for (int p = at * NLD / QUARTER; p < (at + 1) * NLD / QUARTER; ++p) request(p, c0 + NC, buf ^ 1);
             }
             if (kk + AHEAD - 1 < KS)
-                af[(kk + AHEAD - 1) % AHEAD] = *reinterpret_cast<const bf16x8_t *>(tile + (kk + AHEAD - 1) * CTN * 1024);
+                af[(kk + AHEAD - 1) % AHEAD] = frag(kk + AHEAD - 1);
 #pragma unroll
             for (int pt = 0; pt < PT; ++pt)
                 cur[pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk % AHEAD], bfrag[pt][kk], cur[pt], 0, 0, 0);
             argmax_part(prev, kk * E / KS, (kk + 1) * E / KS);
-            if (at >= STEPS - QUARTER) {
-                constexpr int F = STEPS - QUARTER;
-#pragma unroll
-                for (int p = (at - F) * NLD / QUARTER; p < (at - F + 1) * NLD / QUARTER; ++p) put(p, st[p], buf ^ 1);
-            }
             __builtin_amdgcn_sched_barrier(0);   // the order written here is the schedule
         }
         argmax_end(c0 + ct * 32 - 32);
@@ -212,16 +213,17 @@ template <int G> __global__ __launch_bounds__(256, G <= 2 ? 2 : 1) void kmeans_a
     // a tile, its row tiles into x and y in turn.  The next tile goes into the other buffer (past
     // the end: the last centre again, never used).
     auto step = [&](f32x16_t (&x)[PT], f32x16_t (&y)[PT], int buf, int c0) __attribute__((always_inline)) {
-        uint4 st[NLD];
         const float hn_next = hn_at(c0 + NC);
-        row_tile(x, y, 0, buf, c0, st);
-        if constexpr (CTN == 2) row_tile(y, x, 1, buf, c0, st);
+        row_tile(x, y, 0, buf, c0);
+        if constexpr (CTN == 2) row_tile(y, x, 1, buf, c0);
         s_hn[(buf ^ 1) * NC + (tid & (NC - 1))] = hn_next;   // the four waves write the same values
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
     };
 #pragma unroll
-    for (int p = 0; p < NLD; ++p) put(p, fetch(p, 0), 0);
+    for (int p = 0; p < NLD; ++p) request(p, 0, 0);
     s_hn[tid & (NC - 1)] = hn_at(0);
+    __builtin_amdgcn_s_waitcnt(kVmcnt0);   // (the builtin: the compiler then knows that the points are there, and puts no waits into the loop)
     __syncthreads();
     int buf = 0, c0 = 0;
     if constexpr (CTN == 2) {
@@ -243,26 +245,63 @@ template <int G> __global__ __launch_bounds__(256, G <= 2 ? 2 : 1) void kmeans_a
         const int oi = __shfl_xor(bi[pt], 32);
         if (ob > best[pt] || (ob == best[pt] && oi < bi[pt])) bi[pt] = oi;
         const int t = p0 + pt * 32 + col;
-        if (half == 0 && t < s) {
-            a.assign[(size_t)ul * a.s_max + t] = bi[pt];
-            a.rank[(size_t)ul * a.s_max + t] = atomicAdd(&a.counts[(size_t)ul * a.c_max + bi[pt]], 1u);
-        }
+        if (half == 0 && t < s) a.assign[(size_t)ul * a.s_max + t] = bi[pt];
     }
 }
 
-// start[c] = number of positions assigned to centres below c; the blocks of the update behind the first c_max get
-// the further parts of the large centres.  Clears the counts for the next iteration.
-// grid batch*g, 1024 threads (C <= 8192: eight centres per thread)
+// Members of every centre in a stretch of positions, and which of them each position is, by counters in shared memory.
+// (One returning atomic per position on counters in memory, at the end of the assignment, cost every block of it
+// 4-20 us, where nothing else runs on its CU.)  grid (n_stretch, batch*g), 1024 threads, dynamic shared memory c_max words
+__global__ __launch_bounds__(1024) void kmeans_rank_kernel(KmeansArgs a)
+{
+    extern __shared__ __align__(16) uint32_t s_cnt[];
+    const int ul = blockIdx.y, b = ul / a.g, tid = threadIdx.x;
+    const int C = a.n_cent[b], s = a.ctx_lens[b];
+    for (int j = tid; j < C; j += 1024) s_cnt[j] = 0u;
+    __syncthreads();
+    const int t0 = (int)blockIdx.x * a.stretch, t1 = min(s, t0 + a.stretch);
+    const int32_t *as = a.assign + (size_t)ul * a.s_max;
+    uint32_t *rk = a.rank + (size_t)ul * a.s_max;
+    for (int t = t0 + tid; t - tid < t1; t += 4 * 1024) {   // four positions a thread requested together
+        int c[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) c[u] = as[min(t + u * 1024, s - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (t + u * 1024 < t1) rk[t + u * 1024] = atomicAdd(&s_cnt[c[u]], 1u);
+    }
+    __syncthreads();
+    uint32_t *cnt = a.counts + ((size_t)ul * a.n_stretch + blockIdx.x) * a.c_max;
+    for (int j = tid; j < C; j += 1024) cnt[j] = s_cnt[j];
+}
+
+// start[c] = number of positions assigned to centres below c; counts become the members in the stretches before each; the blocks of
+// the update behind the first c_max get the further parts of the large centres.
+// grid batch*g, 1024 threads (C <= 8192: eight centres per thread), dynamic shared memory c_max words
 __global__ __launch_bounds__(1024) void kmeans_offsets_kernel(KmeansArgs a)
 {
+    extern __shared__ __align__(16) uint32_t s_cnt[];
     __shared__ uint32_t s_tmp[32];
     const int ul = blockIdx.x, b = ul / a.g;
     const int C = a.n_cent[b], tid = threadIdx.x;
+    for (int j = tid; j < C; j += 1024) {
+        uint32_t *col = a.counts + (size_t)ul * a.n_stretch * a.c_max + j, x[kStretches], sum = 0;
+#pragma unroll
+        for (int u = 0; u < kStretches; ++u) x[u] = col[(size_t)min(u, a.n_stretch - 1) * a.c_max];
+#pragma unroll
+        for (int u = 0; u < kStretches; ++u)
+            if (u < a.n_stretch) {   // uniform
+                col[(size_t)u * a.c_max] = sum;
+                sum += x[u];
+            }
+        s_cnt[j] = sum;
+    }
+    __syncthreads();
     uint32_t c[8], mine = 0, parts = 0;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         int j = tid * 8 + q;
-        c[q] = j < C ? a.counts[(size_t)ul * a.c_max + j] : 0u;
+        c[q] = j < C ? s_cnt[j] : 0u;
         mine += c[q];
         parts += c[q] ? (c[q] - 1u) / kPartRows : 0u;
     }
@@ -276,23 +315,22 @@ __global__ __launch_bounds__(1024) void kmeans_offsets_kernel(KmeansArgs a)
         if (j < C) {
             a.start[(size_t)ul * a.c_max + j] = before;
             a.slot[(size_t)ul * a.c_max + j] = at;
-            a.counts[(size_t)ul * a.c_max + j] = 0u;
             for (uint32_t p = 1; (p * kPartRows) < c[q]; ++p) a.part[(size_t)ul * a.ext_max + at++] = make_uint2((uint32_t)j, p);
         }
         before += c[q];
     }
 }
 
-// order[start[assign[t]] + rank[t]] = t.  The order inside a centre's range is whatever the counting atomics gave: the
-// sums taken over it are integer sums.  (A second round of atomics for the places took 166 us a launch at 128K x 8
-// heads, served beyond the XCD's cache.)  grid (ceil(s_max/256), batch*g), 256 threads
+// order[start[assign[t]] + members in the stretches before + rank[t]] = t.  The order inside a centre's range is whatever the
+// counters gave: the sums taken over it are integer sums.  grid (ceil(s_max/256), batch*g), 256 threads
 __global__ __launch_bounds__(256) void kmeans_scatter_kernel(KmeansArgs a)
 {
     const int ul = blockIdx.y, b = ul / a.g;
     const int t = blockIdx.x * 256 + threadIdx.x;
     if (t >= a.ctx_lens[b]) return;
     const int c = a.assign[(size_t)ul * a.s_max + t];
-    const uint32_t pos = a.start[(size_t)ul * a.c_max + c] + a.rank[(size_t)ul * a.s_max + t];
+    const uint32_t pos = a.start[(size_t)ul * a.c_max + c] + a.counts[((size_t)ul * a.n_stretch + t / a.stretch) * a.c_max + c] +
+                         a.rank[(size_t)ul * a.s_max + t];
     a.order[(size_t)ul * a.s_max + pos] = t;
 }
 
