@@ -1139,9 +1139,12 @@ template <typename T, int G> int build_lists_exact_mfma(ctkvr_index *ix, const v
     TRY(scratch_mem.get(ix->dev, lay_out(nullptr)));
     lay_out(scratch_mem.base());
     const size_t lds = exact_list_lds(ix);
-    const bool small = ix->s_max <= 8 * 512;
-    const void *fn = small ? (const void *)exact_list_kernel<G, 512, 8> : (const void *)exact_list_kernel<G, 1024, 32>;
-    TRY(want_lds(ix->dev, fn, lds));
+    // threads of a list's block by what they hold of its keys (exact_list_kernel)
+    const int list_threads = ix->s_max <= 32 * 512 ? 512 : 1024;
+    void (*const list_kernel)(ExactListArgs) = ix->s_max <= 8 * 512    ? exact_list_kernel<G, 512, 8>
+                                               : ix->s_max <= 32 * 512 ? exact_list_kernel<G, 512, 32>
+                                                                       : exact_list_kernel<G, 1024, 32>;
+    TRY(want_lds(ix->dev, (const void *)list_kernel, lds));
     const size_t n_m = (size_t)tiles * CT * G;
     fill_u32_kernel<<<dim3((unsigned)((n_m + 255) / 256)), 256, 0, st>>>(m_key, 0u, n_m);
     for (int t0 = 0; t0 < tiles; t0 += chunk) {
@@ -1179,10 +1182,7 @@ template <typename T, int G> int build_lists_exact_mfma(ctkvr_index *ix, const v
         la.z = z;
         la.m_key = sa.m_key;
         la.lists = ix->lists;
-        if (small)
-            exact_list_kernel<G, 512, 8><<<dim3(nt * CT), 512, lds, st>>>(la);
-        else
-            exact_list_kernel<G, 1024, 32><<<dim3(nt * CT), 1024, lds, st>>>(la);
+        list_kernel<<<dim3(nt * CT), list_threads, lds, st>>>(la);
     }
     hipError_t e = hipGetLastError();
     hipError_t es = hipStreamSynchronize(st);   // the scratch is given back

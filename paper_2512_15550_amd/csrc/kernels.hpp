@@ -2759,8 +2759,12 @@ template <typename T, int G> __global__ __launch_bounds__(512) void exact_score_
 // exact_list_kernel: the list of one unit of the chunk per block: denominators of its G heads over all s scores, ranking
 // keys max_h ((z - m_h) - log S_h), the rho largest (select_keys; keys of up to KPT NT positions in registers, the
 // scores of positions beyond that are read again).  The scores are read twice, the second time mostly from the memory-side
-// cache; nothing is written but the list.  grid (chunk units), NT threads (512 for up to 4096 positions, else 1024); dynamic shared
-// memory: kSelLds + 2 kListCap + 4 ceil(s_max / 64) words
+// cache; nothing is written but the list.  Bound by the vector instructions of the exponentials (about 16 us a list of 32K and a
+// CU) and by the latencies of a block's phases, which other blocks on the CU hide: 512 threads up to 16384 positions (two
+// blocks at 108 registers a thread; with 1024 threads one, and 6000 / 10000 / 16384 positions took 70 / 124 / 226 us where
+// this takes 38 / 87 / 177 for 1024 / 1536 / 2048 lists), beyond that 1024 threads held to 64 registers (two blocks in spite of
+// some spilled: 197 -> 176 us for 1024 lists of 32768).
+// grid (chunk units), NT threads; dynamic shared memory: kSelLds + 2 kListCap + 4 ceil(s_max / 64) words
 struct ExactListArgs {
     int g, c_max, tile0, tiles_per_bk, ct;   // ct: centroids per tile
     const int32_t *n_cent, *ctx_lens;
@@ -2770,7 +2774,7 @@ struct ExactListArgs {
     int32_t *lists;                          // [all units][c_max][rho]
 };
 
-template <int G, int NT, int KPT> __global__ __launch_bounds__(NT) void exact_list_kernel(ExactListArgs a)
+template <int G, int NT, int KPT> __global__ __launch_bounds__(NT, (NT == 1024 ? 8 : 1)) void exact_list_kernel(ExactListArgs a)
 {
     extern __shared__ __align__(16) uint32_t smem[];
     constexpr int NW = NT / 64;
