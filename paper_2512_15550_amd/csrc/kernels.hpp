@@ -2405,12 +2405,13 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(1024) void sel
 // (q NT/64 + wave) 64 + lane sit in kreg[q] of their thread (-inf beyond L and where a key is out of the running), those beyond KPT NT come from for_far (f(group of
 // 64 positions, key) for the groups of the calling wave).  Histogram over key buckets in shared memory, the deciding
 // bucket, a bitmap of the positions above it, that bucket's own keys ranked against each other, and the picks in
-// ascending order: either place(q, group, rank) for the lane's own key in kreg[q], and the function returns true, or
-// emit(rank, position) by any thread, and it returns false.  s_hist: kSelLds words whose first kBuckets are zero; s_list: 2 kListCap;
+// ascending order: either (PLACE, all keys in registers) place(q, group, rank) for the lane's own key in kreg[q], and the function
+// returns true, or emit(rank, position) by any thread, and it returns false.  Placing walks all groups of a wave, some twenty
+// instructions each: for callers that need the lane's registers.  s_hist: kSelLds words whose first kBuckets are zero; s_list: 2 kListCap;
 // s_bits: 4 ceil(L / 64); s_res: 4, s_res[3] zero.  The caller places a barrier before and after.
 // key(position) = the key's ordered image, for a crowded deciding bucket (all keys are then walked again).
 // ------------------------------------------------------------------------------
-template <int NT, int KPT, typename FarFn, typename PlaceFn, typename EmitFn, typename KeyFn>
+template <int NT, int KPT, bool PLACE, typename FarFn, typename PlaceFn, typename EmitFn, typename KeyFn>
 __device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int L, const int n_real, const int top_k, FarFn for_far,
                                             PlaceFn place, EmitFn emit, KeyFn key, uint32_t *s_hist, uint32_t *s_list, uint32_t *s_bits, uint32_t *s_res)
 {
@@ -2539,7 +2540,7 @@ __device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int 
                 atomicOr(&s_gt[id >> 5], 1u << (id & 31u));
             }
             __syncthreads();
-            if (L <= KPT * NT) {   // uniform
+            if (PLACE && L <= KPT * NT) {   // uniform
                 // every wave counts the whole bitmap (lane q: the NW groups of round q), scans it by itself, and places its
                 // own groups' picks
                 uint32_t all = 0, before = 0;
@@ -2567,8 +2568,23 @@ __device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int 
                     if (__builtin_amdgcn_inverse_ballot_w64(((uint64_t)hi << 32) | lo)) place(q, gq, pos);
                 }
                 return true;
+            } else if (2 * nw32 >= NT) {
+                // thread t owns the words [t wpt, (t + 1) wpt) of the bitmap: count, scan, emit in ascending order
+                const int wpt = (nw32 + NT - 1) / NT, w0 = min(nw32, tid * wpt), w1 = min(nw32, w0 + wpt);
+                uint32_t cnt = 0;
+                for (int w = w0; w < w1; ++w) cnt += (uint32_t)__popc(s_gt[w]);
+                uint32_t tot;
+                uint32_t pos = block_excl_scan<NT>(cnt, s_scan, &tot);
+                for (int w = w0; w < w1; ++w) {
+                    uint32_t mm = s_gt[w];
+                    while (mm) {
+                        const int bit = __ffs((int)mm) - 1;
+                        mm &= mm - 1u;
+                        emit((int)pos++, w * 32 + bit);
+                    }
+                }
             } else {
-                // thread t owns the bytes [t bpt, (t + 1) bpt) of the bitmap: count, scan, emit in ascending order
+                // the same by bytes, where there are few words
                 const unsigned char *bytes = reinterpret_cast<const unsigned char *>(s_gt);
                 const int nbyte = nw32 * 4, bpt = (nbyte + NT - 1) / NT;
                 const int b0 = min(nbyte, tid * bpt), b1 = min(nbyte, b0 + bpt);
@@ -2855,7 +2871,7 @@ template <int G, int NT, int KPT> __global__ __launch_bounds__(NT, (NT == 1024 ?
         for (int i = tid; i < a.rho; i += NT) dst[i] = a.n_init + i;
         return;
     }
-    select_keys<NT, KPT>(
+    select_keys<NT, KPT, false>(
         kreg, s, n_real, a.rho,
         [&](auto f) __attribute__((always_inline)) {
             for (int gq = KPT * NW + wv; gq * 64 < s; gq += NW) {
@@ -2913,7 +2929,7 @@ template <int NT, int KPT> __global__ __launch_bounds__(NT, 4) void key_list_ker
     for (int w = tid; w < kBuckets / 4; w += NT) reinterpret_cast<uint4 *>(s_hist)[w] = make_uint4(0u, 0u, 0u, 0u);
     if (tid == 0) s_res[3] = 0u;
     __syncthreads();
-    select_keys<NT, KPT>(
+    select_keys<NT, KPT, false>(
         kreg, s, n_real, a.rho,
         [&](auto f) __attribute__((always_inline)) {
             for (int gq = KPT * NW + wv; gq * 64 < s; gq += NW) f(gq, key_at(gq * 64 + ln));
@@ -3156,7 +3172,7 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
         __syncthreads();
     } else {
         n = a.top_k;
-        const bool placed = select_keys<NT, KPT>(
+        const bool placed = select_keys<NT, KPT, true>(
             kreg, L, L, a.top_k, for_far,
             [&](int q, int gq, uint32_t pos) __attribute__((always_inline)) {
                 s_pick[pos] = make_uint2((uint32_t)(gq * 64 + ln), rr[q]);
@@ -3315,7 +3331,7 @@ template <typename T> __global__ __launch_bounds__(kTailThreads) void dcu_select
             for (int r = tid; r < a.d.rho; r += NT) dst[r] = cb[min(r, L - 1)];
             return;
         }
-        select_keys<NT, KPT>(
+        select_keys<NT, KPT, true>(
             kreg, L, L, a.d.rho,
             [&](auto f) __attribute__((always_inline)) {
                 constexpr int NF = 8;   // rounds requested together
