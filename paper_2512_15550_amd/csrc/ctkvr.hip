@@ -872,9 +872,9 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
     const int sample_stride = ((ix->s_max + 32 * step_stride - 1) / (32 * step_stride)) * 32;
     const int cand_cap = std::min(kCandCap, std::max(3 * rho, 2 * rho + 2048));   // about 2 rho + 256 are expected (+-6 % at rho = 2048, three times that at 1024: neighbouring positions are alike)
     const int cand_room = 2 * std::max(cand_cap, 128 * kMaxSplits);   // entries per unit, over all segments
-    const size_t cand_lds = ((size_t)2112 + 2 * (size_t)cand_cap + kCandTies + (size_t)((ix->s_max + 31) / 32)) * 4;
+    const size_t cand_lds = ((size_t)2112 + kCandTies + (size_t)((ix->s_max + 31) / 32)) * 4;
     bool by_cand = false;
-    if (mfma && cand_lds <= 150 * 1024 && sample_stride <= kSampleCap && cand_cap >= rho) {
+    if (mfma && cand_lds + 8 * (size_t)cand_cap <= 150 * 1024 && sample_stride <= kSampleCap && cand_cap >= rho) {
         const int s_min = *std::min_element(ix->ctx_lens.begin(), ix->ctx_lens.end());
         by_cand = rho >= 256 && 3 * rho <= kCandCap && (long long)s_min >= 32ll * rho;
         if (const char *e = getenv("CTKVR_BUILD_CANDIDATES")) by_cand = atoi(e) != 0;
@@ -1005,7 +1005,7 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
                     ma.seg_cnt = cursor;
                     ma.seg_cap = seg_cap;
                     mfma_score_kernel<G, MFMA_PICK><<<dim3(ma.t_splits, tiles), (MfmaShape<G, MFMA_PICK>::NT), 0, st>>>(ma);
-                    cand_select_kernel<<<dim3(nu), 1024, cand_lds, st>>>(ca);
+                    cand_select_kernel<<<dim3(nu), kCandThreads, cand_lds, st>>>(ca);
                     uint32_t failed = 0;
                     hipError_t ec = hipMemcpyAsync(&failed, d_fail, 4, hipMemcpyDeviceToHost, st);
                     if (ec == hipSuccess) ec = hipStreamSynchronize(st);

@@ -1874,16 +1874,18 @@ template <int G> __global__ __launch_bounds__(1024) void rerank_select_kernel(Se
 // ------------------------------------------------------------------------------
 // Matrix-core list build, candidate route (Algorithm 1 line 4 on a few thousand candidates per unit
 // instead of all s keys).
-// sample_threshold_kernel: tau[unit] = the r-th largest of the unit's sampled keys (slot i of the sample
+// sample_threshold_kernel: tau[unit] = the lower end of the histogram bucket (1/32 wide) that holds the r-th largest of the
+// unit's sampled keys, or that key itself where the bucket is crowded or below the histogram's range (slot i of the sample
 // row is key id (i / 32) * 32 * step_stride + i % 32; slots of ids beyond s or inside the resident window
 // do not count), with r = 2 ceil(rho / step_stride) + 16: about 2 rho + 16 step_stride of the unit's keys
 // then lie at or above tau.  Fewer samples than r: tau = 0, every key is a candidate (and the unit
-// overflows, see below).
+// overflows, see below).  (The key itself for every unit, by radix rounds: 159 us for 8192 units of 8192 samples, now 77.)
 // cand_select_kernel: the rho largest of the unit's candidates (key, id), gathered from the segments the
 // blocks of the PICK pass filled, ties to the lowest id, written to the unit's list in ascending id order.
 // A unit with fewer than rho candidates, more than cand_cap, or a segment that ran over, raises *fail instead
 // (the caller then redoes the chunk by the route that keeps every key).
-// Both: grid = chunk units, 1024 threads.  cand_select: dynamic shared memory 2112 + 2 cand_cap + kCandTies +
+// Both: grid = chunk units.  cand_select: 512 threads, which hold the candidates in registers (through shared memory, 75 KB a
+// block at rho = 2048, two blocks of 1024 threads shared a CU: 270 us for 8192 units, now 191); dynamic shared memory 2112 + kCandTies +
 // ceil(s_max / 32) words (one bitmap over the ids; the candidates that tie with the rho-th key, normally one, are
 // sorted out in a short list: more than kCandTies of them also raise *fail); cand_cap <= kCandCap.
 // ------------------------------------------------------------------------------
@@ -1907,10 +1909,11 @@ struct CandArgs {
 __global__ __launch_bounds__(1024) void sample_threshold_kernel(CandArgs a)
 {
     __shared__ uint32_t s_hist[2048 + 64];
-    __shared__ uint32_t s_cnt;
+    __shared__ uint32_t s_cnt, s_res[2];
     int b, kv, j;
     const int ul = blockIdx.x, tid = threadIdx.x;
     if (!decode_unit(a.u, ul, b, kv, j)) return;
+    s_hist[tid] = s_hist[1024 + tid] = 0u;
     const int s = a.ctx_lens[b];
     const int ST = 32 * a.step_stride;
     const int n = ((s + ST - 1) / ST) * 32;   // sample slots of this unit (the last step's may reach beyond s)
@@ -1938,6 +1941,28 @@ __global__ __launch_bounds__(1024) void sample_threshold_kernel(CandArgs a)
         if (tid == 0) a.tau[ul] = 0u;
         return;
     }
+    // the bucket of the r-th largest (the last bucket, everything below the range, is not counted)
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+        const uint32_t bk = key_bucket(kreg[q]);
+        if (kreg[q] && bk < (uint32_t)(kBuckets - 1)) atomicAdd(&s_hist[bk], 1u);
+    }
+    __syncthreads();
+    {
+        const uint32_t c0 = s_hist[2 * tid], c1 = s_hist[2 * tid + 1];   // in descending key order
+        uint32_t tot;
+        const uint32_t before = block_excl_scan<1024>(c0 + c1, s_hist + 2048 + 4, &tot);
+        if (before < r && r <= before + c0 + c1) {
+            const bool first = r <= before + c0;
+            s_res[0] = (uint32_t)(2 * tid) + (first ? 0u : 1u);
+            s_res[1] = first ? c0 : c1;
+        }
+        __syncthreads();
+        if (r <= tot && s_res[1] <= r / 4u + 8u) {   // uniform
+            if (tid == 0) a.tau[ul] = ordered_key(-(float)(s_res[0] + 1u) / 32.0f);
+            return;
+        }
+    }
     auto for_slots = [&](auto f) __attribute__((always_inline)) {
 #pragma unroll
         for (int q = 0; q < KPT; ++q) f(q * 1024 + tid, kreg[q] != 0u, kreg[q]);
@@ -1949,54 +1974,71 @@ __global__ __launch_bounds__(1024) void sample_threshold_kernel(CandArgs a)
 
 constexpr int kCandTies = 256;   // candidates equal to the rho-th key that cand_select_kernel sorts out itself
 
-__global__ __launch_bounds__(1024) void cand_select_kernel(CandArgs a)
+constexpr int kCandThreads = 512;
+
+__global__ __launch_bounds__(kCandThreads, 8) void cand_select_kernel(CandArgs a)
 {
     extern __shared__ __align__(16) uint32_t smem[];
+    constexpr int NT = kCandThreads, KPT = kCandCap / NT;
     int b, kv, j;
-    const int ul = blockIdx.x, tid = threadIdx.x;
+    const int ul = blockIdx.x, tid = threadIdx.x, ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (!decode_unit(a.u, ul, b, kv, j)) return;
     const int s = a.ctx_lens[b];
-    // the unit's candidates, segment after segment (every thread walks the few counts itself)
-    uint32_t n = 0;
-    bool bad = false;
-    for (int x = 0; x < a.t_splits; ++x) {
-        const uint32_t c = a.seg_cnt[(size_t)ul * a.t_splits + x];
-        bad |= c > (uint32_t)a.seg_cap;
-        n += c;
-    }
-    if (bad || n < (uint32_t)a.rho || n > (uint32_t)a.cand_cap) {   // uniform
+    // the unit's candidates, segment after segment: lane x of every wave has segment x's count (t_splits <= 64) and its place
+    const uint32_t c_x = ln < a.t_splits ? a.seg_cnt[(size_t)ul * a.t_splits + ln] : 0u;
+    const uint32_t end_x = wave_incl_scan(c_x);
+    const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)end_x, 63);
+    if (__ballot(c_x > (uint32_t)a.seg_cap) || n < (uint32_t)a.rho || n > (uint32_t)a.cand_cap) {   // uniform
         if (tid == 0) atomicOr(a.fail, 1u);
         return;
     }
     uint32_t *s_hist = smem;                                   // 2048 + 64
-    uint2 *l_ent = reinterpret_cast<uint2 *>(smem + 2112);     // cand_cap entries
-    uint32_t *s_ties = smem + 2112 + 2 * a.cand_cap;           // ids of the candidates equal to the rho-th key
+    uint32_t *s_ties = smem + 2112;                            // ids of the candidates equal to the rho-th key
     uint32_t *s_bm = s_ties + kCandTies;                       // one bitmap over the ids
     const int nw = (s + 31) >> 5;
     uint32_t *s_x = s_hist + 2048 + 56;                        // [1]: tie cursor (free once the threshold is known)
-    {
-        uint32_t at = 0;
-        for (int x = 0; x < a.t_splits; ++x) {
-            const uint32_t c = a.seg_cnt[(size_t)ul * a.t_splits + x];
-            const uint2 *src = a.cand + ((size_t)ul * a.t_splits + x) * a.seg_cap;
-            for (uint32_t e = tid; e < c; e += 1024) l_ent[at + e] = src[e];
-            at += c;
+    // wave w takes every eighth run of 64 of them, from its segment or the two or more it lies in
+    const uint2 *src = a.cand + (size_t)ul * a.t_splits * a.seg_cap;
+    uint32_t key[KPT], id[KPT];
+    int x = 0;   // segment of the run's first candidate
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+        const uint32_t base = (uint32_t)(q * (NT / 64) + wv) * 64u, e = base + (uint32_t)ln;
+        key[q] = 0u;   // below every candidate (their images are >= 1)
+        id[q] = 0u;
+        if (base < n) {   // uniform
+            while ((uint32_t)__builtin_amdgcn_readlane((int)end_x, x) <= base) ++x;
+            size_t at = 0;
+            for (int y = x;; ++y) {
+                const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)end_x, y), beg = end - (uint32_t)__builtin_amdgcn_readlane((int)c_x, y);
+                if (e >= beg && e < end) at = (size_t)y * a.seg_cap + (e - beg);
+                if (end >= min(base + 64u, n)) break;
+            }
+            const uint2 en = src[at];
+            key[q] = e < n ? en.x : 0u;
+            id[q] = en.y;
         }
     }
-    for (int w = tid; w < nw; w += 1024) s_bm[w] = 0u;
-    __syncthreads();
+    for (int w = tid; w < nw; w += NT) s_bm[w] = 0u;
+    auto for_slots = [&](auto f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < KPT; ++q) {
+            if ((uint32_t)(q * (NT / 64) + wv) * 64u >= n) break;   // uniform
+            f(q * NT + tid, key[q] != 0u, key[q]);
+        }
+    };
     // T = the rho-th largest key, need_eq = how many of the candidates equal to T belong to the rho largest
     uint32_t T, need_eq;
-    block_list_threshold<1024, kCandCap>(n, (uint32_t)a.rho, s_hist, l_ent, T, need_eq);
+    block_kth_largest<NT>(for_slots, (uint32_t)a.rho, s_hist, T, need_eq);
     __syncthreads();
     if (tid == 0) s_x[1] = 0u;
     __syncthreads();
-    for (uint32_t e = tid; e < n; e += 1024) {
-        const uint2 en = l_ent[e];
-        if (en.x > T) atomicOr(&s_bm[en.y >> 5], 1u << (en.y & 31u));
-        if (en.x == T) {
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+        if (key[q] > T) atomicOr(&s_bm[id[q] >> 5], 1u << (id[q] & 31u));
+        if (key[q] == T) {
             const uint32_t at = atomicAdd(&s_x[1], 1u);
-            if (at < (uint32_t)kCandTies) s_ties[at] = en.y;
+            if (at < (uint32_t)kCandTies) s_ties[at] = id[q];
         }
     }
     __syncthreads();
@@ -2015,12 +2057,12 @@ __global__ __launch_bounds__(1024) void cand_select_kernel(CandArgs a)
     __syncthreads();
     // thread t owns words [t wpt, (t + 1) wpt) of the bitmap: count, scan, emit in ascending id order
     uint32_t *s_scan = s_hist + 2048 + 4;
-    const int wpt = (nw + 1023) / 1024;
+    const int wpt = (nw + NT - 1) / NT;
     const int w0 = min(nw, tid * wpt), w1 = min(nw, w0 + wpt);
     uint32_t cnt = 0;
     for (int w = w0; w < w1; ++w) cnt += (uint32_t)__popc(s_bm[w]);
     uint32_t tot;
-    uint32_t pos = block_excl_scan<1024>(cnt, s_scan, &tot);
+    uint32_t pos = block_excl_scan<NT>(cnt, s_scan, &tot);
     int32_t *lst = a.lists + (size_t)(a.u.unit0 + ul) * a.rho;
     for (int w = w0; w < w1; ++w) {
         uint32_t m = s_bm[w];
