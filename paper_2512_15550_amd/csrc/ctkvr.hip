@@ -859,6 +859,7 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
     uint32_t *m_key = nullptr;
     unsigned long long *S = nullptr;
     uint32_t *kbuf = nullptr, *ghist = nullptr;
+    float *off = nullptr;     // matrix-core route: what the pairs come to
     float2 *part = nullptr;   // matrix-core route: one (maximum, sum) pair per unit, head and block of the statistics pass
     constexpr int kMaxSplits = 64;
     // Matrix-core route, candidates only (see mfma_score_kernel): when every sequence is long against rho, so that
@@ -900,7 +901,10 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
             cv.take(&m_key, (size_t)chunk * G * 4);
             cv.take(&S, (size_t)chunk * G * 8);
         }
-        if (mfma) cv.take(&part, (size_t)chunk * G * kMaxSplits * sizeof(float2));
+        if (mfma) {
+            cv.take(&part, (size_t)chunk * G * kMaxSplits * sizeof(float2));
+            cv.take(&off, (size_t)chunk * G * 4);
+        }
         if (by_cand) {
             // a segment per block of the statistics split
             cv.take(&ksamp, (size_t)chunk * sample_stride * 4);
@@ -963,6 +967,7 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
                 ma.k = sa.k;
                 ma.l_stride = ix->s_max;
                 ma.part = part;
+                ma.off = off;
                 ma.kbuf = kbuf;
                 ma.n_init = ix->p.n_init;
                 ma.n_local = ix->p.n_local;
@@ -970,6 +975,7 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
                 ma.step_stride = 1;
                 // passes over the same tiles: softmax statistics first
                 mfma_score_kernel<G, MFMA_STAT><<<dim3(ma.t_splits, tiles), (MfmaShape<G, MFMA_STAT>::NT), 0, st>>>(ma);
+                mfma_merge_kernel<<<dim3((unsigned)((nu * G + 255) / 256)), 256, 0, st>>>(ma, nu * G);
                 bool redo = !by_cand;
                 if (by_cand) {
                     // keys of a sample of the positions -> a threshold per unit -> all keys again, those at or above

@@ -954,6 +954,7 @@ struct MfmaScoreArgs {
     Paged k;
     int l_stride;              // s_max
     float2 *part;              // [chunk units][G][t_splits] (maximum of z log2(e), sum of 2^(z log2(e) - maximum)) over a block's keys
+    float *off;                // [chunk units][G] -(m + log S) over all keys (mfma_merge_kernel)
     uint32_t *kbuf;            // KEY: [chunk units][l_stride] ranking keys; SAMPLE: [chunk units][sample_stride]
     int n_init, n_local;       // keys of the resident window get the lowest ranking key
     float scale;
@@ -1047,15 +1048,7 @@ __global__ __launch_bounds__((MfmaShape<G, MODE>::NT), (MfmaShape<G, MODE>::kWav
         for (int ks = 0; ks < 8; ++ks) cfrag[q][ks] = *reinterpret_cast<const bf16x8_t *>(row + ks * 16 + 8 * half);
         mx[q] = -__builtin_huge_valf();
         lsv[q] = off[q] = 0.0f;
-        if constexpr (KEYS) {
-            // the blocks' pairs in block order: the same value in every block that reads them
-            const float2 *pp = a.part + (((size_t)bkl * a.c_max + j) * G + head_of(q)) * a.t_splits;
-            float m = -__builtin_huge_valf();
-            for (int x = 0; x < a.t_splits && x * tper < s; ++x) m = fmaxf(m, pp[x].x);
-            float sum = 0.0f;
-            for (int x = 0; x < a.t_splits && x * tper < s; ++x) sum += pp[x].y * __builtin_amdgcn_exp2f(pp[x].x - m);
-            off[q] = -(m * 0.693147180559945309f + logf(sum));   // the pairs hold base-two maxima
-        }
+        if constexpr (KEYS) off[q] = a.off[((size_t)bkl * a.c_max + j) * G + head_of(q)];
     }
     float tau[SUB];
     uint2 *seg[SUB];   // PICK: the block's segment of the lane's centroid
@@ -1266,6 +1259,28 @@ __global__ __launch_bounds__((MfmaShape<G, MODE>::NT), (MfmaShape<G, MODE>::kWav
             if (j < C) a.part[(((size_t)bkl * a.c_max + j) * G + head_of(q)) * a.t_splits + blockIdx.x] = make_float2(m, l);
         }
     }
+}
+
+// -(m + log S) of every (centroid, head) of a chunk from the blocks' pairs of the statistics pass, in block order.  (Made by every
+// block of the two passes behind it, before its first product, it was most of their time where a tile has many blocks:
+// 50K tokens, 700 centroids, 24 blocks a tile: sample pass 157 -> 49 us, candidate pass 312 -> 214,
+// all keys 400 -> 304; 128K, 2048 centroids, 8 blocks a tile: 160 -> 118, 1241 -> 1180, 1774 -> 1733; this kernel 7 to 9.)
+// grid ceil(chunk units * G / 256), 256 threads
+__global__ __launch_bounds__(256) void mfma_merge_kernel(MfmaScoreArgs a, int n)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    const int u = i / a.G, bkl = u / a.c_max, b = (a.bk0 + bkl) / a.g, s = a.ctx_lens[b];
+    if (u - bkl * a.c_max >= a.n_cent[b]) return;
+    const int tper = (((s + a.t_splits - 1) / a.t_splits) + 31) & ~31, nx = min(a.t_splits, (s + tper - 1) / tper);
+    const float2 *pp = a.part + (size_t)i * a.t_splits;
+    float m = -__builtin_huge_valf();
+#pragma unroll 8
+    for (int x = 0; x < nx; ++x) m = fmaxf(m, pp[x].x);
+    float sum = 0.0f;
+#pragma unroll 8
+    for (int x = 0; x < nx; ++x) sum += pp[x].y * __builtin_amdgcn_exp2f(pp[x].x - m);
+    a.off[i] = -(m * 0.693147180559945309f + logf(sum));   // the pairs hold base-two maxima
 }
 
 // ------------------------------------------------------------------------------
