@@ -862,12 +862,15 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
     float *off = nullptr;     // matrix-core route: what the pairs come to
     float2 *part = nullptr;   // matrix-core route: one (maximum, sum) pair per unit, head and block of the statistics pass
     constexpr int kMaxSplits = 64;
-    // Matrix-core route, candidates only (see mfma_score_kernel): when every sequence is long against rho, so that
-    // about 2 rho candidates are a small part of its keys and a 1-in-16 sample of the positions places the threshold
-    // well, and the selection's bitmaps and candidate list fit the shared memory.  Every key against candidates, lists of
-    // 1024 keys, C = s / 64, one to eight heads a group: 30K 0.66..0.80 / 0.75..1.13 ms, 40K 1.08..1.35 / 1.04..1.49,
-    // 50K 1.61..2.05 / 1.37..1.81, 90K 4.9..7.3 / 2.8..3.5 ms.  CTKVR_BUILD_CANDIDATES=0/1 forces the choice where the second
-    // condition allows it.
+    // Matrix-core route, candidates only (see mfma_score_kernel): when the lists are short against the contexts, so that about
+    // 2 rho candidates are a small part of the keys (a 1-in-16 sample of the positions places the threshold), and the keys of
+    // all lists enough to pay for the two passes and the wait that it has more.  Every key against candidates, whole builds in
+    // us, C = s / 64, 8 KV heads, four query heads each unless noted:
+    //   lists of 1024, one context: 16K 262 / 281, 20K (50 M keys) 363 / 364, 22K 468 / 416, 25K 597 / 482 (one head 502 / 366,
+    //   eight 825 / 776), 30K 778 / 524, 40K 1307 / 820; three of 9K..30K 1128 / 859, four of 2K..30K 1194 / 900;
+    //   contexts against list length: 4 x 8192 tokens, 512 centroids (8 : 1) 902 / 973, 4 x 12K (12 : 1) 578 / 545,
+    //   the same with lists of 2048 (6 : 1) 594 / 633, 4 x 16K with 512 (31 : 1) 822 / 644.
+    // CTKVR_BUILD_CANDIDATES=0/1 forces the choice where the first condition allows it.
     const int rho = ix->p.list_len;
     const int step_stride = std::max(16, ((ix->s_max + 31) / 32 + 255) / 256);
     const int sample_stride = ((ix->s_max + 32 * step_stride - 1) / (32 * step_stride)) * 32;
@@ -876,14 +879,28 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
     const size_t cand_lds = ((size_t)2112 + kCandTies + (size_t)((ix->s_max + 31) / 32)) * 4;
     bool by_cand = false;
     if (mfma && cand_lds + 8 * (size_t)cand_cap <= 150 * 1024 && sample_stride <= kSampleCap && cand_cap >= rho) {
-        const int s_min = *std::min_element(ix->ctx_lens.begin(), ix->ctx_lens.end());
-        by_cand = rho >= 256 && 3 * rho <= kCandCap && (long long)s_min >= 32ll * rho;
+        long long lists = 0, keys = 0;
+        for (int b = 0; b < ix->p.batch; ++b) {
+            const long long n = (long long)ix->p.n_kv_heads * ix->n_cent[b];
+            lists += n;
+            keys += n * ix->ctx_lens[b];
+        }
+        by_cand = rho >= 256 && 3 * rho <= kCandCap && keys >= 60000000ll && keys >= 10ll * rho * lists;
         if (const char *e = getenv("CTKVR_BUILD_CANDIDATES")) by_cand = atoi(e) != 0;
     }
     ix->build_by_cand = by_cand;
     // one block per list behind the keys, where its bitmap of the context fits the shared memory (to 515072 tokens)
     const bool by_list = mfma && exact_list_lds(ix) <= 150 * 1024;
-    if (by_cand) chunk = std::min(chunk, 4 * ix->c_max);   // half the scratch, as fast
+    if (by_cand) {
+        // chunks of about equal size, of 8192 units at most or four (sequence, KV head) groups, whichever is more: enough to
+        // fill the card in every pass, at 1 GB of candidates (four groups whatever their size, each chunk
+        // waited for: 30K tokens, 468 centroids 649 us, now 524; 4 x 16K 1254, now 644)
+        int groups = std::min(chunk / ix->c_max, std::max(4, 8192 / ix->c_max));
+        const int n = (ix->units + groups - 1) / groups;
+        groups = (ix->units + n - 1) / n;
+        chunk = groups * ix->c_max;
+    }
+    const int n_chunks = (total_units + chunk - 1) / chunk;
     const bool redo_always = by_cand && getenv("CTKVR_BUILD_CANDIDATES_REDO") != nullptr;   // tests: take the redo path
     uint32_t *ksamp = nullptr, *tau = nullptr, *cursor = nullptr, *d_fail = nullptr;
     uint2 *cand = nullptr;
@@ -910,7 +927,7 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
             cv.take(&ksamp, (size_t)chunk * sample_stride * 4);
             cv.take(&tau, (size_t)chunk * 4);
             cv.take(&cursor, (size_t)chunk * kMaxSplits * 4);
-            cv.take(&d_fail, 4);
+            cv.take(&d_fail, (size_t)n_chunks * 4);
             cv.take(&cand, (size_t)chunk * cand_room * sizeof(uint2));
         } else {
             if (!mfma) cv.take(&z, (size_t)chunk * per_unit);
@@ -926,7 +943,32 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
                                : ix->s_max <= 32 * 512 ? (const void *)key_list_kernel<512, 32>
                                : ix->s_max <= 64 * 512 ? (const void *)key_list_kernel<512, 64>
                                                        : (const void *)key_list_kernel<1024, 32>, exact_list_lds(ix));
-    for (int u0 = 0; rc == CTKVR_OK && u0 < total_units; u0 += chunk) {
+    // The candidate route goes through all chunks first; a second round takes those it had to hand back by the route that
+    // keeps every key.
+    std::vector<uint32_t> again(n_chunks, 0u);
+    for (int at = 0, round = 0; rc == CTKVR_OK; ++at) {
+        if (at == n_chunks) {
+            if (!by_cand || round == 1) break;
+            hipError_t ec = hipMemcpyAsync(again.data(), d_fail, (size_t)n_chunks * 4, hipMemcpyDeviceToHost, st);
+            if (ec == hipSuccess) ec = hipStreamSynchronize(st);
+            if (ec != hipSuccess) {
+                rc = fail(CTKVR_EHIP, "build: %s", hipGetErrorString(ec));
+                break;
+            }
+            for (uint32_t &x : again) {
+                if (redo_always) x = 1u;
+                ix->build_redone += x != 0u;
+            }
+            if (std::all_of(again.begin(), again.end(), [](uint32_t x) { return x == 0u; })) break;
+            rc = redo_mem.get(ix->dev, lay_out_full(nullptr));
+            if (rc != CTKVR_OK) break;
+            lay_out_full(redo_mem.base());
+            round = 1;
+            at = 0;
+        }
+        if (round == 1 && !again[at]) continue;
+        const bool pick = by_cand && round == 0;
+        const int u0 = at * chunk;
         const int nu = std::min(chunk, total_units - u0);
         Units u = decode_units(ix);
         u.build = 1;
@@ -976,8 +1018,7 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
                 // passes over the same tiles: softmax statistics first
                 mfma_score_kernel<G, MFMA_STAT><<<dim3(ma.t_splits, tiles), (MfmaShape<G, MFMA_STAT>::NT), 0, st>>>(ma);
                 mfma_merge_kernel<<<dim3((unsigned)((nu * G + 255) / 256)), 256, 0, st>>>(ma, nu * G);
-                bool redo = !by_cand;
-                if (by_cand) {
+                if (pick) {
                     // keys of a sample of the positions -> a threshold per unit -> all keys again, those at or above
                     // the threshold kept -> the rho largest of them, exactly
                     ma.kbuf = ksamp;
@@ -1001,9 +1042,7 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
                     ca.t_splits = ma.t_splits;
                     ca.seg_cap = seg_cap;
                     ca.lists = ix->lists;
-                    ca.fail = d_fail;
-                    fill_u32_kernel<<<dim3(1), 64, 0, st>>>(d_fail, 0u, 1);
-                    fill_u32_kernel<<<dim3((unsigned)(((size_t)nu * ma.t_splits + 255) / 256)), 256, 0, st>>>(cursor, 0u, (size_t)nu * ma.t_splits);
+                    ca.fail = d_fail + at;
                     sample_threshold_kernel<<<dim3(nu), 1024, 0, st>>>(ca);
                     ma.step_stride = 1;
                     ma.tau = tau;
@@ -1012,25 +1051,7 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
                     ma.seg_cap = seg_cap;
                     mfma_score_kernel<G, MFMA_PICK><<<dim3(ma.t_splits, tiles), (MfmaShape<G, MFMA_PICK>::NT), 0, st>>>(ma);
                     cand_select_kernel<<<dim3(nu), kCandThreads, cand_lds, st>>>(ca);
-                    uint32_t failed = 0;
-                    hipError_t ec = hipMemcpyAsync(&failed, d_fail, 4, hipMemcpyDeviceToHost, st);
-                    if (ec == hipSuccess) ec = hipStreamSynchronize(st);
-                    if (ec != hipSuccess) {
-                        rc = fail(CTKVR_EHIP, "build: %s", hipGetErrorString(ec));
-                        break;
-                    }
-                    redo = failed != 0 || redo_always;
-                    if (redo) {
-                        ix->build_redone++;
-                        if (!kbuf) {
-                            rc = redo_mem.get(ix->dev, lay_out_full(nullptr));
-                            if (rc != CTKVR_OK) break;
-                            lay_out_full(redo_mem.base());
-                        }
-                        if (ghist) fill_u32_kernel<<<dim3((unsigned)(((size_t)nu * kBuckets + 255) / 256)), 256, 0, st>>>(ghist, 0u, (size_t)nu * kBuckets);
-                    }
-                }
-                if (redo) {   // every key stored, then histogram and selection over all of them
+                } else {   // every key stored, then histogram and selection over all of them
                     ma.kbuf = kbuf;
                     mfma_score_kernel<G, MFMA_KEY><<<dim3(ma.t_splits, tiles), (MfmaShape<G, MFMA_KEY>::NT), 0, st>>>(ma);
                     keys_written = true;

@@ -1915,10 +1915,10 @@ struct CandArgs {
     const uint32_t *ksamp;    // [chunk units][sample_stride]
     uint32_t *tau;            // [chunk units]
     const uint2 *cand;        // [chunk units][t_splits][seg_cap]
-    const uint32_t *seg_cnt;  // [chunk units][t_splits], zero where no block wrote
+    uint32_t *seg_cnt;        // [chunk units][t_splits], zeroed by sample_threshold_kernel for the segments no block writes
     int t_splits, seg_cap;
     int32_t *lists;           // [all units][rho]
-    uint32_t *fail;           // [1]
+    uint32_t *fail;           // [1], zeroed by sample_threshold_kernel
 };
 
 __global__ __launch_bounds__(1024) void sample_threshold_kernel(CandArgs a)
@@ -1927,6 +1927,8 @@ __global__ __launch_bounds__(1024) void sample_threshold_kernel(CandArgs a)
     __shared__ uint32_t s_cnt, s_res[2];
     int b, kv, j;
     const int ul = blockIdx.x, tid = threadIdx.x;
+    if (tid < a.t_splits) a.seg_cnt[(size_t)ul * a.t_splits + tid] = 0u;   // for the candidate pass
+    if (ul == 0 && tid == 0) *a.fail = 0u;
     if (!decode_unit(a.u, ul, b, kv, j)) return;
     s_hist[tid] = s_hist[1024 + tid] = 0u;
     const int s = a.ctx_lens[b];

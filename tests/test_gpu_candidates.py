@@ -35,3 +35,37 @@ def test_candidates_give_the_lists_of_all_keys(h, g, s, C, rho, keys, n_init, n_
         ck.ctkvr_free(idx)
     assert np.array_equal(got[0], got[1])
     assert got[0].min() >= n_init and got[0].max() < s - n_local and (np.diff(got[0], axis=-1) > 0).all()
+
+
+@pytest.mark.parametrize("lens,h,g,C,rho,flat", [
+    ((12000, 2001, 5003), 8, 2, 0, 1000, None),     # short ones beside a long one: every key, or most, a candidate
+    ((3000, 3100), 4, 4, 1100, 256, None), ((3000, 3100), 4, 4, 1100, 256, 0), ((3100, 3000), 4, 4, 1100, 256, 1)])   # two chunks, one handed back
+def test_ragged_batches_and_single_chunks_handed_back(lens, h, g, C, rho, flat, monkeypatch):
+    wl = small_workload("cand_ragged", "bf16", h, g, lens, tuple(range(730, 730 + len(lens))), C, 64, 4, rho, 60, 1)
+    bt = gen_batch(wl)
+    if flat is not None:
+        bt.seqs[flat].K[:] = bt.seqs[flat].K[:, :1]
+        bt = Batch(wl=wl, seqs=bt.seqs, paged=paginate(bt.seqs, wl.page_size, 7))
+    db = H.device_batch(bt)
+    got = []
+    for cand in ("0", "1"):
+        monkeypatch.setenv("CTKVR_BUILD_CANDIDATES", cand)
+        idx = ck.ctkvr_build_index(H.params_of(wl, build_algo=ck.BUILD_MFMA), db.q_prefill, db.cu_seqlens, True, db.k_pages, db.block_table,
+                                   db.ctx_lens)
+        assert ck.ctkvr_index_build_route(idx) == (cand == "1", int(cand == "1" and flat is not None))
+        lists = ck.ctkvr_index_lists(idx)
+        got.append([lists[b, :, :wl.centroids_of(s)].copy() for b, s in enumerate(lens)])
+        ck.ctkvr_free(idx)
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("s,C,rho,want", [(30000, 1000, 700, True), (29000, 1000, 700, False), (30000, 1000, 255, False), (16000, 2000, 1700, False)])
+def test_the_route_is_chosen_by_keys_and_their_share(s, C, rho, want, monkeypatch):
+    """Two KV heads: 60 M keys or more, ten of them for each one listed."""
+    monkeypatch.delenv("CTKVR_BUILD_CANDIDATES", raising=False)
+    wl = small_workload("cand_rule", "bf16", 2, 2, (s,), (760,), C, 0, 4, rho, 60, 1)
+    db = H.device_batch(gen_batch(wl))
+    idx = ck.ctkvr_build_index(H.params_of(wl, build_algo=ck.BUILD_MFMA), db.q_prefill, db.cu_seqlens, True, db.k_pages, db.block_table, db.ctx_lens)
+    assert ck.ctkvr_index_build_route(idx)[0] == want
+    ck.ctkvr_free(idx)
