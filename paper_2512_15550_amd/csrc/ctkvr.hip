@@ -1155,12 +1155,12 @@ template <typename T, int G> int build_lists_exact_mfma(ctkvr_index *ix, const v
     const size_t per_tile = (size_t)CT * G * z_stride * 4;
     const int chunk = (int)std::min<size_t>(tiles, std::max<size_t>(1, kExactChunkBytes / per_tile));
     float *z = nullptr;
-    uint32_t *m_key = nullptr;
+    uint32_t *m_part = nullptr;
     BuildScratch scratch_mem;
     auto lay_out = [&](unsigned char *base) {
         Carver cv{base};
         cv.take(&z, (size_t)chunk * per_tile);
-        cv.take(&m_key, (size_t)tiles * CT * G * 4);
+        cv.take(&m_part, (size_t)std::max(chunk, ix->num_cu) * CT * G * 4);   // t_splits x tiles of a chunk <= CUs, or one split
         return cv.off;
     };
     TRY(scratch_mem.get(ix->dev, lay_out(nullptr)));
@@ -1172,8 +1172,6 @@ template <typename T, int G> int build_lists_exact_mfma(ctkvr_index *ix, const v
                                                : ix->s_max <= 32 * 512 ? exact_list_kernel<G, 512, 32>
                                                                        : exact_list_kernel<G, 1024, 32>;
     TRY(want_lds(ix->dev, (const void *)list_kernel, lds));
-    const size_t n_m = (size_t)tiles * CT * G;
-    fill_u32_kernel<<<dim3((unsigned)((n_m + 255) / 256)), 256, 0, st>>>(m_key, 0u, n_m);
     for (int t0 = 0; t0 < tiles; t0 += chunk) {
         const int nt = std::min(chunk, tiles - t0);
         ExactScoreArgs sa{};
@@ -1183,15 +1181,15 @@ template <typename T, int G> int build_lists_exact_mfma(ctkvr_index *ix, const v
         sa.tile0 = t0;
         sa.tiles_per_bk = tiles_per_bk;
         // one round of blocks, one per CU (eight waves of 64-register fragments; a block's prologue costs as much as four of
-        // its steps), of at least two steps of 32 keys each
-        sa.t_splits = std::max(1, std::min((ix->s_max + 63) / 64, ix->num_cu / nt));
+        // its steps), of at least one step of 32 keys each (4096 tokens, 64 centroids, two KV heads: 16.8 us, of two steps 20.6)
+        sa.t_splits = std::max(1, std::min((ix->s_max + 31) / 32, ix->num_cu / nt));
         sa.n_cent = ix->d_n_cent;
         sa.ctx_lens = ix->d_ctx_lens;
         sa.centroids = ix->centroids;
         sa.k = Paged{k_pages, block_table, max_pages, ix->page_shift};
         sa.z_stride = z_stride;
         sa.z = z;
-        sa.m_key = m_key + (size_t)t0 * CT * G;
+        sa.m_part = m_part;
         sa.scale = ix->scale;
         exact_score_kernel<T, G><<<dim3(sa.t_splits, nt), 512, 0, st>>>(sa);
         ExactListArgs la{};
@@ -1207,7 +1205,8 @@ template <typename T, int G> int build_lists_exact_mfma(ctkvr_index *ix, const v
         la.n_init = ix->p.n_init;
         la.n_local = ix->p.n_local;
         la.z = z;
-        la.m_key = sa.m_key;
+        la.t_splits = sa.t_splits;
+        la.m_part = m_part;
         la.lists = ix->lists;
         list_kernel<<<dim3(nt * CT), list_threads, lds, st>>>(la);
     }

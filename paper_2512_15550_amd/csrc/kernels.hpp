@@ -2676,7 +2676,9 @@ __device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int 
 // bit differs), so the fixed dot product -- sixteen chains of eight fused multiply-adds, combined as a balanced tree -- is
 // sixteen groups of four such instructions, each group from zero, and fifteen vector adds.
 // exact_score_kernel: z[unit][head][key] = (c . k) scale for a chunk of tiles of CT = 32 (8 / G) centroids of one
-// (sequence, KV head), all its G heads and all s keys, and each unit's and head's maximum.  Eight waves, each with one item of 32
+// (sequence, KV head), all its G heads and all s keys, and the block's maximum of each unit and head, for exact_list_kernel to merge
+// (as atomics, with few lists the blocks of all keys met on a few lines: 4096 tokens, 64 centroids, two KV heads 39.2 -> 20.6 us,
+// 8192 tokens, 128 centroids, one 71 -> 22; large builds the same).  Eight waves, each with one item of 32
 // centroids of one head, whose fragments stay in 64 registers (a lane needs every other element: the instruction's two
 // k's sit in the two halves of a wave); the keys go by 32 at a time through shared memory as fp32, even and odd elements of
 // each group of eight apart so that a fragment is one 16-byte read.  Bound by the matrix pipe (64 instructions of 64 clocks
@@ -2694,7 +2696,7 @@ struct ExactScoreArgs {
     Paged k;
     int z_stride;              // floats per (unit, head) row: a multiple of 4, >= s_max
     float *z;                  // [chunk units = tiles * CT][G][z_stride]
-    uint32_t *m_key;           // [chunk units][G] ordered-key maxima, zero on entry
+    uint32_t *m_part;          // [chunk units][t_splits][G] ordered keys of the blocks' maxima
     float scale;
 };
 
@@ -2818,7 +2820,9 @@ template <typename T, int G> __global__ __launch_bounds__(512) void exact_score_
     for (int t0 = tbeg + 64; t0 < tend; t0 += 64) pair(t0, true);
 #pragma unroll
     for (int r = 0; r < 16; ++r) row_out(r, false, lane_off + (uint32_t)pt * 4u);
-    // the maxima over the wave's 32 keys of a row: DPP inside rows of 16 lanes, then the two rows of a half
+    // the maxima over the wave's 32 keys of a row: DPP inside rows of 16 lanes, then the two rows of a half; lane r of a half
+    // stores row r's
+    uint32_t own = 0;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         float v = mx[r];
@@ -2827,8 +2831,9 @@ template <typename T, int G> __global__ __launch_bounds__(512) void exact_score_
         v = fmaxf(v, dpp_f<0x141>(v));
         v = fmaxf(v, dpp_f<0x140>(v));
         v = fmaxf(v, __shfl_xor(v, 16));
-        if (col == r) atomicMax(&a.m_key[(unit0 + 4 * half + 8 * (r >> 2) + (r & 3)) * G + hh], ordered_key(v));
+        own = col == r ? ordered_key(v) : own;
     }
+    if (col < 16) a.m_part[((unit0 + 4 * half + 8 * (col >> 2) + (col & 3)) * a.t_splits + blockIdx.x) * G + hh] = own;
 }
 
 // exact_list_kernel: the list of one unit of the chunk per block: denominators of its G heads over all s scores, ranking
@@ -2845,7 +2850,8 @@ struct ExactListArgs {
     const int32_t *n_cent, *ctx_lens;
     int z_stride, rho, n_init, n_local;
     const float *z;
-    const uint32_t *m_key;
+    int t_splits;                            // of exact_score_kernel
+    const uint32_t *m_part;
     int32_t *lists;                          // [all units][c_max][rho]
 };
 
@@ -2863,9 +2869,21 @@ template <int G, int NT, int KPT> __global__ __launch_bounds__(NT, (NT == 1024 ?
     if (j >= a.n_cent[b]) return;
     const int s = a.ctx_lens[b];
     const float *zb = a.z + (size_t)ul * G * a.z_stride;
+    // the maxima over the scoring blocks that had keys, in every wave
     float m[G];
+    {
+        const int tper = (((s + a.t_splits - 1) / a.t_splits) + 31) & ~31, nx = min(a.t_splits, (s + tper - 1) / tper);
+        const uint32_t *pp = a.m_part + (size_t)ul * a.t_splits * G;
+        uint32_t mk[G];
 #pragma unroll
-    for (int hh = 0; hh < G; ++hh) m[hh] = ordered_value(a.m_key[(size_t)ul * G + hh]);
+        for (int hh = 0; hh < G; ++hh) mk[hh] = 0u;
+        for (int x = ln; x < nx; x += 64) {
+#pragma unroll
+            for (int hh = 0; hh < G; ++hh) mk[hh] = max(mk[hh], pp[x * G + hh]);
+        }
+#pragma unroll
+        for (int hh = 0; hh < G; ++hh) m[hh] = ordered_value(wave_fold_uniform(mk[hh], [](uint32_t x, uint32_t y) { return max(x, y); }));
+    }
     for (int w = tid; w < kBuckets / 4; w += NT) reinterpret_cast<uint4 *>(s_hist)[w] = make_uint4(0u, 0u, 0u, 0u);
     if (tid == 0) s_res[3] = 0u;
     // denominators: four keys per load, two loads in flight per head (terms beyond s count as none)
