@@ -511,7 +511,7 @@ size_t carve_step_ws(StepWs &w, unsigned char *base, const ctkvr_index *ix)
     take(&w.cand, U * L * 4);
     take(&w.ncand, U * 4);
     take(&w.z, U * LS * G * 4);
-    take(&w.m_key, U * G * 4);
+    take(&w.m_key, U * kMaxStride * 4);
     take(&w.crow, U * LS * 4);
     take(&w.gbits, U * (size_t)ix->bitmap_words * 4);
     take(&w.kbuf, U * L * 4);
@@ -522,7 +522,7 @@ size_t carve_step_ws(StepWs &w, unsigned char *base, const ctkvr_index *ix)
     take(&w.ginfo, U * 16);
     take(&w.win, U * (size_t)kWinSplit * G * (2 + 128) * 4);
     take(&w.srow, U * p.top_k * 4);
-    take(&w.S, U * G * 8);
+    take(&w.S, U * kSumStride * 8);
     take(&w.xs, U * G * 8 * 8);
     take(&w.sel, U * p.top_k * 4);
     take(&w.zsel, U * p.top_k * G * 4);
@@ -915,8 +915,8 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
     auto lay_out = [&](unsigned char *base) {
         Carver cv{base};
         if (!mfma) {
-            cv.take(&m_key, (size_t)chunk * G * 4);
-            cv.take(&S, (size_t)chunk * G * 8);
+            cv.take(&m_key, (size_t)chunk * kMaxStride * 4);
+            cv.take(&S, (size_t)chunk * kSumStride * 8);
         }
         if (mfma) {
             cv.take(&part, (size_t)chunk * G * kMaxSplits * sizeof(float2));
@@ -974,8 +974,8 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
         u.build = 1;
         u.unit0 = u0;
         if (!mfma) {
-            fill_u32_kernel<<<dim3((unsigned)((nu * G + 255) / 256)), 256, 0, st>>>(m_key, 0u, (size_t)nu * G);
-            fill_u32_kernel<<<dim3((unsigned)((nu * G * 2 + 255) / 256)), 256, 0, st>>>((uint32_t *)S, 0u, (size_t)nu * G * 2);
+            fill_u32_kernel<<<dim3((unsigned)((nu * kMaxStride + 255) / 256)), 256, 0, st>>>(m_key, 0u, (size_t)nu * kMaxStride);
+            fill_u32_kernel<<<dim3((unsigned)((nu * kSumStride * 2 + 255) / 256)), 256, 0, st>>>((uint32_t *)S, 0u, (size_t)nu * kSumStride * 2);
         }
         if (ghist) fill_u32_kernel<<<dim3((unsigned)(((size_t)nu * kBuckets + 255) / 256)), 256, 0, st>>>(ghist, 0u, (size_t)nu * kBuckets);
         bool keys_written = false;   // kbuf holds this chunk's ranking keys (matrix-core route)
@@ -1265,7 +1265,7 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         w.cand += u0 * L;
         w.ncand += u0;
         w.z += u0 * L * Gs;
-        w.m_key += u0 * Gs;
+        w.m_key += u0 * kMaxStride;
         w.crow += u0 * L;
         w.gbits += (size_t)u0 * ix->bitmap_words;
         w.kbuf += u0 * L;
@@ -1276,7 +1276,7 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         w.ginfo += (size_t)u0 * 4;
         w.win += (size_t)u0 * kWinSplit * Gs * (2 + 128);
         w.srow += (size_t)u0 * p.top_k;
-        w.S += u0 * Gs;
+        w.S += u0 * kSumStride;
         w.xs += u0 * Gs * ix->attn_slices;
         w.sel += (size_t)u0 * p.top_k;
         w.zsel += (size_t)u0 * p.top_k * Gs;

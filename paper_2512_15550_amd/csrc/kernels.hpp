@@ -23,6 +23,12 @@
 
 namespace ctkvr {
 
+// Words and sums of a unit that blocks of the whole chip update by atomics: a cache line to a unit, because atomics on one
+// line are served one after the other (units of a step side by side: 32K, eight units 34.9 -> 34.4 us a step, with the
+// centroid update 41.5 -> 40.7, 4K 22.9 -> 22.7, large batches the same).
+constexpr int kMaxStride = 32;   // maxima, 4 bytes
+constexpr int kSumStride = 16;   // denominators, 8 bytes
+
 // A "unit" is what one selection is made for: in a decode step a (sequence, KV
 // head) pair; in the build a (sequence, KV head, centroid) triple.
 struct Units {
@@ -162,8 +168,8 @@ struct CosArgs {
     const float *inv_norm_c;  // [batch][h][c_max]
     const int32_t *n_cent;
     float *cos;               // [batch*g][c_max]
-    uint32_t *m_key;          // [batch*g][G]  cleared here
-    unsigned long long *S;    // [batch*g][G]  cleared here
+    uint32_t *m_key;          // [batch*g][kMaxStride]  cleared here
+    unsigned long long *S;    // [batch*g][kSumStride]  cleared here
     unsigned long long *xs;   // [batch*g][n_xs] the tail kernel's exchange slots, cleared here (n_xs <= 64; 0: none)
     int n_xs;
     int g, h, c_max;
@@ -178,8 +184,8 @@ template <typename T, int G> __global__ __launch_bounds__(256) void centroid_cos
     const int C = a.n_cent[b];
     const int tid = threadIdx.x, lane16 = tid & 15, grp = tid >> 4;
     if (bx == 0 && tid < G) {
-        a.m_key[ul * G + tid] = 0u;
-        a.S[ul * G + tid] = 0ull;
+        a.m_key[ul * kMaxStride + tid] = 0u;
+        a.S[ul * kSumStride + tid] = 0ull;
     }
     if (bx == 0 && tid < a.n_xs) a.xs[ul * a.n_xs + tid] = 0ull;
     CTKVR_STAMP(0);
@@ -345,7 +351,7 @@ struct ScoreArgs {
     const int32_t *ncand;     // [units] (with crow)
     int l_stride;
     float *z;                 // [units][l_stride][G]
-    uint32_t *m_key;          // [units][G] ordered-key running max (atomicMax)
+    uint32_t *m_key;          // [units][kMaxStride] ordered-key running max per head (atomicMax)
     uint32_t *ghist;          // decode only: [units][kBuckets] key histogram, cleared here for keyhist
     float scale;
 };
@@ -418,7 +424,7 @@ template <typename T, int G, int R> __global__ __launch_bounds__(256) void score
         if (lane_id() < G) atomicMax(&s_max[lane_id()], ordered_key(v));
     }
     __syncthreads();
-    if (tid < G) atomicMax(&a.m_key[ul * G + tid], s_max[tid]);
+    if (tid < G) atomicMax(&a.m_key[ul * kMaxStride + tid], s_max[tid]);
     CTKVR_STAMP(22);
 }
 
@@ -629,7 +635,7 @@ struct RecallScoreArgs {
     int32_t *ncand;           // [units] L
     int32_t *out_ncand;       // optional copy for the caller
     float *z;                 // [units][l_stride][G]
-    uint32_t *m_key;          // [units][G] ordered-key running max (atomicMax)
+    uint32_t *m_key;          // [units][kMaxStride] ordered-key running max per head (atomicMax)
     uint32_t *ghist;          // optional: [units][kBuckets] key histogram, cleared here for keyhist
     float scale;
     int stream_k;             // the keys of all sequences exceed what the memory-side cache holds: load them non-temporal
@@ -912,7 +918,7 @@ template <typename T, int G, bool WIN> __global__ __launch_bounds__(256) void re
         rw[i] = s_rows[i];
     }
     __syncthreads();
-    if (tid < G) atomicMax(&a.m_key[ul * G + tid], s_max[tid]);
+    if (tid < G) atomicMax(&a.m_key[ul * kMaxStride + tid], s_max[tid]);
     CTKVR_STAMP_BLK(3);
 }
 
@@ -1327,7 +1333,7 @@ template <int G> __global__ __launch_bounds__(256) void denom_kernel(DenomArgs a
     // the block has work: one round trip instead of three)
     uint32_t mk[G];
 #pragma unroll
-    for (int hh = 0; hh < G; ++hh) mk[hh] = a.m_key[ul * G + hh];
+    for (int hh = 0; hh < G; ++hh) mk[hh] = a.m_key[ul * kMaxStride + hh];
     const int s_len = a.ctx_lens[b];
     const int L = a.ncand ? a.ncand[ul] : s_len;
     if (a.gcur && bx == 0 && threadIdx.x == 0) a.gcur[ul] = 0u;
@@ -1378,7 +1384,7 @@ template <int G> __global__ __launch_bounds__(256) void denom_kernel(DenomArgs a
         if (lane_id() == 0) s_acc[tid >> 6][hh] = v;
     }
     __syncthreads();
-    if (tid < G) atomicAdd(&a.S[ul * G + tid], s_acc[0][tid] + s_acc[1][tid] + s_acc[2][tid] + s_acc[3][tid]);
+    if (tid < G) atomicAdd(&a.S[ul * kSumStride + tid], s_acc[0][tid] + s_acc[1][tid] + s_acc[2][tid] + s_acc[3][tid]);
 }
 
 // ------------------------------------------------------------------------------
@@ -1411,8 +1417,8 @@ template <int G> __global__ __launch_bounds__(1024) void keyhist_kernel(KeyArgs 
     // the unit's statistics are requested together with L, before L decides whether the block has work
     uint32_t mk[G];
 #pragma unroll
-    for (int hh = 0; hh < G; ++hh) mk[hh] = a.z ? a.m_key[ul * G + hh] : 0u;
-    const unsigned long long S_mine = (a.z && tid < G) ? a.S[ul * G + tid] : 1ull;
+    for (int hh = 0; hh < G; ++hh) mk[hh] = a.z ? a.m_key[ul * kMaxStride + hh] : 0u;
+    const unsigned long long S_mine = (a.z && tid < G) ? a.S[ul * kSumStride + tid] : 1ull;
     const int L = a.ncand ? a.ncand[ul] : a.ctx_lens[b];
     if (a.gcur && bx == 0 && threadIdx.x == 0) a.gcur[ul] = 0u;
     if (bx * 4096 >= L) return;
@@ -1650,8 +1656,8 @@ template <int G> __global__ __launch_bounds__(1024) void keyclass_kernel(KeyClas
     const int tid = threadIdx.x, wv = tid >> 6, ln = lane_id();
     uint32_t mk[G];
 #pragma unroll
-    for (int hh = 0; hh < G; ++hh) mk[hh] = a.m_key[ul * G + hh];
-    const unsigned long long S_mine = tid < G ? a.S[ul * G + tid] : 1ull;
+    for (int hh = 0; hh < G; ++hh) mk[hh] = a.m_key[ul * kMaxStride + hh];
+    const unsigned long long S_mine = tid < G ? a.S[ul * kSumStride + tid] : 1ull;
     const int L = a.ncand ? a.ncand[ul] : a.ctx_lens[b];
     __shared__ uint32_t s_h[kBuckets];
     __shared__ float s_ls[G];
@@ -2107,7 +2113,7 @@ struct AttnArgs {
     float *out;  // [batch*h][128]
     float *out_lse;
     const float *win;   // optional: window_attn_kernel's partial results, [units][kWinSplit][G][2 + 128]
-    const uint32_t *m_key;   // [units][G] ordered-key maxima of the logits over all recalled keys
+    const uint32_t *m_key;   // [units][kMaxStride] ordered-key maxima of the logits over all recalled keys
 };
 
 
@@ -2234,12 +2240,12 @@ __device__ __forceinline__ void attend_unit(const AttnArgs &a, int ul, int slice
     float acc[G][8], lsum[G], mref[G];
 #pragma unroll
     for (int hh = 0; hh < G; ++hh) {
-        mref[hh] = ordered_value(a.m_key[ul * G + hh]);
+        mref[hh] = ordered_value(a.m_key[ul * kMaxStride + hh]);
         lsum[hh] = 0.0f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[hh][e] = 0.0f;
     }
-    if (tid < G) s_m[tid] = ordered_value(a.m_key[ul * G + tid]);
+    if (tid < G) s_m[tid] = ordered_value(a.m_key[ul * kMaxStride + tid]);
     for (int r0 = 0; r0 < nsel; r0 += NU * PASS) {
         if (r0 > 0) {
 #pragma unroll
@@ -3088,7 +3094,7 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
     const int L = a.ncand[ul];
     float m[G];
 #pragma unroll
-    for (int hh = 0; hh < G; ++hh) m[hh] = ordered_value(a.m_key[ul * G + hh]);
+    for (int hh = 0; hh < G; ++hh) m[hh] = ordered_value(a.m_key[ul * kMaxStride + hh]);
     // The unit's keys, as far as they are kept, and their rows: requested by the first wave now, by the others once their
     // denominators are handed over -- a wave's requests are issued in order, 32 of them from eight waves take the CU's one
     // address path 1.5 us, and the exchange waits for the slowest
