@@ -518,7 +518,7 @@ size_t carve_step_ws(StepWs &w, unsigned char *base, const ctkvr_index *ix)
     take(&w.ghist, U * (size_t)kBuckets * 4);
     take(&w.gbm, U * (size_t)(2 * ((L + 63) / 64)) * 4);
     take(&w.glist, U * (size_t)kListCap * 8);
-    take(&w.gcur, U * 4);
+    take(&w.gcur, U * kMaxStride * 4);
     take(&w.ginfo, U * 16);
     take(&w.win, U * (size_t)kWinSplit * G * (2 + 128) * 4);
     take(&w.srow, U * p.top_k * 4);
@@ -1272,7 +1272,7 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         w.ghist += (size_t)u0 * kBuckets;
         w.gbm += (size_t)u0 * (2 * ((L + 63) / 64));
         w.glist += (size_t)u0 * kListCap;
-        w.gcur += u0;
+        w.gcur += u0 * kMaxStride;
         w.ginfo += (size_t)u0 * 4;
         w.win += (size_t)u0 * kWinSplit * Gs * (2 + 128);
         w.srow += (size_t)u0 * p.top_k;

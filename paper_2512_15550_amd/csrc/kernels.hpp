@@ -25,8 +25,8 @@ namespace ctkvr {
 
 // Words and sums of a unit that blocks of the whole chip update by atomics: a cache line to a unit, because atomics on one
 // line are served one after the other (units of a step side by side: 32K, eight units 34.9 -> 34.4 us a step, with the
-// centroid update 41.5 -> 40.7, 4K 22.9 -> 22.7, large batches the same).
-constexpr int kMaxStride = 32;   // maxima, 4 bytes
+// centroid update 41.5 -> 40.7, 4K 22.9 -> 22.7; the list cursors: 128K x 4 124.2 -> 123.6, sixteen of 8K to 64K 146.8 -> 145.7).
+constexpr int kMaxStride = 32;   // maxima and list cursors, 4 bytes
 constexpr int kSumStride = 16;   // denominators, 8 bytes
 
 // A "unit" is what one selection is made for: in a decode step a (sequence, KV
@@ -1320,7 +1320,7 @@ struct DenomArgs {
     uint32_t *gbits;          // decode only: the recall bitmap, cleared here for the next step
     int bitmap_words;
     int by_xcd;               // blocks -> (unit, block of the unit) by unit_block_of
-    uint32_t *gcur;           // optional: [units] list cursors of keyclass_kernel, cleared here
+    uint32_t *gcur;           // optional: [units][kMaxStride] list cursors of keyclass_kernel, cleared here
 };
 
 template <int G> __global__ __launch_bounds__(256) void denom_kernel(DenomArgs a)
@@ -1336,7 +1336,7 @@ template <int G> __global__ __launch_bounds__(256) void denom_kernel(DenomArgs a
     for (int hh = 0; hh < G; ++hh) mk[hh] = a.m_key[ul * kMaxStride + hh];
     const int s_len = a.ctx_lens[b];
     const int L = a.ncand ? a.ncand[ul] : s_len;
-    if (a.gcur && bx == 0 && threadIdx.x == 0) a.gcur[ul] = 0u;
+    if (a.gcur && bx == 0 && threadIdx.x == 0) a.gcur[ul * kMaxStride] = 0u;
     if (a.gbits) {
         const int W = (s_len + 31) >> 5;
         for (int w = bx * 256 + threadIdx.x; w < W; w += gridDim.x * 256) a.gbits[(size_t)ul * a.bitmap_words + w] = 0u;
@@ -1402,7 +1402,7 @@ struct KeyArgs {
     const unsigned long long *S;
     uint32_t *kbuf;     // [units][l_stride]
     uint32_t *ghist;    // [units][kBuckets], zero on entry
-    uint32_t *gcur;     // decode only: [units] list cursors of classify_kernel, cleared here
+    uint32_t *gcur;     // decode only: [units][kMaxStride] list cursors of classify_kernel, cleared here
     int n_init, n_local;   // build only: ids below n_init or from L - n_local on are never listed
     int by_xcd;              // blocks -> (unit, block of the unit) by unit_block_of
 };
@@ -1420,7 +1420,7 @@ template <int G> __global__ __launch_bounds__(1024) void keyhist_kernel(KeyArgs 
     for (int hh = 0; hh < G; ++hh) mk[hh] = a.z ? a.m_key[ul * kMaxStride + hh] : 0u;
     const unsigned long long S_mine = (a.z && tid < G) ? a.S[ul * kSumStride + tid] : 1ull;
     const int L = a.ncand ? a.ncand[ul] : a.ctx_lens[b];
-    if (a.gcur && bx == 0 && threadIdx.x == 0) a.gcur[ul] = 0u;
+    if (a.gcur && bx == 0 && threadIdx.x == 0) a.gcur[ul * kMaxStride] = 0u;
     if (bx * 4096 >= L) return;
     __shared__ uint32_t s_h[kBuckets];
     __shared__ float s_ls[G];
@@ -1531,7 +1531,7 @@ struct ClassifyArgs {
     int bits_stride;         // bitmap words per unit
     uint32_t *gbm;           // [units][bits_stride] ids above the deciding bucket
     uint2 *glist;            // [units][kListCap] (key, id) of the deciding bucket
-    uint32_t *gcur;          // [units] list cursor, zero on entry
+    uint32_t *gcur;          // [units][kMaxStride] list cursor (first word), zero on entry
     uint32_t *ginfo;         // [units][4] deciding bucket, keys wanted from it, its population, unused
     int by_xcd;              // blocks -> (unit, block of the unit) by unit_block_of
 };
@@ -1613,7 +1613,7 @@ __global__ __launch_bounds__(256) void classify_kernel(ClassifyArgs a)
                 if (ln == 0) *reinterpret_cast<uint2 *>(bm + 2 * gq) = make_uint2((uint32_t)above, (uint32_t)(above >> 32));
                 if (listed) {
                     uint32_t at0 = 0;
-                    if (ln == 0) at0 = atomicAdd(&a.gcur[ul], (uint32_t)__popcll(listed));
+                    if (ln == 0) at0 = atomicAdd(&a.gcur[ul * kMaxStride], (uint32_t)__popcll(listed));
                     at0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)at0);
                     if (inb) lst[at0 + (uint32_t)__popcll(listed & below)] = make_uint2(kk[q], (uint32_t)i);
                 }
@@ -1642,7 +1642,7 @@ struct KeyClassArgs {
     int bits_stride;
     uint32_t *gbm;           // [units][bits_stride]
     uint2 *glist;            // [units][kListCap]
-    uint32_t *gcur;          // [units], zero on entry
+    uint32_t *gcur;          // [units][kMaxStride], zero on entry
     uint32_t *ginfo;         // [units][4]
     int by_xcd;              // blocks -> (unit, block of the unit) by unit_block_of
 };
@@ -1745,7 +1745,7 @@ template <int G> __global__ __launch_bounds__(1024) void keyclass_kernel(KeyClas
             if (ln == 0) *reinterpret_cast<uint2 *>(bm + 2 * g0) = make_uint2((uint32_t)above, (uint32_t)(above >> 32));
             if (listed) {
                 uint32_t at0 = 0;
-                if (ln == 0) at0 = atomicAdd(&a.gcur[ul], (uint32_t)__popcll(listed));
+                if (ln == 0) at0 = atomicAdd(&a.gcur[ul * kMaxStride], (uint32_t)__popcll(listed));
                 at0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)at0);
                 if (inb) lst[at0 + (uint32_t)__popcll(listed & below)] = make_uint2(ok, (uint32_t)i);
             }
