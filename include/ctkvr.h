@@ -269,8 +269,9 @@ int ctkvr_profile_collect(ctkvr_index *idx, float *ms_host, int32_t capacity_ste
 /* CTKVR_BUILD_MFMA ranks either all s keys of a (KV head, centroid) unit (their 4-byte ranking keys
  * written once, read for a histogram and read again for the selection) or only the keys at or above
  * a per-unit threshold taken from a 1-in-16 sample of the positions (a few thousand candidates per
- * unit; taken when every sequence is at least 32 rho long, rho is 256..2730 and the selection's
- * shared memory holds a bitmap of the context, i.e. up to about 2^19 tokens).  The second route
+ * unit; taken when the batch has 60 million keys or more over all units, ten or more for each one
+ * listed, rho is 256..2730 and the selection's shared memory holds a bitmap of the context, i.e. up to
+ * about 2^19 tokens).  The second route
  * yields exactly the same lists: a chunk of units in which a unit ends with fewer than rho
  * candidates, more than fit, or hundreds of candidates exactly equal to its rho-th key, is redone
  * by the first route.
