@@ -165,7 +165,7 @@ int ctkvr_decode_step_window(ctkvr_index *idx, const void *q, const void *k_page
  * the same step with the same arguments, results and errors, but every intermediate buffer of
  * the step (cosines, recall bitmap, recalled ids and rows, logits, ranking keys and their
  * histogram, the selection's bitmap and list, the selected rows and logits) lives in a static
- * device array of the library, 32 MiB per GPU, instead of the workspace `idx` owns.  The call
+ * device array of the library, 32.5 MiB per GPU, instead of the workspace `idx` owns.  The call
  * allocates and frees nothing, on the host side of HIP or through it; the array's device
  * address is looked up on the first call on each device.
  *   - The step's buffers must fit: about

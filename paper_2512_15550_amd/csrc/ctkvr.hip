@@ -69,8 +69,9 @@ size_t elem_size(int dtype) { return dtype == CTKVR_BF16 ? 2 : 4; }
 
 // Scratch of the entry point that allocates nothing (ctkvr_decode_step_static): one array per GPU, held
 // until the process ends.  Host code never uses the array's name as an address: the device address
-// is looked up once per device and kept.
-constexpr size_t kStaticScratchBytes = (size_t)32 << 20;
+// is looked up once per device and kept.  32 MiB of a step's buffers, and for the words of a unit that atomics update a cache line each
+// (at most 0.38 KB more a unit than packed, and a unit's buffers take at least 28 KiB: 0.42 MiB in all).
+constexpr size_t kStaticScratchBytes = ((size_t)32 << 20) + ((size_t)512 << 10);
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {

@@ -147,7 +147,7 @@ int hipGetSymbolAddress(void **p, const void *sym)
 {
     std::lock_guard<std::recursive_mutex> l(mu);
     void *&at = symbols[sym];
-    if (!at) at = calloc(1, (size_t)32 << 20);
+    if (!at) at = calloc(1, (size_t)33 << 20);
     *p = at;
     return kOk;
 }

@@ -7,7 +7,7 @@ import numpy as np
 
 import paper_2512_15550_amd as ck
 
-OK, EINVAL, EHIP = 0, -1, -3
+OK, EINVAL, EHIP, EUNSUPPORTED = 0, -1, -3, -4
 
 
 class Host:
@@ -169,7 +169,18 @@ def memory_held(x):
     assert own["small"] <= 5 << 19
 
 
-SCENARIOS = {f.__name__: f for f in (refused_wait, refused_wait_released, refused_build, refused_copy, other_device, path_of_other_device, memory_held)}
+def static_scratch_holds(x):
+    """The static scratch array takes what the step's buffers need with a cache line per unit for the words that atomics update: 1104
+    units of the smallest size need 31.8 MiB without those lines, 32.2 with them; 33 MiB are refused."""
+    ptr = ctypes.c_void_p(4096)              # (kernels do nothing here)
+    for batch, rc in ((138, OK), (142, EUNSUPPORTED)):
+        a, _, _ = x.load(s=64, C=4, rho=16, h=8, g=8, probe=4, top_k=16, batch=batch)
+        assert x.lib.ctkvr_decode_step_static(a, ptr, ptr, ptr, ptr, 4, ptr, None, None, None, None, None) == rc, ck.ctkvr_last_error()
+        x.lib.ctkvr_free(a)
+
+
+SCENARIOS = {f.__name__: f for f in (refused_wait, refused_wait_released, refused_build, refused_copy, other_device, path_of_other_device, memory_held,
+                                     static_scratch_holds)}
 
 if __name__ == "__main__":
     SCENARIOS[sys.argv[1]](Host(sys.argv[2]))
