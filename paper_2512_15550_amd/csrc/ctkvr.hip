@@ -1169,9 +1169,19 @@ template <typename T, int G> int build_lists_exact_mfma(ctkvr_index *ix, const v
     const size_t lds = exact_list_lds(ix);
     // threads of a list's block by what they hold of its keys (exact_list_kernel)
     const int list_threads = ix->s_max <= 32 * 512 ? 512 : 1024;
-    void (*const list_kernel)(ExactListArgs) = ix->s_max <= 8 * 512    ? exact_list_kernel<G, 512, 8>
-                                               : ix->s_max <= 32 * 512 ? exact_list_kernel<G, 512, 32>
-                                                                       : exact_list_kernel<G, 1024, 32>;
+    void (*list_kernel)(ExactListArgs) = ix->s_max <= 8 * 512    ? exact_list_kernel<G, 512, 8>
+                                         : ix->s_max <= 32 * 512 ? exact_list_kernel<G, 512, 32>
+                                                                 : exact_list_kernel<G, 1024, 32>;
+    if constexpr (G <= 4) {
+        // Two blocks of 1024 threads share a CU, at the price of spilled registers, where a chunk has a list for each: more than one a
+        // CU, more than two where keys beyond the 32768 in registers are read again, through more spills.  One / two blocks, whole
+        // builds in us: 2048 lists of 32768, one head 408 / 380, two 630 / 617, four 1132 / 1113; 512 of 32768, four heads 377 / 366;
+        // 1024 of 40000, four heads 812 / 775; 1024 of 65536, two heads 686 / 670, of 131072, one head 860 / 747; at two lists a CU
+        // and chunk, 65536 and four heads 1184 / 1229, 131072 and two 1324 / 1381; 256 of 32768, one head 168 / 178.  Eight heads (79
+        // spilled): 24000 1769 / 1805, 32768 2111 / 2281, 131072 5369 / 5590.
+        const long long at_once = std::min((long long)ix->units * ix->c_max, (long long)chunk * CT);
+        if (ix->s_max > 32 * 512 && at_once > (ix->s_max <= 32 * 1024 ? 1 : 2) * ix->num_cu) list_kernel = exact_list_kernel<G, 1024, 32, true>;
+    }
     TRY(want_lds(ix->dev, (const void *)list_kernel, lds));
     for (int t0 = 0; t0 < tiles; t0 += chunk) {
         const int nt = std::min(chunk, tiles - t0);

@@ -2848,8 +2848,10 @@ template <typename T, int G> __global__ __launch_bounds__(512) void exact_score_
 // cache; nothing is written but the list.  Bound by the vector instructions of the exponentials (about 16 us a list of 32K and a
 // CU) and by the latencies of a block's phases, which other blocks on the CU hide: 512 threads up to 16384 positions (two
 // blocks at 108 registers a thread; with 1024 threads one, and 6000 / 10000 / 16384 positions took 70 / 124 / 226 us where
-// this takes 38 / 87 / 177 for 1024 / 1536 / 2048 lists), beyond that 1024 threads held to 64 registers (two blocks in spite of
-// some spilled: 197 -> 176 us for 1024 lists of 32768).
+// this takes 38 / 87 / 177 for 1024 / 1536 / 2048 lists), beyond that 1024 threads, one block at 102 to 116 registers, or (PAIR)
+// held to 64, two blocks in spite of some 40 spilled (four heads: 197 -> 176 us for 1024 lists of 32768).  The rule is at the launch.
+// The heads' maxima are kept in scalar registers: as vector registers they made a block of eight heads and 131072 positions take 411 us,
+// now 341.
 // grid (chunk units), NT threads; dynamic shared memory: kSelLds + 2 kListCap + 4 ceil(s_max / 64) words
 struct ExactListArgs {
     int g, c_max, tile0, tiles_per_bk, ct;   // ct: centroids per tile
@@ -2861,7 +2863,7 @@ struct ExactListArgs {
     int32_t *lists;                          // [all units][c_max][rho]
 };
 
-template <int G, int NT, int KPT> __global__ __launch_bounds__(NT, (NT == 1024 ? 8 : 1)) void exact_list_kernel(ExactListArgs a)
+template <int G, int NT, int KPT, bool PAIR = false> __global__ __launch_bounds__(NT, (PAIR ? 8 : 1)) void exact_list_kernel(ExactListArgs a)
 {
     extern __shared__ __align__(16) uint32_t smem[];
     constexpr int NW = NT / 64;
@@ -2888,7 +2890,10 @@ template <int G, int NT, int KPT> __global__ __launch_bounds__(NT, (NT == 1024 ?
             for (int hh = 0; hh < G; ++hh) mk[hh] = max(mk[hh], pp[x * G + hh]);
         }
 #pragma unroll
-        for (int hh = 0; hh < G; ++hh) m[hh] = ordered_value(wave_fold_uniform(mk[hh], [](uint32_t x, uint32_t y) { return max(x, y); }));
+        for (int hh = 0; hh < G; ++hh) {
+            const float v = ordered_value(wave_fold_uniform(mk[hh], [](uint32_t x, uint32_t y) { return max(x, y); }));
+            m[hh] = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(v)));
+        }
     }
     for (int w = tid; w < kBuckets / 4; w += NT) reinterpret_cast<uint4 *>(s_hist)[w] = make_uint4(0u, 0u, 0u, 0u);
     if (tid == 0) s_res[3] = 0u;

@@ -32,3 +32,17 @@ def test_exact_lists_equal_the_oracles(dtype, h, g, s, rho, lattice, n_init, n_l
     got = ck.ctkvr_index_lists(idx)[0]
     ck.ctkvr_free(idx)
     assert np.array_equal(got, oracle.build_lists(sq.K, oracle.centroids_last_c(sq.q_tail, C), rho, n_init=n_init, n_local=n_local))
+
+
+@pytest.mark.parametrize("dtype,h,g,s,C,rho", [
+    ("bf16", 4, 1, 16400, 257, 200), ("f32", 2, 1, 16385, 300, 100), ("bf16", 1, 1, 33000, 540, 200),   # more lists than CUs: two blocks a CU
+    ("bf16", 8, 1, 16900, 260, 200), ("bf16", 8, 1, 40001, 33, 400)])                                  # eight heads: one
+def test_exact_lists_of_long_contexts_by_how_many_there_are(dtype, h, g, s, C, rho):
+    wl = small_workload("exact_many", dtype, h, g, (s,), (1500 + s,), C, 0, 4, rho, 64, 1)
+    bt = gen_batch(wl)
+    sq = bt.seqs[0]
+    db = H.device_batch(bt)
+    idx = ck.ctkvr_build_index(H.params_of(wl), db.q_prefill, db.cu_seqlens, True, db.k_pages, db.block_table, db.ctx_lens)
+    got = ck.ctkvr_index_lists(idx)[0]
+    ck.ctkvr_free(idx)
+    assert np.array_equal(got, oracle.build_lists(sq.K, oracle.centroids_last_c(sq.q_tail, C), rho))
