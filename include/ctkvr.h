@@ -272,11 +272,11 @@ int ctkvr_profile_collect(ctkvr_index *idx, float *ms_host, int32_t capacity_ste
  * unit; taken when the batch has 60 million keys or more over all units, ten or more for each one
  * listed, rho is 256..2730 and the selection's shared memory holds a bitmap of the context, i.e. up to
  * about 2^19 tokens).  The second route
- * yields exactly the same lists: a chunk of units in which a unit ends with fewer than rho
+ * yields exactly the same lists: a (sequence, KV head) pair in which a unit ends with fewer than rho
  * candidates, more than fit, or hundreds of candidates exactly equal to its rho-th key, is redone
  * by the first route.
- * by_candidates_host: 1 if the index was built by the candidate route; chunks_redone_host: how many
- * chunks it handed back.  Both HOST, either may be NULL.  The environment variable
+ * by_candidates_host: 1 if the index was built by the candidate route; chunks_redone_host: from how many
+ * of its chunks of units it handed pairs back.  Both HOST, either may be NULL.  The environment variable
  * CTKVR_BUILD_CANDIDATES = 0 | 1, read at build time, forces the choice where the geometry allows it. */
 int ctkvr_index_build_route(const ctkvr_index *idx, int32_t *by_candidates_host, int32_t *chunks_redone_host);
 

@@ -1903,12 +1903,12 @@ template <int G> __global__ __launch_bounds__(1024) void rerank_select_kernel(Se
 // overflows, see below).  (The key itself for every unit, by radix rounds: 159 us for 8192 units of 8192 samples, now 77.)
 // cand_select_kernel: the rho largest of the unit's candidates (key, id), gathered from the segments the
 // blocks of the PICK pass filled, ties to the lowest id, written to the unit's list in ascending id order.
-// A unit with fewer than rho candidates, more than cand_cap, or a segment that ran over, raises *fail instead
-// (the caller then redoes the chunk by the route that keeps every key).
+// A unit with fewer than rho candidates, more than cand_cap, or a segment that ran over, raises the flag of its (sequence, KV head)
+// pair instead (the caller then redoes the pair by the route that keeps every key).
 // Both: grid = chunk units.  cand_select: 512 threads, which hold the candidates in registers (through shared memory, 75 KB a
 // block at rho = 2048, two blocks of 1024 threads shared a CU: 270 us for 8192 units, now 191); dynamic shared memory 2112 + kCandTies +
 // ceil(s_max / 32) words (one bitmap over the ids; the candidates that tie with the rho-th key, normally one, are
-// sorted out in a short list: more than kCandTies of them also raise *fail); cand_cap <= kCandCap.
+// sorted out in a short list: more than kCandTies of them also raise the flag); cand_cap <= kCandCap.
 // ------------------------------------------------------------------------------
 constexpr int kCandCap = 8192;
 constexpr int kSampleCap = 8192;   // sampled keys per unit at most
@@ -1924,7 +1924,7 @@ struct CandArgs {
     uint32_t *seg_cnt;        // [chunk units][t_splits], zeroed by sample_threshold_kernel for the segments no block writes
     int t_splits, seg_cap;
     int32_t *lists;           // [all units][rho]
-    uint32_t *fail;           // [1], zeroed by sample_threshold_kernel
+    uint32_t *fail;           // [chunk's (sequence, KV head) pairs], zeroed by sample_threshold_kernel
 };
 
 __global__ __launch_bounds__(1024) void sample_threshold_kernel(CandArgs a)
@@ -1934,7 +1934,7 @@ __global__ __launch_bounds__(1024) void sample_threshold_kernel(CandArgs a)
     int b, kv, j;
     const int ul = blockIdx.x, tid = threadIdx.x;
     if (tid < a.t_splits) a.seg_cnt[(size_t)ul * a.t_splits + tid] = 0u;   // for the candidate pass
-    if (ul == 0 && tid == 0) *a.fail = 0u;
+    if (tid == 0 && ul % a.u.c_max == 0) a.fail[ul / a.u.c_max] = 0u;
     if (!decode_unit(a.u, ul, b, kv, j)) return;
     s_hist[tid] = s_hist[1024 + tid] = 0u;
     const int s = a.ctx_lens[b];
@@ -2012,7 +2012,7 @@ __global__ __launch_bounds__(kCandThreads, 8) void cand_select_kernel(CandArgs a
     const uint32_t end_x = wave_incl_scan(c_x);
     const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)end_x, 63);
     if (__ballot(c_x > (uint32_t)a.seg_cap) || n < (uint32_t)a.rho || n > (uint32_t)a.cand_cap) {   // uniform
-        if (tid == 0) atomicOr(a.fail, 1u);
+        if (tid == 0) atomicOr(&a.fail[ul / a.u.c_max], 1u);
         return;
     }
     uint32_t *s_hist = smem;                                   // 2048 + 64
@@ -2067,7 +2067,7 @@ __global__ __launch_bounds__(kCandThreads, 8) void cand_select_kernel(CandArgs a
     __syncthreads();
     const uint32_t n_eq = s_x[1];
     if (n_eq > (uint32_t)kCandTies) {   // uniform: more exact ties at the threshold than are sorted out here
-        if (tid == 0) atomicOr(a.fail, 1u);
+        if (tid == 0) atomicOr(&a.fail[ul / a.u.c_max], 1u);
         return;
     }
     // the need_eq lowest ids among the ties join the bitmap

@@ -69,3 +69,26 @@ def test_the_route_is_chosen_by_keys_and_their_share(s, C, rho, want, monkeypatc
     idx = ck.ctkvr_build_index(H.params_of(wl, build_algo=ck.BUILD_MFMA), db.q_prefill, db.cu_seqlens, True, db.k_pages, db.block_table, db.ctx_lens)
     assert ck.ctkvr_index_build_route(idx)[0] == want
     ck.ctkvr_free(idx)
+
+
+@pytest.mark.parametrize("lens,h,g,C,flat,chunks", [
+    ((5003,), 8, 4, 70, [(0, 0), (0, 2), (0, 3)], 1),                 # runs of one and of two pairs beside one that stands
+    ((4000, 5003), 4, 4, 1100, [(0, 3), (1, 0), (1, 2)], 2),          # the last pair of one chunk and the first of the next
+    ((5003, 2500), 16, 2, 40, [(1, 1)], 1)])                          # eight heads
+def test_only_what_failed_is_handed_back_with_its_statistics(lens, h, g, C, flat, chunks, monkeypatch):
+    """Keys of some (sequence, KV head) pairs all equal: ranked by the route of all keys from the statistics of the first round."""
+    wl = small_workload("cand_pairs", "bf16", h, g, lens, tuple(range(770, 770 + len(lens))), C, 0, 4, 256, 60, 1)
+    bt = gen_batch(wl)
+    for b, kv in flat:
+        bt.seqs[b].K[kv] = bt.seqs[b].K[kv, :1]
+    bt = Batch(wl=wl, seqs=bt.seqs, paged=paginate(bt.seqs, wl.page_size, 7))
+    db = H.device_batch(bt)
+    got = []
+    for cand in ("0", "1"):
+        monkeypatch.setenv("CTKVR_BUILD_CANDIDATES", cand)
+        idx = ck.ctkvr_build_index(H.params_of(wl, build_algo=ck.BUILD_MFMA), db.q_prefill, db.cu_seqlens, True, db.k_pages, db.block_table,
+                                   db.ctx_lens)
+        assert ck.ctkvr_index_build_route(idx) == (cand == "1", chunks if cand == "1" else 0)
+        got.append(ck.ctkvr_index_lists(idx))
+        ck.ctkvr_free(idx)
+    assert np.array_equal(*got)
