@@ -875,7 +875,8 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
     const int rho = ix->p.list_len;
     const int step_stride = std::max(16, ((ix->s_max + 31) / 32 + 255) / 256);
     const int sample_stride = ((ix->s_max + 32 * step_stride - 1) / (32 * step_stride)) * 32;
-    const int cand_cap = std::min(kCandCap, std::max(3 * rho, 2 * rho + 2048));   // about 2 rho + 256 are expected (+-6 % at rho = 2048, three times that at 1024: neighbouring positions are alike)
+    // (2 rho + 16 step_stride or somewhat more are expected, +-6 % at rho = 2048, three times that at 1024: neighbouring positions are alike)
+    const int cand_cap = std::min(kCandCap, std::max(3 * rho, 2 * rho + 2048));
     const int cand_room = 2 * std::max(cand_cap, 128 * kMaxSplits);   // entries per unit, over all segments
     const size_t cand_lds = ((size_t)2112 + kCandTies + (size_t)((ix->s_max + 31) / 32)) * 4;
     bool by_cand = false;

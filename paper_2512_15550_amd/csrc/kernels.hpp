@@ -1896,11 +1896,14 @@ template <int G> __global__ __launch_bounds__(1024) void rerank_select_kernel(Se
 // Matrix-core list build, candidate route (Algorithm 1 line 4 on a few thousand candidates per unit
 // instead of all s keys).
 // sample_threshold_kernel: tau[unit] = the lower end of the histogram bucket (1/32 wide) that holds the r-th largest of the
-// unit's sampled keys, or that key itself where the bucket is crowded or below the histogram's range (slot i of the sample
-// row is key id (i / 32) * 32 * step_stride + i % 32; slots of ids beyond s or inside the resident window
-// do not count), with r = 2 ceil(rho / step_stride) + 16: about 2 rho + 16 step_stride of the unit's keys
-// then lie at or above tau.  Fewer samples than r: tau = 0, every key is a candidate (and the unit
-// overflows, see below).  (The key itself for every unit, by radix rounds: 159 us for 8192 units of 8192 samples, now 77.)
+// unit's sampled keys, or that key itself where the bucket is below the histogram's range or so crowded that the candidates might not
+// fit (slot i of the sample row is key id (i / 32) * 32 * step_stride + i % 32; slots of ids beyond s or inside the resident window
+// do not count), with r = 2 ceil(rho / step_stride) + 16.  With n of its samples at or above tau, about n step_stride of the unit's
+// keys are: 2 rho + 16 step_stride at the key itself, more at a bucket's end, which is taken as long as n + 4 sqrt(n) steps are
+// within cand_cap (the count of the sample spreads by sqrt(n)).  Where even the samples equal to the key are twice what fits
+// (equal keys), tau = +inf and the unit has no candidates: it is handed back whatever is collected (storing and
+// counting every key first, a build of 65536 tokens and 1024 centroids, 8 KV heads: 9.16 ms, now 8.05).  Fewer samples than r: tau = 0, every key is a candidate.
+// (The key itself for every unit, by radix rounds: 159 us for 8192 units of 8192 samples, now 77 to 90.)
 // cand_select_kernel: the rho largest of the unit's candidates (key, id), gathered from the segments the
 // blocks of the PICK pass filled, ties to the lowest id, written to the unit's list in ascending id order.
 // A unit with fewer than rho candidates, more than cand_cap, or a segment that ran over, raises the flag of its (sequence, KV head)
@@ -1978,10 +1981,12 @@ __global__ __launch_bounds__(1024) void sample_threshold_kernel(CandArgs a)
         if (before < r && r <= before + c0 + c1) {
             const bool first = r <= before + c0;
             s_res[0] = (uint32_t)(2 * tid) + (first ? 0u : 1u);
-            s_res[1] = first ? c0 : c1;
+            s_res[1] = before + c0 + (first ? 0u : c1);   // samples at or above the bucket's lower end
         }
+        if (tid == 0) s_cnt = 0u;
         __syncthreads();
-        if (r <= tot && s_res[1] <= r / 4u + 8u) {   // uniform
+        const float n_at = (float)s_res[1];
+        if (r <= tot && (n_at + 4.0f * sqrtf(n_at)) * (float)a.step_stride <= (float)a.cand_cap) {   // uniform
             if (tid == 0) a.tau[ul] = ordered_key(-(float)(s_res[0] + 1u) / 32.0f);
             return;
         }
@@ -1992,7 +1997,13 @@ __global__ __launch_bounds__(1024) void sample_threshold_kernel(CandArgs a)
     };
     uint32_t T, need_eq;
     block_kth_largest<1024>(for_slots, r, s_hist, T, need_eq);
-    if (tid == 0) a.tau[ul] = T;
+    uint32_t n_at = 0;
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) n_at += kreg[q] >= T ? 1u : 0u;
+    n_at = wave_sum_uniform(n_at);
+    if ((tid & 63) == 0 && n_at) atomicAdd(&s_cnt, n_at);
+    __syncthreads();
+    if (tid == 0) a.tau[ul] = s_cnt * (uint32_t)a.step_stride > 2u * (uint32_t)a.cand_cap ? 0xff800000u : T;
 }
 
 constexpr int kCandTies = 256;   // candidates equal to the rho-th key that cand_select_kernel sorts out itself

@@ -92,3 +92,23 @@ def test_only_what_failed_is_handed_back_with_its_statistics(lens, h, g, C, flat
         got.append(ck.ctkvr_index_lists(idx))
         ck.ctkvr_free(idx)
     assert np.array_equal(*got)
+
+
+@pytest.mark.parametrize("s,rho", [(131072, 2048), (200001, 2048), (262144, 2048), (262144, 1024)])
+def test_flat_scores_of_long_contexts_fit_their_candidates(s, rho, monkeypatch):
+    """Scores so alike that a bucket of the sample's histogram holds a good part of what is wanted: nothing is handed back."""
+    wl = small_workload("cand_flat", "bf16", 4, 1, (s,), (780,), 129, 0, 4, rho, 60, 1)
+    sq = gen_batch(wl).seqs[0]
+    k = sq.K
+    for scale in (0.03, 0.02, 0.015, 0.01):
+        sq.K = round_to_dtype(k.astype(np.float64) * scale, "bf16")
+        db = H.device_batch(Batch(wl=wl, seqs=[sq], paged=paginate([sq], wl.page_size, 5)))
+        got = []
+        for cand in ("0", "1"):
+            monkeypatch.setenv("CTKVR_BUILD_CANDIDATES", cand)
+            idx = ck.ctkvr_build_index(H.params_of(wl, build_algo=ck.BUILD_MFMA), db.q_prefill, db.cu_seqlens, True, db.k_pages,
+                                       db.block_table, db.ctx_lens)
+            assert ck.ctkvr_index_build_route(idx) == (cand == "1", 0), scale
+            got.append(ck.ctkvr_index_lists(idx))
+            ck.ctkvr_free(idx)
+        assert np.array_equal(*got)
