@@ -1899,7 +1899,7 @@ template <int G> __global__ __launch_bounds__(1024) void rerank_select_kernel(Se
 // unit's sampled keys, or that key itself where the bucket is below the histogram's range or so crowded that the candidates might not
 // fit (slot i of the sample row is key id (i / 32) * 32 * step_stride + i % 32; slots of ids beyond s or inside the resident window
 // do not count), with r = 2 ceil(rho / step_stride) + 16.  With n of its samples at or above tau, about n step_stride of the unit's
-// keys are: 2 rho + 16 step_stride at the key itself, more at a bucket's end, which is taken as long as n + 4 sqrt(n) steps are
+// keys are: 2 rho + 16 step_stride at the key itself, more at a bucket's end, which is taken as long as n + 3.5 sqrt(n) steps are
 // within cand_cap (the count of the sample spreads by sqrt(n)).  Where even the samples equal to the key are twice what fits
 // (equal keys), tau = +inf and the unit has no candidates: it is handed back whatever is collected (storing and
 // counting every key first, a build of 65536 tokens and 1024 centroids, 8 KV heads: 9.16 ms, now 8.05).  Fewer samples than r: tau = 0, every key is a candidate.
@@ -1986,7 +1986,7 @@ __global__ __launch_bounds__(1024) void sample_threshold_kernel(CandArgs a)
         if (tid == 0) s_cnt = 0u;
         __syncthreads();
         const float n_at = (float)s_res[1];
-        if (r <= tot && (n_at + 4.0f * sqrtf(n_at)) * (float)a.step_stride <= (float)a.cand_cap) {   // uniform
+        if (r <= tot && (n_at + 3.5f * sqrtf(n_at)) * (float)a.step_stride <= (float)a.cand_cap) {   // uniform
             if (tid == 0) a.tau[ul] = ordered_key(-(float)(s_res[0] + 1u) / 32.0f);
             return;
         }
