@@ -865,12 +865,16 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
     constexpr int kMaxSplits = 64;
     // Matrix-core route, candidates only (see mfma_score_kernel): when the lists are short against the contexts, so that about
     // 2 rho candidates are a small part of the keys (a 1-in-16 sample of the positions places the threshold), and the keys of
-    // all lists enough to pay for the two passes and the wait that it has more.  Every key against candidates, whole builds in
+    // all lists enough to pay for the two passes and the wait that it has more, or single lists so long that the walk of one block
+    // over all their keys takes longer than those.  Every key against candidates, whole builds in
     // us, C = s / 64, 8 KV heads, four query heads each unless noted:
     //   lists of 1024, one context: 16K 262 / 281, 20K (50 M keys) 363 / 364, 22K 468 / 416, 25K 597 / 482 (one head 502 / 366,
     //   eight 825 / 776), 30K 778 / 524, 40K 1307 / 820; three of 9K..30K 1128 / 859, four of 2K..30K 1194 / 900;
     //   contexts against list length: 4 x 8192 tokens, 512 centroids (8 : 1) 902 / 973, 4 x 12K (12 : 1) 578 / 545,
-    //   the same with lists of 2048 (6 : 1) 594 / 633, 4 x 16K with 512 (31 : 1) 822 / 644.
+    //   the same with lists of 2048 (6 : 1) 594 / 633, 4 x 16K with 512 (31 : 1) 822 / 644;
+    //   few lists, beyond the 32768 keys that key_list_kernel keeps in registers: 33000 tokens and 1024 lists (34 M keys) 296 / 278,
+    //   40000 and 512 (20 M) 237 / 239, 65536 and 256 (17 M) 214 / 212, 512 (34 M) 308 / 250, 98304 and 16 (1.6 M) 223 / 218, 64 (6.3 M)
+    //   244 / 227, 131072 and 400 (52 M) 469 / 323, 262144 and 128 (34 M) 520 / 354 (one head 596 / 468, eight 566 / 404).
     // CTKVR_BUILD_CANDIDATES=0/1 forces the choice where the first condition allows it.
     const int rho = ix->p.list_len;
     const int step_stride = std::max(16, ((ix->s_max + 31) / 32 + 255) / 256);
@@ -887,7 +891,10 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
             lists += n;
             keys += n * ix->ctx_lens[b];
         }
-        by_cand = rho >= 256 && 3 * rho <= kCandCap && keys >= 60000000ll && keys >= 10ll * rho * lists;
+        const int s_min = *std::min_element(ix->ctx_lens.begin(), ix->ctx_lens.end());
+        by_cand = rho >= 256 && 3 * rho <= kCandCap &&
+                  ((keys >= 60000000ll && keys >= 10ll * rho * lists) ||
+                   (s_min > 32768 && s_min >= 32ll * rho && (keys >= 30000000ll || s_min >= 98304)));
         if (const char *e = getenv("CTKVR_BUILD_CANDIDATES")) by_cand = atoi(e) != 0;
     }
     ix->build_by_cand = by_cand;

@@ -112,3 +112,24 @@ def test_flat_scores_of_long_contexts_fit_their_candidates(s, rho, monkeypatch):
             got.append(ck.ctkvr_index_lists(idx))
             ck.ctkvr_free(idx)
         assert np.array_equal(*got)
+
+
+@pytest.mark.parametrize("lens,g,C,rho,want", [
+    ((98304,), 1, 16, 256, True), ((98303,), 1, 16, 256, False),                # few lists: by their length
+    ((32769,), 4, 228, 512, False), ((33000,), 4, 228, 512, True),              # 30.0 M keys, just under and over
+    ((32768,), 4, 230, 512, False), ((33000,), 4, 228, 1100, False),            # (not longer than 32768; fewer than 32 for each one listed)
+    ((100000, 30000), 1, 16, 256, False)])
+def test_the_route_of_few_long_lists(lens, g, C, rho, want, monkeypatch):
+    monkeypatch.delenv("CTKVR_BUILD_CANDIDATES", raising=False)
+    wl = small_workload("cand_long", "bf16", g, g, lens, tuple(range(790, 790 + len(lens))), C, 0, 4, rho, 60, 1)
+    db = H.device_batch(gen_batch(wl))
+    lists = []
+    for forced in (None, "0"):
+        if forced:
+            monkeypatch.setenv("CTKVR_BUILD_CANDIDATES", forced)
+        idx = ck.ctkvr_build_index(H.params_of(wl, build_algo=ck.BUILD_MFMA), db.q_prefill, db.cu_seqlens, True, db.k_pages, db.block_table,
+                                   db.ctx_lens)
+        assert ck.ctkvr_index_build_route(idx) == (want and not forced, 0)
+        lists.append(ck.ctkvr_index_lists(idx))
+        ck.ctkvr_free(idx)
+    assert np.array_equal(*lists)
