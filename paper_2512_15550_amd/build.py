@@ -18,6 +18,8 @@ HIPCC_FLAGS = [
     # matrix results in ordinary vector registers: a kernel of 512 registers a wave otherwise gets them in the accumulation
     # half, and every vector instruction on a result first copies it
     "-mllvm", "-amdgpu-mfma-vgpr-form=1",
+    # what a statement in assembly leaves open is an error
+    "-Werror=inline-asm",
 ]
 
 

@@ -57,6 +57,15 @@ __device__ __forceinline__ Chunk<bf16_t> load_chunk(const bf16_t *row, int lane1
     c.w = *reinterpret_cast<const uint4 *>(row + 8 * lane16);
     return c;
 }
+// 16 bytes a lane from `from` + off (uniform pointer, 32-bit offset per lane) straight into shared memory, at byte `to` + 16 * lane
+// (uniform `to`); waited for like a load.  In assembly because the compiler waits for every such load it knows of before any read of
+// shared memory.  It does not look into the statement: a scalar pair written by a vector instruction needs five wait states before a
+// memory instruction reads it, one written by a scalar instruction none, hence the copy (also the wait state that m0 needs).
+__device__ __forceinline__ void load_to_lds(uint32_t to, const void *from, uint32_t off)
+{
+    uint64_t pair;
+    asm volatile("s_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0" : "=&s"(pair) : "{m0}"(to), "v"(off), "s"(from) : "memory");
+}
 // the same chunks with a non-temporal hint: rows that are read once per step and never again
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));

@@ -941,13 +941,6 @@ template <typename T, int G, bool WIN> __global__ __launch_bounds__(256) void re
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 
-// 16 bytes a lane from `from` + off (uniform pointer, 32-bit offset per lane) straight into shared memory, at byte `to` + 16 * lane
-// (uniform `to`); waited for like a load.  In assembly because the compiler waits for every such load it knows of before any read of
-// shared memory.
-__device__ __forceinline__ void load_to_lds(uint32_t to, const void *from, uint32_t off)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(off), "s"(from) : "memory", "m0");
-}
 constexpr int kVmcnt0 = 0x0f70;   // s_waitcnt: all vector memory, nothing else
 
 struct MfmaScoreArgs {
