@@ -271,8 +271,8 @@ int ctkvr_profile_collect(ctkvr_index *idx, float *ms_host, int32_t capacity_ste
  * a per-unit threshold taken from a 1-in-16 sample of the positions (a few thousand candidates per
  * unit; taken when the batch has 60 million keys or more over all units, ten or more for each one
  * listed, or every sequence has more than 32768 tokens, 32 or more for each one listed, and the units 30 million keys or
- * the sequences 98304 tokens; when rho is 256..2730; and when the selection's shared memory holds a bitmap of the context, i.e. up to
- * about 2^19 tokens).  The second route
+ * the sequences 98304 tokens; when rho is 256..2730; and when the threshold leaves room for the spread of its sample, i.e. up to
+ * 400 to 550 thousand tokens by rho).  The second route
  * yields exactly the same lists: a (sequence, KV head) pair in which a unit ends with fewer than rho
  * candidates, more than fit, or hundreds of candidates exactly equal to its rho-th key, is redone
  * by the first route.

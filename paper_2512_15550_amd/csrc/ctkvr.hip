@@ -875,7 +875,11 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
     //   few lists, beyond the 32768 keys that key_list_kernel keeps in registers: 33000 tokens and 1024 lists (34 M keys) 296 / 278,
     //   40000 and 512 (20 M) 237 / 239, 65536 and 256 (17 M) 214 / 212, 512 (34 M) 308 / 250, 98304 and 16 (1.6 M) 223 / 218, 64 (6.3 M)
     //   244 / 227, 131072 and 400 (52 M) 469 / 323, 262144 and 128 (34 M) 520 / 354 (one head 596 / 468, eight 566 / 404).
-    // CTKVR_BUILD_CANDIDATES=0/1 forces the choice where the first condition allows it.
+    // And where the samples at the threshold with two and a half spreads of their count stand for no more keys than fit: the longer the
+    // context, the more keys each stands for, and a build handed back costs a fifth where one that is not gains two thirds.  Every key /
+    // candidates: 400000 tokens and 128 lists a head of 2048 1449 / 444, 440000 and 1024 lists of 1024 7240 / 1966; handed back: 400000 and 128 of
+    // 1024 810 / 935, 470000 and 128 of 2048 1720 / 1979 (not taken by this line, nor are) 500000 and 128 1019 / 1303, 1024 8763 / 10021.
+    // CTKVR_BUILD_CANDIDATES=0/1 forces the choice where the shared memory allows it.
     const int rho = ix->p.list_len;
     const int step_stride = std::max(16, ((ix->s_max + 31) / 32 + 255) / 256);
     const int sample_stride = ((ix->s_max + 32 * step_stride - 1) / (32 * step_stride)) * 32;
@@ -884,7 +888,7 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
     const int cand_room = 2 * std::max(cand_cap, 128 * kMaxSplits);   // entries per unit, over all segments
     const size_t cand_lds = ((size_t)2112 + kCandTies + (size_t)((ix->s_max + 31) / 32)) * 4;
     bool by_cand = false;
-    if (mfma && cand_lds + 8 * (size_t)cand_cap <= 150 * 1024 && sample_stride <= kSampleCap && cand_cap >= rho) {
+    if (mfma && cand_lds <= 150 * 1024 && sample_stride <= kSampleCap && cand_cap >= rho) {
         long long lists = 0, keys = 0;
         for (int b = 0; b < ix->p.batch; ++b) {
             const long long n = (long long)ix->p.n_kv_heads * ix->n_cent[b];
@@ -892,7 +896,8 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
             keys += n * ix->ctx_lens[b];
         }
         const int s_min = *std::min_element(ix->ctx_lens.begin(), ix->ctx_lens.end());
-        by_cand = rho >= 256 && 3 * rho <= kCandCap &&
+        const float n_at = (float)(2 * ((rho + step_stride - 1) / step_stride) + 16);   // samples at the threshold
+        by_cand = rho >= 256 && 3 * rho <= kCandCap && (n_at + 2.5f * sqrtf(n_at)) * (float)step_stride <= (float)cand_cap &&
                   ((keys >= 60000000ll && keys >= 10ll * rho * lists) ||
                    (s_min > 32768 && s_min >= 32ll * rho && (keys >= 30000000ll || s_min >= 98304)));
         if (const char *e = getenv("CTKVR_BUILD_CANDIDATES")) by_cand = atoi(e) != 0;

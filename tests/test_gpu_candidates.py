@@ -133,3 +133,29 @@ def test_the_route_of_few_long_lists(lens, g, C, rho, want, monkeypatch):
         lists.append(ck.ctkvr_index_lists(idx))
         ck.ctkvr_free(idx)
     assert np.array_equal(*lists)
+
+
+@pytest.mark.parametrize("s,want", [(475136, True), (475137, False)])
+def test_the_route_ends_where_the_sample_is_too_small(s, want, monkeypatch):
+    """1 in 58 positions sampled: 52 of them at the threshold, and 2.5 sqrt(52) more, stand for 4061 of the 4096 keys that fit; 1 in 59: for 4131."""
+    monkeypatch.delenv("CTKVR_BUILD_CANDIDATES", raising=False)
+    wl = small_workload("cand_end", "bf16", 1, 1, (s,), (810,), 3, 0, 2, 1024, 60, 1)
+    db = H.device_batch(gen_batch(wl))
+    idx = ck.ctkvr_build_index(H.params_of(wl, build_algo=ck.BUILD_MFMA), db.q_prefill, db.cu_seqlens, True, db.k_pages, db.block_table, db.ctx_lens)
+    assert ck.ctkvr_index_build_route(idx)[0] == want
+    ck.ctkvr_free(idx)
+
+
+@pytest.mark.parametrize("s,rho", [(700001, 2048), (1 << 20, 300)])
+def test_forced_candidates_of_the_longest_contexts(s, rho, monkeypatch):
+    """Bitmaps beyond what once shared the memory with the candidates: the lists of all keys, handed back or not."""
+    wl = small_workload("cand_longest", "bf16", 1, 1, (s,), (811,), 9, 0, 2, rho, 60, 1)
+    db = H.device_batch(gen_batch(wl))
+    lists = []
+    for cand in ("0", "1"):
+        monkeypatch.setenv("CTKVR_BUILD_CANDIDATES", cand)
+        idx = ck.ctkvr_build_index(H.params_of(wl, build_algo=ck.BUILD_MFMA), db.q_prefill, db.cu_seqlens, True, db.k_pages, db.block_table, db.ctx_lens)
+        assert ck.ctkvr_index_build_route(idx)[0] == (cand == "1")
+        lists.append(ck.ctkvr_index_lists(idx))
+        ck.ctkvr_free(idx)
+    assert np.array_equal(*lists)
