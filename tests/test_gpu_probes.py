@@ -1,5 +1,6 @@
 """The probed centroids (Algorithm 2 line 3) where their selection changes form: a wave's share of 64, 128, 256, 512 and
-2048 ids by the table's size, the candidates of one to four waves, 64 probes and more, fewer centroids than the table
+2048 ids by the table's size, the candidates of one to four waves, 64 probes and more (by the block, at every number of
+ids a thread holds), fewer centroids than the table
 holds; and values that crowd -- copies of a few vectors (ties go to the lowest id) and values some units in the last place
 apart."""
 import numpy as np
@@ -26,7 +27,7 @@ def _centroids(kind, rng, h, C):
 @pytest.mark.parametrize("kind", ["random", "copies", "near"])
 @pytest.mark.parametrize("C,n_probe", [(2, 1), (9, 8), (64, 8), (65, 64), (65, 1), (129, 9), (256, 64), (257, 32), (512, 32),
                                        (513, 5), (1024, 64), (1025, 17), (2048, 4), (2048, 64), (2049, 8), (5000, 40), (300, 65),
-                                       (2100, 100), (100, 100)])
+                                       (2100, 100), (100, 100), (200, 65), (256, 100), (900, 80), (1500, 70)])
 def test_probes_equal_the_oracles(kind, C, n_probe):
     h, g, rho = 4, 2, 8
     rng = np.random.Generator(np.random.Philox(1000 + C + n_probe))
