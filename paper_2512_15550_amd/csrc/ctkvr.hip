@@ -1505,7 +1505,8 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         }
         sa.nbx = nbx;
         if (by_rank) {
-            // the bitmap with the ids before each word, and the block table of a sequence, where they fit 64 KB beside the block's ids
+            // the bitmap with the ids before each word, and the block table of a sequence, where they fit 60 KB beside the block's ids (with the
+            // window's own arrays 66.6 KB at most: two blocks share a CU's 160 KB, as many as the launch has for it)
             const int words = (((ix->bitmap_words + 255) / 256 + 3) & ~3) * 256;
             sa.lds.words = words <= kRecallWords ? words : 0;
             const int pages = (std::min(max_pages, ((ix->s_max - 1) >> ix->page_shift) + 1) + 255) & ~255;

@@ -1,6 +1,8 @@
 """GPU parity of the resident window (Algorithm 1 lines 5-6, Algorithm 2 lines 10-11): lists
 built without the initial and local keys, attention over the window -- which grows with the
 tokens decoded after the build -- merged with the sparse attention, against the oracle."""
+import functools
+
 import numpy as np
 import pytest
 
@@ -126,6 +128,14 @@ def test_window_build_and_decode_match_the_oracle(ck, case):
             worst = max(worst, e)
     print(f"[window {name}] ok, max rel err {worst:.2e}", flush=True)
     ck.ctkvr_free(idx)
+
+
+def test_window_beside_the_kept_bitmap_of_the_longest_context(ck, monkeypatch):
+    """The scoring launch with the most shared memory it takes: the bitmap of 131072 tokens with the ids before each word, the block table of
+    2048 pages, and the window's own arrays (66.6 KB)."""
+    monkeypatch.setenv("CTKVR_SCORE_BY_RANK", "1")
+    monkeypatch.setitem(globals(), "small_workload", functools.partial(small_workload, page_size=64))
+    test_window_build_and_decode_match_the_oracle(ck, ("ctx_128k", "bf16", 4, 1, (131072,), 8, 3, 3000, 500, 100, 300, 3, 3))
 
 
 def test_window_leaves_too_few_keys_is_an_error(ck):
