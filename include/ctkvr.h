@@ -276,6 +276,8 @@ int ctkvr_profile_collect(ctkvr_index *idx, float *ms_host, int32_t capacity_ste
  * yields exactly the same lists: a (sequence, KV head) pair in which a unit ends with fewer than rho
  * candidates, more than fit, or hundreds of candidates exactly equal to its rho-th key, is redone
  * by the first route.
+ * The second route's scratch is 140 to 170 KB a unit, for at most 8192 units or four (sequence, KV head) pairs, whichever is more:
+ * up to 1.4 GB, twice that where a pair has 4096 centroids; a build that hands pairs back takes 4 bytes a key of those of a chunk besides.
  * by_candidates_host: 1 if the index was built by the candidate route; chunks_redone_host: from how many
  * of its chunks of units it handed pairs back.  Both HOST, either may be NULL.  The environment variable
  * CTKVR_BUILD_CANDIDATES = 0 | 1, read at build time, forces the choice where the geometry allows it. */

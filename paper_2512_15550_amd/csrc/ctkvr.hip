@@ -907,8 +907,8 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
     const bool by_list = mfma && exact_list_lds(ix) <= 150 * 1024;
     if (by_cand) {
         // chunks of about equal size, of 8192 units at most or four (sequence, KV head) groups, whichever is more: enough to
-        // fill the card in every pass, at 1 GB of candidates (four groups whatever their size, each chunk
-        // waited for: 30K tokens, 468 centroids 649 us, now 524; 4 x 16K 1254, now 644)
+        // fill the card in every pass, at 1.1 GB of candidates (2.1 with four groups of 4096 centroids or two of 8192).  (Four groups
+        // whatever their size, each chunk waited for: 30K tokens, 468 centroids 649 us, now 524; 4 x 16K 1254, now 644)
         int groups = std::min(chunk / ix->c_max, std::max(4, 8192 / ix->c_max));
         const int n = (ix->units + groups - 1) / groups;
         groups = (ix->units + n - 1) / n;

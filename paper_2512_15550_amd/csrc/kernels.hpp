@@ -970,15 +970,15 @@ struct MfmaScoreArgs {
 // running sum of exp(z - m), rescaled whenever the maximum moves, in fp32 with the hardware
 // exponential (this route's lists are compared with the fixed arithmetic inside an error band anyway,
 // and the band has room for a denominator that is a few 1e-5 off); one (m, sum) pair per block, merged
-// in block order by the next pass.  MFMA_KEY: ranking keys max_h ((z - m_h) - log S_h), written as
+// in block order by mfma_merge_kernel.  MFMA_KEY: ranking keys max_h ((z - m_h) - log S_h), written as
 // ordered uint32 (4 bytes per (centroid, key) instead of 4 G bytes of scores read twice).
 // Writing, and twice re-reading, a key for every (centroid, key) pair is most of that route's time, and only
 // rho of a unit's s keys are wanted.  MFMA_SAMPLE computes the keys of every step_stride-th step only (a
 // systematic sample of the positions) into a small buffer, from which a threshold tau per unit is taken
 // (a sample rank chosen so that about 2 rho keys of the unit lie at or above it); MFMA_PICK then computes all
 // keys again and keeps the (key, id) pairs at or above tau -- a few thousand per unit -- from which the rho
-// largest are selected exactly.  Should a unit end with fewer than rho candidates, or more than fit, the
-// chunk is redone by the KEY route: the result never depends on the sample.
+// largest are selected exactly.  Should a unit end with fewer than rho candidates, or more than fit, its
+// (sequence, KV head) pair is redone by the KEY route: the result never depends on the sample.
 enum { MFMA_STAT = 0, MFMA_KEY = 2, MFMA_SAMPLE = 3, MFMA_PICK = 4 };
 
 // A wave's share of a block: ITEMS (head, 32-centroid sub-tile) pairs with their fragments resident, against one of
@@ -3086,7 +3086,7 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
     uint32_t *s_list = smem + kSelLds;                     // 2 * kListCap
     uint32_t *s_bits = s_list + 2 * kListCap;              // bits_words: two bitmaps over the recalled ids
     uint2 *s_pick = (uint2 *)(s_bits + a.bits_words);      // top_k: (position among the recalled keys, row) of the picks, ascending
-    float *s_p = (float *)(s_pick + kpad);                 // top_k * G: their scores (the two-pass fallback)
+    float *s_p = (float *)(s_pick + kpad);                 // top_k * G: their scores
     int ul, slice;
     attn_block_of<SL>(ul, slice);
     const int tid = threadIdx.x, ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -3305,7 +3305,6 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
                               const uint32_t r = s_pick[max(min(t, n - 1), 0)].y;
                               return n > 0 ? r : 0u;
                           },
-                          // (the picks' scores travel with their value rows: kept in shared memory, writing them cost 0.7 us)
                           [&](int t, float(&zv)[G]) { load_z<G>(s_p, max(min(t, n - 1), 0), zv); }, [&]() { return n; });
     if (p0 + tid < p1) put_ids(p0 + tid, my_id);
     for (int pos = p0 + NT + tid; pos < p1; pos += NT) put_ids(pos, pos < n ? cb[s_pick[pos].x] : -1);
