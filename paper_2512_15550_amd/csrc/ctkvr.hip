@@ -69,9 +69,11 @@ size_t elem_size(int dtype) { return dtype == CTKVR_BF16 ? 2 : 4; }
 
 // Scratch of the entry point that allocates nothing (ctkvr_decode_step_static): one array per GPU, held
 // until the process ends.  Host code never uses the array's name as an address: the device address
-// is looked up once per device and kept.  32 MiB of a step's buffers, and for the words of a unit that atomics update a cache line each
-// (at most 0.38 KB more a unit than packed, and a unit's buffers take at least 28 KiB: 0.42 MiB in all).
-constexpr size_t kStaticScratchBytes = ((size_t)32 << 20) + ((size_t)512 << 10);
+// is looked up once per device and kept.  It takes every step whose buffers are 32 MiB or less with the words of a unit that atomics
+// update packed and the bitmap's rows unpadded, and has room for what a cache line each and the padding add: at most 0.38 KB a unit, whose
+// buffers take at least 28 KiB, i.e. 0.42 MiB in all.
+constexpr size_t kStaticStepBytes = (size_t)32 << 20;
+constexpr size_t kStaticScratchBytes = kStaticStepBytes + ((size_t)512 << 10);
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
@@ -497,8 +499,8 @@ int check_params(const ctkvr_params *p, const int32_t *ctx_lens)
 }
 
 // Lays the step's buffers out from `base` (each 256-byte aligned) and returns the bytes they take;
-// with base == nullptr only the size is computed.  The geometry is the index's.
-size_t carve_step_ws(StepWs &w, unsigned char *base, const ctkvr_index *ix)
+// with base == nullptr only the size is computed.  The geometry is the index's.  `packed` (size only): see kStaticStepBytes.
+size_t carve_step_ws(StepWs &w, unsigned char *base, const ctkvr_index *ix, bool packed = false)
 {
     Carver cv{base};
     auto take = [&](auto **ptr, size_t bytes) { cv.take(ptr, bytes); };
@@ -512,18 +514,18 @@ size_t carve_step_ws(StepWs &w, unsigned char *base, const ctkvr_index *ix)
     take(&w.cand, U * L * 4);
     take(&w.ncand, U * 4);
     take(&w.z, U * LS * G * 4);
-    take(&w.m_key, U * kMaxStride * 4);
+    take(&w.m_key, U * (packed ? G : kMaxStride) * 4);
     take(&w.crow, U * LS * 4);
-    take(&w.gbits, U * (size_t)ix->bitmap_words * 4);
+    take(&w.gbits, U * (size_t)(packed ? (ix->s_max + 31) / 32 : ix->bitmap_words) * 4);
     take(&w.kbuf, U * L * 4);
     take(&w.ghist, U * (size_t)kBuckets * 4);
     take(&w.gbm, U * (size_t)(2 * ((L + 63) / 64)) * 4);
     take(&w.glist, U * (size_t)kListCap * 8);
-    take(&w.gcur, U * kMaxStride * 4);
+    take(&w.gcur, U * (packed ? 1 : kMaxStride) * 4);
     take(&w.ginfo, U * 16);
     take(&w.win, U * (size_t)kWinSplit * G * (2 + 128) * 4);
     take(&w.srow, U * p.top_k * 4);
-    take(&w.S, U * kSumStride * 8);
+    take(&w.S, U * (packed ? G : kSumStride) * 8);
     take(&w.xs, U * G * 8 * 8);
     take(&w.sel, U * p.top_k * 4);
     take(&w.zsel, U * p.top_k * G * 4);
@@ -2068,10 +2070,10 @@ int ctkvr_decode_step_static(ctkvr_index *idx, const void *q, const void *k_page
     if (max_pages < min_pages_needed(idx))
         return fail(CTKVR_EINVAL, "max_pages %d < %d pages of the longest sequence", max_pages, min_pages_needed(idx));
     StepWs w;
-    const size_t need = carve_step_ws(w, nullptr, idx);
-    if (need > kStaticScratchBytes)
+    const size_t need = carve_step_ws(w, nullptr, idx, true);
+    if (need > kStaticStepBytes || carve_step_ws(w, nullptr, idx) > kStaticScratchBytes)   // (the second follows from the first)
         return fail(CTKVR_EUNSUPPORTED, "the step's workspace (%zu bytes) exceeds the static scratch of %zu bytes", need,
-                    kStaticScratchBytes);
+                    kStaticStepBytes);
     unsigned char *base = nullptr;
     TRY(static_scratch(&base));
     carve_step_ws(w, base, idx);

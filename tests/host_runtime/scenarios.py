@@ -171,11 +171,14 @@ def memory_held(x):
 
 def static_scratch_holds(x):
     """The static scratch array takes what the step's buffers need with a cache line per unit for the words that atomics update: 1104
-    units of the smallest size need 31.8 MiB without those lines, 32.2 with them; 33 MiB are refused."""
+    units of the smallest size need 31.8 MiB without those lines, 32.2 with them; what needs more than 32 without them is refused, also where
+    it would fit the room that is there for the lines."""
     ptr = ctypes.c_void_p(4096)              # (kernels do nothing here)
-    for batch, rc in ((138, OK), (142, EUNSUPPORTED)):
-        a, _, _ = x.load(s=64, C=4, rho=16, h=8, g=8, probe=4, top_k=16, batch=batch)
-        assert x.lib.ctkvr_decode_step_static(a, ptr, ptr, ptr, ptr, 4, ptr, None, None, None, None, None) == rc, ck.ctkvr_last_error()
+    small = dict(s=64, C=4, rho=16, h=8, g=8, probe=4, top_k=16)
+    long = dict(s=100000, C=64, rho=2048, h=8, g=2, probe=64, top_k=2048, batch=4)
+    for geo, rc in ((dict(small, batch=138), OK), (dict(small, batch=142), EUNSUPPORTED), (long, EUNSUPPORTED)):
+        a, _, _ = x.load(**geo)
+        assert x.lib.ctkvr_decode_step_static(a, ptr, ptr, ptr, ptr, -(-geo["s"] // 16), ptr, None, None, None, None, None) == rc, ck.ctkvr_last_error()
         x.lib.ctkvr_free(a)
 
 
