@@ -1,6 +1,6 @@
 // gfx950 kernels of the CTkvr path.
 //
-// Decode step (Algorithm 2 lines 1-9), seven or eight launches:
+// Decode step (Algorithm 2 lines 1-9), four to eight launches:
 //   centroid_cos  lines 1-2   cosine to every centroid, max over the GQA group
 //   recall_gather lines 3-4a  top-C' centroids; their lists OR-ed into a bitmap
 //   recall_score  lines 4b-5a the bitmap as an ascending id list plus each id's physical
@@ -13,10 +13,9 @@
 //   rerank_select line 6b     top-rho' ids
 //   sparse_attn   lines 7-9   softmax(z_sel) . V_sel, one block per slice of the
 //                             head dimension (no cross-block reduction)
-//   (select_attn = the last two in one launch, for small batches)
-// The exact index build (Algorithm 1 lines 2-4) runs score -> denom -> keyhist -> rerank_select with
-// "the recalled set" = all s keys and the centroid in the role of the query,
-// which is literally the same formula.
+//   (keyclass = keyhist and classify, select_attn = the last two in one launch, tail = all from denom on, for small batches)
+// The exact index build (Algorithm 1 lines 2-4) takes the same formula with "the recalled set" = all s keys and the centroid in the
+// role of the query: exact_score -> exact_list, beyond 515072 tokens score -> denom -> keyhist -> rerank_select.
 #pragma once
 #include "arith.hpp"
 #include "common.hpp"

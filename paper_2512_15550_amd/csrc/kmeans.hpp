@@ -76,8 +76,8 @@ template <int G> __global__ __launch_bounds__(256) void kmeans_halfnorm_kernel(K
 // through two shared-memory buffers, the next tile loaded straight into shared memory while this one is multiplied, one barrier
 // per tile.  With a
 // single wave per SIMD nothing else hides the vector work, so the accumulators are two sets: the argmax of a
-// row tile runs between the matrix instructions of the next.  128K points x 2048 centres x 8 heads of G = 4: 1.86 ms,
-// 1.18 PFLOP/s (32 points a wave, two waves per SIMD, 1.95 ms).
+// row tile runs between the matrix instructions of the next.  128K points x 2048 centres x 8 heads of G = 4: 1.57 to
+// 1.68 ms, 1.31 to 1.40 PFLOP/s (tiles through registers 1.86, also with 32 points a wave and two waves per SIMD 1.95 ms).
 // With G = 8 (a point takes 256 registers) a wave has one column tile and the centre tiles are half as high.
 // The accumulators start from -|mu_c|^2/2, so the result tile
 // is the score itself.
