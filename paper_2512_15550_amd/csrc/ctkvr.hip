@@ -1490,15 +1490,16 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     sa.by_xcd = by_xcd_all;
     {
         // Few rows per CU (a small batch): a block's rows are one round trip to memory and the slowest block
-        // is the launch, so the ids are split by rank -- three blocks per two CUs (steps at two: 32K 36.4 against 36.1 us, with a
-        // resident window, whose blocks come on top, 43.7 against 42.5), at least 32 per unit and 64 ranks
-        // per block.  Otherwise by id range: enough blocks to fill the chip a few times over, each owning
-        // 8..64 words of the bitmap.
+        // is the launch, so the ids are split by rank -- two blocks a CU (with twelve rows a lane group in flight, see
+        // recall_score_kernel: 32K 33.9 us a step at three blocks per two CUs and eight rows, 34.4 with twelve, 32.9 at two; with a
+        // resident window 42.4 and 42.7), at least 32 per unit and 128 list entries per block, of which a quarter to a
+        // half are recalled (four probes of 1280, four KV heads: 64 entries 33.9, 128 33.3, 256 34.9).  Otherwise by id
+        // range: enough blocks to fill the chip a few times over, each owning 8..64 words of the bitmap.
         const bool by_rank = ix->score_by_rank < 0 ? (long long)ix->l_stride * U <= 2048ll * ix->num_cu : ix->score_by_rank != 0;
         sa.by_rank = by_rank;
         int nbx;
         if (by_rank) {
-            nbx = std::min(std::max(32, (3 * ix->num_cu / 2 + U - 1) / U), (ix->l_stride + 63) / 64);
+            nbx = std::min(std::max(32, (2 * ix->num_cu + U - 1) / U), (ix->l_stride + 127) / 128);
             nbx = std::max({1, nbx, (ix->l_stride + kRecallCap - 1) / kRecallCap});
         } else {
             const int target = std::max(32, (8 * ix->num_cu + U - 1) / U);
@@ -1520,15 +1521,21 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
             sa.lds.words = 0;
         }
         const size_t slds = (size_t)sa.lds.total() * 4;
-        bool launched = false;
-        if constexpr (G <= 4) {
-            if (window) {
-                sa.win = wa;
-                recall_score_kernel<T, G, true><<<dim3(nbx + kWinSplit, U), 256, slds, st>>>(sa);
-                launched = true;
+        auto launch = [&](auto rows) {
+            constexpr int R = decltype(rows)::value;
+            if constexpr (G <= 4) {
+                if (window) {
+                    sa.win = wa;
+                    recall_score_kernel<T, G, true, R><<<dim3(nbx + kWinSplit, U), 256, slds, st>>>(sa);
+                    return;
+                }
             }
-        }
-        if (!launched) recall_score_kernel<T, G, false><<<dim3(nbx, U), 256, slds, st>>>(sa);
+            recall_score_kernel<T, G, false, R><<<dim3(nbx, U), 256, slds, st>>>(sa);
+        };
+        if (by_rank)
+            launch(std::integral_constant<int, kRankRows<T>>{});
+        else
+            launch(std::integral_constant<int, 8>{});
     }
     if (whole) ix->mark(3, st);
 

@@ -614,6 +614,10 @@ template <typename T, int G> __global__ __launch_bounds__(256) void window_attn_
 // ------------------------------------------------------------------------------
 constexpr int kRecallWpb = 64;     // by id range: at most 2048 ids per block
 constexpr int kRecallCap = 2048;   // ids per block at most
+// Rows in flight per 16-lane group.  By id range eight: four blocks a CU.  By rank a CU has two blocks and the registers are free, and
+// twelve take the 125 to 170 rows of a block of the 32K step in one trip, not two (step 33.9 -> 32.9 us with two blocks a CU; sixteen:
+// the same; rows of 512 bytes: no gain at 4K, eight).
+template <typename T> constexpr int kRankRows = sizeof(T) == 2 ? 12 : 8;
 constexpr int kRecallWords = 4096; // by rank: bitmap words (contexts up to 128K) that the prologue takes in one trip
 
 // words of shared memory: ids and rows of the block, block-table entries, by rank the bitmap and the ids before each word
@@ -645,9 +649,9 @@ struct RecallScoreArgs {
     WindowArgs win;
 };
 
-template <typename T, int G, bool WIN> __global__ __launch_bounds__(256) void recall_score_kernel(RecallScoreArgs a)
+template <typename T, int G, bool WIN, int R> __global__ __launch_bounds__(256) void recall_score_kernel(RecallScoreArgs a)
 {
-    constexpr int R = 8, TILE = 16 * R;
+    constexpr int TILE = 16 * R;
     extern __shared__ __align__(16) uint32_t smem[];
     uint32_t *s_ids = smem, *s_rows = smem + kRecallCap;     // ids of this block's ranks, their rows
     int32_t *s_page = (int32_t *)(smem + 2 * kRecallCap);    // block-table entries
@@ -2504,6 +2508,7 @@ __device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int 
         count(q, kreg[q]);
     }
     for_far(count);
+    CTKVR_STAMP(67);
     __syncthreads();
     uint32_t *s_scan = s_hist + 2048 + 4;
     {
@@ -2536,6 +2541,7 @@ __device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int 
     }
     __syncthreads();
     const uint32_t bkt = s_res[0], rem = s_res[1], nb = s_res[2];
+    CTKVR_STAMP(68);
     // the deciding bucket as an interval of keys: x > hi is above it, lo < x <= hi in it (exact: x * 32 is)
     const float hi_k = bkt == 0u ? __builtin_huge_valf() : -(float)bkt / 32.0f;
     const float lo_k = bkt == (uint32_t)(kBuckets - 1) ? -__builtin_huge_valf() : -(float)(bkt + 1u) / 32.0f;
@@ -2589,6 +2595,7 @@ __device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int 
         if (!few)
             for (int w = tid; w < nw32; w += NT) s_eq[w] = 0u;
         __syncthreads();
+        CTKVR_STAMP(69);
         if (few) {
             uint32_t cap = 64;
             while (cap < nb) cap <<= 1;
@@ -2608,6 +2615,7 @@ __device__ __forceinline__ bool select_keys(const float (&kreg)[KPT], const int 
                 atomicOr(&s_gt[id >> 5], 1u << (id & 31u));
             }
             __syncthreads();
+            CTKVR_STAMP(70);
             if (PLACE && L <= KPT * NT) {   // uniform
                 // every wave counts the whole bitmap (lane q: the NW groups of round q), scans it by itself, and places its
                 // own groups' picks
