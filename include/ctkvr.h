@@ -165,10 +165,10 @@ int ctkvr_decode_step_window(ctkvr_index *idx, const void *q, const void *k_page
  * the same step with the same arguments, results and errors, but every intermediate buffer of
  * the step (cosines, recall bitmap, recalled ids and rows, logits, ranking keys and their
  * histogram, the selection's bitmap and list, the selected rows and logits) lives in a static
- * device array of the library, 32.5 MiB per GPU, instead of the workspace `idx` owns.  The call
+ * device array of the library, 36 MiB per GPU, instead of the workspace `idx` owns.  The call
  * allocates and frees nothing, on the host side of HIP or through it; the array's device
  * address is looked up on the first call on each device.
- *   - The step's buffers must fit 32 MiB of it (the rest gives the words that atomics update a cache line to a unit): about
+ *   - The step's buffers must fit 32 MiB of it (the rest is for the words that blocks of a launch hand to each other): about
  *       units * (l_stride * (16 + 4 G) + 4 C_max + s_max / 8 + top_k * (8 + 4 G) + 30 KiB)
  *     bytes, units = batch * g, plus, on geometries that allow the single-launch form (units at most
  *     the number of compute units), units * 32 * (4 top_k + 21 KiB) for its per-block slots (the 32K

@@ -440,7 +440,7 @@ __device__ __forceinline__ void block_kth_largest(SlotsFn for_slots, uint32_t k,
 // over the wave totals, and every wave writes its picks in place with ballot ranks -- no atomics
 // decide an order.
 template <int NT, int KPT, typename KeyFn, typename EmitFn>
-__device__ int block_select_topk(KeyFn key, int n, int k, EmitFn emit, uint32_t *s_hist)
+__device__ __forceinline__ int block_select_topk(KeyFn key, int n, int k, EmitFn emit, uint32_t *s_hist)
 {
     constexpr int NW = NT / 64;
     const int tid = threadIdx.x;

@@ -70,10 +70,11 @@ size_t elem_size(int dtype) { return dtype == CTKVR_BF16 ? 2 : 4; }
 // Scratch of the entry point that allocates nothing (ctkvr_decode_step_static): one array per GPU, held
 // until the process ends.  Host code never uses the array's name as an address: the device address
 // is looked up once per device and kept.  It takes every step whose buffers are 32 MiB or less with the words of a unit that atomics
-// update packed and the bitmap's rows unpadded, and has room for what a cache line each and the padding add: at most 0.38 KB a unit, whose
-// buffers take at least 28 KiB, i.e. 0.42 MiB in all.
+// update packed, the bitmap's rows unpadded and share_tail_kernel's exchange left out, and has room for those: a cache line each and the
+// padding at most 0.38 KB a unit, whose buffers take at least 28 KiB, i.e. 0.42 MiB in all; the exchange 4 KiB a unit and up to 5.2 KiB
+// a block, for 128 units at most and a block a CU, i.e. 1.8 MiB on 256 CUs.
 constexpr size_t kStaticStepBytes = (size_t)32 << 20;
-constexpr size_t kStaticScratchBytes = kStaticStepBytes + ((size_t)512 << 10);
+constexpr size_t kStaticScratchBytes = kStaticStepBytes + ((size_t)4 << 20);
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
@@ -409,6 +410,9 @@ struct ctkvr_index {
     size_t fused_lds = 0;   // non-zero: selection and attention run as one launch (select_attn_kernel)
     size_t dcu_lds = 0;     // non-zero: the update's ranking with a budget of its own runs as one launch (dcu_select_kernel)
     size_t tail_lds = 0;    // non-zero: everything after the scoring can run as one launch (tail_kernel)
+    size_t share_lds = 0;   // non-zero: ... with a unit's recalled keys shared out over its share_nb blocks (share_tail_kernel)
+    int share_nb = 1;
+    size_t xs_words = 0;    // exchange slots per unit
     int tail_spins = kTailSpins;
     int tail = -1;          // ... : -1 chosen per batch, 0 never, 1 whenever possible
     int keyclass = -1;      // key histogram + classification as one launch: -1 chosen per batch, 0 never, 1 always
@@ -526,7 +530,7 @@ size_t carve_step_ws(StepWs &w, unsigned char *base, const ctkvr_index *ix, bool
     take(&w.win, U * (size_t)kWinSplit * G * (2 + 128) * 4);
     take(&w.srow, U * p.top_k * 4);
     take(&w.S, U * (packed ? G : kSumStride) * 8);
-    take(&w.xs, U * G * 8 * 8);
+    take(&w.xs, U * (packed ? G * 8 : ix->xs_words) * 8);
     take(&w.sel, U * p.top_k * 4);
     take(&w.zsel, U * p.top_k * G * 4);
     take(&w.nsel, U * 4);
@@ -594,6 +598,7 @@ template <typename T, int G> int want_decode_lds(const ctkvr_index *ix)
         const void *fn = s8 ? (const void *)tail_kernel<T, G, 8> : (const void *)tail_kernel<T, G, 4>;
         TRY(want_lds(dev, fn, ix->tail_lds));
     }
+    if (ix->share_lds) TRY(want_lds(dev, (const void *)share_tail_kernel<T, G>, ix->share_lds));
     return want_lds(dev, s8 ? (const void *)sparse_attn_kernel<T, G, 8> : (const void *)sparse_attn_kernel<T, G, 4>, ix->attn_lds);
 }
 
@@ -692,6 +697,16 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, bool clear_tabl
     if (const char *e = getenv("CTKVR_DECODE_PATH")) {
         if (!strcmp(e, "staged")) ix->decode_path = CTKVR_PATH_STAGED;
         else if (!strcmp(e, "fused") && ix->fused_bpu) ix->decode_path = CTKVR_PATH_FUSED;
+    }
+    // What follows the scoring, a unit's recalled keys shared out over its blocks: as many blocks as there are CUs for them, eight at
+    // most (every block reads what all others of its unit publish)
+    {
+        int nb = 1;
+        while (nb < kShareBlocks && 2 * nb * (int)U <= ix->num_cu) nb *= 2;
+        ix->share_nb = nb;
+        const size_t lds = share_smem_words(((ix->l_stride + 63) / 64 + nb - 1) / nb, ix->G) * 4;
+        if (p->top_k <= kShareCut && lds <= 150 * 1024) ix->share_lds = lds;
+        ix->xs_words = std::max<size_t>(8 * ix->G, ix->share_lds ? share_words(nb, ix->G) : 0);
     }
     // one allocation for all of it
     size_t edge = 256;
@@ -1316,7 +1331,7 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         w.win += (size_t)u0 * kWinSplit * Gs * (2 + 128);
         w.srow += (size_t)u0 * p.top_k;
         w.S += u0 * kSumStride;
-        w.xs += u0 * Gs * ix->attn_slices;
+        w.xs += u0 * ix->xs_words;
         w.sel += (size_t)u0 * p.top_k;
         w.zsel += (size_t)u0 * p.top_k * Gs;
         w.nsel += u0;
@@ -1446,6 +1461,11 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
                       (ix->tail < 0 ? (long long)ix->l_stride * U <= 2048ll * ix->num_cu && ix->l_stride <= tail_most : ix->tail != 0);
     ca.xs = w.xs;
     ca.n_xs = tail ? ix->attn_slices * G : 0;
+    // Beyond that one launch all the same, with a unit's recalled keys shared out over its blocks (share_tail_kernel): 128K x 4
+    // 125.8 -> 116.7 us a step, sixteen of 8K to 64K 144.9 -> 130.0, against the separate launches, which are left to budgets beyond
+    // kShareCut and shares whose bitmap the shared memory does not take.  Small batches would lose with it (32K 31.9 -> 34.9 us, 4K 23.5 -> 28.7: every
+    // block's chain is as long, and waits three times more for the others).
+    const bool share = !tail && ix->share_lds && ix->keyclass < 0;
     if (whole) ix->mark(0, st);
     centroid_cos_kernel<T, G><<<dim3((ix->c_max + 15) / 16, U), 256, 0, st>>>(ca);
     if (whole) ix->mark(1, st);
@@ -1485,7 +1505,13 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     sa.out_ncand = out_ncand;
     sa.z = w.z;
     sa.m_key = w.m_key;
-    sa.ghist = tail ? nullptr : w.ghist;
+    if (share) {
+        sa.clear = (uint4 *)w.xs;
+        sa.clear_n = (int)(ix->xs_words / 2);
+    } else if (!tail) {
+        sa.clear = (uint4 *)w.ghist;
+        sa.clear_n = kBuckets / 4;
+    }
     sa.scale = ix->scale;
     sa.by_xcd = by_xcd_all;
     {
@@ -1589,6 +1615,34 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
             tail_kernel<T, G, 8><<<dim3(8 * U), kTailThreads, ix->tail_lds, st>>>(ta);
         else
             tail_kernel<T, G, 4><<<dim3(4 * U), kTailThreads, ix->tail_lds, st>>>(ta);
+        return finish();
+    }
+
+    if (share) {
+        ShareArgs ta{};
+        ta.ctx_lens = d_ctx_lens;
+        ta.ncand = w.ncand;
+        ta.cand = w.cand;
+        ta.crow = w.crow;
+        ta.l_stride = ix->l_stride;
+        ta.top_k = p.top_k;
+        ta.nb = ix->share_nb;
+        ta.z = w.z;
+        ta.m_key = w.m_key;
+        ta.xs = w.xs;
+        ta.spins = ix->tail_spins;
+        ta.gbits = w.gbits;
+        ta.bitmap_words = ix->bitmap_words;
+        ta.kbuf = w.kbuf;
+        ta.alone = (uint32_t *)w.zsel;
+        ta.keep_keys = p.list_len != p.top_k && &w_all == &ix->ws;
+        ta.sel = w.sel;
+        ta.nsel = w.nsel;
+        ta.out_sel = out_sel;
+        ta.at = aa;
+        if (whole)
+            for (int k = 4; k <= 7; ++k) ix->mark(k, st);   // stages of this launch: an event pair's cost each
+        share_tail_kernel<T, G><<<dim3(ix->share_nb * U), kTailThreads, ix->share_lds, st>>>(ta);
         return finish();
     }
 

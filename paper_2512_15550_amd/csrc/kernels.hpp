@@ -639,7 +639,8 @@ struct RecallScoreArgs {
     int32_t *out_ncand;       // optional copy for the caller
     float *z;                 // [units][l_stride][G]
     uint32_t *m_key;          // [units][kMaxStride] ordered-key running max per head (atomicMax)
-    uint32_t *ghist;          // optional: [units][kBuckets] key histogram, cleared here for keyhist
+    uint4 *clear;             // optional: [units][clear_n] words that the launches behind expect to find zero, cleared here
+    int clear_n;
     float scale;
     int stream_k;             // the keys of all sequences exceed what the memory-side cache holds: load them non-temporal
     int by_rank;              // how the bitmap is split over a unit's blocks
@@ -693,9 +694,8 @@ template <typename T, int G, bool WIN, int R> __global__ __launch_bounds__(256) 
             ++rk;
         } while (m);
     };
-    auto clear_hist = [&]() {
-        if (a.ghist)
-            for (int w = bx * 256 + tid; w < kBuckets; w += (uint32_t)a.nbx * 256) a.ghist[(size_t)ul * kBuckets + w] = 0u;
+    auto clear = [&]() {
+        for (int w = bx * 256 + tid; w < a.clear_n; w += a.nbx * 256) a.clear[(size_t)ul * a.clear_n + w] = make_uint4(0u, 0u, 0u, 0u);
     };
     uint32_t r0, r1;   // the block's ranks
     if (a.by_rank && a.lds.words) {
@@ -711,7 +711,7 @@ template <typename T, int G, bool WIN, int R> __global__ __launch_bounds__(256) 
 #pragma unroll
         for (int i = 0; i < NP; ++i)
             if (i * 256 < a.lds.pages) pg[i] = bt_row[min(i * 256 + tid, a.k.max_pages - 1)];   // uniform
-        clear_hist();
+        clear();
         uint32_t cnt = 0;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
@@ -760,7 +760,7 @@ template <typename T, int G, bool WIN, int R> __global__ __launch_bounds__(256) 
         // longer contexts: two passes over the words, the second over those between the block's first and last rank
         const int wpt = ((((a.bitmap_words + 255) >> 8) + 3) >> 2) << 2;
         const int w0 = tid * wpt, w1 = min(w0 + wpt, a.bitmap_words);
-        clear_hist();
+        clear();
         uint32_t cnt = 0;
 #pragma unroll 4
         for (int w = w0; w < w1; w += 4) {
@@ -817,7 +817,7 @@ template <typename T, int G, bool WIN, int R> __global__ __launch_bounds__(256) 
         const int W = (a.ctx_lens[b] + 31) >> 5;
         const int wpb = min(kRecallWpb, (W + a.nbx - 1) / a.nbx);
         const int w_beg = bx * wpb, w_end = min(W, w_beg + wpb);
-        clear_hist();
+        clear();
         if (w_beg >= W) return;
         const int mine = w_beg + (tid >> 2), part = tid & 3;
         uint32_t word = gb[min(mine, W - 1)];
@@ -3316,6 +3316,793 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
     if (p0 + tid < p1) put_ids(p0 + tid, my_id);
     for (int pos = p0 + NT + tid; pos < p1; pos += NT) put_ids(pos, pos < n ? cb[s_pick[pos].x] : -1);
     if (slice == 0 && tid == 0) a.nsel[ul] = n;
+}
+
+// ------------------------------------------------------------------------------
+// Algorithm 2 lines 5b-9 in ONE launch with a unit's recalled keys SHARED OUT over its blocks: denominators, ranking, selection and
+// attention, where denom, keyhist, classify, selection and attention as launches of their own took 35 us (128K x 4) and 43 us
+// (sixteen of 8K to 64K), of which the passes over memory are the smaller part: each begins with a ramp and a chain of loads and
+// ends with a drain.  This one takes 25 and 27 us, bound by its chain: 2.8 us to the scores, 2.0 for the exponentials (vector issue), 1.6, 2
+// and 2.8 for the words of the others, 2.5 for the picks, 3 for their value rows, 2 to 4 for weighing them.  Block x of a unit's nb takes every step for its own share, a contiguous stretch of the recalled keys (whose scores
+// and ranking keys stay in its registers), and what must be known of the others crosses over in 64-bit words that are zero
+// before the launch and carry their own validity, written and read by single atomics, so that no fence is needed:
+//   1. the share's denominator sums (a word per head);
+//   2. the share's histogram of ranking keys (four buckets a word): every block then knows the unit's deciding bucket,
+//      and from the others' histograms how many picks and how many of that bucket's keys come before its own;
+//   3. the deciding bucket's keys (key and position).  The value rows of the share's sure picks and of its keys of that bucket are
+//      requested before the others' are waited for;
+//   4. the share's weighted sums of value rows, relative to the unit's maxima over all recalled keys: added up in block order,
+//      128 G / nb elements by each block.
+// Every wait is bounded (kTailSpins reads).  A block that gives up takes the denominators of all keys itself, or later goes on alone: it
+// selects among all the unit's keys, attends over all picks and writes its part of the results, so that no progress
+// depends on the other blocks being resident.  It does the same where the bucket is crowded (more than kShareList keys), and where
+// some head's picks all lie so far below its maximum that their weights vanish (weights relative to the picks' own maxima then).
+// grid nb*batch*g, nb a power of two, kTailThreads threads; dynamic shared memory: share_smem_words.  Same integers as the separate kernels.
+// ------------------------------------------------------------------------------
+constexpr int kShareList = 512;    // keys of the deciding bucket that are ranked against each other
+constexpr int kShareBlocks = 8;    // blocks per unit at most
+constexpr int kShareBuckets = 256; // buckets of a histogram: 1/4 wide in the log domain, then 1/1024 wide inside one of those
+constexpr int kShareCut = 8191;    // a share's count in the exchange is cut there; top_k is at most that, so that a bucket with
+                                   // such a count is the deciding one, or comes after it, with or without the cut
+constexpr int kSharePicks = 128;   // picks that a wave attends over at a time
+
+struct ShareArgs {
+    const int32_t *ctx_lens, *ncand, *cand;
+    const uint32_t *crow;
+    int l_stride, top_k;
+    int nb;                     // blocks per unit
+    const float *z;
+    const uint32_t *m_key;
+    unsigned long long *xs;     // [units][share_words]: the exchange, zero on entry
+    int spins;                  // reads before a block gives up (kTailSpins)
+    uint32_t *gbits;            // the recall bitmap, cleared here for the next step
+    int bitmap_words;
+    uint32_t *kbuf;             // [units][l_stride] the ranking keys, written where a block goes on alone
+    uint32_t *alone;            // [units][top_k] the picks' positions, likewise
+    int keep_keys;              // kbuf is always written (for the dynamic centroid update)
+    int32_t *sel, *nsel, *out_sel;
+    AttnArgs at;
+};
+
+// 64-bit words of a unit's exchange: sums, histograms, the bucket's keys, weighted sums of value rows, sums of weights
+__host__ __device__ __forceinline__ size_t share_words(int nb, int G)
+{
+    return nb > 1 ? (size_t)nb * (G + 2 * (kShareBuckets / 4) + 64 * G + G) + kShareList : 0;
+}
+// words of shared memory that the histograms, the bucket's keys and later the waves' partial results take
+__host__ __device__ __forceinline__ int share_front_words(int G)
+{
+    const int sel = kSelLds + 2 * kShareList, out = kTailThreads / 64 * G * kD;
+    return ((sel > out ? sel : out) + 3) & ~3;
+}
+// share: groups of 64 keys in the largest share
+__host__ __device__ __forceinline__ size_t share_smem_words(int share, int G)
+{
+    return share_front_words(G) + (size_t)(kTailThreads / 64) * kSharePicks * (2 + G) + 2 * (size_t)share;
+}
+
+// two values summed over the halves of a wave, lane by lane: the lower half gets the sum of a, the upper that of b
+__device__ __forceinline__ float half_pair_sum(float a, float b)
+{
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+
+template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void share_tail_kernel(ShareArgs a)
+{
+    extern __shared__ __align__(16) uint32_t smem[];
+    constexpr int NT = kTailThreads, NW = NT / 64;
+    constexpr int KPT = G == 8 ? 8 : 16;           // groups of 64 keys that a wave keeps in registers
+    constexpr int NF = 4;                          // groups of later keys requested together
+    constexpr int NU = sizeof(T) == 2 ? 16 : 8;    // value rows in flight per 16-lane group
+    constexpr int W = G * 64;                      // pairs of output elements of a unit
+    constexpr int NH = kShareBuckets / 4;          // words of a histogram in the exchange
+    static_assert(NH == 64 && kShareList <= NT && NW * kShareBuckets <= 2048, "a word of a histogram per lane, a key of the list per thread");
+    __shared__ unsigned long long s_acc[NW][G];
+    __shared__ float s_ls[G], s_m[G], s_l[NW][G];
+    __shared__ uint32_t s_res[5];          // deciding bucket, keys wanted from it, its population, those in earlier shares, some wave gave up
+    __shared__ uint32_t s_before, s_cur;   // picks of earlier shares; cursor of the share's part of the bucket's list
+    __shared__ uint32_t s_cnt[NW];         // picks of each wave
+    uint32_t *s_hist = smem;                                    // a histogram per wave
+    uint2 *s_ent = reinterpret_cast<uint2 *>(smem + kSelLds);   // kShareList: (key, position) of the deciding bucket
+    float *s_o = reinterpret_cast<float *>(smem);               // [NW][G][128], once those two are done with
+    const int tid = threadIdx.x, ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // the wave's picks: row, position (with a mark on the sure ones), scores and then weights
+    uint32_t *w_row = smem + share_front_words(G) + wv * kSharePicks, *w_pos = w_row + NW * kSharePicks;
+    float *w_z = reinterpret_cast<float *>(smem + share_front_words(G) + 2 * NW * kSharePicks) + wv * kSharePicks * G;
+    uint32_t *s_bits = smem + share_front_words(G) + NW * kSharePicks * (2 + G);   // the share's picks from the deciding bucket
+    const int nb = a.nb;
+    int ul, x;
+    {
+        const int lin = blockIdx.x, nu = gridDim.x / nb;
+        if ((nu & 7) == 0) {   // a unit's blocks on one XCD
+            ul = (lin >> 3) / nb * 8 + (lin & 7);
+            x = (lin >> 3) % nb;
+        } else {
+            ul = lin / nb;
+            x = lin % nb;
+        }
+    }
+    const float *zb = a.z + (size_t)ul * a.l_stride * G;
+    const uint32_t *rb = a.crow + (size_t)ul * a.l_stride;
+    const int32_t *cb = a.cand + (size_t)ul * a.l_stride;
+    unsigned long long *xsum = a.xs + (size_t)ul * share_words(nb, G), *xhist = xsum + nb * G, *xlist = xhist + 2 * nb * NH;
+    unsigned long long *xout = xlist + kShareList, *xl = xout + nb * W;
+    constexpr unsigned long long kValid = 1ull << 63;
+    auto put = [](unsigned long long *p, unsigned long long v) __attribute__((always_inline)) {
+        __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto get = [](const unsigned long long *p) __attribute__((always_inline)) {
+        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto rank_in = [](uint64_t mask, uint32_t base) __attribute__((always_inline)) {   // base + lanes of the mask below this one
+        return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, base));
+    };
+    CTKVR_STAMP(60);
+    const int L = a.ncand[ul];
+    float m[G];
+#pragma unroll
+    for (int hh = 0; hh < G; ++hh) m[hh] = ordered_value(a.m_key[ul * kMaxStride + hh]);
+    // the share, in groups of 64 keys, and this wave's stretch of it
+    const int ng = (L + 63) >> 6, gpb = (ng + nb - 1) / nb, gpw = (gpb + NW - 1) / NW;
+    const int g0 = min(ng, x * gpb), g1 = min(ng, g0 + gpb);
+    const int wg0 = min(g1, g0 + wv * gpw), nwg = min(g1, wg0 + gpw) - wg0;
+    const int end = min(L, (wg0 + nwg) * 64);
+    auto key_at = [&](int q) __attribute__((always_inline)) { return (wg0 + q) * 64 + ln; };
+    float zr[KPT][G];   // scores, less the unit's maxima
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+        if (q % 2 == 0 && q >= nwg) break;   // uniform, here and below: the wave's groups two by two, its last one perhaps without keys
+        load_z<G>(zb, min(key_at(q), L - 1), zr[q]);
+    }
+    reinterpret_cast<uint4 *>(s_hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
+    for (int w = tid; w < 2 * gpb; w += NT) s_bits[w] = 0u;
+    if (tid == 0) {
+        s_res[4] = 0u;
+        s_before = 0u;
+        s_cur = 0u;
+    }
+    if (tid < G) s_m[tid] = ordered_value(a.m_key[ul * kMaxStride + tid]);
+    {
+        const int nwd = (a.ctx_lens[ul / a.at.g] + 31) >> 5;
+        for (int w = x * NT + tid; w < nwd; w += nb * NT) a.gbits[(size_t)ul * a.bitmap_words + w] = 0u;
+    }
+    CTKVR_STAMP(61);
+    // --- 1. denominators ----------------------------------------------------------------------------------
+    // (positions from `to` on: -inf, whose term is zero and whose key ranks last)
+    auto less_max = [&](float(&v)[G], const int i, const int to) __attribute__((always_inline)) {
+#pragma unroll
+        for (int hh = 0; hh < G; ++hh) v[hh] = i < to ? v[hh] - m[hh] : -__builtin_huge_valf();
+    };
+    // sums of the terms of n groups from `first` by the calling wave (KEPT: the first KPT of them in registers), as one 64-bit word
+    // per head
+    auto sum_terms = [&](auto kept, const int first, const int n) __attribute__((always_inline)) {
+        uint32_t shi[G], slo[G];
+#pragma unroll
+        for (int hh = 0; hh < G; ++hh) shi[hh] = slo[hh] = 0u;
+        auto add = [&](const float(&v)[G]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int hh = 0; hh < G; ++hh) {
+                uint32_t hi, lo;
+                exp_fixed40_parts(v[hh], hi, lo);
+                shi[hh] += hi;
+                slo[hh] += lo;
+            }
+        };
+        auto carry = [&]() __attribute__((always_inline)) {   // lo < 2^24 a term: at least every 255 terms
+#pragma unroll
+            for (int hh = 0; hh < G; ++hh) {
+                shi[hh] += slo[hh] >> 24;
+                slo[hh] &= 0xffffffu;
+            }
+        };
+        constexpr bool KEPT = decltype(kept)::value;
+        if constexpr (KEPT) {
+#pragma unroll
+            for (int q = 0; q < KPT; ++q) {
+                if (q % 2 == 0 && q >= nwg) break;
+                less_max(zr[q], key_at(q), end);
+                add(zr[q]);
+            }
+            carry();
+        }
+#pragma unroll 1
+        for (int q = KEPT ? KPT : 0; q < n; q += NF) {
+            float zf[NF][G];
+#pragma unroll
+            for (int u = 0; u < NF; ++u) load_z<G>(zb, min((first + q + u) * 64 + ln, L - 1), zf[u]);
+#pragma unroll
+            for (int u = 0; u < NF; ++u) {
+                if (q + u >= n) break;
+                less_max(zf[u], (first + q + u) * 64 + ln, L);
+                add(zf[u]);
+            }
+            carry();
+        }
+        // hi <= 2^16 a term, so that a lane's sum fits 32 bits; a wave's does too up to 2^9 terms a lane, and is put together from halves beyond
+#pragma unroll
+        for (int hh = 0; hh < G; ++hh) {
+            const uint32_t l = wave_sum_last(slo[hh]);
+            unsigned long long h;
+            if (n > 500)   // uniform
+                h = ((unsigned long long)wave_sum_last(shi[hh] >> 16) << 16) + wave_sum_last(shi[hh] & 0xffffu);
+            else
+                h = wave_sum_last(shi[hh]);
+            if (ln == 63) s_acc[wv][hh] = (h << 24) + l;
+        }
+    };
+    sum_terms(std::true_type{}, wg0, nwg);
+    CTKVR_STAMP(62);
+    __syncthreads();
+    uint32_t rr[KPT];   // the rows, requested while the others' sums are waited for
+    auto request_rows = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < KPT; ++q) {
+            if (q % 2 == 0 && q >= nwg) break;
+            rr[q] = rb[min(key_at(q), L - 1)];
+        }
+    };
+    if (wv) request_rows();
+    if (wv == 0) {
+        unsigned long long v = 0;
+        if (ln < G) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) v += s_acc[w][ln];
+        }
+        bool all = true;
+        if (nb > 1) {
+            if (ln < G) put(&xsum[x * G + ln], v | kValid);   // (a sum is below 2^20 * 2^40)
+            all = false;
+            v = kValid;
+            for (int it = 0; it < a.spins && !all; ++it) {
+                if (ln < nb * G) v = get(&xsum[ln]);
+                all = __all((v & kValid) != 0ull);
+            }
+            v &= ~kValid;
+#pragma unroll
+            for (int o = G; o < 64; o <<= 1) v += __shfl_xor(v, o);
+        }
+        request_rows();
+        if (ln < G) s_ls[ln] = (float)log_fixed40(v);
+        if (ln == 0) s_res[0] = all ? 1u : 0u;
+    }
+    __syncthreads();
+    CTKVR_STAMP(63);
+    if (!s_res[0]) {   // (uniform) a sibling is late: all terms here
+        const int per = (ng + NW - 1) / NW, f = min(ng, wv * per);
+        sum_terms(std::false_type{}, f, min(ng, f + per) - f);
+        __syncthreads();
+        if (tid < G) {
+            unsigned long long v = 0;
+            for (int w = 0; w < NW; ++w) v += s_acc[w][tid];
+            s_ls[tid] = (float)log_fixed40(v);
+        }
+        __syncthreads();
+    }
+    float ls[G];
+#pragma unroll
+    for (int hh = 0; hh < G; ++hh) ls[hh] = s_ls[hh];
+    // --- 2. ranking keys, their histogram, the deciding bucket ------------------------------------------------
+    auto key_of = [&](const float(&v)[G]) __attribute__((always_inline)) {
+        float best = v[0] - ls[0];
+#pragma unroll
+        for (int hh = 1; hh < G; ++hh) best = fmaxf(best, v[hh] - ls[hh]);
+        return fmaxf(best, -3.0e38f);   // (above the -inf of the slots beyond L)
+    };
+    float kreg[KPT];
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+        if (q % 2 == 0 && q >= nwg) break;
+        kreg[q] = key_at(q) < end ? key_of(zr[q]) : -__builtin_huge_valf();
+    }
+    // NF groups of the stretch from `q` on, beyond those in registers: their scores less the maxima
+    auto load_far = [&](int q, float(&zf)[NF][G]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < NF; ++u) load_z<G>(zb, min(key_at(q + u), L - 1), zf[u]);
+#pragma unroll
+        for (int u = 0; u < NF; ++u) less_max(zf[u], key_at(q + u), end);
+    };
+    auto far_key = [&](int q, const float(&v)[G]) __attribute__((always_inline)) { return key_at(q) < end ? key_of(v) : -__builtin_huge_valf(); };
+    // f(group of the stretch, key) for the wave's groups
+    auto for_keys = [&](auto f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < KPT; ++q) {
+            if (q % 2 == 0 && q >= nwg) break;
+            f(q, kreg[q]);
+        }
+#pragma unroll 1
+        for (int q = KPT; q < nwg; q += NF) {
+            float zf[NF][G];
+            load_far(q, zf);
+#pragma unroll
+            for (int u = 0; u < NF; ++u) {
+                if (q + u >= nwg) break;
+                f(q + u, far_key(q + u, zf[u]));
+            }
+        }
+    };
+    if (a.keep_keys) {
+        uint32_t *kb = a.kbuf + (size_t)ul * a.l_stride;
+        for_keys([&](int q, float kk) __attribute__((always_inline)) {
+            if (key_at(q) < end) kb[key_at(q)] = ordered_key(kk);
+        });
+    }
+    const bool every = a.top_k >= L;   // every recalled key is kept
+    bool alone = false;
+    // x > hi_k is a sure pick, lo_k < x <= hi_k is in the deciding bucket (exact: the bounds are multiples of 1/1024 above -65)
+    float hi_k = -__builtin_huge_valf(), lo_k = hi_k;
+    uint32_t rem = (uint32_t)a.top_k, n_bkt = 0, e0 = 0;   // keys wanted from the deciding bucket, its population, those in earlier shares
+#pragma unroll 1
+    for (int level = 0; level < 2 && !every; ++level) {
+        // 256 buckets a quarter wide; where more keys than are listed share the deciding one, 256 inside it.  A histogram per wave
+        uint32_t *hist = s_hist + wv * kShareBuckets, *spare = reinterpret_cast<uint32_t *>(s_ent) + tid;
+        const uint32_t first = level ? (uint32_t)(hi_k * -1024.0f) : 0u;   // (hi_k = inf, the first bucket: 0)
+        const float scale = level ? -1024.0f : -4.0f;
+        // not counted: at first the last bucket, all below (L minus the others); then what is not in the deciding one
+        const float over = level ? lo_k : -(float)(kShareBuckets - 1) / 4.0f, upto = level ? hi_k : __builtin_huge_valf();
+        for_keys([&](int, float kk) __attribute__((always_inline)) {
+            uint32_t *bin = hist + ((uint32_t)fmaxf(kk * scale, 0.0f) - first);
+            bin = kk > over && kk <= upto ? bin : spare;
+            atomicAdd(bin, 1u);
+        });
+        __syncthreads();
+        CTKVR_STAMP(64);
+        if (wv == 0) {
+            // lane l has the buckets 4 l .. 4 l + 3, in descending key order, 16 bits each in two words
+            uint4 c = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const uint4 t = reinterpret_cast<const uint4 *>(s_hist + w * kShareBuckets)[ln];
+                c.x += t.x;
+                c.y += t.y;
+                c.z += t.z;
+                c.w += t.w;
+            }
+            constexpr uint32_t kCut = (uint32_t)kShareCut;
+            uint32_t t_lo = min(c.x, kCut) | min(c.y, kCut) << 16, t_hi = min(c.z, kCut) | min(c.w, kCut) << 16;   // the unit's
+            uint32_t b_lo = 0u, b_hi = 0u;                                                                         // earlier shares'
+            bool all = true;
+            if (nb > 1) {
+                unsigned long long *xh = xhist + level * nb * NH, hw[kShareBlocks];
+                put(&xh[x * NH + ln], kValid | ((unsigned long long)t_hi << 32) | t_lo);
+                all = false;
+                for (int it = 0; it < a.spins && !all; ++it) {
+                    unsigned long long v = kValid;
+#pragma unroll
+                    for (int y = 0; y < kShareBlocks; ++y)
+                        if (y < nb) hw[y] = get(&xh[y * NH + ln]);   // uniform
+#pragma unroll
+                    for (int y = 0; y < kShareBlocks; ++y)
+                        if (y < nb) v &= hw[y];
+                    all = __all((v & kValid) != 0ull);
+                }
+                t_lo = t_hi = 0u;
+#pragma unroll
+                for (int y = 0; y < kShareBlocks; ++y)
+                    if (y < nb) {
+                        const uint32_t lo = (uint32_t)hw[y], hi = (uint32_t)(hw[y] >> 32) & 0x7fffffffu;
+                        b_lo += y < x ? lo : 0u;
+                        b_hi += y < x ? hi : 0u;
+                        t_lo += lo;
+                        t_hi += hi;
+                    }
+            }
+            CTKVR_STAMP(65);
+            auto nth = [](uint32_t lo, uint32_t hi, uint32_t j) __attribute__((always_inline)) {
+                return ((j & 2u ? hi : lo) >> ((j & 1u) * 16)) & 0xffffu;
+            };
+            auto sum4 = [](uint32_t lo, uint32_t hi) __attribute__((always_inline)) {
+                return (lo & 0xffffu) + (lo >> 16) + (hi & 0xffffu) + (hi >> 16);
+            };
+            const uint32_t mine = sum4(t_lo, t_hi), inc = wave_incl_scan(mine), tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+            uint32_t above;   // picks of earlier shares
+            if (!all || rem > tot) {   // a block did not answer, or the last bucket decides
+                above = wave_sum_last(sum4(b_lo, b_hi));
+                if (ln == 63) {
+                    s_res[0] = (uint32_t)(kShareBuckets - 1);
+                    s_res[1] = rem - tot;
+                    s_res[2] = all ? (uint32_t)L - tot : ~0u;
+                    s_res[3] = (uint32_t)min(L, g0 * 64) - above;
+                }
+            } else {
+                const uint64_t has = __ballot(inc >= rem);   // the first of these lanes has the bucket
+                const int src = __ffsll((long long)has) - 1;
+                uint32_t at = inc - mine, j = 0;
+#pragma unroll
+                for (uint32_t i = 0; i < 3; ++i)
+                    if (j == i && at + nth(t_lo, t_hi, i) < rem) {
+                        at += nth(t_lo, t_hi, i);
+                        j = i + 1;
+                    }
+                if (ln == src) {
+                    s_res[0] = 4u * (uint32_t)src + j;
+                    s_res[1] = rem - at;
+                    s_res[2] = nth(t_lo, t_hi, j);
+                    s_res[3] = nth(b_lo, b_hi, j);
+                }
+                above = ln < src ? sum4(b_lo, b_hi) : 0u;
+                if (ln == src)
+#pragma unroll
+                    for (uint32_t i = 0; i < 3; ++i) above += i < j ? nth(b_lo, b_hi, i) : 0u;
+                above = wave_sum_last(above);
+            }
+            if (ln == 63) s_before += above;
+        }
+        __syncthreads();
+        const uint32_t bkt = s_res[0];
+        rem = s_res[1];
+        n_bkt = s_res[2];
+        e0 = s_res[3];
+        alone = n_bkt > (uint32_t)kShareList;
+        const bool last_bkt = level == 0 && bkt == (uint32_t)(kShareBuckets - 1);
+        if (first + bkt) hi_k = (float)(first + bkt) / scale;
+        else hi_k = __builtin_huge_valf();
+        lo_k = last_bkt ? -__builtin_huge_valf() : (float)(first + bkt + 1u) / scale;
+        if (!alone || n_bkt == ~0u || last_bkt) break;   // uniform
+        reinterpret_cast<uint4 *>(hist)[ln] = make_uint4(0u, 0u, 0u, 0u);
+    }
+    CTKVR_STAMP(66);
+    // --- 3. the share's keys of the deciding bucket, for all; its picks, sure ones and those, ascending, for the wave -----------
+    const int lane16 = ln & 15, row4 = ln >> 4;
+    const T *V = (const T *)a.at.v_pages;
+    Chunk<T> cv[NU];
+    int n_l = 0, qn = 0;   // picks at hand; the wave's next group
+    int my_id[kSharePicks / 64];
+    // the wave's picks from group qn on, as many groups as fit: the first time from the registers, later from memory
+    auto append = [&](int q, float kk, const float(&v)[G], auto row) __attribute__((always_inline)) {
+        const uint64_t all = __ballot(kk > lo_k);
+        const int n = __popcll(all);
+        if (n_l + n > kSharePicks) return;   // uniform
+        if (kk > lo_k) {
+            const uint32_t p = rank_in(all, (uint32_t)n_l);
+            w_row[p] = row();
+            w_pos[p] = (uint32_t)key_at(q) | (kk > hi_k ? 0x80000000u : 0u);
+            store_z<G>(w_z, (int)p, v);
+        }
+        n_l += n;
+        qn = q + 1;
+    };
+    auto fill_again = [&]() __attribute__((always_inline)) {
+        n_l = 0;
+#pragma unroll 1
+        for (int q = qn; q < nwg && qn == q; q += NF) {
+            float zf[NF][G];
+            load_far(q, zf);
+#pragma unroll
+            for (int u = 0; u < NF; ++u)
+                if (qn == q + u && q + u < nwg) append(q + u, far_key(q + u, zf[u]), zf[u], [&]() { return rb[min(key_at(q + u), L - 1)]; });
+        }
+    };
+    auto request = [&](int r0) __attribute__((always_inline)) {   // value rows of the picks from r0 on
+        uint32_t row[NU];
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            if (u % 4 == 0 && r0 + u * 4 >= n_l) break;   // uniform
+            row[u] = w_row[min(r0 + u * 4 + row4, n_l - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            if (u % 4 == 0 && r0 + u * 4 >= n_l) break;
+            cv[u] = load_chunk(V + (size_t)row[u] * kD, lane16);
+        }
+    };
+    auto begin = [&]() __attribute__((always_inline)) {   // ids and value rows requested, scores to weights
+        if (n_l == 0) return;
+#pragma unroll
+        for (int i = 0; i < kSharePicks / 64; ++i) my_id[i] = cb[w_pos[min(i * 64 + ln, n_l - 1)] & 0x7fffffffu];
+        request(0);
+#pragma unroll
+        for (int i = 0; i < kSharePicks / 64; ++i)
+            if (i * 64 + ln < n_l) {
+                float w[G];
+                load_z<G>(w_z, i * 64 + ln, w);
+#pragma unroll
+                for (int hh = 0; hh < G; ++hh) w[hh] = __expf(w[hh]);
+                store_z<G>(w_z, i * 64 + ln, w);
+            }
+    };
+    if (!alone) {
+        uint32_t n_gt = 0;
+        for_keys([&](int q, float kk) __attribute__((always_inline)) {
+            const uint64_t gt = __ballot(kk > hi_k), in = __ballot(kk > lo_k) & ~gt;
+            n_gt += (uint32_t)__popcll(gt);
+            if (in) {   // uniform
+                uint32_t e = 0;
+                if (ln == 0) e = atomicAdd(&s_cur, (uint32_t)__popcll(in));
+                e = rank_in(in, e0 + (uint32_t)__builtin_amdgcn_readfirstlane((int)e));
+                if (__builtin_amdgcn_inverse_ballot_w64(in)) {
+                    if (nb > 1)
+                        put(&xlist[e], ((unsigned long long)ordered_key(kk) << 32) | 0x80000000u | (uint32_t)key_at(q));
+                    else
+                        s_ent[e] = make_uint2(ordered_key(kk), (uint32_t)key_at(q));
+                }
+            }
+        });
+        if (ln == 0) s_cnt[wv] = n_gt;
+        s_hist[tid] = 0u;   // the ranks of the bucket's keys (everyone has read the histograms)
+#pragma unroll
+        for (int q = 0; q < KPT; ++q) {
+            if (q % 2 == 0 && q >= nwg) break;
+            if (q == qn) append(q, kreg[q], zr[q], [&]() { return rr[q]; });   // uniform
+        }
+        begin();
+        CTKVR_STAMP(67);
+        if (!every) {
+            // which of the bucket's keys are picks: ranked against each other, ids decide between equal keys
+            if (nb > 1) {
+                unsigned long long v = 1ull;
+                bool all = false;
+                for (int it = 0; it < a.spins && !all; ++it) {
+                    if (tid < (int)n_bkt) v = get(&xlist[tid]);
+                    all = __all(v != 0ull);
+                }
+                if (!all) s_res[4] = 1u;
+                if (tid < (int)n_bkt) s_ent[tid] = make_uint2((uint32_t)(v >> 32), (uint32_t)v & 0x7fffffffu);
+            }
+            __syncthreads();
+            CTKVR_STAMP(68);
+            uint32_t cap = 64;
+            while (cap < n_bkt) cap <<= 1;
+            const uint32_t parts = (uint32_t)NT / cap, e = (uint32_t)tid & (cap - 1u), part = (uint32_t)tid / cap;
+            if (e < n_bkt) {
+                const uint2 me = s_ent[e];
+                uint32_t rank = 0;
+                for (uint32_t f = part; f < n_bkt; f += 4 * parts) {
+                    uint2 o[4];
+#pragma unroll
+                    for (uint32_t i = 0; i < 4; ++i) o[i] = s_ent[min(f + i * parts, n_bkt - 1)];
+#pragma unroll
+                    for (uint32_t i = 0; i < 4; ++i)
+                        rank += f + i * parts < n_bkt && ((o[i].x > me.x) || (o[i].x == me.x && o[i].y < me.y));
+                }
+                atomicAdd(&s_hist[e], rank);
+            }
+            __syncthreads();
+            if (tid < (int)n_bkt && s_hist[tid] < rem) {
+                const int pos = (int)s_ent[tid].y, rel = pos - g0 * 64;
+                if (rel < 0) {
+                    atomicAdd(&s_before, 1u);
+                } else if (pos < g1 * 64) {
+                    atomicOr(&s_bits[rel >> 5], 1u << (rel & 31));
+                    atomicAdd(&s_cnt[(rel >> 6) / gpw], 1u);
+                }
+            }
+        }
+        __syncthreads();
+        alone = s_res[4] != 0u;
+    }
+    CTKVR_STAMP(69);
+    // --- 4. attention over them, or over all the unit's picks where a block goes on alone --------------------------
+    const int n = min(L, a.top_k);
+    const int per_w = W / nb, word = x * per_w + tid;   // the block's part of the output, a pair of elements a thread
+    float2 o = make_float2(0.0f, 0.0f);
+    float l_o = 0.0f;
+    float acc[G][8], lsum[G];
+    auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int hh = 0; hh < G; ++hh) {
+            lsum[hh] = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[hh][e] = 0.0f;
+        }
+    };
+    auto add_row = [&](const Chunk<T> &c, const float(&w)[G]) __attribute__((always_inline)) {
+        float vx[8];
+        unpack(c, vx);
+#pragma unroll
+        for (int hh = 0; hh < G; ++hh)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[hh][e] = __fmaf_rn(w[hh], vx[e], acc[hh][e]);
+    };
+    // over the wave's four rows of lanes (each is left with two of the eight values; the weights: over all lanes); then, block_pair and block_l, over the waves
+    auto hand_over = [&]() __attribute__((always_inline)) {
+        const int e = (ln >> 4 & 1) * 4 + (ln >> 5) * 2;
+#pragma unroll
+        for (int hh = 0; hh < G; ++hh) {
+            float h4[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) h4[j] = row_pair_sum(acc[hh][j], acc[hh][j + 4]);
+            *reinterpret_cast<float2 *>(s_o + (wv * G + hh) * kD + lane16 * 8 + e) =
+                make_float2(half_pair_sum(h4[0], h4[2]), half_pair_sum(h4[1], h4[3]));
+            float l = group16_sum(lsum[hh]);
+            l = row_pair_sum(l, l);
+            l = half_pair_sum(l, l);
+            if (ln == 0) s_l[wv][hh] = l;
+        }
+        __syncthreads();
+    };
+    auto block_pair = [&](int w) __attribute__((always_inline)) {   // pair w of the block's sums
+        float2 v = make_float2(0.0f, 0.0f);
+#pragma unroll
+        for (int p = 0; p < NW; ++p) {
+            const float2 t = *reinterpret_cast<const float2 *>(s_o + p * G * kD + 2 * w);
+            v.x += t.x;
+            v.y += t.y;
+        }
+        return v;
+    };
+    auto block_l = [&](int hh) __attribute__((always_inline)) {
+        float v = 0.0f;
+#pragma unroll
+        for (int p = 0; p < NW; ++p) v += s_l[p][hh];
+        return v;
+    };
+    if (!alone) {   // uniform
+        clear();
+        uint32_t rank = every ? (uint32_t)min(L, g0 * 64) : s_before;   // picks before the wave's
+#pragma unroll
+        for (int w = 0; w < NW; ++w) rank += w < wv ? s_cnt[w] : 0u;
+        for (;;) {
+            // a pick a lane: those of the deciding bucket that are none lose their place, the others' ids are written
+#pragma unroll
+            for (int i = 0; i < kSharePicks / 64; ++i) {
+                const int p = i * 64 + ln;
+                if (i * 64 >= n_l) break;   // uniform
+                bool ok = false;
+                if (p < n_l) {
+                    const uint32_t pos = w_pos[p], rel = (pos & 0x7fffffffu) - (uint32_t)(g0 * 64);
+                    ok = (int32_t)(pos | s_bits[rel >> 5] << (31u - (rel & 31u))) < 0;   // (a sure pick's bit is not set, nor looked at)
+                    w_pos[p] = ok;
+                }
+                const uint64_t mask = __ballot(ok);
+                if (ok) {
+                    float w[G];
+                    load_z<G>(w_z, p, w);
+#pragma unroll
+                    for (int hh = 0; hh < G; ++hh) lsum[hh] += w[hh];
+                    const uint32_t r = rank_in(mask, rank);
+                    a.sel[(size_t)ul * a.top_k + r] = my_id[i];
+                    if (a.out_sel) a.out_sel[(size_t)ul * a.top_k + r] = my_id[i];
+                }
+                rank += (uint32_t)__popcll(mask);
+            }
+#pragma unroll 1
+            for (int r0 = 0; r0 < n_l; r0 += NU * 4) {
+                if (r0) request(r0);
+#pragma unroll
+                for (int u = 0; u < NU; ++u) {
+                    if (u % 4 == 0 && r0 + u * 4 >= n_l) break;   // uniform
+                    const int p = min(r0 + u * 4 + row4, n_l - 1);
+                    const bool ok = r0 + u * 4 + row4 < n_l && w_pos[p] != 0u;
+                    float w[G];
+                    load_z<G>(w_z, p, w);
+                    if (ok) add_row(cv[u], w);
+                }
+            }
+            if (qn >= nwg) break;   // uniform
+            fill_again();
+            begin();
+        }
+        CTKVR_STAMP(70);
+        hand_over();
+        if (nb == 1) {   // uniform
+            if (tid < per_w) {
+                o = block_pair(word);
+                l_o = block_l(word >> 6);
+            }
+        } else {
+            if (tid < W) {
+                const float2 v = block_pair(tid);
+                const unsigned long long w = ((unsigned long long)__float_as_uint(v.y) << 32) | __float_as_uint(v.x);
+                put(&xout[x * W + tid], w ? w : 0x80000000u);   // (a zero that counts as written is -0)
+            }
+            if (tid < G) put(&xl[x * G + tid], (1ull << 32) | __float_as_uint(block_l(tid)));
+            if (tid < per_w) {
+                unsigned long long w[kShareBlocks], lw[kShareBlocks];
+                bool all = false;
+                for (int it = 0; it < a.spins && !all; ++it) {
+                    all = true;
+#pragma unroll
+                    for (int y = 0; y < kShareBlocks; ++y)
+                        if (y < nb) {
+                            w[y] = get(&xout[y * W + word]);
+                            lw[y] = get(&xl[y * G + (word >> 6)]);
+                        }
+#pragma unroll
+                    for (int y = 0; y < kShareBlocks; ++y)
+                        if (y < nb) all = all && w[y] != 0ull && lw[y] != 0ull;
+                }
+                if (all) {
+#pragma unroll
+                    for (int y = 0; y < kShareBlocks; ++y)
+                        if (y < nb) {
+                            o.x += __uint_as_float((uint32_t)w[y]);
+                            o.y += __uint_as_float((uint32_t)(w[y] >> 32));
+                            l_o += __uint_as_float((uint32_t)lw[y]);
+                        }
+                }
+            }
+        }
+        CTKVR_STAMP(72);
+        // a head whose picks' weights all vanish beside its maximum (or a block that did not answer, and l_o = 0)
+        alone = __syncthreads_or(tid < per_w && L > 0 && !(l_o >= 1e-30f));
+    }
+    if (alone) {   // uniform
+        clear();
+        // all the unit's keys to memory (whoever else does so writes the same), the selection from there, the picks' maxima, then
+        // four rows a wave at a time
+        __syncthreads();
+        uint32_t *kb = a.kbuf + (size_t)ul * a.l_stride, *pk = a.alone + (size_t)ul * a.top_k;
+#pragma unroll 1
+        for (int i = tid; i < L; i += NT) {
+            float v[G];
+            load_z<G>(zb, i, v);
+            less_max(v, i, L);
+            kb[i] = ordered_key(key_of(v));
+        }
+        __threadfence_block();
+        __syncthreads();
+        block_select_topk<NT, 0>([kb](int i) { return kb[i]; }, L, a.top_k, [pk](int pos, int i) { pk[pos] = (uint32_t)i; }, s_hist);
+        __threadfence_block();
+        __syncthreads();
+        const int per = (a.top_k + nb - 1) / nb;
+        float mx[G];
+#pragma unroll
+        for (int hh = 0; hh < G; ++hh) mx[hh] = -__builtin_huge_valf();
+#pragma unroll 1
+        for (int p = tid; p < n; p += NT) {
+            float v[G];
+            load_z<G>(zb, (int)pk[p], v);
+#pragma unroll
+            for (int hh = 0; hh < G; ++hh) mx[hh] = fmaxf(mx[hh], v[hh]);
+            if (p >= x * per && p < (x + 1) * per) {
+                const int id = cb[pk[p]];
+                a.sel[(size_t)ul * a.top_k + p] = id;
+                if (a.out_sel) a.out_sel[(size_t)ul * a.top_k + p] = id;
+            }
+        }
+#pragma unroll
+        for (int hh = 0; hh < G; ++hh) {
+            float v = mx[hh];
+#pragma unroll
+            for (int s = 32; s >= 1; s >>= 1) v = fmaxf(v, __shfl_xor(v, s));
+            if (ln == 0) s_l[wv][hh] = v;
+        }
+        __syncthreads();
+        if (tid < G) {
+            float v = s_l[0][tid];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) v = fmaxf(v, s_l[w][tid]);
+            s_m[tid] = v;
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int p = wv * 4 + row4; p < n; p += NW * 4) {
+            const int i = (int)pk[p];
+            float v[G];
+            load_z<G>(zb, i, v);
+            const Chunk<T> c = load_chunk(V + (size_t)rb[i] * kD, lane16);
+#pragma unroll
+            for (int hh = 0; hh < G; ++hh) {
+                v[hh] = __expf(v[hh] - s_m[hh]);
+                if (lane16 == 0) lsum[hh] += v[hh];
+            }
+            add_row(c, v);
+        }
+        hand_over();
+        if (tid < per_w) {
+            o = block_pair(word);
+            l_o = block_l(word >> 6);
+        }
+    }
+    if (tid < per_w) {
+        const int hh = word >> 6, dim = 2 * (word & 63), b = ul / a.at.g, head = b * a.at.h + (ul - b * a.at.g) * G + hh;
+        const float mh = s_m[hh];
+        float lse;
+        float2 r;
+        r.x = merge_window<G>(a.at.win, ul, hh, dim, o.x, mh, l_o, lse);
+        r.y = merge_window<G>(a.at.win, ul, hh, dim + 1, o.y, mh, l_o, lse);
+        *reinterpret_cast<float2 *>(a.at.out + (size_t)head * kD + dim) = r;
+        if (dim == 0 && a.at.out_lse) a.at.out_lse[head] = lse;
+    }
+    CTKVR_STAMP(47);
+    if (x == 0) {
+        for (int p = n + tid; p < a.top_k; p += NT) {
+            a.sel[(size_t)ul * a.top_k + p] = -1;
+            if (a.out_sel) a.out_sel[(size_t)ul * a.top_k + p] = -1;
+        }
+        if (tid == 0) a.nsel[ul] = n;
+    }
 }
 
 // ------------------------------------------------------------------------------
