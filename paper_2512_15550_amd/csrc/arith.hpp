@@ -125,6 +125,64 @@ __device__ __forceinline__ float row_pair_sum(float a, float b)
     return __uint_as_float(s[0]) + __uint_as_float(s[1]);
 }
 
+// group16_sum of G values at once, the same sums of the same pairs, each left in lanes of its own: value head_of_lane<G>(lane16) in every
+// lane.  Past the steps inside a quad all its lanes agree, so that two values fit one
+// register from there on, quad by quad (bank masks), and four from the last step: 14 adds and no selects for four values, where four
+// separate sums and the choice among them were 27 instructions.  In assembly because the compiler merges no add with a partial bank
+// mask; a DPP operand must have been written two instructions before, hence the order and the s_nops.  Every lane active.
+template <int G> __device__ __forceinline__ int head_of_lane(int lane16)
+{
+    return G == 1 ? 0 : G == 2 ? lane16 >> 2 & 1 : G == 4 ? lane16 >> 2 : (lane16 >> 2) + ((lane16 & 2) << 1);
+}
+__device__ __forceinline__ float group16_sum4(float a, float b, float c, float d)
+{
+    float r;
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %3, %3, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %4, %4, %4 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %2, %2, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %3, %3, %3 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %4, %4, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %2, %2, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %3, %3, %3 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %3, %4, %4 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %1, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "v_add_f32_dpp %0, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "s_nop 0\n\t"
+        "v_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0x3"
+        : "=&v"(r), "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+    return r;
+}
+template <int G> __device__ __forceinline__ float group16_sums(const float (&v)[G], int lane16)
+{
+    if constexpr (G == 1) {
+        return group16_sum(v[0]);
+    } else if constexpr (G == 2) {
+        float a = v[0], b = v[1];
+        asm("s_nop 1\n\t"
+            "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+            "s_nop 0\n\t"
+            "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+            "s_nop 0\n\t"
+            "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+            "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+            "s_nop 1\n\t"
+            "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf"
+            : "+v"(a), "+v"(b));
+        return a;
+    } else if constexpr (G == 4) {
+        return group16_sum4(v[0], v[1], v[2], v[3]);
+    } else {
+        const float lo = group16_sum4(v[0], v[1], v[2], v[3]), hi = group16_sum4(v[4], v[5], v[6], v[7]);
+        return lane16 & 2 ? hi : lo;
+    }
+}
+
 __device__ __forceinline__ float lane_partial(const float (&a)[8], const float (&b)[8])
 {
     float acc = 0.0f;

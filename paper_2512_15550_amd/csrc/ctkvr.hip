@@ -1492,7 +1492,6 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     Units u = units;
     RecallScoreArgs sa{};
     sa.u = u;
-    sa.stream_k = stream_k;
     sa.q = q;
     sa.k = Paged{k_pages, bt, max_pages, ix->page_shift};
     sa.ctx_lens = d_ctx_lens;
@@ -1522,7 +1521,6 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         // half are recalled (four probes of 1280, four KV heads: 64 entries 33.9, 128 33.3, 256 34.9).  Otherwise by id
         // range: enough blocks to fill the chip a few times over, each owning 8..64 words of the bitmap.
         const bool by_rank = ix->score_by_rank < 0 ? (long long)ix->l_stride * U <= 2048ll * ix->num_cu : ix->score_by_rank != 0;
-        sa.by_rank = by_rank;
         int nbx;
         if (by_rank) {
             nbx = std::min(std::max(32, (2 * ix->num_cu + U - 1) / U), (ix->l_stride + 127) / 128);
@@ -1541,27 +1539,33 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
             const int pages = (std::min(max_pages, ((ix->s_max - 1) >> ix->page_shift) + 1) + 255) & ~255;
             RecallLds all = sa.lds;
             all.pages = pages;
-            sa.lds.pages = words && pages <= kRecallWords && all.total() * 4 <= 60 * 1024 ? pages : 0;
+            sa.lds.pages = words && pages <= kRecallWords && all.total() * 4 <= 61 * 1024 ? pages : 0;
         } else {
             sa.lds.pages = 256;
             sa.lds.words = 0;
         }
         const size_t slds = (size_t)sa.lds.total() * 4;
-        auto launch = [&](auto rows) {
-            constexpr int R = decltype(rows)::value;
+        auto launch = [&](auto rank, auto stream) {
+            constexpr bool RANK = decltype(rank)::value, STREAM = decltype(stream)::value;
             if constexpr (G <= 4) {
                 if (window) {
                     sa.win = wa;
-                    recall_score_kernel<T, G, true, R><<<dim3(nbx + kWinSplit, U), 256, slds, st>>>(sa);
+                    recall_score_kernel<T, G, true, RANK, STREAM><<<dim3(nbx + kWinSplit, U), 256, slds, st>>>(sa);
                     return;
                 }
             }
-            recall_score_kernel<T, G, false, R><<<dim3(nbx, U), 256, slds, st>>>(sa);
+            recall_score_kernel<T, G, false, RANK, STREAM><<<dim3(nbx, U), 256, slds, st>>>(sa);
+        };
+        auto launch_rank = [&](auto rank) {
+            if (stream_k)
+                launch(rank, std::true_type{});
+            else
+                launch(rank, std::false_type{});
         };
         if (by_rank)
-            launch(std::integral_constant<int, kRankRows<T>>{});
+            launch_rank(std::true_type{});
         else
-            launch(std::integral_constant<int, 8>{});
+            launch_rank(std::false_type{});
     }
     if (whole) ix->mark(3, st);
 

@@ -614,6 +614,7 @@ template <typename T, int G> __global__ __launch_bounds__(256) void window_attn_
 // ------------------------------------------------------------------------------
 constexpr int kRecallWpb = 64;     // by id range: at most 2048 ids per block
 constexpr int kRecallCap = 2048;   // ids per block at most
+constexpr int kRecallPad = 256;    // words behind the rows: a tile beyond the last is requested too
 // Rows in flight per 16-lane group.  By id range eight: four blocks a CU.  By rank a CU has two blocks and the registers are free, and
 // twelve take the 125 to 170 rows of a block of the 32K step in one trip, not two (step 33.9 -> 32.9 us with two blocks a CU; sixteen:
 // the same; rows of 512 bytes: no gain at 4K, eight).
@@ -623,7 +624,7 @@ constexpr int kRecallWords = 4096; // by rank: bitmap words (contexts up to 128K
 // words of shared memory: ids and rows of the block, block-table entries, by rank the bitmap and the ids before each word
 struct RecallLds {
     int pages, words;
-    __host__ __device__ int total() const { return 2 * kRecallCap + pages + 2 * words; }
+    __host__ __device__ int total() const { return 2 * kRecallCap + kRecallPad + pages + 2 * words; }
 };
 
 struct RecallScoreArgs {
@@ -642,21 +643,22 @@ struct RecallScoreArgs {
     uint4 *clear;             // optional: [units][clear_n] words that the launches behind expect to find zero, cleared here
     int clear_n;
     float scale;
-    int stream_k;             // the keys of all sequences exceed what the memory-side cache holds: load them non-temporal
-    int by_rank;              // how the bitmap is split over a unit's blocks
     int by_xcd;               // blocks -> (unit, block of the unit) by unit_block_of
     RecallLds lds;            // by rank: words = 0 where the bitmap is read again instead, pages = 0 where the pages do not fit
     int nbx;                  // blocks per unit that score; with WIN blocks nbx .. nbx + kWinSplit - 1 take the resident window
     WindowArgs win;
 };
 
-template <typename T, int G, bool WIN, int R> __global__ __launch_bounds__(256) void recall_score_kernel(RecallScoreArgs a)
+// RANK: how the bitmap is split over a unit's blocks.  STREAM: the keys of all sequences exceed what the memory-side cache holds, and are
+// loaded non-temporal
+template <typename T, int G, bool WIN, bool RANK, bool STREAM> __global__ __launch_bounds__(256) void recall_score_kernel(RecallScoreArgs a)
 {
-    constexpr int TILE = 16 * R;
+    constexpr int R = RANK ? kRankRows<T> : 8, TILE = 16 * R;
+    static_assert(TILE <= kRecallPad, "rows requested beyond the block's");
     extern __shared__ __align__(16) uint32_t smem[];
     uint32_t *s_ids = smem, *s_rows = smem + kRecallCap;     // ids of this block's ranks, their rows
-    int32_t *s_page = (int32_t *)(smem + 2 * kRecallCap);    // block-table entries
-    uint32_t *s_word = smem + 2 * kRecallCap + a.lds.pages, *s_before = s_word + a.lds.words;
+    int32_t *s_page = (int32_t *)(smem + 2 * kRecallCap + kRecallPad);    // block-table entries
+    uint32_t *s_word = (uint32_t *)s_page + a.lds.pages, *s_before = s_word + a.lds.words;
     __shared__ uint32_t s_tmp[8];
     __shared__ uint32_t s_edge[3];                // first word, ids before it, last word
     __shared__ uint32_t s_max[G];
@@ -698,7 +700,7 @@ template <typename T, int G, bool WIN, int R> __global__ __launch_bounds__(256) 
         for (int w = bx * 256 + tid; w < a.clear_n; w += a.nbx * 256) a.clear[(size_t)ul * a.clear_n + w] = make_uint4(0u, 0u, 0u, 0u);
     };
     uint32_t r0, r1;   // the block's ranks
-    if (a.by_rank && a.lds.words) {
+    if (RANK && a.lds.words) {
         // thread t counts words [t wpt, (t + 1) wpt), wpt a multiple of four, and keeps them (those from the sequence's end up to
         // the row's are zero)
         constexpr int NV = kRecallWords / 1024, NP = kRecallWords / 256;
@@ -756,7 +758,7 @@ template <typename T, int G, bool WIN, int R> __global__ __launch_bounds__(256) 
             else
                 expand(word, w, part, rk, r0, r1, [&](int p) { return bt_row[p]; });
         }
-    } else if (a.by_rank) {
+    } else if (RANK) {
         // longer contexts: two passes over the words, the second over those between the block's first and last rank
         const int wpt = ((((a.bitmap_words + 255) >> 8) + 3) >> 2) << 2;
         const int w0 = tid * wpt, w1 = min(w0 + wpt, a.bitmap_words);
@@ -816,6 +818,8 @@ template <typename T, int G, bool WIN, int R> __global__ __launch_bounds__(256) 
         // batch still uses all of them)
         const int W = (a.ctx_lens[b] + 31) >> 5;
         const int wpb = min(kRecallWpb, (W + a.nbx - 1) / a.nbx);
+        // (rows beyond the block's, which are requested with the last ones: row 0 of the pool)
+        for (int w = tid; w < (kRecallCap + kRecallPad) / 4; w += 256) reinterpret_cast<uint4 *>(s_rows)[w] = make_uint4(0u, 0u, 0u, 0u);
         const int w_beg = bx * wpb, w_end = min(W, w_beg + wpb);
         clear();
         if (w_beg >= W) return;
@@ -869,50 +873,82 @@ template <typename T, int G, bool WIN, int R> __global__ __launch_bounds__(256) 
     const T *qb = (const T *)a.q + ((size_t)b * a.u.h + kv * G) * kD;
 #pragma unroll
     for (int hh = 0; hh < G; ++hh) unpack(load_chunk(qb + (size_t)hh * kD, lane16), q[hh]);
-    // lane l of a 16-lane group keeps head (l mod G): its score, and that head's running maximum
+    // a lane keeps the score of one head, and that head's running maximum
     float mxl = -__builtin_huge_valf();
-    const int myh = lane16 & (G - 1);
+    const int myh = head_of_lane<G>(lane16);
+    constexpr int SUB = G == 8 ? 2 : 4;      // lanes of a head that stand for a round of rows each when scores are written
+    const int sub = lane16 & (SUB - 1);
+    static_assert(R % SUB == 0, "rounds are written SUB at a time");
     const int last = (int)n_blk - 1;
-    for (int t0 = 0; t0 < (int)n_blk; t0 += TILE) {
-        Chunk<T> ck[R];
-        const T *krow[R];
-        // (rounds of sixteen rows of which the tile has none are left out, uniformly, the first four aside)
-        constexpr int R0 = 4;
+    Chunk<T> ck[R];
+    auto row_at = [&](int i) __attribute__((always_inline)) { return s_rows[RANK ? min(i, last) : i]; };
+    auto request = [&](int r, uint32_t row) __attribute__((always_inline)) {
+        const T *p = K + (size_t)row * kD;
+        ck[r] = STREAM ? load_chunk_nt(p, lane16) : load_chunk(p, lane16);
+    };
+    auto score = [&](const float(&kx)[8]) __attribute__((always_inline)) {
+        float part[G];
 #pragma unroll
-        for (int r = 0; r < R; ++r) krow[r] = K + (size_t)s_rows[min(t0 + r * 16 + grp, last)] * kD;
-        if (a.stream_k) {
+        for (int hh = 0; hh < G; ++hh) part[hh] = lane_partial(q[hh], kx);
+        return group16_sums<G>(part, lane16) * a.scale;
+    };
+    auto keep = [&](float z) __attribute__((always_inline)) { asm("v_max_f32 %0, %0, %1" : "+v"(mxl) : "v"(z)); };
+    {
+        uint32_t row[R];
 #pragma unroll
-            for (int r = 0; r < R; ++r)
-                if (r < R0 || t0 + r * 16 <= last) ck[r] = load_chunk_nt(krow[r], lane16);
-        } else {
+        for (int r = 0; r < R; ++r) row[r] = row_at(r * 16 + grp);
 #pragma unroll
-            for (int r = 0; r < R; ++r)
-                if (r < R0 || t0 + r * 16 <= last) ck[r] = load_chunk(krow[r], lane16);
+        for (int r = 0; r < R; ++r) request(r, row[r]);
+    }
+    // Each round of rows is requested again for the next tile as soon as it is unpacked, so that a wave always has all its R rounds but
+    // one in flight; requested a tile at a time, and rounds without rows left out by branches, the first round was waited for
+    // together with most others.  (No branch between these requests either: what may not have been requested is waited for as well.)
+    // With that and 60 vector instructions a round where there were 80: steps of 128K x 4 111.8 -> 104.8 us, sixteen of 8K to 64K
+    // 122.3 -> 114.5, 32K 31.9 -> 31.2.
+    float *zl = zb + (size_t)(sub * 16 + grp) * G + myh;
+    int t0 = 0;
+#pragma unroll 1
+    for (; t0 + TILE < (int)n_blk; t0 += TILE) {
+        uint32_t row[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) row[r] = row_at(t0 + TILE + r * 16 + grp);
+#pragma unroll
+        for (int r0 = 0; r0 < R; r0 += SUB) {
+            float zw = 0.0f;
+#pragma unroll
+            for (int r = r0; r < r0 + SUB; ++r) {
+                float kx[8];
+                unpack(ck[r], kx);
+                request(r, row[r]);
+                __builtin_amdgcn_sched_barrier(0);   // (moved together, the rounds would all be waited for first)
+                const float z = score(kx);
+                keep(z);
+                zw = r == r0 || sub == r - r0 ? z : zw;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            zl[(size_t)(t0 + r0 * 16) * G] = zw;
         }
+    }
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (r >= R0 && t0 + r * 16 > last) break;
+    for (int r0 = 0; r0 < R; r0 += SUB) {
+        if (t0 + r0 * 16 > last) break;   // uniform
+        float zw = 0.0f;
+#pragma unroll
+        for (int r = r0; r < r0 + SUB; ++r) {
+            if (t0 + r * 16 > last) break;   // uniform
             float kx[8];
             unpack(ck[r], kx);
-            float mine_z = 0.0f;
-#pragma unroll
-            for (int hh = 0; hh < G; ++hh) {
-                float tot = group16_sum(lane_partial(q[hh], kx));
-                if (hh == 0 || myh == hh) mine_z = tot;
-            }
-            mine_z = mine_z * a.scale;
-            const int i = t0 + r * 16 + grp;
-            if (i <= last) {
-                mxl = __builtin_amdgcn_fmed3f(mxl, mine_z, __builtin_huge_valf());   // max of two non-NaN values
-                if (lane16 < G) zb[(size_t)i * G + lane16] = mine_z;
-            }
+            const float z = score(kx);
+            keep(t0 + r * 16 + grp <= last ? z : -__builtin_huge_valf());
+            zw = r == r0 || sub == r - r0 ? z : zw;
         }
+        if (t0 + (r0 + sub) * 16 + grp <= last) zl[(size_t)(t0 + r0 * 16) * G] = zw;
     }
     {
         float v = mxl;
         v = __builtin_amdgcn_fmed3f(v, __shfl_xor(v, 16), __builtin_huge_valf());
         v = __builtin_amdgcn_fmed3f(v, __shfl_xor(v, 32), __builtin_huge_valf());
-        if (lane_id() < G) atomicMax(&s_max[lane_id()], ordered_key(v));
+        if (ln < 16 && (G == 1 ? lane16 == 0 : G == 2 ? (lane16 & 11) == 0 : sub == 0)) atomicMax(&s_max[myh], ordered_key(v));
     }
     int32_t *cd = a.cand + (size_t)ul * a.l_stride + base;
     uint32_t *rw = a.crow + (size_t)ul * a.l_stride + base;
