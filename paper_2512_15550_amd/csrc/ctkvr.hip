@@ -1087,7 +1087,11 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
                     ca.seg_cap = seg_cap;
                     ca.lists = ix->lists;
                     ca.fail = d_fail + u0 / ix->c_max;
-                    sample_threshold_kernel<<<dim3(nu), 1024, 0, st>>>(ca);
+                    // eight samples a thread, or sixteen
+                    if (sample_stride <= 2048)
+                        sample_threshold_kernel<256, 8><<<dim3(nu), 256, 0, st>>>(ca);
+                    else
+                        sample_threshold_kernel<512, 16><<<dim3(nu), 512, 0, st>>>(ca);
                     ma.step_stride = 1;
                     ma.tau = tau;
                     ma.cand = cand;

@@ -1935,7 +1935,9 @@ template <int G> __global__ __launch_bounds__(1024) void rerank_select_kernel(Se
 // within cand_cap (the count of the sample spreads by sqrt(n)).  Where even the samples equal to the key are twice what fits
 // (equal keys), tau = +inf and the unit has no candidates: it is handed back whatever is collected (storing and
 // counting every key first, a build of 65536 tokens and 1024 centroids, 8 KV heads: 9.16 ms, now 8.05).  Fewer samples than r: tau = 0, every key is a candidate.
-// (The key itself for every unit, by radix rounds: 159 us for 8192 units of 8192 samples, now 77 to 90.)
+// (The key itself for every unit, by radix rounds: 159 us for 8192 units of 8192 samples, 83 by the histogram.)  Bound by the latencies of a
+// unit's phases, which many small blocks on a CU hide better than few of 1024 threads: 512 threads of sixteen samples 83 -> 58 us (256 of
+// 32: 59.5), up to 2048 samples 256 of eight, 4860 units 38 -> 12.6.
 // cand_select_kernel: the rho largest of the unit's candidates (key, id), gathered from the segments the
 // blocks of the PICK pass filled, ties to the lowest id, written to the unit's list in ascending id order.
 // A unit with fewer than rho candidates, more than cand_cap, or a segment that ran over, raises the flag of its (sequence, KV head)
@@ -1962,7 +1964,7 @@ struct CandArgs {
     uint32_t *fail;           // [chunk's (sequence, KV head) pairs], zeroed by sample_threshold_kernel
 };
 
-__global__ __launch_bounds__(1024) void sample_threshold_kernel(CandArgs a)
+template <int NT, int KPT> __global__ __launch_bounds__(NT) void sample_threshold_kernel(CandArgs a)
 {
     __shared__ uint32_t s_hist[2048 + 64];
     __shared__ uint32_t s_cnt, s_res[2];
@@ -1971,18 +1973,18 @@ __global__ __launch_bounds__(1024) void sample_threshold_kernel(CandArgs a)
     if (tid < a.t_splits) a.seg_cnt[(size_t)ul * a.t_splits + tid] = 0u;   // for the candidate pass
     if (tid == 0 && ul % a.u.c_max == 0) a.fail[ul / a.u.c_max] = 0u;
     if (!decode_unit(a.u, ul, b, kv, j)) return;
-    s_hist[tid] = s_hist[1024 + tid] = 0u;
+#pragma unroll
+    for (int q = 0; q < BPT; ++q) s_hist[q * NT + tid] = 0u;
     const int s = a.ctx_lens[b];
     const int ST = 32 * a.step_stride;
     const int n = ((s + ST - 1) / ST) * 32;   // sample slots of this unit (the last step's may reach beyond s)
     const uint32_t *ks = a.ksamp + (size_t)ul * a.sample_stride;
     if (tid == 0) s_cnt = 0u;
-    constexpr int KPT = kSampleCap / 1024;
     uint32_t kreg[KPT];
     uint32_t mine = 0;
 #pragma unroll
     for (int q = 0; q < KPT; ++q) {
-        const int i = q * 1024 + tid;
+        const int i = q * NT + tid;
         const int t = (i >> 5) * ST + (i & 31);
         const bool valid = i < n && t < s - a.n_local && t >= a.n_init;
         kreg[q] = ks[min(i, n - 1)];
@@ -1991,6 +1993,8 @@ __global__ __launch_bounds__(1024) void sample_threshold_kernel(CandArgs a)
     }
     __syncthreads();
     mine = wave_sum_uniform(mine);
+    static_assert(NT >= 64, "a segment's counter per thread");
+    constexpr int BPT = kBuckets / NT;   // buckets per thread
     if ((tid & 63) == 0 && mine) atomicAdd(&s_cnt, mine);
     __syncthreads();
     const uint32_t n_valid = s_cnt;
@@ -2007,13 +2011,21 @@ __global__ __launch_bounds__(1024) void sample_threshold_kernel(CandArgs a)
     }
     __syncthreads();
     {
-        const uint32_t c0 = s_hist[2 * tid], c1 = s_hist[2 * tid + 1];   // in descending key order
+        uint32_t c[BPT], sum = 0;   // in descending key order
+#pragma unroll
+        for (int q = 0; q < BPT; ++q) {
+            c[q] = s_hist[BPT * tid + q];
+            sum += c[q];
+        }
         uint32_t tot;
-        const uint32_t before = block_excl_scan<1024>(c0 + c1, s_hist + 2048 + 4, &tot);
-        if (before < r && r <= before + c0 + c1) {
-            const bool first = r <= before + c0;
-            s_res[0] = (uint32_t)(2 * tid) + (first ? 0u : 1u);
-            s_res[1] = before + c0 + (first ? 0u : c1);   // samples at or above the bucket's lower end
+        uint32_t before = block_excl_scan<NT>(sum, s_hist + 2048 + 4, &tot);
+#pragma unroll
+        for (int q = 0; q < BPT; ++q) {
+            if (before < r && r <= before + c[q]) {
+                s_res[0] = (uint32_t)(BPT * tid + q);
+                s_res[1] = before + c[q];   // samples at or above the bucket's lower end
+            }
+            before += c[q];
         }
         if (tid == 0) s_cnt = 0u;
         __syncthreads();
@@ -2025,10 +2037,10 @@ __global__ __launch_bounds__(1024) void sample_threshold_kernel(CandArgs a)
     }
     auto for_slots = [&](auto f) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < KPT; ++q) f(q * 1024 + tid, kreg[q] != 0u, kreg[q]);
+        for (int q = 0; q < KPT; ++q) f(q * NT + tid, kreg[q] != 0u, kreg[q]);
     };
     uint32_t T, need_eq;
-    block_kth_largest<1024>(for_slots, r, s_hist, T, need_eq);
+    block_kth_largest<NT>(for_slots, r, s_hist, T, need_eq);
     uint32_t n_at = 0;
 #pragma unroll
     for (int q = 0; q < KPT; ++q) n_at += kreg[q] >= T ? 1u : 0u;
