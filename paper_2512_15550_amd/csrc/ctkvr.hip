@@ -628,8 +628,8 @@ int upload_ints(int32_t *dst, const int32_t *src, int n, hipStream_t st)
 
 // Lays out and takes everything an index holds; fills the host-side geometry.  What a step expects to find zero is
 // cleared on `st`; so are the tables if a later step of the build leaves rows of them unwritten (clear_tables: sequences
-// with fewer than c_max centroids).
-int create_index(const ctkvr_params *p, const int32_t *ctx_lens, bool clear_tables, hipStream_t st, ctkvr_index **out)
+// with fewer than c_max centroids).  first_row (builds; else null) goes to the device with the lengths.
+int create_index(const ctkvr_params *p, const int32_t *ctx_lens, const int32_t *first_row, bool clear_tables, hipStream_t st, ctkvr_index **out)
 {
     ctkvr_index *ix = new (std::nothrow) ctkvr_index();
     if (!ix) return fail(CTKVR_ENOMEM, "host allocation failed");
@@ -795,11 +795,25 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, bool clear_tabl
         zero(ix->ws.srow, U * (size_t)p->top_k);   // always valid rows (see sparse_attn_kernel)
         size_t most = 0;
         for (int i = 0; i < z.n; ++i) most = std::max(most, z.words[i]);
-        zero_ranges_kernel<<<dim3((unsigned)std::min<size_t>(256, (most + 1023) / 1024), z.n), 256, 0, st>>>(z);
+        const unsigned gx = (unsigned)std::max<size_t>(1, std::min<size_t>(256, (most + 1023) / 1024));
+        const int32_t *src[IntRows::kMax] = {ix->ctx_lens.data(), ix->n_cent.data(), first_row};
+        int32_t *dst[IntRows::kMax] = {ix->d_ctx_lens, ix->d_n_cent, first_row ? ix->d_first : nullptr};
+        if (IntRows::kMax * B <= IntPack::kMax) {   // the usual batch: one launch (of four, each some 3 us of a short build)
+            IntRows rows{};
+            IntPack pack;
+            rows.n = B;
+            for (int r = 0; r < IntRows::kMax; ++r) {
+                rows.dst[r] = dst[r];
+                if (dst[r]) memcpy(pack.v + r * B, src[r], (size_t)B * 4);
+            }
+            set_up_kernel<<<dim3(gx, z.n + 1), 256, 0, st>>>(z, rows, pack);
+        } else {
+            zero_ranges_kernel<<<dim3(gx, z.n), 256, 0, st>>>(z);
+            for (int r = 0; r < IntRows::kMax && rc == CTKVR_OK; ++r)
+                if (dst[r]) rc = upload_ints(dst[r], src[r], B, st);
+        }
         e = hipGetLastError();
     }
-    if (rc == CTKVR_OK && e == hipSuccess) rc = upload_ints(ix->d_ctx_lens, ix->ctx_lens.data(), B, st);
-    if (rc == CTKVR_OK && e == hipSuccess) rc = upload_ints(ix->d_n_cent, ix->n_cent.data(), B, st);
     if (rc == CTKVR_OK && e == hipSuccess && clear_tables && *std::min_element(ix->n_cent.begin(), ix->n_cent.end()) < ix->c_max) {
         ZeroRanges z{};
         z.n = 2;
@@ -2029,25 +2043,23 @@ int ctkvr_build_index(const ctkvr_params *p, const void *q_prefill, const int32_
     }
     ctkvr_index *ix = nullptr;
     hipStream_t st = (hipStream_t)hip_stream;
-    TRY(create_index(p, ctx_lens, true, st, &ix));
-    int rc = upload_ints(ix->d_first, first_row.data(), p->batch, st);
+    TRY(create_index(p, ctx_lens, first_row.data(), true, st, &ix));
+    int rc = CTKVR_OK;
     const int32_t *d_first = ix->d_first;
-    if (rc == CTKVR_OK) {
-        dim3 grid(ix->c_max, p->n_q_heads, p->batch);
+    {
+        dim3 grid((ix->c_max + 15) / 16, p->n_q_heads, p->batch);
         if (kmeans) {
             rc = run_kmeans(ix, (const bf16_t *)q_prefill, d_first, init_pos, st);
             if (rc == CTKVR_OK) rc = launch_inv_norms<bf16_t>(ix, st);
             if (rc == CTKVR_OK) rc = build_lists_dispatch<bf16_t>(ix, k_pages, block_table, max_pages, st);
         } else if (p->dtype == CTKVR_BF16) {
-            copy_centroids_kernel<bf16_t><<<grid, 128, 0, st>>>((const bf16_t *)q_prefill, d_first, ix->d_n_cent,
-                                                                 p->n_q_heads, ix->c_max, (bf16_t *)ix->centroids);
-            rc = launch_inv_norms<bf16_t>(ix, st);
-            if (rc == CTKVR_OK) rc = build_lists_dispatch<bf16_t>(ix, k_pages, block_table, max_pages, st);
+            copy_centroids_kernel<bf16_t><<<grid, 256, 0, st>>>((const bf16_t *)q_prefill, d_first, ix->d_n_cent, p->n_q_heads,
+                                                                 ix->c_max, (bf16_t *)ix->centroids, ix->inv_norm_c);
+            rc = build_lists_dispatch<bf16_t>(ix, k_pages, block_table, max_pages, st);
         } else {
-            copy_centroids_kernel<float><<<grid, 128, 0, st>>>((const float *)q_prefill, d_first, ix->d_n_cent,
-                                                                p->n_q_heads, ix->c_max, (float *)ix->centroids);
-            rc = launch_inv_norms<float>(ix, st);
-            if (rc == CTKVR_OK) rc = build_lists_dispatch<float>(ix, k_pages, block_table, max_pages, st);
+            copy_centroids_kernel<float><<<grid, 256, 0, st>>>((const float *)q_prefill, d_first, ix->d_n_cent, p->n_q_heads,
+                                                                ix->c_max, (float *)ix->centroids, ix->inv_norm_c);
+            rc = build_lists_dispatch<float>(ix, k_pages, block_table, max_pages, st);
         }
     }
     if (rc == CTKVR_OK) {
@@ -2071,7 +2083,7 @@ int ctkvr_index_load(const ctkvr_params *p, const int32_t *ctx_lens, const void 
     if (!centroids || !lists) return fail(CTKVR_EINVAL, "a required pointer is NULL");
     ctkvr_index *ix = nullptr;
     hipStream_t st = (hipStream_t)hip_stream;
-    TRY(create_index(p, ctx_lens, false, st, &ix));
+    TRY(create_index(p, ctx_lens, nullptr, false, st, &ix));
     const size_t es = elem_size(p->dtype);
     const CopySeg segs[2] = {{ix->centroids, centroids, (size_t)p->batch * p->n_q_heads * ix->c_max * 128 * es},
                              {ix->lists, lists, (size_t)ix->units * ix->c_max * p->list_len * 4}};

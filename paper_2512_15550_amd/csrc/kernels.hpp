@@ -87,7 +87,7 @@ struct ZeroRanges {
     size_t words[kMax];
     int n;
 };
-__global__ void zero_ranges_kernel(ZeroRanges z)
+__device__ __forceinline__ void zero_range(const ZeroRanges &z)
 {
     uint32_t *p = z.p[blockIdx.y];
     const size_t n = z.words[blockIdx.y], step = (size_t)gridDim.x * blockDim.x, n4 = n / 4;
@@ -95,6 +95,7 @@ __global__ void zero_ranges_kernel(ZeroRanges z)
     for (size_t i = i0; i < n4; i += step) reinterpret_cast<uint4 *>(p)[i] = make_uint4(0u, 0u, 0u, 0u);
     for (size_t i = 4 * n4 + i0; i < n; i += step) p[i] = 0u;
 }
+__global__ void zero_ranges_kernel(ZeroRanges z) { zero_range(z); }
 
 // integers that travel as a kernel argument
 struct IntPack {
@@ -104,6 +105,24 @@ struct IntPack {
 __global__ void put_ints_kernel(int32_t *dst, int n, IntPack pack)
 {
     for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = pack.v[i];
+}
+
+// both in one launch: grid (any, z.n + 1); the pack holds rows.n integers for each of the destinations (null: not wanted), one after the other
+struct IntRows {
+    static constexpr int kMax = 3;
+    int32_t *dst[kMax];
+    int n;
+};
+__global__ void set_up_kernel(ZeroRanges z, IntRows rows, IntPack pack)
+{
+    if ((int)blockIdx.y < z.n) {
+        zero_range(z);
+        return;
+    }
+    if (blockIdx.x) return;
+    for (int r = 0; r < IntRows::kMax; ++r)
+        if (rows.dst[r])
+            for (int i = threadIdx.x; i < rows.n; i += blockDim.x) rows.dst[r][i] = pack.v[r * rows.n + i];
 }
 
 // The lowest flat index of a list entry that is not a key id of its sequence goes to *bad (~0: none).  grid (c_max, units)
@@ -131,17 +150,24 @@ __global__ void zero3_u32_kernel(uint32_t *p0, size_t n0, uint32_t *p1, size_t n
     }
 }
 
-// Algorithm 1 line 1: centroid j of sequence b, head hd = prompt query at position s_b - C_b + j.
-// q_prefill rows [first_row_b + j][h][128] -> centroids [b][h][c_max][128]
+// Algorithm 1 line 1: centroid j of sequence b, head hd = prompt query at position s_b - C_b + j, and its inverse norm.
+// q_prefill rows [first_row_b + j][h][128] -> centroids [b][h][c_max][128]; the norms of rows beyond n_cent are 0, the rows
+// themselves are left alone (zeros).  A row is 16 bytes a lane of 16, or twice that (an element a thread and the norms in a launch of
+// their own: 2048 centroids of 32 heads, bf16, 20.4 + 4.5 us).  grid (ceil(c_max / 16), h, batch), 256 threads
 template <typename T>
-__global__ void copy_centroids_kernel(const T *q_prefill, const int32_t *first_row /*[batch]*/, const int32_t *n_cent,
-                                      int h, int c_max, T *centroids)
+__global__ __launch_bounds__(256) void copy_centroids_kernel(const T *q_prefill, const int32_t *first_row /*[batch]*/,
+                                                             const int32_t *n_cent, int h, int c_max, T *centroids, float *inv_norm)
 {
-    int j = blockIdx.x, hd = blockIdx.y, b = blockIdx.z;
-    if (j >= n_cent[b]) return;
-    const T *src = q_prefill + ((size_t)(first_row[b] + j) * h + hd) * kD;
-    T *dst = centroids + (((size_t)b * h + hd) * c_max + j) * kD;
-    dst[threadIdx.x] = src[threadIdx.x];
+    const int j = blockIdx.x * 16 + (threadIdx.x >> 4), lane16 = threadIdx.x & 15, hd = blockIdx.y, b = blockIdx.z;
+    const int C = n_cent[b];
+    const size_t row = ((size_t)b * h + hd) * c_max + j;
+    Chunk<T> c;   // (the caller's rows start on any element)
+    __builtin_memcpy(&c, q_prefill + ((size_t)(first_row[b] + min(j, C - 1)) * h + hd) * kD + 8 * lane16, sizeof c);
+    float x[8];
+    unpack(c, x);
+    const float n2 = group16_sum(lane_partial(x, x));
+    if (j < C) __builtin_memcpy(__builtin_assume_aligned(centroids + row * kD + 8 * lane16, 16), &c, sizeof c);
+    if (j < c_max && lane16 == 0) inv_norm[row] = j < C ? inv_norm_from_sq(n2) : 0.0f;
 }
 
 // inverse norms of n rows of 128
