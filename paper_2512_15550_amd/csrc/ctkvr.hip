@@ -981,7 +981,10 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
     };
     int rc = scratch_mem.get(ix->dev, lay_out(nullptr));
     if (rc == CTKVR_OK) lay_out(scratch_mem.base());
-    if (rc == CTKVR_OK && by_cand) rc = want_lds(ix->dev, (const void *)cand_select_kernel, cand_lds);
+    // a thread holds 16 candidates (cand_select_kernel)
+    const bool cand_small = cand_cap <= 16 * 256;
+    if (rc == CTKVR_OK && by_cand)
+        rc = want_lds(ix->dev, cand_small ? (const void *)cand_select_kernel<256, 16> : (const void *)cand_select_kernel<512, kCandCap / 512>, cand_lds);
     if (rc == CTKVR_OK && by_list)
         rc = want_lds(ix->dev, ix->s_max <= 8 * 512    ? (const void *)key_list_kernel<512, 8>
                                : ix->s_max <= 32 * 512 ? (const void *)key_list_kernel<512, 32>
@@ -1112,7 +1115,10 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
                     ma.seg_cnt = cursor;
                     ma.seg_cap = seg_cap;
                     mfma_score_kernel<G, MFMA_PICK><<<dim3(ma.t_splits, tiles), (MfmaShape<G, MFMA_PICK>::NT), 0, st>>>(ma);
-                    cand_select_kernel<<<dim3(nu), kCandThreads, cand_lds, st>>>(ca);
+                    if (cand_small)
+                        cand_select_kernel<256, 16><<<dim3(nu), 256, cand_lds, st>>>(ca);
+                    else
+                        cand_select_kernel<512, kCandCap / 512><<<dim3(nu), 512, cand_lds, st>>>(ca);
                 } else {   // every key stored, then histogram and selection over all of them
                     ma.kbuf = kbuf;
                     mfma_score_kernel<G, MFMA_KEY><<<dim3(ma.t_splits, tiles), (MfmaShape<G, MFMA_KEY>::NT), 0, st>>>(ma);

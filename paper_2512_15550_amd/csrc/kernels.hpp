@@ -1968,8 +1968,9 @@ template <int G> __global__ __launch_bounds__(1024) void rerank_select_kernel(Se
 // blocks of the PICK pass filled, ties to the lowest id, written to the unit's list in ascending id order.
 // A unit with fewer than rho candidates, more than cand_cap, or a segment that ran over, raises the flag of its (sequence, KV head)
 // pair instead (the caller then redoes the pair by the route that keeps every key).
-// Both: grid = chunk units.  cand_select: 512 threads, which hold the candidates in registers (through shared memory, 75 KB a
-// block at rho = 2048, two blocks of 1024 threads shared a CU: 270 us for 8192 units, now 191); dynamic shared memory 2112 + kCandTies +
+// Both: grid = chunk units, NT threads of KPT slots.  cand_select holds the candidates in registers (through shared memory, 75 KB a
+// block at rho = 2048, two blocks of 1024 threads shared a CU: 270 us for 8192 units, now 184): sixteen a thread, 256 threads where cand_cap
+// allows it (4860 units of 4096 at most 59 -> 54 us, a build of three of 9K..30K 806 -> 784), 512 beyond (256 of 32 a thread: 266); dynamic shared memory 2112 + kCandTies +
 // ceil(s_max / 32) words (one bitmap over the ids; the candidates that tie with the rho-th key, normally one, are
 // sorted out in a short list: more than kCandTies of them also raise the flag); cand_cap <= kCandCap.
 // ------------------------------------------------------------------------------
@@ -2078,12 +2079,9 @@ template <int NT, int KPT> __global__ __launch_bounds__(NT) void sample_threshol
 
 constexpr int kCandTies = 256;   // candidates equal to the rho-th key that cand_select_kernel sorts out itself
 
-constexpr int kCandThreads = 512;
-
-__global__ __launch_bounds__(kCandThreads, 8) void cand_select_kernel(CandArgs a)
+template <int NT, int KPT> __global__ __launch_bounds__(NT, 8) void cand_select_kernel(CandArgs a)
 {
     extern __shared__ __align__(16) uint32_t smem[];
-    constexpr int NT = kCandThreads, KPT = kCandCap / NT;
     int b, kv, j;
     const int ul = blockIdx.x, tid = threadIdx.x, ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (!decode_unit(a.u, ul, b, kv, j)) return;
