@@ -1085,7 +1085,11 @@ int build_lists_exact(ctkvr_index *ix, const void *k_pages, const int32_t *block
                     ma.kbuf = ksamp;
                     ma.step_stride = step_stride;
                     ma.sample_stride = sample_stride;
-                    mfma_score_kernel<G, MFMA_SAMPLE><<<dim3(ma.t_splits, tiles), (MfmaShape<G, MFMA_SAMPLE>::NT), 0, st>>>(ma);
+                    // (one round of blocks: a sixteenth of the steps does not pay for the fragments of a second.  128K, 2048 centroids 107 ->
+                    // 103 us, half a round 133; three of 9K..30K 28.3 -> 27.6)
+                    MfmaScoreArgs ms = ma;
+                    ms.t_splits = std::max(1, std::min(ma.t_splits, (2 * ix->num_cu + tiles - 1) / tiles));
+                    mfma_score_kernel<G, MFMA_SAMPLE><<<dim3(ms.t_splits, tiles), (MfmaShape<G, MFMA_SAMPLE>::NT), 0, st>>>(ms);
                     CandArgs ca{};
                     ca.u = u;
                     ca.ctx_lens = ix->d_ctx_lens;
