@@ -1849,7 +1849,7 @@ template <int G> int run_kmeans_g(ctkvr_index *ix, KmeansArgs ka, hipStream_t st
         kmeans_rank_kernel<<<dim3(ka.n_stretch, U), 1024, (size_t)ix->c_max * 4, st>>>(ka);
         kmeans_offsets_kernel<<<dim3(U), 1024, (size_t)ix->c_max * 4, st>>>(ka);
         kmeans_scatter_kernel<<<dim3((ix->s_max + 255) / 256, U), 256, 0, st>>>(ka);
-        kmeans_reduce_kernel<G><<<dim3(ix->c_max + ka.ext_max, U), 512, 0, st>>>(ka);
+        kmeans_reduce_kernel<G><<<dim3(ix->c_max + ka.ext_max, U), ReduceShape<G>::NT, 0, st>>>(ka);
     }
     HIP_TRY(hipGetLastError());
     return CTKVR_OK;

@@ -336,16 +336,24 @@ __global__ __launch_bounds__(256) void kmeans_scatter_kernel(KmeansArgs a)
 
 // One block per centre: sum_c = sum of llrint(x * 2^20) over its members (int64 per element, in
 // registers), mu_c = sum / count (fp64 divide, rounded to fp32, then to bf16 nearest-even); an
-// empty centre keeps its place.  Four groups of 128 threads take the members eight at a time in
+// empty centre keeps its place.  Groups of 128 threads take the members eight at a time in
 // turn (their ids are requested one round ahead of their rows); thread e of a group owns the G
 // consecutive elements e*G .. e*G+G-1 of the G*128-element point, and the groups' integer sums
 // are added through shared memory.  A centre of more than kPartRows members is summed by several blocks (the first
 // iterations have centres of many times the average: their one block was most of the launch, 1.3 ms against 0.27):
 // each adds its sums to the centre's 64-bit accumulators, and the last of them takes those and leaves zeros.
-// grid (c_max + ext_max, batch*g), 512 threads
-template <int G> __global__ __launch_bounds__(512) void kmeans_reduce_kernel(KmeansArgs a)
+// Where a wave's values of a round are all below 128 (27 bits each), the round's eight are summed in 32 bits, five vector instructions
+// an element; converted and added one by one in 64 bits, which the others still are, twelve, and those bounded the launch.  131072 points, 2048
+// centres, eight KV heads of four 332 -> 300 us (now bound by the rows' 1 GB), 20000 and 600 42.7 -> 33.0; of two heads 40000 and 900
+// 51 -> 38.5 (with two groups; four 44.2); of eight 50001 and 777 97 -> 94; of one 30000 and 500 29.9 -> 28.4.
+// grid (c_max + ext_max, batch*g), ReduceShape<G>::NT threads
+template <int G> struct ReduceShape {
+    static constexpr int NG = G <= 2 ? 2 : 4, NT = 128 * NG;   // groups; a row of one or two heads is 256 or 512 bytes
+};
+template <int G> __global__ __launch_bounds__((ReduceShape<G>::NT)) void kmeans_reduce_kernel(KmeansArgs a)
 {
-    __shared__ long long s_part[3][128][G];
+    constexpr int NG = ReduceShape<G>::NG;
+    __shared__ long long s_part[NG - 1][128][G];
     const int ul = blockIdx.y, b = ul / a.g, kv = ul - b * a.g;
     __shared__ uint32_t s_last;
     const int C = a.n_cent[b];
@@ -362,48 +370,66 @@ template <int G> __global__ __launch_bounds__(512) void kmeans_reduce_kernel(Kme
     const uint32_t n_all = (c + 1 < C ? a.start[(size_t)ul * a.c_max + c + 1] : (uint32_t)a.ctx_lens[b]) - st;
     const uint32_t n = min(n_all - p * kPartRows, kPartRows);   // of this part
     const int32_t *ord = a.order + (size_t)ul * a.s_max + st + p * kPartRows;
-    const int e = threadIdx.x & 127, grp = threadIdx.x >> 7;
-    const bf16_t *base = a.q + ((size_t)a.first_row[b] * a.h + kv * G) * kD + e * G;
+    const int e = threadIdx.x & 127, grp = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 7);
+    const bf16_t *base = a.q + ((size_t)a.first_row[b] * a.h + kv * G) * kD;
     const size_t rstride = (size_t)a.h * kD;
     long long acc[G];
 #pragma unroll
     for (int r = 0; r < G; ++r) acc[r] = 0;
+    // element r of a thread's G, with 20 added to its exponent (of normal values below 128: times 2^20, exact; of zeros and subnormals
+    // still nothing)
+    constexpr int NWD = (G + 1) / 2;   // words of G elements
+    constexpr uint32_t kUp = 20u << 23;
+    auto scaled = [&](const uint32_t (&w)[NWD], int r) __attribute__((always_inline)) {
+        return __uint_as_float(r & 1 ? (w[r >> 1] & 0xffff0000u) + kUp : (w[r >> 1] << 16) + kUp);
+    };
     int t[8];
     if (n) {
 #pragma unroll
         for (int u = 0; u < 8; ++u) t[u] = ord[min((uint32_t)(grp * 8 + u), n - 1)];
     }
-    for (uint32_t m0 = grp * 8; m0 < n; m0 += 32) {
+    for (uint32_t m0 = grp * 8; m0 < n; m0 += NG * 8) {
+        uint32_t w[8][NWD];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            w[u][NWD - 1] = 0u;
+            __builtin_memcpy(w[u], base + (size_t)t[u] * rstride + (uint32_t)(e * G), G * sizeof(bf16_t));
+        }
         int tn[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) tn[u] = ord[min(m0 + 32 + u, n - 1)];
-        bf16_t x[8][G];
+        for (int u = 0; u < 8; ++u) tn[u] = ord[min(m0 + NG * 8 + u, n - 1)];
+        typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+        u16x2_t most = {0, 0};
 #pragma unroll
         for (int u = 0; u < 8; ++u)
 #pragma unroll
-            for (int r = 0; r < G; ++r) x[u][r] = base[(size_t)t[u] * rstride + r];
-        // x * 2^20 is exact in fp32 (a bf16 value, an exponent shift); below 2^30 it converts with
-        // the one-instruction fp32 -> int32 rounding, and the wave checks that together
-        bool small = true;
+            for (int k = 0; k < NWD; ++k) most = __builtin_elementwise_max(most, __builtin_bit_cast(u16x2_t, w[u][k] & 0x7fff7fffu));
+        if (__all(max((uint32_t)most.x, (uint32_t)most.y) < 0x4300u)) {   // |x| < 128
+            int sum[G];
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
+            for (int r = 0; r < G; ++r) sum[r] = 0;
+            if (m0 + 8 <= n) {   // uniform
 #pragma unroll
-            for (int r = 0; r < G; ++r) small = small && ((uint32_t)x[u][r] & 0x7fffu) < 0x4480u;   // |x| < 1024
-        if (__all(small)) {
+                for (int u = 0; u < 8; ++u)
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (m0 + u < n) {
+                    for (int r = 0; r < G; ++r) sum[r] += __float2int_rn(scaled(w[u], r));
+            } else {
 #pragma unroll
-                    for (int r = 0; r < G; ++r)
-                        acc[r] += (long long)__float2int_rn(__uint_as_float((uint32_t)x[u][r] << 16) * 1048576.0f);
-                }
+                for (int u = 0; u < 8; ++u)
+                    if (m0 + u < n) {
+#pragma unroll
+                        for (int r = 0; r < G; ++r) sum[r] += __float2int_rn(scaled(w[u], r));
+                    }
+            }
+#pragma unroll
+            for (int r = 0; r < G; ++r) acc[r] += sum[r];
         } else {
 #pragma unroll
             for (int u = 0; u < 8; ++u)
                 if (m0 + u < n) {
 #pragma unroll
                     for (int r = 0; r < G; ++r)
-                        acc[r] += __float2ll_rn(__uint_as_float((uint32_t)x[u][r] << 16) * 1048576.0f);
+                        acc[r] += __float2ll_rn(__uint_as_float(r & 1 ? w[u][r >> 1] & 0xffff0000u : w[u][r >> 1] << 16) * 1048576.0f);
                 }
         }
 #pragma unroll
@@ -418,7 +444,11 @@ template <int G> __global__ __launch_bounds__(512) void kmeans_reduce_kernel(Kme
     long long tot[G];
     if (grp == 0) {
 #pragma unroll
-        for (int r = 0; r < G; ++r) tot[r] = acc[r] + s_part[0][e][r] + s_part[1][e][r] + s_part[2][e][r];
+        for (int r = 0; r < G; ++r) {
+            tot[r] = acc[r];
+#pragma unroll
+            for (int y = 0; y < NG - 1; ++y) tot[r] += s_part[y][e][r];
+        }
     }
     if (n_parts > 1) {
         const size_t slot = (size_t)ul * a.ext_max + a.slot[(size_t)ul * a.c_max + c];
