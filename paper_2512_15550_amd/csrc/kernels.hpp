@@ -1993,6 +1993,8 @@ struct CandArgs {
 
 template <int NT, int KPT> __global__ __launch_bounds__(NT) void sample_threshold_kernel(CandArgs a)
 {
+    static_assert(NT >= 64, "a segment's counter per thread");
+    constexpr int BPT = kBuckets / NT;   // buckets per thread
     __shared__ uint32_t s_hist[2048 + 64];
     __shared__ uint32_t s_cnt, s_res[2];
     int b, kv, j;
@@ -2020,8 +2022,6 @@ template <int NT, int KPT> __global__ __launch_bounds__(NT) void sample_threshol
     }
     __syncthreads();
     mine = wave_sum_uniform(mine);
-    static_assert(NT >= 64, "a segment's counter per thread");
-    constexpr int BPT = kBuckets / NT;   // buckets per thread
     if ((tid & 63) == 0 && mine) atomicAdd(&s_cnt, mine);
     __syncthreads();
     const uint32_t n_valid = s_cnt;
