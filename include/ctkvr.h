@@ -255,11 +255,12 @@ int ctkvr_profile_collect(ctkvr_index *idx, float *ms_host, int32_t capacity_ste
  *                                  (default: by rank for small batches)
  *   CTKVR_KEYCLASS           = 0|1 ranking-key histogram and classification as two launches / one
  *                                  (default: one for small batches)
- *   CTKVR_TAIL               = 0|1 what follows the scoring as separate launches / as one (default: one for small batches
- *                                  of up to 32768 candidate slots per unit, 65536 where a unit has an XCD of its own, unless
- *                                  CTKVR_KEYCLASS is set)
- *   CTKVR_TAIL_SPINS         = n   how often a block of that launch looks for its siblings' sums before it takes all of them
- *                                  itself (0..256, default 256)
+ *   CTKVR_TAIL               = 0|1|2 what follows the scoring as separate launches / as one whose blocks all walk a unit's
+ *                                  recalled keys / as one that shares those out over a unit's blocks (default: the second for small
+ *                                  batches of up to 32768 candidate slots per unit, 65536 where a unit has an XCD of its own, else the
+ *                                  third, unless CTKVR_KEYCLASS is set)
+ *   CTKVR_TAIL_SPINS         = n   how often a block of those launches looks for its siblings' words before it does without them
+ *                                  (0..256, default 256)
  *   CTKVR_FUSED_THREADS      = 256|1024  block size of the single-launch step
  *   CTKVR_BUILD_CANDIDATES   = 0|1 see ctkvr_index_build_route
  *   CTKVR_BUILD_CANDIDATES_REDO    (set: the candidate route also hands every chunk back; tests)

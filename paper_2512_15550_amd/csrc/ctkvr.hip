@@ -414,7 +414,7 @@ struct ctkvr_index {
     int share_nb = 1;
     size_t xs_words = 0;    // exchange slots per unit
     int tail_spins = kTailSpins;
-    int tail = -1;          // ... : -1 chosen per batch, 0 never, 1 whenever possible
+    int tail = -1;          // ... : -1 chosen per batch, 0 separate launches, 1 tail_kernel and 2 share_tail_kernel whenever possible
     int keyclass = -1;      // key histogram + classification as one launch: -1 chosen per batch, 0 never, 1 always
     int attn_slices = 4;    // blocks per unit of the attention (head-dimension slices): 8 while each has a CU of its own
     int build_redone = 0;   // chunks of the matrix-core list build that the candidate route had to hand back
@@ -690,7 +690,7 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, const int32_t *
         if (const char *e = getenv("CTKVR_XCD_UNITS")) ix->xcd_units = atoi(e) != 0;
         if (const char *e = getenv("CTKVR_SCORE_BY_RANK")) ix->score_by_rank = atoi(e) != 0;
         if (const char *e = getenv("CTKVR_KEYCLASS")) ix->keyclass = atoi(e) != 0;
-        if (const char *e = getenv("CTKVR_TAIL")) ix->tail = atoi(e) != 0;
+        if (const char *e = getenv("CTKVR_TAIL")) ix->tail = std::max(0, std::min(2, atoi(e)));
         if (const char *e = getenv("CTKVR_TAIL_SPINS")) ix->tail_spins = std::max(0, std::min((int)kTailSpins, atoi(e)));
         ix->n_groups = ng;
     }
@@ -1486,14 +1486,14 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     // distinct.  Not where one of the forms it replaces is asked for.
     const int tail_most = by_xcd ? 65536 : 32768;
     const bool tail = ix->tail_lds && ix->keyclass < 0 &&
-                      (ix->tail < 0 ? (long long)ix->l_stride * U <= 2048ll * ix->num_cu && ix->l_stride <= tail_most : ix->tail != 0);
+                      (ix->tail < 0 ? (long long)ix->l_stride * U <= 2048ll * ix->num_cu && ix->l_stride <= tail_most : ix->tail == 1);
     ca.xs = w.xs;
     ca.n_xs = tail ? ix->attn_slices * G : 0;
     // Beyond that one launch all the same, with a unit's recalled keys shared out over its blocks (share_tail_kernel): 128K x 4
     // 125.8 -> 116.7 us a step, sixteen of 8K to 64K 144.9 -> 130.0, against the separate launches, which are left to budgets beyond
     // kShareCut and shares whose bitmap the shared memory does not take.  Small batches would lose with it (32K 31.9 -> 34.9 us, 4K 23.5 -> 28.7: every
     // block's chain is as long, and waits three times more for the others).
-    const bool share = !tail && ix->share_lds && ix->keyclass < 0;
+    const bool share = !tail && ix->tail != 0 && ix->share_lds && ix->keyclass < 0;
     if (whole) ix->mark(0, st);
     centroid_cos_kernel<T, G><<<dim3((ix->c_max + 15) / 16, U), 256, 0, st>>>(ca);
     if (whole) ix->mark(1, st);

@@ -148,18 +148,18 @@ def _second_ranking(ck, batch, s, g, n_probe, rho, top_k, equal):
             assert (new[b, kv, 0, n:] == new[b, kv, 0, n - 1]).all()
 
 
-@pytest.mark.parametrize("step", ["tail", "keyclass", "separate"])
+@pytest.mark.parametrize("step", ["tail", "keyclass", "separate", "share"])
 @pytest.mark.parametrize("g,n_probe,rho,top_k,equal", [(2, *c, False) for c in SECOND] + [(8, 12, 1024, 300, False), (8, 13, 4000, 700, False),
                          (2, 12, 1024, 300, True), (2, 13, 5000, 1000, True)])
 def test_second_ranking_is_the_selection_of_a_step_with_that_budget(ck, g, n_probe, rho, top_k, equal, step, monkeypatch):
-    monkeypatch.setenv("CTKVR_TAIL", "1" if step == "tail" else "0")
-    if step == "separate":
-        monkeypatch.setenv("CTKVR_KEYCLASS", "0")
+    monkeypatch.setenv("CTKVR_TAIL", {"tail": "1", "share": "2"}.get(step, "0"))
+    if step in ("keyclass", "separate"):
+        monkeypatch.setenv("CTKVR_KEYCLASS", "1" if step == "keyclass" else "0")
     _second_ranking(ck, 1, 65537, g, n_probe, rho, top_k, equal)
 
 
 @pytest.mark.parametrize("n_probe,rho", [(12, 4096), (15, 4000)])
 def test_second_ranking_where_groups_of_a_batch_step_in_different_forms(ck, n_probe, rho, monkeypatch):
-    """Two sequences of four KV heads in one group (one launch behind the scoring), three in the other (separate launches)."""
+    """Two sequences of four KV heads in one group (tail_kernel), three in the other (share_tail_kernel)."""
     monkeypatch.setenv("CTKVR_DECODE_GROUPS", "2")
     _second_ranking(ck, 5, 61000, 4, n_probe, rho, 700, False)

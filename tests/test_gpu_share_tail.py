@@ -96,14 +96,27 @@ def test_shared_out_keys_equal_the_separate_launches(name, monkeypatch):
         assert ref[0][3].max() <= p.top_k
     if name == "later_keys_g8":
         assert ref[0][3].max() > 8 * 512 * 8        # more than eight blocks keep
-    _same(_run(p, s, data, {"CTKVR_TAIL": "0"}, monkeypatch), ref, "shared out")
-    _same(_run(p, s, data, {"CTKVR_TAIL": "0", "CTKVR_TAIL_SPINS": "0"}, monkeypatch), ref, "alone")
+    _same(_run(p, s, data, {"CTKVR_TAIL": "2"}, monkeypatch), ref, "shared out")
+    _same(_run(p, s, data, {"CTKVR_TAIL": "2", "CTKVR_TAIL_SPINS": "0"}, monkeypatch), ref, "alone")
 
 
 def test_shared_out_keys_of_groups_and_on_the_static_scratch(monkeypatch):
     p, s, data = _params("four_blocks_f32")
     ref = _run(p, s, data, SEPARATE, monkeypatch)
-    _same(_run(p, s, data, {"CTKVR_TAIL": "0", "CTKVR_DECODE_GROUPS": "3"}, monkeypatch), ref, "three groups")
+    _same(_run(p, s, data, {"CTKVR_TAIL": "2", "CTKVR_DECODE_GROUPS": "3"}, monkeypatch), ref, "three groups")
     p, s, data = _params("eight_blocks")
     ref = _run(p, s, data, SEPARATE, monkeypatch)
-    _same(_run(p, s, data, {"CTKVR_TAIL": "0"}, monkeypatch, static=True), ref, "static scratch")
+    _same(_run(p, s, data, {"CTKVR_TAIL": "2"}, monkeypatch, static=True), ref, "static scratch")
+
+
+@pytest.mark.parametrize("top_k", [8191, 8192])
+def test_the_choice_on_both_sides_of_the_largest_budget(top_k, monkeypatch):
+    """Larger batches take share_tail_kernel up to budgets of 8191 and the separate launches beyond: the same integers, and the bits of
+    the attention tell which form ran (the separate launches' are the same in every call)."""
+    p = ck.Params(batch=4, n_q_heads=16, n_kv_heads=8, n_centroids=48, list_len=4000, n_probe=8, top_k=top_k, dtype=ck.BF16)
+    data = _inputs("bf16", 4, 2, 8, 20000, 4000, top_k, 1.0, 0, 4100)
+    ref = _run(p, 20000, data, SEPARATE, monkeypatch)
+    assert ref[0][3].min() > top_k
+    got = _run(p, 20000, data, {}, monkeypatch)
+    _same(got, ref, "default")
+    assert np.array_equal(got[0][0], ref[0][0]) == (top_k > 8191)

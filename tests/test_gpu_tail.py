@@ -27,7 +27,7 @@ CASES = {  # dtype, h, g, ctx_lens, C, n_probe, rho, top_k, lattice
 
 
 def _steps(wl, bt, env, monkeypatch):
-    for k in ("CTKVR_TAIL", "CTKVR_TAIL_SPINS"):
+    for k in ("CTKVR_TAIL", "CTKVR_TAIL_SPINS", "CTKVR_KEYCLASS"):
         monkeypatch.delenv(k, raising=False)
     for k, v in env.items():
         monkeypatch.setenv(k, v)
@@ -68,8 +68,9 @@ def test_one_launch_equals_the_separate_ones(name, monkeypatch):
 
 @pytest.mark.parametrize("g,s,one", [(2, 32768, True), (2, 32769, False), (8, 65536, True), (8, 65537, False)])
 def test_the_choice_on_both_sides_of_its_lines(g, s, one, monkeypatch):
-    """One launch up to l_stride 32768, or 65536 with a multiple of eight units; the same integers either way, and the bits of the
-    attention, which each form sums in its own order, tell which form ran."""
+    """tail_kernel up to l_stride 32768, or 65536 with a multiple of eight units, and share_tail_kernel beyond; the same integers in
+    every form, and the bits of the attention, which each form sums in its own order, tell which form ran.  CTKVR_TAIL=0 is the
+    separate launches: the bits they have with either way to the selection."""
     h, C, n_probe, rho, top_k = 4 * g, 40, 24, 3000, 700
     gen = torch.Generator(device="cuda")
     gen.manual_seed(s)
@@ -83,10 +84,13 @@ def test_the_choice_on_both_sides_of_its_lines(g, s, one, monkeypatch):
     lists = np.stack([np.sort(rng.choice(s, rho, replace=False)) for _ in range(g * C)]).astype(np.int32).reshape(1, g, C, rho)
     p = ck.Params(batch=1, n_q_heads=h, n_kv_heads=g, n_centroids=C, list_len=rho, n_probe=n_probe, top_k=top_k)
     got = {}
-    for tail in (None, "0", "1"):
+    forms = {None: {}, "0": {"CTKVR_TAIL": "0"}, "1": {"CTKVR_TAIL": "1"}, "2": {"CTKVR_TAIL": "2"}, "two": {"CTKVR_KEYCLASS": "0"},
+             "merged": {"CTKVR_KEYCLASS": "1"}}
+    for tail, env in forms.items():
         monkeypatch.delenv("CTKVR_TAIL", raising=False)
-        if tail:
-            monkeypatch.setenv("CTKVR_TAIL", tail)
+        monkeypatch.delenv("CTKVR_KEYCLASS", raising=False)
+        for name, value in env.items():
+            monkeypatch.setenv(name, value)
         idx = ck.ctkvr_index_load(p, [s], cen, lists)
         assert ck.ctkvr_index_info(idx)["l_stride"] == s
         out = torch.full((1, h, 128), float("nan"), device="cuda")
@@ -94,7 +98,10 @@ def test_the_choice_on_both_sides_of_its_lines(g, s, one, monkeypatch):
         ck.ctkvr_decode_step(idx, q, k, v, table, out, out_sel=sel)
         got[tail] = (out.cpu().numpy(), sel.cpu().numpy())
         ck.ctkvr_free(idx)
-    assert np.array_equal(got["0"][1], got["1"][1]) and np.array_equal(got[None][1], got["1"][1])
-    assert np.allclose(got["0"][0], got["1"][0], rtol=2e-5, atol=2e-5 * np.abs(got["1"][0]).max())
-    assert not np.array_equal(got["0"][0], got["1"][0])
-    assert np.array_equal(got[None][0], got["1" if one else "0"][0])
+    for tail in forms:
+        assert np.array_equal(got[tail][1], got["1"][1])
+        assert np.allclose(got[tail][0], got["1"][0], rtol=2e-5, atol=2e-5 * np.abs(got["1"][0]).max())
+    assert np.array_equal(got["0"][0], got["two"][0]) and np.array_equal(got["0"][0], got["merged"][0])
+    assert not np.array_equal(got["0"][0], got["1"][0]) and not np.array_equal(got["0"][0], got["2"][0])
+    # (share_tail_kernel's bits differ between calls where a wait expires)
+    assert np.array_equal(got[None][0], got["1"][0]) == one and not np.array_equal(got[None][0], got["0"][0])
