@@ -1574,24 +1574,26 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
             sa.lds.words = 0;
         }
         const size_t slds = (size_t)sa.lds.total() * 4;
-        auto launch = [&](auto rank, auto stream) {
-            constexpr bool RANK = decltype(rank)::value, STREAM = decltype(stream)::value;
+        auto launch = [&](auto rank, auto stream, auto few) {
+            constexpr bool RANK = decltype(rank)::value, STREAM = decltype(stream)::value, SHORT = decltype(few)::value;
             if constexpr (G <= 4) {
                 if (window) {
                     sa.win = wa;
-                    recall_score_kernel<T, G, true, RANK, STREAM><<<dim3(nbx + kWinSplit, U), 256, slds, st>>>(sa);
+                    recall_score_kernel<T, G, true, RANK, STREAM, SHORT><<<dim3(nbx + kWinSplit, U), 256, slds, st>>>(sa);
                     return;
                 }
             }
-            recall_score_kernel<T, G, false, RANK, STREAM><<<dim3(nbx, U), 256, slds, st>>>(sa);
+            recall_score_kernel<T, G, false, RANK, STREAM, SHORT><<<dim3(nbx, U), 256, slds, st>>>(sa);
         };
         auto launch_rank = [&](auto rank) {
             if (stream_k)
-                launch(rank, std::true_type{});
+                launch(rank, std::true_type{}, std::false_type{});
             else
-                launch(rank, std::false_type{});
+                launch(rank, std::false_type{}, std::false_type{});
         };
-        if (by_rank)
+        if (by_rank && !stream_k && ix->l_stride <= 16 * kShortRows * nbx)
+            launch(std::true_type{}, std::false_type{}, std::true_type{});
+        else if (by_rank)
             launch_rank(std::true_type{});
         else
             launch_rank(std::false_type{});

@@ -641,10 +641,14 @@ template <typename T, int G> __global__ __launch_bounds__(256) void window_attn_
 constexpr int kRecallWpb = 64;     // by id range: at most 2048 ids per block
 constexpr int kRecallCap = 2048;   // ids per block at most
 constexpr int kRecallPad = 256;    // words behind the rows: a tile beyond the last is requested too
-// Rows in flight per 16-lane group.  By id range eight: four blocks a CU.  By rank a CU has two blocks and the registers are free, and
-// twelve take the 125 to 170 rows of a block of the 32K step in one trip, not two (step 33.9 -> 32.9 us with two blocks a CU; sixteen:
+// Rows in flight per 16-lane group.  By id range eight: four blocks a CU in bf16 with groups up to four.  By rank a CU has two blocks and the
+// registers are free, and twelve take the 125 to 170 rows of a block of the 32K step in one trip, not two (step 33.9 -> 32.9 us with two blocks a CU; sixteen:
 // the same; rows of 512 bytes: no gain at 4K, eight).
 template <typename T> constexpr int kRankRows = sizeof(T) == 2 ? 12 : 8;
+// By rank where a block has 64 ids at most (recall_score_kernel's SHORT).  The loop's requests have no branches, and twelve or eight where a
+// block has rows for two or four cost their issue and their answers: one fp32 sequence of 4K, two KV heads 22.84 -> 22.56 us a step, two
+// of 4K in bf16, eight KV heads 23.16 -> 23.05.
+constexpr int kShortRows = 4;
 constexpr int kRecallWords = 4096; // by rank: bitmap words (contexts up to 128K) that the prologue takes in one trip
 
 // words of shared memory: ids and rows of the block, block-table entries, by rank the bitmap and the ids before each word
@@ -676,10 +680,11 @@ struct RecallScoreArgs {
 };
 
 // RANK: how the bitmap is split over a unit's blocks.  STREAM: the keys of all sequences exceed what the memory-side cache holds, and are
-// loaded non-temporal
-template <typename T, int G, bool WIN, bool RANK, bool STREAM> __global__ __launch_bounds__(256) void recall_score_kernel(RecallScoreArgs a)
+// loaded non-temporal.  SHORT: by rank, and no block has more than 16 kShortRows ids
+template <typename T, int G, bool WIN, bool RANK, bool STREAM, bool SHORT = false>
+__global__ __launch_bounds__(256) void recall_score_kernel(RecallScoreArgs a)
 {
-    constexpr int R = RANK ? kRankRows<T> : 8, TILE = 16 * R;
+    constexpr int R = SHORT ? kShortRows : RANK ? kRankRows<T> : 8, TILE = 16 * R;
     static_assert(TILE <= kRecallPad, "rows requested beyond the block's");
     extern __shared__ __align__(16) uint32_t smem[];
     uint32_t *s_ids = smem, *s_rows = smem + kRecallCap;     // ids of this block's ranks, their rows

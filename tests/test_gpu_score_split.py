@@ -27,3 +27,20 @@ def test_recalled_ids_and_rows_match_the_oracle(h, g, lens, page, rho, n_probe, 
         H.run_decode_parity(bt, H.oracle_index(bt), idx, db)
     finally:
         ck.ctkvr_free(idx)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("h,g,batch,rho", [(8, 8, 8, 1024), (16, 8, 8, 1024), (32, 8, 8, 1024), (32, 8, 8, 1025), (64, 8, 8, 1024), (64, 8, 8, 1025)])
+def test_blocks_of_few_ids_by_rank(dtype, h, g, batch, rho, monkeypatch):
+    """64 units of 32 blocks: at most 64 ids a block (four rounds of rows), or 65 (as many rounds as the registers allow)."""
+    monkeypatch.setenv("CTKVR_SCORE_BY_RANK", "1")
+    lens = tuple(3201 + 13 * i for i in range(batch))
+    wl = small_workload("few_ids", dtype, h, g, lens, tuple(850 + i for i in range(batch)), 4, 0, 2, rho, 100, 1)
+    bt = gen_batch(wl)
+    db = H.device_batch(bt)
+    idx = ck.ctkvr_build_index(H.params_of(wl), db.q_prefill, db.cu_seqlens, True, db.k_pages, db.block_table, db.ctx_lens)
+    try:
+        assert ck.ctkvr_index_info(idx)["l_stride"] == 2 * rho
+        H.run_decode_parity(bt, H.oracle_index(bt), idx, db)
+    finally:
+        ck.ctkvr_free(idx)
