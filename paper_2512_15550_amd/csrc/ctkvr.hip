@@ -1544,15 +1544,17 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     {
         // Few rows per CU (a small batch): a block's rows are one round trip to memory and the slowest block
         // is the launch, so the ids are split by rank -- two blocks a CU (with twelve rows a lane group in flight, see
-        // recall_score_kernel: 32K 33.9 us a step at three blocks per two CUs and eight rows, 34.4 with twelve, 32.9 at two; with a
-        // resident window 42.4 and 42.7), at least 32 per unit and 64 list entries per block (128 leave CUs idle where units are few and
+        // recall_score_kernel: 32K 33.9 us a step at three blocks per two CUs and eight rows, 34.4 with twelve, 32.9 at two), those of a
+        // resident window, which ride in the launch, counted in (on top of them: eight units of 32K, window of 640 and 100 decoded tokens
+        // 42.7 us with the update, now 41.9; two units of 16K in fp32 40.6, now 35.2), at least 32 per unit and 64 list entries per block (128 leave CUs idle where units are few and
         // their lists short: two probes of 495, 16 units of eight heads 28.5 us, 128 29.3; four of 495, four units 31.5, 128 32.5; four of 1280,
         // four units 33.0 either way).  Otherwise by id
         // range: enough blocks to fill the chip a few times over, each owning 8..64 words of the bitmap.
         const bool by_rank = ix->score_by_rank < 0 ? (long long)ix->l_stride * U <= 2048ll * ix->num_cu : ix->score_by_rank != 0;
         int nbx;
         if (by_rank) {
-            nbx = std::min(std::max(32, (2 * ix->num_cu + U - 1) / U), (ix->l_stride + 63) / 64);
+            const int beside = window && G <= 4 ? kWinSplit * U : 0;
+            nbx = std::min(std::max(32, (2 * ix->num_cu - beside + U - 1) / U), (ix->l_stride + 63) / 64);
             nbx = std::max({1, nbx, (ix->l_stride + kRecallCap - 1) / kRecallCap});
         } else {
             const int target = std::max(32, (8 * ix->num_cu + U - 1) / U);
