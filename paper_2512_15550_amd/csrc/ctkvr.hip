@@ -71,8 +71,8 @@ size_t elem_size(int dtype) { return dtype == CTKVR_BF16 ? 2 : 4; }
 // until the process ends.  Host code never uses the array's name as an address: the device address
 // is looked up once per device and kept.  It takes every step whose buffers are 32 MiB or less with the words of a unit that atomics
 // update packed, the bitmap's rows unpadded and share_tail_kernel's exchange left out, and has room for those: a cache line each and the
-// padding at most 0.38 KB a unit, whose buffers take at least 28 KiB, i.e. 0.42 MiB in all; the exchange 4 KiB a unit and up to 5.2 KiB
-// a block, for 128 units at most and a block a CU, i.e. 1.8 MiB on 256 CUs.
+// padding at most 0.38 KB a unit, whose buffers take at least 28 KiB, i.e. 0.42 MiB in all; the exchange 4 KiB a unit and up to 5.7 KiB
+// a block, for 128 units at most and a block a CU, i.e. 1.9 MiB on 256 CUs.
 constexpr size_t kStaticStepBytes = (size_t)32 << 20;
 constexpr size_t kStaticScratchBytes = kStaticStepBytes + ((size_t)4 << 20);
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];

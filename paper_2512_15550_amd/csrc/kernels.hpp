@@ -3404,7 +3404,7 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
 // and ranking keys stay in its registers), and what must be known of the others crosses over in 64-bit words that are zero
 // before the launch and carry their own validity, written and read by single atomics, so that no fence is needed:
 //   1. the share's denominator sums (a word per head);
-//   2. the share's histogram of ranking keys (four buckets a word): every block then knows the unit's deciding bucket,
+//   2. the share's histograms of ranking keys (four buckets a word; one, two or three of them): every block then knows the unit's deciding bucket,
 //      and from the others' histograms how many picks and how many of that bucket's keys come before its own;
 //   3. the deciding bucket's keys (key and position).  The value rows of the share's sure picks and of its keys of that bucket are
 //      requested before the others' are waited for;
@@ -3412,13 +3412,16 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
 //      128 G / nb elements by each block.
 // Every wait is bounded (kTailSpins reads).  A block that gives up takes the denominators of all keys itself, or later goes on alone: it
 // selects among all the unit's keys, attends over all picks and writes its part of the results, so that no progress
-// depends on the other blocks being resident.  It does the same where the bucket is crowded (more than kShareList keys), and where
+// depends on the other blocks being resident.  It does the same where the bucket is crowded (more than kShareList keys, in the finest
+// histogram or below -318), and where
 // some head's picks all lie so far below its maximum that their weights vanish (weights relative to the picks' own maxima then).
 // grid nb*batch*g, nb a power of two, kTailThreads threads; dynamic shared memory: share_smem_words.  Same integers as the separate kernels.
 // ------------------------------------------------------------------------------
 constexpr int kShareList = 512;    // keys of the deciding bucket that are ranked against each other
 constexpr int kShareBlocks = 8;    // blocks per unit at most
-constexpr int kShareBuckets = 256; // buckets of a histogram: 1/4 wide in the log domain, then 1/1024 wide inside one of those
+constexpr int kShareBuckets = 256; // buckets of a histogram: 1/4 wide in the log domain, 1 wide below them, 1/256 of either inside one
+constexpr uint32_t kShareFar = 63; // the buckets of 1 begin at -63, of which what lies above the quarters' end (-63.75) is empty
+constexpr int kShareLevels = 3;    // histograms at most
 constexpr int kShareCut = 8191;    // a share's count in the exchange is cut there; top_k is at most that, so that a bucket with
                                    // such a count is the deciding one, or comes after it, with or without the cut
 constexpr int kSharePicks = 128;   // picks that a wave attends over at a time
@@ -3444,7 +3447,7 @@ struct ShareArgs {
 // 64-bit words of a unit's exchange: sums, histograms, the bucket's keys, weighted sums of value rows, sums of weights
 __host__ __device__ __forceinline__ size_t share_words(int nb, int G)
 {
-    return nb > 1 ? (size_t)nb * (G + 2 * (kShareBuckets / 4) + 64 * G + G) + kShareList : 0;
+    return nb > 1 ? (size_t)nb * (G + kShareLevels * (kShareBuckets / 4) + 64 * G + G) + kShareList : 0;
 }
 // words of shared memory that the histograms, the bucket's keys and later the waves' partial results take
 __host__ __device__ __forceinline__ int share_front_words(int G)
@@ -3503,7 +3506,7 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
     const float *zb = a.z + (size_t)ul * a.l_stride * G;
     const uint32_t *rb = a.crow + (size_t)ul * a.l_stride;
     const int32_t *cb = a.cand + (size_t)ul * a.l_stride;
-    unsigned long long *xsum = a.xs + (size_t)ul * share_words(nb, G), *xhist = xsum + nb * G, *xlist = xhist + 2 * nb * NH;
+    unsigned long long *xsum = a.xs + (size_t)ul * share_words(nb, G), *xhist = xsum + nb * G, *xlist = xhist + kShareLevels * nb * NH;
     unsigned long long *xout = xlist + kShareList, *xl = xout + nb * W;
     constexpr unsigned long long kValid = 1ull << 63;
     auto put = [](unsigned long long *p, unsigned long long v) __attribute__((always_inline)) {
@@ -3706,17 +3709,23 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
     }
     const bool every = a.top_k >= L;   // every recalled key is kept
     bool alone = false;
-    // x > hi_k is a sure pick, lo_k < x <= hi_k is in the deciding bucket (exact: the bounds are multiples of 1/1024 above -65)
-    float hi_k = -__builtin_huge_valf(), lo_k = hi_k;
-    uint32_t rem = (uint32_t)a.top_k, n_bkt = 0, e0 = 0;   // keys wanted from the deciding bucket, its population, those in earlier shares
+    // x > hi_k is a sure pick, lo_k < x <= hi_k is in the deciding bucket (exact: the bounds are multiples of 1/1024 above -65, or of
+    // 1/256 above -319)
+    float hi_k = every ? -__builtin_huge_valf() : __builtin_huge_valf(), lo_k = -__builtin_huge_valf();
+    // keys wanted from the deciding bucket, its population, those in earlier shares (at first of all keys)
+    uint32_t rem = (uint32_t)a.top_k, n_bkt = (uint32_t)L, e0 = (uint32_t)min(L, g0 * 64);
+    // 256 buckets a quarter wide; where more keys than are listed share the deciding one, 256 inside it (fine).  The last bucket is all
+    // below, and where it decides, 256 buckets of 1 follow first: keys spread with the queries' norms, and a large budget's last
+    // one lies beyond -63.75 in earnest (8 units of one head, 33000 keys and 4096 picks 64.2 us a step, going alone there 83.2, separate
+    // launches 66.7; of two heads, 89000 keys and 2048 picks 105, 237 and 168)
+    float scale = -4.0f, upto = hi_k;
+    uint32_t first = 0;     // number of the first bucket, from zero on downwards
+    bool fine = false;
 #pragma unroll 1
-    for (int level = 0; level < 2 && !every; ++level) {
-        // 256 buckets a quarter wide; where more keys than are listed share the deciding one, 256 inside it.  A histogram per wave
+    for (int level = 0; level < kShareLevels && !every; ++level) {
+        // a histogram per wave.  Not counted: the last bucket (what the others leave); when fine, what is not in the deciding one
         uint32_t *hist = s_hist + wv * kShareBuckets, *spare = reinterpret_cast<uint32_t *>(s_ent) + tid;
-        const uint32_t first = level ? (uint32_t)(hi_k * -1024.0f) : 0u;   // (hi_k = inf, the first bucket: 0)
-        const float scale = level ? -1024.0f : -4.0f;
-        // not counted: at first the last bucket, all below (L minus the others); then what is not in the deciding one
-        const float over = level ? lo_k : -(float)(kShareBuckets - 1) / 4.0f, upto = level ? hi_k : __builtin_huge_valf();
+        const float over = fine ? lo_k : (float)(first + kShareBuckets - 1) / scale;
         for_keys([&](int, float kk) __attribute__((always_inline)) {
             uint32_t *bin = hist + ((uint32_t)fmaxf(kk * scale, 0.0f) - first);
             bin = kk > over && kk <= upto ? bin : spare;
@@ -3740,7 +3749,7 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
             uint32_t b_lo = 0u, b_hi = 0u;                                                                         // earlier shares'
             bool all = true;
             if (nb > 1) {
-                unsigned long long *xh = xhist + level * nb * NH, hw[kShareBlocks];
+                unsigned long long *xh = xhist + level * nb * NH, hw[kShareBlocks] = {};
                 put(&xh[x * NH + ln], kValid | ((unsigned long long)t_hi << 32) | t_lo);
                 all = false;
                 for (int it = 0; it < a.spins && !all; ++it) {
@@ -3778,8 +3787,8 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
                 if (ln == 63) {
                     s_res[0] = (uint32_t)(kShareBuckets - 1);
                     s_res[1] = rem - tot;
-                    s_res[2] = all ? (uint32_t)L - tot : ~0u;
-                    s_res[3] = (uint32_t)min(L, g0 * 64) - above;
+                    s_res[2] = all ? n_bkt - tot : ~0u;
+                    s_res[3] = e0 - above;
                 }
             } else {
                 const uint64_t has = __ballot(inc >= rem);   // the first of these lanes has the bucket
@@ -3811,11 +3820,15 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
         n_bkt = s_res[2];
         e0 = s_res[3];
         alone = n_bkt > (uint32_t)kShareList;
-        const bool last_bkt = level == 0 && bkt == (uint32_t)(kShareBuckets - 1);
-        if (first + bkt) hi_k = (float)(first + bkt) / scale;
-        else hi_k = __builtin_huge_valf();
-        lo_k = last_bkt ? -__builtin_huge_valf() : (float)(first + bkt + 1u) / scale;
-        if (!alone || n_bkt == ~0u || last_bkt) break;   // uniform
+        const bool below = !fine && bkt == (uint32_t)(kShareBuckets - 1);
+        hi_k = first + bkt ? fminf(upto, (float)(first + bkt) / scale) : upto;
+        lo_k = below ? -__builtin_huge_valf() : (float)(first + bkt + 1u) / scale;
+        if (!alone || n_bkt == ~0u || fine || (below && level)) break;   // uniform
+        fine = !below;
+        if (fine) scale *= (float)kShareBuckets;
+        else scale = -1.0f;
+        first = fine ? (uint32_t)(lo_k * scale) - kShareBuckets : kShareFar;
+        upto = hi_k;
         reinterpret_cast<uint4 *>(hist)[ln] = make_uint4(0u, 0u, 0u, 0u);
     }
     CTKVR_STAMP(66);
