@@ -258,7 +258,8 @@ int ctkvr_profile_collect(ctkvr_index *idx, float *ms_host, int32_t capacity_ste
  *   CTKVR_TAIL               = 0|1|2 what follows the scoring as separate launches / as one whose blocks all walk a unit's
  *                                  recalled keys / as one that shares those out over a unit's blocks (default: the second for small
  *                                  batches of up to 32768 candidate slots per unit, 65536 where a unit has an XCD of its own, else the
- *                                  third, unless CTKVR_KEYCLASS is set)
+ *                                  third, or the first beyond a top_k of 8191 and for long contexts of more units than half the
+ *                                  CUs; the first where CTKVR_KEYCLASS is set)
  *   CTKVR_TAIL_SPINS         = n   how often a block of those launches looks for its siblings' words before it does without them
  *                                  (0..256, default 256)
  *   CTKVR_FUSED_THREADS      = 256|1024  block size of the single-launch step

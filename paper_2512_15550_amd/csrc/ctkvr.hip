@@ -412,6 +412,7 @@ struct ctkvr_index {
     size_t tail_lds = 0;    // non-zero: everything after the scoring can run as one launch (tail_kernel)
     size_t share_lds = 0;   // non-zero: ... with a unit's recalled keys shared out over its share_nb blocks (share_tail_kernel)
     int share_nb = 1;
+    bool share_pays = true; // ... and is taken for larger batches
     size_t xs_words = 0;    // exchange slots per unit
     int tail_spins = kTailSpins;
     int tail = -1;          // ... : -1 chosen per batch, 0 separate launches, 1 tail_kernel and 2 share_tail_kernel whenever possible
@@ -706,6 +707,18 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, const int32_t *
         ix->share_nb = nb;
         const size_t lds = share_smem_words(((ix->l_stride + 63) / 64 + nb - 1) / nb, ix->G) * 4;
         if (p->top_k <= kShareCut && lds <= 150 * 1024) ix->share_lds = lds;
+        // With one block a unit the CUs that the last round of blocks leaves idle are idle for all of it, and from some length on the
+        // separate launches, whose passes use the whole card, are faster.  Steps with / without, l_stride 32768, 65536 and 131072, 2048
+        // picks, groups of four, us:
+        //   136 units  231/228  285/278  345/327     160 units  256/261  320/316  394/379     192 units  293/303  367/371  451/448
+        //   224 units  330/353  420/434  507/514     264 units  445/429  547/525     -        320 units  503/490  634/610     -
+        //   512 units  717/750  923/973     -        (l_stride 16384: 264 units 189/196, 320 215/227)
+        // Groups of one and two cross within 2 % of these, of eight (whose separate launches are slower) nowhere.  Where the lists
+        // hardly overlap and 131072 slots hold 43000 keys, all of them lose 6 to 13 %: hence at most 98304.  Two blocks a unit and more: -2 to
+        // -7 % (72 to 120 units, 65536 and 131072), at most 1 % the other way at 43000 keys.
+        const long long rounds = (U + ix->num_cu - 1) / ix->num_cu, cus = rounds * ix->num_cu;
+        if (nb == 1 && ix->G <= 4)
+            ix->share_pays = ix->l_stride < 16384 + std::min(81920ll, 131072 * (2 * (long long)U - cus) / (cus * rounds));
         ix->xs_words = std::max<size_t>(8 * ix->G, ix->share_lds ? share_words(nb, ix->G) : 0);
     }
     // one allocation for all of it
@@ -1491,9 +1504,9 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     ca.n_xs = tail ? ix->attn_slices * G : 0;
     // Beyond that one launch all the same, with a unit's recalled keys shared out over its blocks (share_tail_kernel): 128K x 4
     // 125.8 -> 116.7 us a step, sixteen of 8K to 64K 144.9 -> 130.0, against the separate launches, which are left to budgets beyond
-    // kShareCut and shares whose bitmap the shared memory does not take.  Small batches would lose with it (32K 31.9 -> 34.9 us, 4K 23.5 -> 28.7: every
+    // kShareCut, shares whose bitmap the shared memory does not take, and long contexts of more units than half the CUs (share_pays).  Small batches would lose with it (32K 31.9 -> 34.9 us, 4K 23.5 -> 28.7: every
     // block's chain is as long, and waits three times more for the others).
-    const bool share = !tail && ix->tail != 0 && ix->share_lds && ix->keyclass < 0;
+    const bool share = !tail && ix->share_lds && ix->keyclass < 0 && (ix->tail == 2 || (ix->tail != 0 && ix->share_pays));
     if (whole) ix->mark(0, st);
     centroid_cos_kernel<T, G><<<dim3((ix->c_max + 15) / 16, U), 256, 0, st>>>(ca);
     if (whole) ix->mark(1, st);

@@ -33,11 +33,11 @@ CASES = {  # dtype, batch, G, g, s, lists' length, probes, top_k, scale of the q
 }
 
 
-def _inputs(dtype, B, G, g, s, rho, top_k, scale, win, seed):
+def _inputs(dtype, B, G, g, s, rho, top_k, scale, win, seed, C=48):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(seed)
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
-    h, C, n_pages = G * g, 48, (s + 15) // 16
+    h, n_pages = G * g, (s + 15) // 16
     k = torch.randn((B * n_pages, g, 16, 128), generator=gen, device="cuda").to(dt)
     v = torch.randn((B * n_pages, g, 16, 128), generator=gen, device="cuda").to(dt)
     q = (scale * torch.randn((B, h, 128), generator=gen, device="cuda")).to(dt)
@@ -122,3 +122,17 @@ def test_the_choice_on_both_sides_of_the_largest_budget(top_k, monkeypatch):
     got = _run(p, 20000, data, {}, monkeypatch)
     _same(got, ref, "default")
     assert np.array_equal(got[0][0], ref[0][0]) == (top_k > 8191)
+
+
+@pytest.mark.parametrize("batch,G,s", [(8, 1, 24575), (8, 1, 24576), (16, 2, 20479), (16, 2, 20480)])
+def test_the_choice_on_both_sides_of_the_line_of_one_block_a_unit(batch, G, s, monkeypatch):
+    """136 units, 16 of 256 CUs more than half: the separate launches from 24576 slots a unit on; 272 units, 32 of 512 in two rounds:
+    from 20480."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the line is that of 256 CUs")
+    p = ck.Params(batch=batch, n_q_heads=17 * G, n_kv_heads=17, n_centroids=8, list_len=3500, n_probe=8, top_k=900, dtype=ck.BF16)
+    data = _inputs("bf16", batch, G, 17, s, 3500, 900, 1.0, 0, 4200, C=8)
+    ref = _run(p, s, data, SEPARATE, monkeypatch)
+    got = _run(p, s, data, {}, monkeypatch)
+    _same(got, ref, "default")
+    assert np.array_equal(got[0][0], ref[0][0]) == (s % 2 == 0)
