@@ -3718,14 +3718,14 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
     // below, and where it decides, 256 buckets of 1 follow first: keys spread with the queries' norms, and a large budget's last
     // one lies beyond -63.75 in earnest (8 units of one head, 33000 keys and 4096 picks 64.2 us a step, going alone there 83.2, separate
     // launches 66.7; of two heads, 89000 keys and 2048 picks 105, 237 and 168)
-    float scale = -4.0f, upto = hi_k;
+    float scale = -4.0f, width = -0.25f, upto = hi_k;   // width: 1 / scale, exactly
     uint32_t first = 0;     // number of the first bucket, from zero on downwards
     bool fine = false;
 #pragma unroll 1
     for (int level = 0; level < kShareLevels && !every; ++level) {
         // a histogram per wave.  Not counted: the last bucket (what the others leave); when fine, what is not in the deciding one
         uint32_t *hist = s_hist + wv * kShareBuckets, *spare = reinterpret_cast<uint32_t *>(s_ent) + tid;
-        const float over = fine ? lo_k : (float)(first + kShareBuckets - 1) / scale;
+        const float over = fine ? lo_k : (float)(first + kShareBuckets - 1) * width;
         for_keys([&](int, float kk) __attribute__((always_inline)) {
             uint32_t *bin = hist + ((uint32_t)fmaxf(kk * scale, 0.0f) - first);
             bin = kk > over && kk <= upto ? bin : spare;
@@ -3749,7 +3749,7 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
             uint32_t b_lo = 0u, b_hi = 0u;                                                                         // earlier shares'
             bool all = true;
             if (nb > 1) {
-                unsigned long long *xh = xhist + level * nb * NH, hw[kShareBlocks] = {};
+                unsigned long long *xh = xhist + level * nb * NH, hw[kShareBlocks];
                 put(&xh[x * NH + ln], kValid | ((unsigned long long)t_hi << 32) | t_lo);
                 all = false;
                 for (int it = 0; it < a.spins && !all; ++it) {
@@ -3762,10 +3762,10 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
                         if (y < nb) v &= hw[y];
                     all = __all((v & kValid) != 0ull);
                 }
-                t_lo = t_hi = 0u;
+                t_lo = t_hi = 0u;   // (and stay so where a block did not answer: nothing of the levels counts then)
 #pragma unroll
                 for (int y = 0; y < kShareBlocks; ++y)
-                    if (y < nb) {
+                    if (all && y < nb) {
                         const uint32_t lo = (uint32_t)hw[y], hi = (uint32_t)(hw[y] >> 32) & 0x7fffffffu;
                         b_lo += y < x ? lo : 0u;
                         b_hi += y < x ? hi : 0u;
@@ -3821,12 +3821,12 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
         e0 = s_res[3];
         alone = n_bkt > (uint32_t)kShareList;
         const bool below = !fine && bkt == (uint32_t)(kShareBuckets - 1);
-        hi_k = first + bkt ? fminf(upto, (float)(first + bkt) / scale) : upto;
-        lo_k = below ? -__builtin_huge_valf() : (float)(first + bkt + 1u) / scale;
+        hi_k = first + bkt ? fminf(upto, (float)(first + bkt) * width) : upto;
+        lo_k = below ? -__builtin_huge_valf() : (float)(first + bkt + 1u) * width;
         if (!alone || n_bkt == ~0u || fine || (below && level)) break;   // uniform
         fine = !below;
-        if (fine) scale *= (float)kShareBuckets;
-        else scale = -1.0f;
+        scale = fine ? scale * (float)kShareBuckets : -1.0f;
+        width = fine ? width / (float)kShareBuckets : -1.0f;
         first = fine ? (uint32_t)(lo_k * scale) - kShareBuckets : kShareFar;
         upto = hi_k;
         reinterpret_cast<uint4 *>(hist)[ln] = make_uint4(0u, 0u, 0u, 0u);
@@ -3838,6 +3838,12 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
     Chunk<T> cv[NU];
     int n_l = 0, qn = 0;   // picks at hand; the wave's next group
     int my_id[kSharePicks / 64];
+    // (lanes of the wave read in w_row, w_pos and w_z what others wrote: a wave's accesses to shared memory are served in order, and this
+    // keeps the compiler to it)
+    auto handed = []() __attribute__((always_inline)) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
     // the wave's picks from group qn on, as many groups as fit: the first time from the registers, later from memory
     auto append = [&](int q, float kk, const float(&v)[G], auto row) __attribute__((always_inline)) {
         const uint64_t all = __ballot(kk > lo_k);
@@ -3853,6 +3859,7 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
         qn = q + 1;
     };
     auto fill_again = [&]() __attribute__((always_inline)) {
+        handed();
         n_l = 0;
 #pragma unroll 1
         for (int q = qn; q < nwg && qn == q; q += NF) {
@@ -3877,7 +3884,8 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
         }
     };
     auto begin = [&]() __attribute__((always_inline)) {   // ids and value rows requested, scores to weights
-        if (n_l == 0) return;
+        if (n_l == 0) return;   // uniform
+        handed();
 #pragma unroll
         for (int i = 0; i < kSharePicks / 64; ++i) my_id[i] = cb[w_pos[min(i * 64 + ln, n_l - 1)] & 0x7fffffffu];
         request(0);
@@ -3890,6 +3898,7 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
                 for (int hh = 0; hh < G; ++hh) w[hh] = __expf(w[hh]);
                 store_z<G>(w_z, i * 64 + ln, w);
             }
+        handed();
     };
     if (!alone) {
         uint32_t n_gt = 0;
@@ -4046,6 +4055,7 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
                 }
                 rank += (uint32_t)__popcll(mask);
             }
+            handed();
 #pragma unroll 1
             for (int r0 = 0; r0 < n_l; r0 += NU * 4) {
                 if (r0) request(r0);
