@@ -262,6 +262,8 @@ int ctkvr_profile_collect(ctkvr_index *idx, float *ms_host, int32_t capacity_ste
  *                                  CUs; the first where CTKVR_KEYCLASS is set)
  *   CTKVR_TAIL_SPINS         = n   how often a block of those launches looks for its siblings' words before it does without them
  *                                  (0..256, default 256)
+ *   CTKVR_SHARE_LATE         = w[:b]  (tests) in the third form, the wait that block b of every unit, or each block, gives up at once:
+ *                                  0 for the sums, 1 the histograms, 2 the deciding bucket's keys, 3 the outputs
  *   CTKVR_FUSED_THREADS      = 256|1024  block size of the single-launch step
  *   CTKVR_BUILD_CANDIDATES   = 0|1 see ctkvr_index_build_route
  *   CTKVR_BUILD_CANDIDATES_REDO    (set: the candidate route also hands every chunk back; tests)

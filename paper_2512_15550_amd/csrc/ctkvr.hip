@@ -415,6 +415,7 @@ struct ctkvr_index {
     bool share_pays = true; // ... and is taken for larger batches
     size_t xs_words = 0;    // exchange slots per unit
     int tail_spins = kTailSpins;
+    int share_late = -1, share_late_block = -1;   // share_tail_kernel: the wait (0..3) that is given up at once, and by which block (-1: all)
     int tail = -1;          // ... : -1 chosen per batch, 0 separate launches, 1 tail_kernel and 2 share_tail_kernel whenever possible
     int keyclass = -1;      // key histogram + classification as one launch: -1 chosen per batch, 0 never, 1 always
     int attn_slices = 4;    // blocks per unit of the attention (head-dimension slices): 8 while each has a CU of its own
@@ -693,6 +694,10 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, const int32_t *
         if (const char *e = getenv("CTKVR_KEYCLASS")) ix->keyclass = atoi(e) != 0;
         if (const char *e = getenv("CTKVR_TAIL")) ix->tail = std::max(0, std::min(2, atoi(e)));
         if (const char *e = getenv("CTKVR_TAIL_SPINS")) ix->tail_spins = std::max(0, std::min((int)kTailSpins, atoi(e)));
+        if (const char *e = getenv("CTKVR_SHARE_LATE")) {
+            ix->share_late = std::max(-1, std::min(3, atoi(e)));
+            if (const char *colon = strchr(e, ':')) ix->share_late_block = atoi(colon + 1);
+        }
         ix->n_groups = ng;
     }
     if (const char *e = getenv("CTKVR_DECODE_PATH")) {
@@ -1680,7 +1685,10 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         ta.z = w.z;
         ta.m_key = w.m_key;
         ta.xs = w.xs;
-        ta.spins = ix->tail_spins;
+        ta.spins = (uint32_t)(ix->tail_spins + 1) / 2 * 0x01010101u;
+        ta.late_spins = ix->share_late < 0 ? ta.spins : ta.spins & ~(0xffu << (8 * ix->share_late));
+        ta.late_block = ix->share_late_block;
+        if (ta.late_block < 0) ta.spins = ta.late_spins;
         ta.gbits = w.gbits;
         ta.bitmap_words = ix->bitmap_words;
         ta.kbuf = w.kbuf;

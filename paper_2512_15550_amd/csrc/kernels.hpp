@@ -3434,7 +3434,9 @@ struct ShareArgs {
     const float *z;
     const uint32_t *m_key;
     unsigned long long *xs;     // [units][share_words]: the exchange, zero on entry
-    int spins;                  // reads before a block gives up (kTailSpins)
+    uint32_t spins;             // reads before a block gives up (kTailSpins), halved, a byte for each of the four waits
+    uint32_t late_spins;        // the same for block late_block (tests)
+    int late_block;
     uint32_t *gbits;            // the recall bitmap, cleared here for the next step
     int bitmap_words;
     uint32_t *kbuf;             // [units][l_stride] the ranking keys, written where a block goes on alone
@@ -3515,6 +3517,8 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
     auto get = [](const unsigned long long *p) __attribute__((always_inline)) {
         return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
+    const uint32_t spins = x == a.late_block ? a.late_spins : a.spins;   // (one register: with a test at each wait 128K x 4 took 1 us more)
+    auto reads = [&](int wait) __attribute__((always_inline)) { return (int)(spins >> (8 * wait) & 0xffu) * 2; };
     auto rank_in = [](uint64_t mask, uint32_t base) __attribute__((always_inline)) {   // base + lanes of the mask below this one
         return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, base));
     };
@@ -3634,7 +3638,7 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
             if (ln < G) put(&xsum[x * G + ln], v | kValid);   // (a sum is below 2^20 * 2^40)
             all = false;
             v = kValid;
-            for (int it = 0; it < a.spins && !all; ++it) {
+            for (int it = 0; it < reads(0) && !all; ++it) {
                 if (ln < nb * G) v = get(&xsum[ln]);
                 all = __all((v & kValid) != 0ull);
             }
@@ -3752,7 +3756,7 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
                 unsigned long long *xh = xhist + level * nb * NH, hw[kShareBlocks];
                 put(&xh[x * NH + ln], kValid | ((unsigned long long)t_hi << 32) | t_lo);
                 all = false;
-                for (int it = 0; it < a.spins && !all; ++it) {
+                for (int it = 0; it < reads(1) && !all; ++it) {
                     unsigned long long v = kValid;
 #pragma unroll
                     for (int y = 0; y < kShareBlocks; ++y)
@@ -3931,7 +3935,7 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
             if (nb > 1) {
                 unsigned long long v = 1ull;
                 bool all = false;
-                for (int it = 0; it < a.spins && !all; ++it) {
+                for (int it = 0; it < reads(2) && !all; ++it) {
                     if (tid < (int)n_bkt) v = get(&xlist[tid]);
                     all = __all(v != 0ull);
                 }
@@ -4090,7 +4094,7 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
             if (tid < per_w) {
                 unsigned long long w[kShareBlocks], lw[kShareBlocks];
                 bool all = false;
-                for (int it = 0; it < a.spins && !all; ++it) {
+                for (int it = 0; it < reads(3) && !all; ++it) {
                     all = true;
 #pragma unroll
                     for (int y = 0; y < kShareBlocks; ++y)

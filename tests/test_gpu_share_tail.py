@@ -54,7 +54,7 @@ def _inputs(dtype, B, G, g, s, rho, top_k, scale, win, seed, C=48):
 
 
 def _run(p, s, data, env, monkeypatch, static=False):
-    for name in ("CTKVR_TAIL", "CTKVR_KEYCLASS", "CTKVR_TAIL_SPINS", "CTKVR_DECODE_GROUPS"):
+    for name in ("CTKVR_TAIL", "CTKVR_KEYCLASS", "CTKVR_TAIL_SPINS", "CTKVR_SHARE_LATE", "CTKVR_DECODE_GROUPS"):
         monkeypatch.delenv(name, raising=False)
     for name, value in env.items():
         monkeypatch.setenv(name, value)
@@ -100,6 +100,17 @@ def test_shared_out_keys_equal_the_separate_launches(name, monkeypatch):
         assert ref[0][3].max() > 8 * 512 * 8        # more than eight blocks keep
     _same(_run(p, s, data, {"CTKVR_TAIL": "2"}, monkeypatch), ref, "shared out")
     _same(_run(p, s, data, {"CTKVR_TAIL": "2", "CTKVR_TAIL_SPINS": "0"}, monkeypatch), ref, "alone")
+
+
+@pytest.mark.parametrize("block", ["", ":0", ":1"])
+@pytest.mark.parametrize("wait", [0, 1, 2, 3])
+@pytest.mark.parametrize("name", ["two_blocks_g8", "four_blocks_f32", "eight_blocks", "many_below_the_range"])
+def test_a_wait_that_expires_in_every_block_or_in_one(name, wait, block, monkeypatch):
+    """Of the sums, the histograms, the deciding bucket's keys or the outputs: all blocks of a unit go on alone, or one does and the
+    others, which wait for what it never writes, follow it or have finished."""
+    p, s, data = _params(name)
+    _same(_run(p, s, data, {"CTKVR_TAIL": "2", "CTKVR_SHARE_LATE": f"{wait}{block}"}, monkeypatch), _run(p, s, data, SEPARATE, monkeypatch),
+          f"wait {wait}{block}")
 
 
 def test_shared_out_keys_of_groups_and_on_the_static_scratch(monkeypatch):
