@@ -532,7 +532,6 @@ size_t carve_step_ws(StepWs &w, unsigned char *base, const ctkvr_index *ix, bool
     take(&w.win, U * (size_t)kWinSplit * G * (2 + 128) * 4);
     take(&w.srow, U * p.top_k * 4);
     take(&w.S, U * (packed ? G : kSumStride) * 8);
-    take(&w.xs, U * (packed ? G * 8 : ix->xs_words) * 8);
     take(&w.sel, U * p.top_k * 4);
     take(&w.zsel, U * p.top_k * G * 4);
     take(&w.nsel, U * 4);
@@ -548,6 +547,8 @@ size_t carve_step_ws(StepWs &w, unsigned char *base, const ctkvr_index *ix, bool
         take(&w.slot_sure, U * bpu * (size_t)p.top_k * 4);
         take(&w.slot_bkt, U * bpu * (size_t)kFusedListCap * 16);
     }
+    // (last: its size is no other buffer's place; 0.1 us of the 4K and 32K steps against a place before the selection's)
+    take(&w.xs, U * (packed ? G * 8 : ix->xs_words) * 8);
     return cv.off;
 }
 
