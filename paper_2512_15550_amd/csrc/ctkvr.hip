@@ -1562,18 +1562,22 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     sa.by_xcd = by_xcd_all;
     {
         // Few rows per CU (a small batch): a block's rows are one round trip to memory and the slowest block
-        // is the launch, so the ids are split by rank -- two blocks a CU (with twelve rows a lane group in flight, see
-        // recall_score_kernel: 32K 33.9 us a step at three blocks per two CUs and eight rows, 34.4 with twelve, 32.9 at two), those of a
+        // is the launch, so the ids are split by rank -- two blocks a CU (32K, eight units 32.9 us a step; 1.5: 34.4), those of a
         // resident window, which ride in the launch, counted in (on top of them: eight units of 32K, window of 640 and 100 decoded tokens
-        // 42.7 us with the update, now 41.9; two units of 16K in fp32 40.6, now 35.2), at least 32 per unit and 64 list entries per block (128 leave CUs idle where units are few and
+        // 42.7 us with the update, now 41.9; two units of 16K in fp32 40.6, now 35.2), but from 96 a unit on 1.5 blocks a CU: each
+        // reads the unit's whole bitmap, and their atomics meet on the unit's line (one, two and four units of 32K in bf16 33.2, 32.2
+        // and 31.3 us, now 31.5, 30.6 and 30.8; in fp32 34.1, 33.2 and 32.4, now 32.5, 30.9 and 31.7).  At least 32 per
+        // unit and 64 list entries per block (128 leave CUs idle where units are few and
         // their lists short: two probes of 495, 16 units of eight heads 28.5 us, 128 29.3; four of 495, four units 31.5, 128 32.5; four of 1280,
         // four units 33.0 either way).  Otherwise by id
         // range: enough blocks to fill the chip a few times over, each owning 8..64 words of the bitmap.
         const bool by_rank = ix->score_by_rank < 0 ? (long long)ix->l_stride * U <= 2048ll * ix->num_cu : ix->score_by_rank != 0;
+        const bool win_beside = window && G <= 4;
         int nbx;
         if (by_rank) {
-            const int beside = window && G <= 4 ? kWinSplit * U : 0;
-            nbx = std::min(std::max(32, (2 * ix->num_cu - beside + U - 1) / U), (ix->l_stride + 63) / 64);
+            nbx = std::min((2 * ix->num_cu + U - 1) / U, std::max(96, (3 * ix->num_cu / 2 + U - 1) / U));
+            if (win_beside) nbx = std::min(nbx, 2 * ix->num_cu / U - kWinSplit);
+            nbx = std::min(std::max(32, nbx), (ix->l_stride + 63) / 64);
             nbx = std::max({1, nbx, (ix->l_stride + kRecallCap - 1) / kRecallCap});
         } else {
             const int target = std::max(32, (8 * ix->num_cu + U - 1) / U);
@@ -1598,7 +1602,7 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         auto launch = [&](auto rank, auto stream, auto few) {
             constexpr bool RANK = decltype(rank)::value, STREAM = decltype(stream)::value, SHORT = decltype(few)::value;
             if constexpr (G <= 4) {
-                if (window) {
+                if (win_beside) {
                     sa.win = wa;
                     recall_score_kernel<T, G, true, RANK, STREAM, SHORT><<<dim3(nbx + kWinSplit, U), 256, slds, st>>>(sa);
                     return;
@@ -1606,18 +1610,19 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
             }
             recall_score_kernel<T, G, false, RANK, STREAM, SHORT><<<dim3(nbx, U), 256, slds, st>>>(sa);
         };
-        auto launch_rank = [&](auto rank) {
+        auto launch_rows = [&](auto rank, auto few) {
             if (stream_k)
-                launch(rank, std::true_type{}, std::false_type{});
+                launch(rank, std::true_type{}, few);
             else
-                launch(rank, std::false_type{}, std::false_type{});
+                launch(rank, std::false_type{}, few);
         };
-        if (by_rank && !stream_k && ix->l_stride <= 16 * kShortRows * nbx)
-            launch(std::true_type{}, std::false_type{}, std::true_type{});
+        constexpr bool kTwo = kRankRows<T> != kShortRows;   // by rank with different numbers of rows
+        if (kTwo && by_rank && (ix->l_stride <= 16 * kShortRows * nbx || (nbx * U > 2 * ix->num_cu && !win_beside)))
+            launch_rows(std::bool_constant<true>{}, std::bool_constant<kTwo>{});
         else if (by_rank)
-            launch_rank(std::true_type{});
+            launch_rows(std::true_type{}, std::false_type{});
         else
-            launch_rank(std::false_type{});
+            launch_rows(std::false_type{}, std::false_type{});
     }
     if (whole) ix->mark(3, st);
 

@@ -641,13 +641,15 @@ template <typename T, int G> __global__ __launch_bounds__(256) void window_attn_
 constexpr int kRecallWpb = 64;     // by id range: at most 2048 ids per block
 constexpr int kRecallCap = 2048;   // ids per block at most
 constexpr int kRecallPad = 256;    // words behind the rows: a tile beyond the last is requested too
-// Rows in flight per 16-lane group.  By id range eight: four blocks a CU in bf16 with groups up to four.  By rank a CU has two blocks and the
-// registers are free, and twelve take the 125 to 170 rows of a block of the 32K step in one trip, not two (step 33.9 -> 32.9 us with two blocks a CU; sixteen:
-// the same; rows of 512 bytes: no gain at 4K, eight).
-template <typename T> constexpr int kRankRows = sizeof(T) == 2 ? 12 : 8;
-// By rank where a block has 64 ids at most (recall_score_kernel's SHORT).  The loop's requests have no branches, and twelve or eight where a
-// block has rows for two or four cost their issue and their answers: one fp32 sequence of 4K, two KV heads 22.84 -> 22.56 us a step, two
-// of 4K in bf16, eight KV heads 23.16 -> 23.05.
+// Rows in flight per 16-lane group.  By id range eight: four blocks a CU in bf16 with groups up to four.  By rank in bf16 twelve, which take
+// the 125 to 170 rows of a block of the 32K step in one trip, not two (step 33.9 -> 32.9 us with two blocks a CU; sixteen: the same).  In fp32
+// four: eight are 169 to 220 registers, with groups of two and more two blocks a CU where the grid often has three and more, and no faster
+// where it has two (24 units of 16K, groups of two 42.2 -> 36.5 us a step, of four 47.2 -> 41.3; eight units of 32K, groups of four 34.6 -> 34.1).
+template <typename T> constexpr int kRankRows = sizeof(T) == 2 ? 12 : 4;
+// In bf16 by rank (recall_score_kernel's SHORT) four too where a block has 64 ids at most, or a CU more than two blocks: the loop's
+// requests have no branches, and twelve where a block has rows for two or four cost their issue and their answers, and 98 to 163
+// registers, i.e. four or three blocks a CU (in a launch with a resident window its blocks' registers set that).  Steps: sixteen units of 4K, groups of four 23.16 -> 23.05 us; 40 of 8K 36.0 -> 33.5, 128 of 4K 49.7
+// -> 43.8, 32 of 16K, groups of eight 48.2 -> 45.0.
 constexpr int kShortRows = 4;
 constexpr int kRecallWords = 4096; // by rank: bitmap words (contexts up to 128K) that the prologue takes in one trip
 
@@ -680,7 +682,7 @@ struct RecallScoreArgs {
 };
 
 // RANK: how the bitmap is split over a unit's blocks.  STREAM: the keys of all sequences exceed what the memory-side cache holds, and are
-// loaded non-temporal.  SHORT: by rank, and no block has more than 16 kShortRows ids
+// loaded non-temporal.  SHORT: by rank, with kShortRows
 template <typename T, int G, bool WIN, bool RANK, bool STREAM, bool SHORT = false>
 __global__ __launch_bounds__(256) void recall_score_kernel(RecallScoreArgs a)
 {

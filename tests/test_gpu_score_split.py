@@ -2,6 +2,7 @@
 eight ids of a byte of the bitmap, pages larger than a block's ids, block tables that fit beside the bitmap and not (beyond
 4096 entries), contexts whose bitmap is kept (to 4096 words) and read again (beyond), lengths that end inside a word, few
 recalled ids for many blocks; by id range and by rank."""
+import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -10,6 +11,7 @@ pytestmark = pytest.mark.gpu
 import paper_2512_15550_amd as ck
 from ctkvr_inputs import gen_batch, small_workload
 from tests import harness as H
+from tests.test_gpu_share_tail import _inputs, _run
 
 
 @pytest.mark.parametrize("by_rank", [0, 1])
@@ -30,9 +32,11 @@ def test_recalled_ids_and_rows_match_the_oracle(h, g, lens, page, rho, n_probe, 
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("h,g,batch,rho", [(8, 8, 8, 1024), (16, 8, 8, 1024), (32, 8, 8, 1024), (32, 8, 8, 1025), (64, 8, 8, 1024), (64, 8, 8, 1025)])
+@pytest.mark.parametrize("h,g,batch,rho", [(8, 8, 2, 1024), (16, 8, 2, 1024), (32, 8, 2, 1024), (64, 8, 2, 1024), (8, 8, 2, 1025), (16, 8, 2, 1025),
+                                           (32, 8, 2, 1025), (64, 8, 2, 1025), (32, 8, 3, 1025), (5, 5, 1, 1300), (4, 4, 1, 1300)])
 def test_blocks_of_few_ids_by_rank(dtype, h, g, batch, rho, monkeypatch):
-    """64 units of 32 blocks: at most 64 ids a block (four rounds of rows), or 65 (as many rounds as the registers allow)."""
+    """Four rounds of rows in flight or twelve, on both sides of the lines between them (256 CUs): 16 units of 32 blocks with at most 64 ids
+    a block, or 65; 24 units, and more than two blocks a CU; four and five units, and fewer blocks."""
     monkeypatch.setenv("CTKVR_SCORE_BY_RANK", "1")
     lens = tuple(3201 + 13 * i for i in range(batch))
     wl = small_workload("few_ids", dtype, h, g, lens, tuple(850 + i for i in range(batch)), 4, 0, 2, rho, 100, 1)
@@ -44,3 +48,18 @@ def test_blocks_of_few_ids_by_rank(dtype, h, g, batch, rho, monkeypatch):
         H.run_decode_parity(bt, H.oracle_index(bt), idx, db)
     finally:
         ck.ctkvr_free(idx)
+
+
+@pytest.mark.parametrize("B,g,s,rho,n_probe", [(9, 4, 22277, 514, 10), (1, 5, 131072, 4000, 8)])
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_streamed_rows_by_rank_and_by_id_range_give_the_same_bits(G, B, g, s, rho, n_probe, monkeypatch):
+    """More than 128 MiB of keys (non-temporal loads), more and fewer than two blocks a CU by rank."""
+    p = ck.Params(batch=B, n_q_heads=G * g, n_kv_heads=g, n_centroids=16, list_len=rho, n_probe=n_probe, top_k=300, dtype=ck.BF16)
+    assert B * g * s * 256 > 128 << 20
+    data = _inputs("bf16", B, G, g, s, rho, 300, 1.0, 0, 4300, C=16)
+    got = []
+    for by_rank in ("0", "1"):
+        monkeypatch.setenv("CTKVR_SCORE_BY_RANK", by_rank)
+        got.append(_run(p, s, data, {"CTKVR_TAIL": "0"}, monkeypatch))
+    for a, b in zip(*got):
+        assert all(np.array_equal(x, y) for x, y in zip(a, b))
