@@ -3419,7 +3419,11 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
 // some head's picks all lie so far below its maximum that their weights vanish (weights relative to the picks' own maxima then).
 // grid nb*batch*g, nb a power of two, kTailThreads threads; dynamic shared memory: share_smem_words.  Same integers as the separate kernels.
 // ------------------------------------------------------------------------------
-constexpr int kShareList = 512;    // keys of the deciding bucket that are ranked against each other
+constexpr int kShareList = 512;    // keys of the deciding bucket that are ranked against each other at most
+// ... where a finer histogram is to be had: more are counted again.  A histogram more is 2 us, ranking 128 keys 0.4, 256 2 and 512 8 (a key and its
+// position compared one after the other instead of as one word: 8 and 30).  Scores of little spread, 32 units of 4096 recalled keys,
+// 1024 picks: 75.2 us a step (every bucket up to 512 keys ranked), now 41.9; 128 units of 8192 keys 139 -> 102 (separate launches 46.1 and 114)
+constexpr int kShareRank = 128;
 constexpr int kShareBlocks = 8;    // blocks per unit at most
 constexpr int kShareBuckets = 256; // buckets of a histogram: 1/4 wide in the log domain, 1 wide below them, 1/256 of either inside one
 constexpr uint32_t kShareFar = 63; // the buckets of 1 begin at -63, of which what lies above the quarters' end (-63.75) is empty
@@ -3465,6 +3469,12 @@ __host__ __device__ __forceinline__ size_t share_smem_words(int share, int G)
     return share_front_words(G) + (size_t)(kTailThreads / 64) * kSharePicks * (2 + G) + 2 * (size_t)share;
 }
 
+// a key of the deciding bucket and its position as one word that is never zero: of two, the larger comes first in the ranking
+__device__ __forceinline__ unsigned long long share_entry(float key, int pos)
+{
+    return (unsigned long long)ordered_key(key) << 32 | ~(uint32_t)pos;
+}
+
 // two values summed over the halves of a wave, lane by lane: the lower half gets the sum of a, the upper that of b
 __device__ __forceinline__ float half_pair_sum(float a, float b)
 {
@@ -3488,7 +3498,7 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
     __shared__ uint32_t s_before, s_cur;   // picks of earlier shares; cursor of the share's part of the bucket's list
     __shared__ uint32_t s_cnt[NW];         // picks of each wave
     uint32_t *s_hist = smem;                                    // a histogram per wave
-    uint2 *s_ent = reinterpret_cast<uint2 *>(smem + kSelLds);   // kShareList: (key, position) of the deciding bucket
+    unsigned long long *s_ent = reinterpret_cast<unsigned long long *>(smem + kSelLds);   // kShareList: share_entry of the deciding bucket
     float *s_o = reinterpret_cast<float *>(smem);               // [NW][G][128], once those two are done with
     const int tid = threadIdx.x, ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the wave's picks: row, position (with a mark on the sure ones), scores and then weights
@@ -3720,7 +3730,7 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
     float hi_k = every ? -__builtin_huge_valf() : __builtin_huge_valf(), lo_k = -__builtin_huge_valf();
     // keys wanted from the deciding bucket, its population, those in earlier shares (at first of all keys)
     uint32_t rem = (uint32_t)a.top_k, n_bkt = (uint32_t)L, e0 = (uint32_t)min(L, g0 * 64);
-    // 256 buckets a quarter wide; where more keys than are listed share the deciding one, 256 inside it (fine).  The last bucket is all
+    // 256 buckets a quarter wide; where more than kShareRank keys share the deciding one, 256 inside it (fine).  The last bucket is all
     // below, and where it decides, 256 buckets of 1 follow first: keys spread with the queries' norms, and a large budget's last
     // one lies beyond -63.75 in earnest (8 units of one head, 33000 keys and 4096 picks 64.2 us a step, going alone there 83.2, separate
     // launches 66.7; of two heads, 89000 keys and 2048 picks 105, 237 and 168)
@@ -3825,11 +3835,11 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
         rem = s_res[1];
         n_bkt = s_res[2];
         e0 = s_res[3];
-        alone = n_bkt > (uint32_t)kShareList;
+        alone = n_bkt > (uint32_t)kShareList;   // (or ~0: a block did not answer)
         const bool below = !fine && bkt == (uint32_t)(kShareBuckets - 1);
         hi_k = first + bkt ? fminf(upto, (float)(first + bkt) * width) : upto;
         lo_k = below ? -__builtin_huge_valf() : (float)(first + bkt + 1u) * width;
-        if (!alone || n_bkt == ~0u || fine || (below && level)) break;   // uniform
+        if (n_bkt <= (uint32_t)kShareRank || n_bkt == ~0u || fine || (below && level)) break;   // uniform
         fine = !below;
         scale = fine ? scale * (float)kShareBuckets : -1.0f;
         width = fine ? width / (float)kShareBuckets : -1.0f;
@@ -3917,9 +3927,9 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
                 e = rank_in(in, e0 + (uint32_t)__builtin_amdgcn_readfirstlane((int)e));
                 if (__builtin_amdgcn_inverse_ballot_w64(in)) {
                     if (nb > 1)
-                        put(&xlist[e], ((unsigned long long)ordered_key(kk) << 32) | 0x80000000u | (uint32_t)key_at(q));
+                        put(&xlist[e], share_entry(kk, key_at(q)));
                     else
-                        s_ent[e] = make_uint2(ordered_key(kk), (uint32_t)key_at(q));
+                        s_ent[e] = share_entry(kk, key_at(q));
                 }
             }
         });
@@ -3933,7 +3943,10 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
         begin();
         CTKVR_STAMP(67);
         if (!every) {
-            // which of the bucket's keys are picks: ranked against each other, ids decide between equal keys
+            // which of the bucket's keys are picks: ranked against each other, ids decide between equal keys.  (Zeros, below every entry,
+            // to the next power of two.)
+            uint32_t cap = 64;
+            while (cap < n_bkt) cap <<= 1;
             if (nb > 1) {
                 unsigned long long v = 1ull;
                 bool all = false;
@@ -3942,29 +3955,27 @@ template <typename T, int G> __global__ __launch_bounds__(kTailThreads) void sha
                     all = __all(v != 0ull);
                 }
                 if (!all) s_res[4] = 1u;
-                if (tid < (int)n_bkt) s_ent[tid] = make_uint2((uint32_t)(v >> 32), (uint32_t)v & 0x7fffffffu);
+                if (tid < (int)n_bkt) s_ent[tid] = v;
             }
+            if (tid >= (int)n_bkt && tid < (int)cap) s_ent[tid] = 0ull;
             __syncthreads();
             CTKVR_STAMP(68);
-            uint32_t cap = 64;
-            while (cap < n_bkt) cap <<= 1;
             const uint32_t parts = (uint32_t)NT / cap, e = (uint32_t)tid & (cap - 1u), part = (uint32_t)tid / cap;
             if (e < n_bkt) {
-                const uint2 me = s_ent[e];
+                const unsigned long long me = s_ent[e];
                 uint32_t rank = 0;
-                for (uint32_t f = part; f < n_bkt; f += 4 * parts) {
-                    uint2 o[4];
+                for (uint32_t f = part; f < n_bkt; f += 4 * parts) {   // (f + 3 parts < cap, a multiple of 4 parts)
+                    unsigned long long o[4];
 #pragma unroll
-                    for (uint32_t i = 0; i < 4; ++i) o[i] = s_ent[min(f + i * parts, n_bkt - 1)];
+                    for (uint32_t i = 0; i < 4; ++i) o[i] = s_ent[f + i * parts];
 #pragma unroll
-                    for (uint32_t i = 0; i < 4; ++i)
-                        rank += f + i * parts < n_bkt && ((o[i].x > me.x) || (o[i].x == me.x && o[i].y < me.y));
+                    for (uint32_t i = 0; i < 4; ++i) rank += o[i] > me ? 1u : 0u;
                 }
                 atomicAdd(&s_hist[e], rank);
             }
             __syncthreads();
             if (tid < (int)n_bkt && s_hist[tid] < rem) {
-                const int pos = (int)s_ent[tid].y, rel = pos - g0 * 64;
+                const int pos = (int)~(uint32_t)s_ent[tid], rel = pos - g0 * 64;
                 if (rel < 0) {
                     atomicAdd(&s_before, 1u);
                 } else if (pos < g1 * 64) {

@@ -1,7 +1,8 @@
 """What follows the scoring with a unit's recalled keys shared out over its blocks (share_tail_kernel) against the separate
 launches: the same integers bit for bit and outputs within rounding, where its branches change -- one to eight blocks a unit, keys
 beyond those in registers, a wave with more picks than it takes at a time, shares without keys, every key kept, flat scores (a
-second histogram), scores below the histogram's range (a second and a third, or a block goes on alone), equal keys (likewise), a head whose picks' weights vanish, the
+second histogram), a bucket of 129 to 512 keys (likewise; so many equal ones are ranked all the same), scores below the histogram's range (a second
+and a third, or a block goes on alone), equal keys (likewise), a head whose picks' weights vanish, the
 resident window, groups of sequences side by side, the static scratch, and blocks that never see their siblings' words."""
 import numpy as np
 import pytest
@@ -24,6 +25,8 @@ CASES = {  # dtype, batch, G, g, s, lists' length, probes, top_k, scale of the q
     "every_key": ("bf16", 2, 4, 8, 3000, 100, 3, 301, 1.0, 0),
     "flat_scores": ("bf16", 1, 4, 8, 30000, 3000, 16, 1000, 0.01, 0),
     "equal_keys": ("bf16", 1, 4, 8, 5000, 300, 8, 700, 0.0, 0),
+    "crowded_bucket": ("bf16", 4, 4, 8, 4099, 350, 12, 1024, 1.0, 0),
+    "few_equal_keys": ("bf16", 2, 4, 8, 450, 100, 8, 200, 0.0, 0),
     "below_the_range": ("bf16", 1, 2, 8, 2000, 300, 8, 1100, 40.0, 0),
     "many_below_the_range": ("bf16", 1, 1, 2, 120001, 20000, 40, 8000, 26.0, 0),
     "below_both_ranges": ("bf16", 1, 2, 8, 3000, 300, 8, 900, 300.0, 0),
