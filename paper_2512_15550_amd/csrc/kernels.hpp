@@ -641,11 +641,13 @@ template <typename T, int G> __global__ __launch_bounds__(256) void window_attn_
 constexpr int kRecallWpb = 64;     // by id range: at most 2048 ids per block
 constexpr int kRecallCap = 2048;   // ids per block at most
 constexpr int kRecallPad = 256;    // words behind the rows: a tile beyond the last is requested too
-// Rows in flight per 16-lane group.  By id range eight: four blocks a CU in bf16 with groups up to four.  By rank in bf16 twelve, which take
+// Rows in flight per 16-lane group.  By id range in bf16 eight: four blocks a CU with groups up to four.  By rank in bf16 twelve, which take
 // the 125 to 170 rows of a block of the 32K step in one trip, not two (step 33.9 -> 32.9 us with two blocks a CU; sixteen: the same).  In fp32
-// four: eight are 169 to 220 registers, with groups of two and more two blocks a CU where the grid often has three and more, and no faster
-// where it has two (24 units of 16K, groups of two 42.2 -> 36.5 us a step, of four 47.2 -> 41.3; eight units of 32K, groups of four 34.6 -> 34.1).
+// four: eight are 169 to 220 registers, with groups of two and more two blocks a CU, where the grid often has three and more, and no faster
+// where it has two (by rank, 24 units of 16K, groups of two 42.2 -> 36.5 us a step, of four 47.2 -> 41.3; eight units of 32K, groups of four 34.6 -> 34.1;
+// by id range, sixteen sequences of 8K to 32K on eight KV heads, groups of four, the launch 115.7 -> 109.9, on four, of eight 68.8 -> 65.3).
 template <typename T> constexpr int kRankRows = sizeof(T) == 2 ? 12 : 4;
+template <typename T> constexpr int kRangeRows = sizeof(T) == 2 ? 8 : 4;
 // In bf16 by rank (recall_score_kernel's SHORT) four too where a block has 64 ids at most, or a CU more than two blocks: the loop's
 // requests have no branches, and twelve where a block has rows for two or four cost their issue and their answers, and 98 to 163
 // registers, i.e. four or three blocks a CU (in a launch with a resident window its blocks' registers set that).  Steps: sixteen units of 4K, groups of four 23.16 -> 23.05 us; 40 of 8K 36.0 -> 33.5, 128 of 4K 49.7
@@ -686,7 +688,7 @@ struct RecallScoreArgs {
 template <typename T, int G, bool WIN, bool RANK, bool STREAM, bool SHORT = false>
 __global__ __launch_bounds__(256) void recall_score_kernel(RecallScoreArgs a)
 {
-    constexpr int R = SHORT ? kShortRows : RANK ? kRankRows<T> : 8, TILE = 16 * R;
+    constexpr int R = SHORT ? kShortRows : RANK ? kRankRows<T> : kRangeRows<T>, TILE = 16 * R;
     static_assert(TILE <= kRecallPad, "rows requested beyond the block's");
     extern __shared__ __align__(16) uint32_t smem[];
     uint32_t *s_ids = smem, *s_rows = smem + kRecallCap;     // ids of this block's ranks, their rows
