@@ -1593,7 +1593,7 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
             const int pages = (std::min(max_pages, ((ix->s_max - 1) >> ix->page_shift) + 1) + 255) & ~255;
             RecallLds all = sa.lds;
             all.pages = pages;
-            sa.lds.pages = words && pages <= kRecallWords && all.total() * 4 <= 61 * 1024 ? pages : 0;
+            sa.lds.pages = words && pages <= kRecallWords && all.total() * 4 <= 60 * 1024 ? pages : 0;
         } else {
             sa.lds.pages = 256;
             sa.lds.words = 0;

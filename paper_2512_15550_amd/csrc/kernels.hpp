@@ -640,7 +640,6 @@ template <typename T, int G> __global__ __launch_bounds__(256) void window_attn_
 // ------------------------------------------------------------------------------
 constexpr int kRecallWpb = 64;     // by id range: at most 2048 ids per block
 constexpr int kRecallCap = 2048;   // ids per block at most
-constexpr int kRecallPad = 256;    // words behind the rows: a tile beyond the last is requested too
 // Rows in flight per 16-lane group.  By id range in bf16 eight: four blocks a CU with groups up to four.  By rank in bf16 twelve, which take
 // the 125 to 170 rows of a block of the 32K step in one trip, not two (step 33.9 -> 32.9 us with two blocks a CU; sixteen: the same).  In fp32
 // four: eight are 169 to 220 registers, with groups of two and more two blocks a CU, where the grid often has three and more, and no faster
@@ -658,7 +657,7 @@ constexpr int kRecallWords = 4096; // by rank: bitmap words (contexts up to 128K
 // words of shared memory: ids and rows of the block, block-table entries, by rank the bitmap and the ids before each word
 struct RecallLds {
     int pages, words;
-    __host__ __device__ int total() const { return 2 * kRecallCap + kRecallPad + pages + 2 * words; }
+    __host__ __device__ int total() const { return 2 * kRecallCap + pages + 2 * words; }
 };
 
 struct RecallScoreArgs {
@@ -689,10 +688,9 @@ template <typename T, int G, bool WIN, bool RANK, bool STREAM, bool SHORT = fals
 __global__ __launch_bounds__(256) void recall_score_kernel(RecallScoreArgs a)
 {
     constexpr int R = SHORT ? kShortRows : RANK ? kRankRows<T> : kRangeRows<T>, TILE = 16 * R;
-    static_assert(TILE <= kRecallPad, "rows requested beyond the block's");
     extern __shared__ __align__(16) uint32_t smem[];
     uint32_t *s_ids = smem, *s_rows = smem + kRecallCap;     // ids of this block's ranks, their rows
-    int32_t *s_page = (int32_t *)(smem + 2 * kRecallCap + kRecallPad);    // block-table entries
+    int32_t *s_page = (int32_t *)(smem + 2 * kRecallCap);    // block-table entries
     uint32_t *s_word = (uint32_t *)s_page + a.lds.pages, *s_before = s_word + a.lds.words;
     __shared__ uint32_t s_tmp[8];
     __shared__ uint32_t s_edge[3];                // first word, ids before it, last word
@@ -853,8 +851,6 @@ __global__ __launch_bounds__(256) void recall_score_kernel(RecallScoreArgs a)
         // batch still uses all of them)
         const int W = (a.ctx_lens[b] + 31) >> 5;
         const int wpb = min(kRecallWpb, (W + a.nbx - 1) / a.nbx);
-        // (rows beyond the block's, which are requested with the last ones: row 0 of the pool)
-        for (int w = tid; w < (kRecallCap + kRecallPad) / 4; w += 256) reinterpret_cast<uint4 *>(s_rows)[w] = make_uint4(0u, 0u, 0u, 0u);
         const int w_beg = bx * wpb, w_end = min(W, w_beg + wpb);
         clear();
         if (w_beg >= W) return;
@@ -916,7 +912,9 @@ __global__ __launch_bounds__(256) void recall_score_kernel(RecallScoreArgs a)
     static_assert(R % SUB == 0, "rounds are written SUB at a time");
     const int last = (int)n_blk - 1;
     Chunk<T> ck[R];
-    auto row_at = [&](int i) __attribute__((always_inline)) { return s_rows[RANK ? min(i, last) : i]; };
+    // (beyond the block's rows its own last one, whose line is at hand: row 0 of the pool for all blocks cost fp32 0.4 to 1.6 % of a step, 128K x 4
+    // 0.2 to 0.3)
+    auto row_at = [&](int i) __attribute__((always_inline)) { return s_rows[min(i, last)]; };
     auto request = [&](int r, uint32_t row) __attribute__((always_inline)) {
         const T *p = K + (size_t)row * kD;
         ck[r] = STREAM ? load_chunk_nt(p, lane16) : load_chunk(p, lane16);
