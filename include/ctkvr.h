@@ -133,6 +133,9 @@ int ctkvr_index_load(const ctkvr_params *p, const int32_t *ctx_lens, const void 
  *   out_ncand  int32 [batch][g]: L;
  *   out_probe  int32 [batch][g][C'] probed centroid ids ascending.
  * The KV cache must hold the same first ctx_len_i keys the index was built on.
+ * The integers are the same in every call with the same arguments.  out and out_lse are too, except that in
+ * a larger batch's one launch behind the scoring (CTKVR_TAIL = 2 below) a block whose bounded wait for its siblings'
+ * words expires, as beside other work that holds the compute units, sums in another order: they may then differ in rounding.
  * Asynchronous on hip_stream; uses the index's workspace, so steps on one index
  * must not overlap.  Errors: EINVAL (null required pointer, max_pages too small).
  */
@@ -228,9 +231,9 @@ int ctkvr_index_last_candidates(const ctkvr_index *idx, int32_t *dst_host);
 /* The decode step runs these kernels in order: 0 centroid cosine, 1 probe select + list
  * gather into a bitmap, 2 bitmap expansion into the recalled id list fused with key scoring,
  * 3 softmax denominators, 4 ranking keys + their histogram, 5 chip-wide pass over the
- * ranking keys (bitmap + deciding bucket's list), 6 rerank select, 7 sparse attention.  For
- * small batches 3 to 7 are one launch, for medium ones 6 and 7, timed as stage 7 (the others then read as
- * the cost of an event pair).  While timing is enabled a ninth, empty kernel follows (stage 8): its
+ * ranking keys (bitmap + deciding bucket's list), 6 rerank select, 7 sparse attention.  As a rule 3 to 7 are one
+ * launch, timed as stage 7 (the others then read as the cost of an event pair), and where they are not (CTKVR_TAIL = 0 below)
+ * 6 and 7 are for up to 64 (batch, KV head) pairs.  While timing is enabled a ninth, empty kernel follows (stage 8): its
  * figure is what a pair of events costs around a kernel that does nothing. */
 #define CTKVR_N_STAGES 9
 /* After this call every decode step on `idx` records a HIP event before its first
@@ -244,7 +247,7 @@ int ctkvr_profile_enable(ctkvr_index *idx, int32_t max_steps);
 int ctkvr_profile_collect(ctkvr_index *idx, float *ms_host, int32_t capacity_steps, int32_t *n_steps);
 
 /* ---- environment variables ------------------------------------------------------------- */
-/* Read when an index is created (ctkvr_build_index, ctkvr_index_load); none changes a result, all
+/* Read when an index is created (ctkvr_build_index, ctkvr_index_load); none changes a result beyond the outputs' rounding, all
  * exist so that each form of a launch can be measured and tested against the other:
  *   CTKVR_DECODE_PATH        = staged | fused | auto   default of ctkvr_index_set_decode_path
  *   CTKVR_DECODE_GROUPS      = n   sequences stepped as n forked groups (default 1)

@@ -1495,14 +1495,18 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     // Everything after the scoring as one launch (tail_kernel): for small batches, whose step is a chain of latencies,
     // and only up to a number of recalled keys: every block of a unit walks all of them, and beyond the 8192 it keeps, reads
     // them three times (one CU takes about 20 GB/s).  The number of recalled keys L is known on the device only; l_stride bounds
-    // it, and neighbouring lists overlap: L is 0.2 to 0.28 of l_stride on the benchmark inputs.  Step with / without, G = 4, us:
-    //   L           8192        16384       32768        65536
-    //   4 units     40.8/48.6   50.7/50.5   70.5/56.8    110.1/72.1    (loads from other XCDs' caches: unit_block_of)
-    //   8 units     39.0/45.9   46.0/49.5   63.0/59.1    101.3/85.8
-    //   16 units    44.0/51.8   55.3/58.7   84.0/82.0    136.1/114.7
-    //   32 units    53.0/61.1   73.3/77.9   118.1/116.4  196.7/179.4
-    // (G = 1, 2 and 8 cross at the same L.)  The lines are twice the crossings: no loss while at most half the probed entries are
-    // distinct.  Not where one of the forms it replaces is asked for.
+    // it, and neighbouring lists overlap: L is 0.2 to 0.28 of l_stride on the benchmark inputs.  Steps with tail_kernel / share_tail_kernel / the
+    // separate launches, G = 4, 1024 picks, us:
+    //   L           4096            8192            16384           32768           65536
+    //   4 units     27.8/31.7/33.3  30.4/32.8/36.8  43.3/35.1/41.5  64.4/42.8/50.3  108/56.2/65.2   (loads from other XCDs' caches: unit_block_of)
+    //   8 units     27.1/31.5/31.9  29.7/32.5/35.4  42.4/38.9/42.5  58.7/48.2/53.0  94.7/66.6/72.9
+    //   16 units    29.1/33.2/34.3  35.0/37.9/41.2  48.4/45.3/49.6  70.4/60.3/66.6
+    //   24 units    30.0/34.3/35.0  37.0/40.1/43.0  53.1/50.7/55.0
+    //   32 units    31.8/36.1/36.6  40.1/43.3/46.0  61.5/59.8/63.9
+    // (G = 1, 2 and 8 cross in the same places.)  The lines were drawn at twice the crossings with the separate launches: no loss against those
+    // while at most half the probed entries are distinct.  share_tail_kernel crosses sooner, near L = 12000: at l_stride = 32768 with a quarter distinct
+    // tail_kernel is still the faster (8 units 31.0/33.5, 16 34.3/37.2), at 65536 no longer (8 units 41.6/39.1).  Not where one of the
+    // forms it replaces is asked for.
     const int tail_most = by_xcd ? 65536 : 32768;
     const bool tail = ix->tail_lds && ix->keyclass < 0 &&
                       (ix->tail < 0 ? (long long)ix->l_stride * U <= 2048ll * ix->num_cu && ix->l_stride <= tail_most : ix->tail == 1);
@@ -1510,8 +1514,11 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     ca.n_xs = tail ? ix->attn_slices * G : 0;
     // Beyond that one launch all the same, with a unit's recalled keys shared out over its blocks (share_tail_kernel): 128K x 4
     // 125.8 -> 116.7 us a step, sixteen of 8K to 64K 144.9 -> 130.0, against the separate launches, which are left to budgets beyond
-    // kShareCut, shares whose bitmap the shared memory does not take, and long contexts of more units than half the CUs (share_pays).  Small batches would lose with it (32K 31.9 -> 34.9 us, 4K 23.5 -> 28.7: every
-    // block's chain is as long, and waits three times more for the others).
+    // kShareCut, shares whose bitmap the shared memory does not take, and long contexts of more units than half the CUs (share_pays).  Small
+    // batches would lose with it (32K 31.9 -> 34.9 us, 4K 23.5 -> 28.7: every block's chain is as long, and waits three times more for the
+    // others).  Scores of little spread (logits of unit variance), 1024 picks, with / without: 32 units, l_stride 65536, L 8192, 16384 and 32768
+    // 52.1/56.3, 66.0/69.8, 95.8/98.9; 128 units 114/124, 172/182, 300/300.  Lists without any overlap cost it 1 to 8 % from L = 65536 (and 128
+    // units, 32768) on.
     const bool share = !tail && ix->share_lds && ix->keyclass < 0 && (ix->tail == 2 || (ix->tail != 0 && ix->share_pays));
     if (whole) ix->mark(0, st);
     centroid_cos_kernel<T, G><<<dim3((ix->c_max + 15) / 16, U), 256, 0, st>>>(ca);
@@ -1726,8 +1733,8 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
     denom_kernel<G><<<dim3(std::max(1, std::min(chunks, (4 * ix->num_cu + U - 1) / U)), U), 256, 0, st>>>(da);
     if (whole) ix->mark(4, st);
 
-    // Small batches: the key histogram and the classification pass as one launch, every block taking the unit's
-    // whole histogram itself (keyclass_kernel); otherwise two chip-wide launches.
+    // The separate launches.  Of small batches (that is, with budgets beyond kShareCut, or where they are asked for) the key histogram and
+    // the classification pass are one, every block taking the unit's whole histogram itself (keyclass_kernel); otherwise two chip-wide ones.
     const bool keyclass = ix->sel_bits && (ix->keyclass < 0 ? (long long)ix->l_stride * U <= 2048ll * ix->num_cu : ix->keyclass != 0);
     if (keyclass) {
         KeyClassArgs kc{};

@@ -3402,9 +3402,10 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
 // attention, where denom, keyhist, classify, selection and attention as launches of their own took 35 us (128K x 4) and 43 us
 // (sixteen of 8K to 64K), of which the passes over memory are the smaller part: each begins with a ramp and a chain of loads and
 // ends with a drain.  This one takes 25 and 27 us, bound by its chain: 2.8 us to the scores, 2.0 for the exponentials (vector issue), 1.6, 2
-// and 2.8 for the words of the others, 2.5 for the picks, 3 for their value rows, 2 to 4 for weighing them.  Block x of a unit's nb takes every step for its own share, a contiguous stretch of the recalled keys (whose scores
-// and ranking keys stay in its registers), and what must be known of the others crosses over in 64-bit words that are zero
-// before the launch and carry their own validity, written and read by single atomics, so that no fence is needed:
+// and 2.8 for the words of the others, 2.5 for the picks, 3 for their value rows, 2 to 4 for weighing them.  Block x of a unit's nb takes every
+// step for its own share, a contiguous stretch of the recalled keys (whose scores and ranking keys stay in its registers), and what must be
+// known of the others crosses over in 64-bit words that are zero before the launch and carry their own validity, written and read by single
+// atomics, so that no fence is needed:
 //   1. the share's denominator sums (a word per head);
 //   2. the share's histograms of ranking keys (four buckets a word; one, two or three of them): every block then knows the unit's deciding bucket,
 //      and from the others' histograms how many picks and how many of that bucket's keys come before its own;
@@ -3417,6 +3418,8 @@ template <typename T, int G, int SL> __global__ __launch_bounds__(kTailThreads) 
 // depends on the other blocks being resident.  It does the same where the bucket is crowded (more than kShareList keys, in the finest
 // histogram or below -318), and where
 // some head's picks all lie so far below its maximum that their weights vanish (weights relative to the picks' own maxima then).
+// The integers never depend on who gave up, and neither do the denominators; a block that goes on alone sums the weighted rows in another
+// order, so that the outputs' last bits may differ between two calls, and within a head, where a wait expired in one.
 // grid nb*batch*g, nb a power of two, kTailThreads threads; dynamic shared memory: share_smem_words.  Same integers as the separate kernels.
 // ------------------------------------------------------------------------------
 constexpr int kShareList = 512;    // keys of the deciding bucket that are ranked against each other at most
