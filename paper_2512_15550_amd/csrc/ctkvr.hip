@@ -714,17 +714,18 @@ int create_index(const ctkvr_params *p, const int32_t *ctx_lens, const int32_t *
         const size_t lds = share_smem_words(((ix->l_stride + 63) / 64 + nb - 1) / nb, ix->G) * 4;
         if (p->top_k <= kShareCut && lds <= 150 * 1024) ix->share_lds = lds;
         // With one block a unit the CUs that the last round of blocks leaves idle are idle for all of it, and from some length on the
-        // separate launches, whose passes use the whole card, are faster.  Steps with / without, l_stride 32768, 65536 and 131072, 2048
-        // picks, groups of four, us:
-        //   136 units  231/228  285/278  345/327     160 units  256/261  320/316  394/379     192 units  293/303  367/371  451/448
-        //   224 units  330/353  420/434  507/514     264 units  445/429  547/525     -        320 units  503/490  634/610     -
-        //   512 units  717/750  923/973     -        (l_stride 16384: 264 units 189/196, 320 215/227)
-        // Groups of one and two cross within 2 % of these, of eight (whose separate launches are slower) nowhere.  Where the lists
-        // hardly overlap and 131072 slots hold 43000 keys, all of them lose 6 to 13 %: hence at most 98304.  Two blocks a unit and more: -2 to
-        // -7 % (72 to 120 units, 65536 and 131072), at most 1 % the other way at 43000 keys.
+        // separate launches, whose passes use the whole card, are faster.  Steps with / without, groups of four, lists of which a quarter is distinct, us:
+        //   l_stride     32768       65536       131072
+        //   136 units    124/137     203/207     399/387     160 units    137/152     228/234     454/443
+        //   192 units    154/171     260/275     520/513     224 units    173/198     299/321
+        //   264 units    227/237     380/382     (U - 256 of 256 CUs in a second round)
+        // and by recalled keys L, where they cross near 20000: 160 units, l_stride 65536, L 8192, 16384 and 32768 139/151, 222/228 and 405/375; l_stride
+        // 32768 all distinct 384/365.  The lines lie where a quarter to a third distinct loses nothing: l_stride 49152 where just more than half the CUs (of a round) have a block, 81920
+        // where three quarters have, at most 98304.  Groups of one and two cross within 2 % of these, of eight (whose separate launches are
+        // slower) nowhere; two blocks a unit and more: -2 to -13 % (72 to 128 units to 131072).
         const long long rounds = (U + ix->num_cu - 1) / ix->num_cu, cus = rounds * ix->num_cu;
         if (nb == 1 && ix->G <= 4)
-            ix->share_pays = ix->l_stride < 16384 + std::min(81920ll, 131072 * (2 * (long long)U - cus) / (cus * rounds));
+            ix->share_pays = ix->l_stride <= 49152 + std::min(49152ll, 65536 * (2 * (long long)U - cus) / (cus * rounds));
         ix->xs_words = std::max<size_t>(8 * ix->G, ix->share_lds ? share_words(nb, ix->G) : 0);
     }
     // one allocation for all of it
