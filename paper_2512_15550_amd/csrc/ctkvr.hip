@@ -1572,9 +1572,10 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         // Few rows per CU (a small batch): a block's rows are one round trip to memory and the slowest block
         // is the launch, so the ids are split by rank -- two blocks a CU (32K, eight units 32.9 us a step; 1.5: 34.4), those of a
         // resident window, which ride in the launch, counted in (on top of them: eight units of 32K, window of 640 and 100 decoded tokens
-        // 42.7 us with the update, now 41.9; two units of 16K in fp32 40.6, now 35.2), but from 96 a unit on 1.5 blocks a CU: each
-        // reads the unit's whole bitmap, and their atomics meet on the unit's line (one, two and four units of 32K in bf16 33.2, 32.2
-        // and 31.3 us, now 31.5, 30.6 and 30.8; in fp32 34.1, 33.2 and 32.4, now 32.5, 30.9 and 31.7).  At least 32 per
+        // 42.7 us with the update, now 41.9; two units of 16K in fp32 40.6, now 35.2), but beyond 128 a unit 1.5 blocks a CU: each
+        // reads the unit's whole bitmap, and their atomics meet on the unit's line (one and two units of 32K in bf16 33.2 and 32.2 us,
+        // now 31.5 and 30.6; in fp32 34.1 and 33.2, now 32.5 and 30.9; four units, 96 or 128 blocks each: of 8192 recalled keys in bf16 31.0 and
+        // 31.1, in fp32 32.4 and 31.9, of 32768 46.1 and 45.7, 52.1 and 49.6).  At least 32 per
         // unit and 64 list entries per block (128 leave CUs idle where units are few and
         // their lists short: two probes of 495, 16 units of eight heads 28.5 us, 128 29.3; four of 495, four units 31.5, 128 32.5; four of 1280,
         // four units 33.0 either way).  Otherwise by id
@@ -1583,7 +1584,7 @@ int decode_launch_group(ctkvr_index *ix, const StepWs &w_all, int b0, int nb, bo
         const bool win_beside = window && G <= 4;
         int nbx;
         if (by_rank) {
-            nbx = std::min((2 * ix->num_cu + U - 1) / U, std::max(96, (3 * ix->num_cu / 2 + U - 1) / U));
+            nbx = std::min((2 * ix->num_cu + U - 1) / U, std::max(128, (3 * ix->num_cu / 2 + U - 1) / U));
             if (win_beside) nbx = std::min(nbx, 2 * ix->num_cu / U - kWinSplit);
             nbx = std::min(std::max(32, nbx), (ix->l_stride + 63) / 64);
             nbx = std::max({1, nbx, (ix->l_stride + kRecallCap - 1) / kRecallCap});
